@@ -33,7 +33,7 @@
  *   - Supported shapes: d in {32, 64, 128}; B, H, N >= 1 (N == 0 is accepted and does
  *     nothing but define the outputs that do not depend on rows); chunk in {0, 64, 128, 256}
  *     for the 16-bit types (0 = library default, 64; d = 128 supports 64 only), and chunk in
- *     {0, 32} for fp32.
+ *     {0, 32} for fp32 (MFMA products of fp32 operands).
  *     N need not be a multiple of chunk.  64 is the tuned chunk size: 128 and 256 are exact
  *     and tested but slower in this design (more registers than two workgroups per compute
  *     unit leave a wave), and are kept for experiments with the state traffic.
@@ -146,8 +146,8 @@ int cottn_fwd_causal_from_state(const void* Q, const void* K, const void* V, con
  *   K, V, B, H, N, d, chunk, dtype and eps used, untouched since (device pointer, read only,
  *   fwd_workspace_bytes as passed there).  It holds the forward-time segment states of
  *   Kh^T V, which the backward needs again: given them it does not rebuild them from K and V.
- *   They are taken over only for the 16-bit types and when forward and backward split the sequence
- *   the same way (cottn_segments agrees for both ops); otherwise the argument is ignored.
+ *   They are taken over only when forward and backward split the sequence the same way
+ *   (cottn_segments agrees for both ops); otherwise the argument is ignored.
  *   Contents that do not come from such a call give wrong gradients, not an error. */
 int cottn_bwd_causal(const void* Q, const void* K, const void* V, const float* s, const void* dO,
                      void* dQ, void* dK, void* dV, float* ds, const void* fwd_workspace,
@@ -187,8 +187,8 @@ int cottn_fwd_bidir(const void* Q, const void* K, const void* V, const float* s,
  * (the gradient formulas of Sec. 4 with the mask M removed).
  *   fwd_workspace: NULL, or the workspace of the matching completed cottn_fwd_bidir call,
  *   untouched since (same rules as for cottn_bwd_causal): it holds the segment totals of
- *   Kh^T V, which the backward then does not reduce again.  Taken over for bfloat16 and a
- *   split into few segments; otherwise ignored. */
+ *   Kh^T V, which the backward then does not reduce again.  Taken over for a split into few
+ *   segments; otherwise ignored. */
 int cottn_bwd_bidir(const void* Q, const void* K, const void* V, const float* s, const void* dO,
                     void* dQ, void* dK, void* dV, float* ds, const void* fwd_workspace,
                     size_t fwd_workspace_bytes, void* workspace, size_t workspace_bytes, int B,

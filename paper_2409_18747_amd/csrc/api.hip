@@ -54,6 +54,8 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   } else {
     C = chunk == 0 ? 32 : chunk;
     if (C != 32) return false;
+    // (the bidirectional kernels have no quadratic part inside a chunk and take 64 rows a time)
+    if (op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR) C = 64;
   }
   const long units = long(B) * H;
   const long n_chunks = (long(N) + C - 1) / C;
@@ -348,7 +350,7 @@ int bwd_causal_any(const void* Q, const void* K, const void* V, const float* s, 
   a.eps = eps; a.stream = stream;
   // the forward's segment states are taken over only if the forward split the sequence as
   // the backward does
-  if (fwd_workspace != nullptr && dtype != COTTN_F32 && plan.G > 1) {
+  if (fwd_workspace != nullptr && plan.G > 1) {
     SeqPlan fwd_plan;
     if (make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dtype, &fwd_plan) &&
         fwd_plan.C == plan.C && fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows) {
@@ -405,7 +407,7 @@ int bwd_bidir_any(const void* Q, const void* K, const void* V, const float* s, c
   a.workspace = workspace; a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
   a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
   a.eps = eps; a.stream = stream;
-  if (fwd_workspace != nullptr && dtype != COTTN_F32 && plan.G <= kMaxSegmentsSummedInScan) {
+  if (fwd_workspace != nullptr && plan.G <= kMaxSegmentsSummedInScan) {
     SeqPlan fwd_plan;
     if (make_plan(COTTN_OP_FWD_BIDIR, B, H, N, dk, dv, 0, dtype, &fwd_plan) && fwd_plan.C == plan.C &&
         fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows) {

@@ -1,6 +1,7 @@
-// Bidirectional cosine attention, forward and backward, 16-bit storage / 16-bit MFMA / fp32
-// accumulation (gfx950).  Written for a 16-bit element type: this file builds the bfloat16
-// kernels, and the IEEE half ones when it is included with COTTN_ELEM_F16 defined.
+// Bidirectional cosine attention, forward and backward: MFMA products with fp32 accumulation
+// (gfx950).  Written against an element type: this file builds the bfloat16 kernels, the IEEE
+// half ones when it is included with COTTN_ELEM_F16 defined and the fp32 ones with
+// COTTN_ELEM_F32.
 //
 // Sec. 4 eq. subQuadCos: without a mask the product reassociates to O = s_h Qh (Kh^T V), so
 // the d x d matrix S = Kh^T V is reduced once over the whole sequence and then applied to
@@ -50,44 +51,32 @@ struct BiCfg {
   // the forward stages finished output rows (DV wide) in the wave's own dead query rows when
   // those are wide enough, else in a tile of their own
   static constexpr bool FWD_OWN_STAGE = lds_pitch(DV) > TPK;
+  // the dQ sweep stages finished rows in a tile of their own when the LDS has room for it,
+  // otherwise behind a barrier in the dead dO tile (fp32 with wide heads)
+  static constexpr bool DQ_OWN_STAGE =
+      lds_pitch(DK) > TPV || ELEM * (2 * TILEK + TILEV + STATE) + 8 * C <= 160 * 1024;
 };
 
-// Slot 0 of each pair <- sum over g of the slots, one matrix element per thread (grid:
-// elems/256 workgroups per (batch, head)); `state` (may be null) receives pair 0; with
-// n_pairs == 2 every workgroup leaves sum_e S[e] * G[e] over its 256 elements in
-// ds_partial[unit][blockIdx.x], i.e. elems/256 partial sums per (batch, head).
-__global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals, size_t pair_stride,
-                                                     int n_pairs, int G, int elems,
-                                                     float* __restrict__ state,
-                                                     float* __restrict__ ds_partial) {
-  __shared__ float red[4];
+// Slot 0 <- sum over g of the slots, one matrix element per thread (grid: elems/256 workgroups
+// per (batch, head)); `state` (may be null) receives it too.
+__global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals, int G, int elems,
+                                                     float* __restrict__ state) {
   // one grid dimension: (unit, 256-element block of the matrix), so that B*H is not limited to
   // the 65535 of the other grid dimensions
   const int blocks_per_unit = elems / 256;
   const int unit = blockIdx.x / blocks_per_unit, blk = blockIdx.x % blocks_per_unit;
   const int e = blk * 256 + threadIdx.x;
-  float* p0 = totals + size_t(unit) * G * elems;
-  float* p1 = p0 + pair_stride;
+  float* p = totals + size_t(unit) * G * elems;
   float a = 0.f;
-  for (int g = 0; g < G; ++g) a += p0[size_t(g) * elems + e];
-  p0[e] = a;
+  for (int g = 0; g < G; ++g) a += p[size_t(g) * elems + e];
+  p[e] = a;
   if (state != nullptr) state[size_t(unit) * elems + e] = a;
-  if (n_pairs == 2) {
-    float b = 0.f;
-    for (int g = 0; g < G; ++g) b += p1[size_t(g) * elems + e];
-    p1[e] = b;
-    const float prod = group_sum<64>(a * b);
-    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = prod;
-    __syncthreads();
-    if (threadIdx.x == 0)
-      ds_partial[size_t(unit) * blocks_per_unit + blk] = (red[0] + red[1]) + (red[2] + red[3]);
-  }
 }
 
-// dst (LDS, bf16, row-major [DK][DV] with row pitch SP) <- sum of the first n_sum of the
+// dst (LDS, elements, row-major [DK][DV] with row pitch SP) <- sum of the first n_sum of the
 // [DK][DV] fp32 matrices at src; the fp32 sum also goes to `copy` when that is not null.
 template <int DK, int DV, int NT, int SP>
-__device__ __forceinline__ void stage_summed_matrix(e16_t* dst, const float* __restrict__ src,
+__device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __restrict__ src,
                                                     int n_sum, float* __restrict__ copy) {
   for (int e = 4 * threadIdx.x; e < DK * DV; e += 4 * NT) {
     f32x4 a = *reinterpret_cast<const f32x4*>(src + e);
@@ -97,10 +86,7 @@ __device__ __forceinline__ void stage_summed_matrix(e16_t* dst, const float* __r
       for (int v = 0; v < 4; ++v) a[v] += b[v];
     }
     if (copy != nullptr) *reinterpret_cast<f32x4*>(copy + e) = a;
-    uint2 pk;
-    pk.x = pack2(a[0], a[1]);
-    pk.y = pack2(a[2], a[3]);
-    *reinterpret_cast<uint2*>(dst + (e / DV) * SP + e % DV) = pk;
+    store4(dst + (e / DV) * SP + e % DV, a[0], a[1], a[2], a[3]);
   }
 }
 
@@ -109,15 +95,15 @@ __device__ __forceinline__ void stage_summed_matrix(e16_t* dst, const float* __r
 // writes their sum to `state` when that is asked for.
 template <int DK, int DV, int C>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
-    const e16_t* __restrict__ Q, const float* __restrict__ s, e16_t* __restrict__ O,
+    const elem_t* __restrict__ Q, const float* __restrict__ s, elem_t* __restrict__ O,
     const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, int H, int N,
     int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
   constexpr int TP = Cfg::TPK, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) e16_t Qs[Cfg::TILEK];  // raw q
-  __shared__ __attribute__((aligned(16))) e16_t Sl[Cfg::STATE];  // [d_key][d_value]
-  __shared__ __attribute__((aligned(16))) e16_t Os[Cfg::FWD_OWN_STAGE ? Cfg::TILEV : 8];
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];  // raw q
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];  // [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? Cfg::TILEV : 8];
   __shared__ float rq[C];
 
   fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
@@ -126,8 +112,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const e16_t* Qu = Q + size_t(unit) * N * DK;
-  e16_t* Ou = O + size_t(unit) * N * DV;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  elem_t* Ou = O + size_t(unit) * N * DV;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
@@ -142,7 +128,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
   RowPieces<DV> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
-  e16_t* stage = Cfg::FWD_OWN_STAGE ? Os + 16 * w * Cfg::TPV : Qs + 16 * w * TP;
+  elem_t* stage = Cfg::FWD_OWN_STAGE ? Os + 16 * w * Cfg::TPV : Qs + 16 * w * TP;
   for (int row0 = row_begin; row0 < row_end; row0 += C) {
     {
       float rqv[Stage::PASSES];
@@ -160,10 +146,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
     frag8 qf[Cfg::KSK], sf[Cfg::KSK][Cfg::DTV];
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks) {
-      qf[ks] = lds_row_frag(Qs + (16 * w + r) * TP + 32 * ks + 8 * q4);
+      qf[ks] = lds_row_frag(Qs + (16 * w + r) * TP + 32 * ks, q4);
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTV; ++nt)
-        sf[ks][nt] = lds_col_frag(Sl, SP, 32 * ks + 8 * q4, 32 * ks + 8 * q4 + 4, 16 * nt, r);
+        sf[ks][nt] = lds_col_frag_ks(Sl, SP, ks, q4, 16 * nt, r);
     }
     __builtin_amdgcn_sched_barrier(0);  // all LDS reads are issued before the first MFMA
 #pragma unroll
@@ -180,7 +166,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
     const int last = row_begin + (row_end - row_begin - 1) / C * C;
     store_row_pieces<DV>(finished, Ou, last + 16 * w, row_end, l);
   }
-  if (seq_len != nullptr) zero_rows_e16<DV>(Ou, row_end, seg_end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
 }
 
 // Backward, first sweep: dQ rows of one segment and the segment's total of Qh^T dO.  It needs
@@ -190,11 +176,12 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
 //   G_segment = sum over the rows of qh_i^T dO_i,  ds share = sum of qh_i . dqh_i.
 // Q is stored in LDS as qh = r_i q_i: it is contracted over the tokens in G, and the chain
 // rule wants the normalised row anyway.  Every wave reads all rows of both tiles (the total
-// contracts them over the tokens), so finished dQ rows are staged in a tile of their own.
+// contracts them over the tokens), so finished dQ rows are staged in a tile of their own where
+// that fits.
 template <int DK, int DV, int C>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
-    const e16_t* __restrict__ Q, const e16_t* __restrict__ dO, const float* __restrict__ s,
-    e16_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
+    const elem_t* __restrict__ Q, const elem_t* __restrict__ dO, const float* __restrict__ s,
+    elem_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
     float* __restrict__ g_totals, float* __restrict__ ds_partial, int H, int N, int G,
     int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
@@ -202,10 +189,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) e16_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) e16_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) e16_t Os[Cfg::TILEK];   // finished dQ rows
-  __shared__ __attribute__((aligned(16))) e16_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh = r_i q_i
+  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
   __shared__ float rq[C];
   __shared__ float ds_wave[Cfg::NW];
 
@@ -215,9 +202,9 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const e16_t* Qu = Q + size_t(unit) * N * DK;
-  const e16_t* Gu = dO + size_t(unit) * N * DV;
-  e16_t* dQu = dQ + size_t(unit) * N * DK;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Gu = dO + size_t(unit) * N * DV;
+  elem_t* dQu = dQ + size_t(unit) * N * DK;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
@@ -260,11 +247,11 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
     for (int nt = 0; nt < Cfg::DTK; ++nt) dq[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks) {
-      const frag8 gf = lds_row_frag(Gs + (16 * w + r) * TPV + 32 * ks + 8 * q4);
+      const frag8 gf = lds_row_frag(Gs + (16 * w + r) * TPV + 32 * ks, q4);
       frag8 srow[Cfg::DTK];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt)
-        srow[nt] = lds_row_frag(Sl + (16 * nt + r) * SP + 32 * ks + 8 * q4);
+        srow[nt] = lds_row_frag(Sl + (16 * nt + r) * SP + 32 * ks, q4);
       __builtin_amdgcn_sched_barrier(0);  // all LDS reads are issued before the first MFMA
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt) dq[nt] = mma16(srow[nt], gf, dq[nt]);
@@ -291,16 +278,20 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
       }
     }
     const float ri = rq[16 * w + r];
-    const float rho = project_out_row<DK, TPK, true>(dq, Qs + 16 * w * TPK, ri, inv_eps, r, q4);
+    float xv[Cfg::DTK][4];
+    const float t = dot_with_row<Cfg::DTK, TPK>(dq, Qs + 16 * w * TPK, 0, xv, r, q4);
+    const float rho = project_out_row<Cfg::DTK, true>(dq, xv, t, ri, inv_eps);
     if (q4 == 0) ds_lane += rho;
-    gather_rows_transposed<DK>(dq, scale * ri, Os + 16 * w * TPK, l, finished);
+    if (!Cfg::DQ_OWN_STAGE) __syncthreads();  // every wave is done with the dO tile
+    gather_rows_transposed<DK>(dq, scale * ri,
+                               Cfg::DQ_OWN_STAGE ? Os + 16 * w * TPK : Gs + 16 * w * TPV, l, finished);
     __syncthreads();
   }
   if (row_begin < row_end) {
     const int last = row_begin + (row_end - row_begin - 1) / C * C;
     store_row_pieces<DK>(finished, dQu, last + 16 * w, row_end, l);
   }
-  if (seq_len != nullptr) zero_rows_e16<DK>(dQu, row_end, seg_end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, seg_end);  // rows that do not exist
 
   if (RT::active(w)) {
     float* out = g_totals + (size_t(unit) * slots + g) * DK * DV;
@@ -330,17 +321,17 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
 //   dk_j = s r_j (dkh_j - kh_j (kh_j . dkh_j)),  dv_j = s r_j (k_j G).
 template <int DK, int DV, int C>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
-    const e16_t* __restrict__ K, const e16_t* __restrict__ V, const float* __restrict__ s,
-    e16_t* __restrict__ dK, e16_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
+    const elem_t* __restrict__ K, const elem_t* __restrict__ V, const float* __restrict__ s,
+    elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
     int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, int H,
     int N, int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) e16_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) e16_t Vs[Cfg::TILEV];
-  __shared__ __attribute__((aligned(16))) e16_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // raw k
+  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
+  __shared__ __attribute__((aligned(16))) elem_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
   __shared__ float rk[C];
 
   fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
@@ -349,10 +340,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const e16_t* Ku = K + size_t(unit) * N * DK;
-  const e16_t* Vu = V + size_t(unit) * N * DV;
-  e16_t* dKu = dK + size_t(unit) * N * DK;
-  e16_t* dVu = dV + size_t(unit) * N * DV;
+  const elem_t* Ku = K + size_t(unit) * N * DK;
+  const elem_t* Vu = V + size_t(unit) * N * DV;
+  elem_t* dKu = dK + size_t(unit) * N * DK;
+  elem_t* dVu = dV + size_t(unit) * N * DV;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
@@ -408,11 +399,11 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     // G V^T contracts over d_value (row fragments of Gl along its rows)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks) {
-      const frag8 vf = lds_row_frag(Vs + (16 * w + r) * TPV + 32 * ks + 8 * q4);
+      const frag8 vf = lds_row_frag(Vs + (16 * w + r) * TPV + 32 * ks, q4);
       frag8 grow[Cfg::DTK];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt)
-        grow[nt] = lds_row_frag(Gl + (16 * nt + r) * SP + 32 * ks + 8 * q4);
+        grow[nt] = lds_row_frag(Gl + (16 * nt + r) * SP + 32 * ks, q4);
       __builtin_amdgcn_sched_barrier(0);  // all LDS reads are issued before the first MFMA
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt) dk[nt] = mma16(grow[nt], vf, dk[nt]);
@@ -421,11 +412,11 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     // G^T k^T contracts over d_key (fragments down the rows of Gl)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks) {
-      const frag8 kf = lds_row_frag(Ks + (16 * w + r) * TPK + 32 * ks + 8 * q4);
+      const frag8 kf = lds_row_frag(Ks + (16 * w + r) * TPK + 32 * ks, q4);
       frag8 gcol[Cfg::DTV];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTV; ++nt)
-        gcol[nt] = lds_col_frag(Gl, SP, 32 * ks + 8 * q4, 32 * ks + 8 * q4 + 4, 16 * nt, r);
+        gcol[nt] = lds_col_frag_ks(Gl, SP, ks, q4, 16 * nt, r);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTV; ++nt) dv[nt] = mma16(gcol[nt], kf, dv[nt]);
@@ -434,7 +425,9 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     // every tile row is private to its wave here: chain rule on the raw rows, then the
     // results are staged in place (K rows for dK, V rows for dV)
     const float rj = rk[16 * w + r];
-    project_out_row<DK, TPK, false>(dk, Ks + 16 * w * TPK, rj, inv_eps, r, q4);
+    float xv[Cfg::DTK][4];
+    const float t = dot_with_row<Cfg::DTK, TPK>(dk, Ks + 16 * w * TPK, 0, xv, r, q4);
+    project_out_row<Cfg::DTK, false>(dk, xv, t, rj, inv_eps);
     wave_lds_sync();  // own rows of Ks, Vs were read before the staging writes
     gather_rows_transposed<DK>(dk, scale * rj, Ks + 16 * w * TPK, l, done_k);
     gather_rows_transposed<DV>(dv, scale * rj, Vs + 16 * w * TPV, l, done_v);
@@ -446,8 +439,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     store_row_pieces<DV>(done_v, dVu, last + 16 * w, row_end, l);
   }
   if (seq_len != nullptr) {  // rows that do not exist
-    zero_rows_e16<DK>(dKu, row_end, seg_end);
-    zero_rows_e16<DV>(dVu, row_end, seg_end);
+    zero_rows<DK>(dKu, row_end, seg_end);
+    zero_rows<DV>(dVu, row_end, seg_end);
   }
 }
 
@@ -471,12 +464,12 @@ hipError_t run_fwd_bidir(const CausalArgs& a) {
   // few segments: the apply workgroups add the totals up themselves (and write `state`)
   const bool sum_in_apply = a.G <= kMaxSegmentsSummedInScan;
   if (!sum_in_apply) {
-    err = launch_bidir_combine(totals, 0, 1, units, a.G, DK * DV, a.state, nullptr, a.stream);
+    err = launch_bidir_combine(totals, units, a.G, DK * DV, a.state, a.stream);
     if (err != hipSuccess) return err;
   }
   return launch_kernel(COTTN_SYM_STR(fwd_bidir_apply), COTTN_SYM(fwd_bidir_apply)<DK, DV, C>, dim3(units * a.G),
-                       dim3(Cfg::NT), 0, a.stream, static_cast<const e16_t*>(a.Q), a.s,
-                       static_cast<e16_t*>(a.O), totals, a.G, sum_in_apply ? a.G : 1,
+                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q), a.s,
+                       static_cast<elem_t*>(a.O), totals, a.G, sum_in_apply ? a.G : 1,
                        sum_in_apply ? a.state : nullptr, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps,
                        a.seq_len, a.s_per_unit);
 }
@@ -502,35 +495,35 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
     err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, s_totals));
     if (err != hipSuccess) return err;
     if (!few) {
-      err = launch_bidir_combine(s_totals, 0, 1, units, a.G, DK * DV, nullptr, nullptr, a.stream);
+      err = launch_bidir_combine(s_totals, units, a.G, DK * DV, nullptr, a.stream);
       if (err != hipSuccess) return err;
     }
     s_src = s_totals;
   }
   err = launch_kernel(COTTN_SYM_STR(bwd_bidir_dq), COTTN_SYM(bwd_bidir_dq)<DK, DV, C>, dim3(units * a.G),
-                      dim3(Cfg::NT), 0, a.stream, static_cast<const e16_t*>(a.Q),
-                      static_cast<const e16_t*>(a.dO), a.s, static_cast<e16_t*>(a.dQ), s_src, a.G,
+                      dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q),
+                      static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ), s_src, a.G,
                       few ? a.G : 1, g_totals, ds_partial, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps,
                       a.seq_len, a.s_per_unit);
   if (err != hipSuccess) return err;
   if (!few) {
-    err = launch_bidir_combine(g_totals, 0, 1, units, a.G, DK * DV, nullptr, nullptr, a.stream);
+    err = launch_bidir_combine(g_totals, units, a.G, DK * DV, nullptr, a.stream);
     if (err != hipSuccess) return err;
   }
   return launch_kernel(COTTN_SYM_STR(bwd_bidir_dkdv), COTTN_SYM(bwd_bidir_dkdv)<DK, DV, C>, dim3(units * a.G),
-                       dim3(Cfg::NT), 0, a.stream, static_cast<const e16_t*>(a.K),
-                       static_cast<const e16_t*>(a.V), a.s, static_cast<e16_t*>(a.dK),
-                       static_cast<e16_t*>(a.dV), g_totals, a.G, few ? a.G : 1, ds_partial, a.G, a.ds,
+                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.K),
+                       static_cast<const elem_t*>(a.V), a.s, static_cast<elem_t*>(a.dK),
+                       static_cast<elem_t*>(a.dV), g_totals, a.G, few ? a.G : 1, ds_partial, a.G, a.ds,
                        a.B, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps, a.seq_len, a.s_per_unit);
 }
 
 }  // namespace
 
-#ifndef COTTN_ELEM_F16  // not specific to the element type: defined once, by the bf16 build
-hipError_t launch_bidir_combine(float* totals, size_t pair_stride, int n_pairs, int units, int G,
-                                int elems, float* state, float* ds_partial, hipStream_t st) {
+#if !defined(COTTN_ELEM_F16) && !defined(COTTN_ELEM_F32)  // not specific to the element type
+hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, float* state,
+                                hipStream_t st) {
   return launch_kernel("bidir_combine", bidir_combine, dim3(unsigned(elems / 256) * units), dim3(256), 0, st,
-                       totals, pair_stride, n_pairs, G, elems, state, ds_partial);
+                       totals, G, elems, state);
 }
 #endif
 

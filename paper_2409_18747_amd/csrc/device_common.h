@@ -1,33 +1,47 @@
-// Device-side primitives shared by the gfx950 kernels: vector types, the 16-bit MFMA
-// wrapper, LDS fragment reads (plain and transposing), packing, lane reductions.
+// Device-side primitives shared by the gfx950 kernels: vector types, the MFMA wrapper, LDS
+// fragment reads (plain and transposing), packing, lane reductions.
 // Nothing in here knows about attention.
 //
-// The MFMA kernels are written once for a 16-bit floating-point element and compiled twice:
+// The MFMA kernels are written once for a floating-point element and compiled three times:
 // bfloat16 by default, IEEE half when the translation unit defines COTTN_ELEM_F16 before
-// including anything (the *_f16.hip files do exactly that and then include the kernel
-// source).  COTTN_SYM(name) appends the element's suffix to kernel and launcher names.
+// including anything, fp32 with COTTN_ELEM_F32 (the *_f16.hip and *_f32.hip files do exactly
+// that and then include the kernel source).  COTTN_SYM(name) appends the element's suffix to
+// kernel and launcher names.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace cottn {
 
-#ifdef COTTN_ELEM_F16
-typedef _Float16 elem_native;  // the compiler's type for one element
+#if defined(COTTN_ELEM_F32)
+typedef float elem_native;  // the compiler's type for one element
+typedef float elem_t;       // storage type of an element in global memory and LDS
+#define COTTN_SYM(name) name##_f32
+#define COTTN_SYM_STR(name) #name "_f32"
+#elif defined(COTTN_ELEM_F16)
+typedef _Float16 elem_native;
+typedef uint16_t elem_t;
 #define COTTN_SYM(name) name##_f16
 #define COTTN_SYM_STR(name) #name "_f16"
 #else
 typedef __bf16 elem_native;
+typedef uint16_t elem_t;
 #define COTTN_SYM(name) name##_bf16
 #define COTTN_SYM_STR(name) #name "_bf16"
 #endif
+#ifdef COTTN_ELEM_F32
+constexpr bool ELEM_IS_F32 = true;
+#else
+constexpr bool ELEM_IS_F32 = false;
+#endif
+constexpr int ELEM = int(sizeof(elem_t));
+constexpr int EPP = 16 / ELEM;  // elements in a 16-byte piece of a row
 typedef __attribute__((ext_vector_type(8))) elem_native frag8;  // one MFMA operand fragment
 typedef __attribute__((ext_vector_type(2))) elem_native elem2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef uint16_t e16_t;  // storage type of a 16-bit element in global memory and LDS
 
 #define COTTN_LDS __attribute__((address_space(3)))
 
@@ -46,66 +60,94 @@ typedef uint16_t e16_t;  // storage type of a 16-bit element in global memory an
 // cols + 16 (unless four such tiles and a state copy would not fit the 160 KB of a compute
 // unit: 256-row chunks at d = 64), the state copies and the staging of finished rows
 // (8-byte writes) cols + 8.
+// fp32 rows take cols + 8 everywhere: a row fragment is two 16-byte reads (below) whose 16 rows
+// then fall into banks like those of the 16-bit tiles at cols + 16.
 __host__ __device__ constexpr int lds_pitch(int cols) { return cols + 8; }
 __host__ __device__ constexpr int tile_pitch(int cols, int rows) {
-  return 2 * (4 * rows * (cols + 16) + cols * lds_pitch(cols)) + 1024 <= 160 * 1024 ? cols + 16
-                                                                                  : cols + 8;
+  return !ELEM_IS_F32 && 2 * (4 * rows * (cols + 16) + cols * lds_pitch(cols)) + 1024 <= 160 * 1024
+             ? cols + 16
+             : cols + 8;
 }
 
-// D(16x16) += A(16x32) * B(32x16), 16-bit elements in, fp32 accumulate.
-// Lane l = 16*g + r holds  A[row r][k = 8g..8g+7],  B[k = 8g..8g+7][col r],
+// D(16x16) += A(16x32) * B(32x16), fp32 accumulate.
+// Lane l = 16*g + r holds  A[row r][k slots of g],  B[k slots of g][col r],
 // and D[row 4g+v][col r] in acc[v].  The order of the k slots is free as long as A and B
 // use the same one, which several kernels exploit to feed an accumulator tile straight
-// back in as an operand.
+// back in as an operand.  16-bit elements: one instruction.  fp32: eight of the 16x16x4 kind,
+// the j-th over the j-th element of every lane's fragment (256 flop per cycle and compute
+// unit, a sixteenth of the bf16 rate; the vector ALU without packed instructions reaches half
+// of that and would need its operands spread over the lanes by hand).
 __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
-#ifdef COTTN_ELEM_F16
+#if defined(COTTN_ELEM_F32)
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+  return acc;
+#elif defined(COTTN_ELEM_F16)
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
 #else
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 #endif
 }
 
-__device__ __forceinline__ frag8 zero_frag() {
-  s16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-  return __builtin_bit_cast(frag8, z);
-}
+// The k slots of lane row g = lane / 16 in a fragment whose k index runs over 32 consecutive
+// columns (or rows) of an LDS tile: elements 0..3 at slot_lo(g).., elements 4..7 at
+// slot_hi(g)...  16-bit: eight consecutive elements, one 16-byte read; fp32: two groups of four
+// 16 apart, so that the four lane rows of one 16-byte read cover 64 consecutive bytes.
+__device__ __forceinline__ int slot_lo(int g) { return ELEM_IS_F32 ? 4 * g : 8 * g; }
+__device__ __forceinline__ int slot_hi(int g) { return ELEM_IS_F32 ? 16 + 4 * g : 8 * g + 4; }
 
-// Operand fragment whose k index runs along an LDS row: 8 consecutive elements.
-__device__ __forceinline__ frag8 lds_row_frag(const e16_t* p) {
-  return __builtin_bit_cast(frag8, *reinterpret_cast<const uint4*>(p));
+// Operand fragment whose k index runs along an LDS row; p: the row at the first of the 32
+// columns, g: lane / 16.
+__device__ __forceinline__ frag8 lds_row_frag(const elem_t* p, int g) {
+#ifdef COTTN_ELEM_F32
+  const f32x4 lo = *reinterpret_cast<const f32x4*>(p + slot_lo(g));
+  const f32x4 hi = *reinterpret_cast<const f32x4*>(p + slot_hi(g));
+  return frag8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#else
+  return __builtin_bit_cast(frag8, *reinterpret_cast<const uint4*>(p + slot_lo(g)));
+#endif
 }
 
 // Transposing 8-byte LDS read (gfx950): inside each group of 16 lanes, lane i passes the
 // address of 4 consecutive elements, taken as row i/4, columns 4*(i%4).. of a 4x16 block;
 // it receives column i of the block's 4 rows.
-__device__ __forceinline__ s16x4 lds_read_tr(const e16_t* p) {
+#ifndef COTTN_ELEM_F32
+__device__ __forceinline__ s16x4 lds_read_tr(const elem_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((COTTN_LDS s16x4*)(p));
 }
+#endif
 
 // Operand fragment whose k index runs DOWN the rows of a row-major LDS tile (pitch in
 // elements): the lane with r = lane%16 receives tile[k0 + 0..3][col0 + r] and
 // tile[k1 + 0..3][col0 + r].  k0/k1 are the first rows of the two 4-row groups that
 // fill this lane's 8 k slots.
-__device__ __forceinline__ frag8 lds_col_frag(const e16_t* tile, int pitch, int k0, int k1,
+__device__ __forceinline__ frag8 lds_col_frag(const elem_t* tile, int pitch, int k0, int k1,
                                                int col0, int r) {
+#ifdef COTTN_ELEM_F32
+  // (no transposing read of 4-byte elements: a lane reads its column element by element)
+  frag8 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    v[j] = tile[(k0 + j) * pitch + col0 + r];
+    v[4 + j] = tile[(k1 + j) * pitch + col0 + r];
+  }
+  return v;
+#else
   const int sub_row = r >> 2, sub_col = (r & 3) * 4;
   s16x4 lo = lds_read_tr(tile + (k0 + sub_row) * pitch + col0 + sub_col);
   s16x4 hi = lds_read_tr(tile + (k1 + sub_row) * pitch + col0 + sub_col);
   s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   return __builtin_bit_cast(frag8, v);
-}
-
-// element <-> fp32; to_e16 rounds to nearest even
-__device__ __forceinline__ float from_e16(e16_t b) {
-#ifdef COTTN_ELEM_F16
-  return float(__builtin_bit_cast(_Float16, b));
-#else
-  return __builtin_bit_cast(float, uint32_t(b) << 16);
 #endif
 }
-__device__ __forceinline__ e16_t to_e16(float f) {
-  return __builtin_bit_cast(e16_t, static_cast<elem_native>(f));
+// The same over rows 32 ks .. 32 ks + 31, in the slot order of lds_row_frag.
+__device__ __forceinline__ frag8 lds_col_frag_ks(const elem_t* tile, int pitch, int ks, int g,
+                                                  int col0, int r) {
+  return lds_col_frag(tile, pitch, 32 * ks + slot_lo(g), 32 * ks + slot_hi(g), col0, r);
 }
+
+// Elements <-> fp32; conversions to the element type round to nearest even.
+#ifndef COTTN_ELEM_F32
 // two values rounded and packed into one word (low half first): written as one vector
 // conversion so that it becomes the packed convert instruction, not two converts and a merge
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
@@ -132,19 +174,74 @@ __device__ __forceinline__ float dot2_self(uint32_t w, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(p, p, acc, false);
 #endif
 }
-__device__ __forceinline__ void unpack8(uint4 raw, float* f) {
+#endif
+// four consecutive elements
+__device__ __forceinline__ void store4(elem_t* dst, float a, float b, float c, float d) {
+#ifdef COTTN_ELEM_F32
+  *reinterpret_cast<f32x4*>(dst) = f32x4{a, b, c, d};
+#else
+  uint2 pk;
+  pk.x = pack2(a, b);
+  pk.y = pack2(c, d);
+  *reinterpret_cast<uint2*>(dst) = pk;
+#endif
+}
+__device__ __forceinline__ void load4(const elem_t* src, float* f) {
+#ifdef COTTN_ELEM_F32
+  const f32x4 v = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = v[i];
+#else
+  const uint2 raw = *reinterpret_cast<const uint2*>(src);
   unpack2(raw.x, f[0], f[1]);
   unpack2(raw.y, f[2], f[3]);
-  unpack2(raw.z, f[4], f[5]);
-  unpack2(raw.w, f[6], f[7]);
+#endif
 }
-__device__ __forceinline__ uint4 pack8(const float* f) {
-  uint4 r;
-  r.x = pack2(f[0], f[1]);
-  r.y = pack2(f[2], f[3]);
-  r.z = pack2(f[4], f[5]);
-  r.w = pack2(f[6], f[7]);
-  return r;
+// a 16-byte piece of a row (EPP elements): its sum of squares, and the piece times a factor
+__device__ __forceinline__ float piece_sum_sq(uint4 raw) {
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  float ss = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#ifdef COTTN_ELEM_F32
+    const float x = __builtin_bit_cast(float, w[e]);
+    ss += x * x;
+#else
+    ss = dot2_self(w[e], ss);
+#endif
+  }
+  return ss;
+}
+__device__ __forceinline__ uint4 piece_times(uint4 raw, float f) {
+  uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#ifdef COTTN_ELEM_F32
+    w[e] = __builtin_bit_cast(uint32_t, f * __builtin_bit_cast(float, w[e]));
+#else
+    float lo, hi;
+    unpack2(w[e], lo, hi);
+    w[e] = pack2(f * lo, f * hi);
+#endif
+  }
+  return uint4{w[0], w[1], w[2], w[3]};
+}
+
+// Fills half of an operand fragment with a masked accumulator tile: the tile's element [v] of
+// lane row g is k slot 16 half + 4 g + v of the fragment.
+__device__ __forceinline__ void put_half(frag8& frag, int half, f32x4 acc, bool k0, bool k1,
+                                         bool k2, bool k3) {
+#ifdef COTTN_ELEM_F32
+  frag[4 * half + 0] = k0 ? acc[0] : 0.f;
+  frag[4 * half + 1] = k1 ? acc[1] : 0.f;
+  frag[4 * half + 2] = k2 ? acc[2] : 0.f;
+  frag[4 * half + 3] = k3 ? acc[3] : 0.f;
+#else
+  u32x4 words = __builtin_bit_cast(u32x4, frag);
+  words[2 * half + 0] = pack2(k0 ? acc[0] : 0.f, k1 ? acc[1] : 0.f);
+  words[2 * half + 1] = pack2(k2 ? acc[2] : 0.f, k3 ? acc[3] : 0.f);
+  frag = __builtin_bit_cast(frag8, words);
+#endif
 }
 
 // x of another lane of the same row of 16 lanes, chosen by a DPP control word: no LDS
@@ -193,10 +290,10 @@ __device__ __forceinline__ float unit_scale(const float* __restrict__ s, int uni
                                             int per_unit) {
   return s[per_unit ? unit : unit % H];
 }
-// Zeros rows row_lo..row_hi-1 of a [.][D] tensor of 2-byte elements (whole workgroup).
+// Zeros rows row_lo..row_hi-1 of a [.][D] tensor of elements (whole workgroup).
 template <int D>
-__device__ __forceinline__ void zero_rows_e16(e16_t* __restrict__ dst, int row_lo, int row_hi) {
-  const long pieces = long(max(0, row_hi - row_lo)) * (D / 8);
+__device__ __forceinline__ void zero_rows(elem_t* __restrict__ dst, int row_lo, int row_hi) {
+  const long pieces = long(max(0, row_hi - row_lo)) * (D / EPP);
   uint4* p = reinterpret_cast<uint4*>(dst + size_t(row_lo) * D);
   for (long i = threadIdx.x; i < pieces; i += blockDim.x) p[i] = uint4{0u, 0u, 0u, 0u};
 }
@@ -295,6 +392,12 @@ __device__ __forceinline__ void exclusive_running_sum(float* __restrict__ p, int
 // 1 / max(sqrt(sum_sq), eps)
 __device__ __forceinline__ float inv_norm(float sum_sq, float eps) {
   return 1.0f / fmaxf(sqrtf(sum_sq), eps);
+}
+
+// The row factor of the tile kernels, min(1 / sqrt(sum_sq), inv_eps): the reciprocal square root
+// instruction (1 ulp of fp32) for 16-bit rows, correctly rounded steps for fp32 ones.
+__device__ __forceinline__ float row_inv_norm(float sum_sq, float inv_eps) {
+  return fminf(ELEM_IS_F32 ? 1.0f / sqrtf(sum_sq) : __builtin_amdgcn_rsqf(sum_sq), inv_eps);
 }
 
 }  // namespace cottn

@@ -1,6 +1,6 @@
-// Causal cosine attention forward, 16-bit storage / 16-bit MFMA / fp32 accumulation (gfx950).
-// Written for a 16-bit element type: this file builds the bfloat16 kernels, and the IEEE half
-// ones when it is included with COTTN_ELEM_F16 defined.
+// Causal cosine attention forward: MFMA products with fp32 accumulation (gfx950).
+// Written against an element type: this file builds the bfloat16 kernels, the IEEE half ones
+// when it is included with COTTN_ELEM_F16 defined and the fp32 ones with COTTN_ELEM_F32.
 //
 // Sec. 4 eq. attn_2 writes the causal output as an inclusive cumulative sum over the sequence
 // of the outer products kh_j^T v_j, contracted with qh_i.  Regrouping that sum exactly:
@@ -60,7 +60,7 @@ struct FwdCfg {
   // finished output rows (DV wide) are staged in the wave's own dead query rows when those are
   // wide enough, else in a tile of their own
   static constexpr bool OWN_STAGE = lds_pitch(DV) > TPK;
-  static constexpr int LDS_BYTES = 2 * (2 * TILEK + TILEV + STATE + (OWN_STAGE ? TILEV : 0)) + 4 * C;
+  static constexpr int LDS_BYTES = ELEM * (2 * TILEK + TILEV + STATE + (OWN_STAGE ? TILEV : 0)) + 4 * C;
   static constexpr int WG_PER_CU = (160 * 1024) / LDS_BYTES;
   // waves per SIMD the register allocation is capped for (two workgroups per compute unit
   // when LDS allows, never more than the hardware needs for one workgroup)
@@ -74,7 +74,7 @@ struct FwdCfg {
   static constexpr int waves_per_eu() {
     if (CS == 1) return WAVES_PER_EU;
     const int own = NW * CS / 4;
-    const int wg = (160 * 1024) / (LDS_BYTES + 2 * TILEV) >= 2 ? 2 : 1;
+    const int wg = (160 * 1024) / (LDS_BYTES + ELEM * TILEV) >= 2 ? 2 : 1;
     return own * wg > 4 ? (own > 4 ? own : 4) : own * wg;
   }
 };
@@ -83,8 +83,11 @@ struct FwdCfg {
 // two at d = 128, where one workgroup fills the LDS of a compute unit and four waves are too
 // few to cover latencies (+6 % on a 2048-token prefill of 4096 heads); at d = 64 and 32 the
 // two variants time the same and the smaller workgroup is kept.
-template <int DK, int DV, int C> struct FwdSplit { static constexpr int CS = 1; };
+template <int DK, int DV, int C> struct FwdSplit { static constexpr int CS = ELEM_IS_F32 ? 2 : 1; };
 template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
+// (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four;
+// B8 H12 N1024 d64 44 us, of which 14 us is MFMA time and 20 us the rows' way through HBM; the
+// vector-ALU kernel it replaces took 91 us)
 
 // ---------------------------------------------------------------------------------------
 // Kernel 1: T[unit][g] = sum over the rows of segment g of kh^T v   (fp32, d_key x d_value;
@@ -98,15 +101,15 @@ template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
 // by tile, TILED = true).
 template <int DK, int DV, int C, bool TILED>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
-    const e16_t* __restrict__ K, const e16_t* __restrict__ V, float* __restrict__ seg_state,
+    const elem_t* __restrict__ K, const elem_t* __restrict__ V, float* __restrict__ seg_state,
     int N, int n_slots, int n_compute, int seg_rows, float inv_eps,
     const int* __restrict__ seq_len, int H) {
   using Cfg = FwdCfg<DK, DV, C>;
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) e16_t Ks[Cfg::TILEK];
-  __shared__ __attribute__((aligned(16))) e16_t Vs[Cfg::TILEV];
+  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];
+  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
 
   fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H);
   int unit, g;
@@ -114,8 +117,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   if (g >= n_compute) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const e16_t* Ku = K + size_t(unit) * N * DK;
-  const e16_t* Vu = V + size_t(unit) * N * DV;
+  const elem_t* Ku = K + size_t(unit) * N * DK;
+  const elem_t* Vu = V + size_t(unit) * N * DV;
   const int row_begin = g * seg_rows;
   const int row_end = min(valid_rows(seq_len, unit, H, N), row_begin + seg_rows);
 
@@ -146,14 +149,13 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
     if (ST::active(w)) {
 #pragma unroll
       for (int p = 0; p < Cfg::NP; ++p) {
-        const int k0 = 32 * p + 8 * q4;
         frag8 bv[ST::NCT], ak[ST::NRT];
 #pragma unroll
         for (int x = 0; x < ST::NCT; ++x)
-          bv[x] = lds_col_frag(Vs, Cfg::TPV, k0, k0 + 4, 16 * ST::col_tile(w, x), r);
+          bv[x] = lds_col_frag_ks(Vs, Cfg::TPV, p, q4, 16 * ST::col_tile(w, x), r);
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y)
-          ak[y] = lds_col_frag(Ks, Cfg::TPK, k0, k0 + 4, 16 * ST::row_tile(w, y), r);
+          ak[y] = lds_col_frag_ks(Ks, Cfg::TPK, p, q4, 16 * ST::row_tile(w, y), r);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y)
@@ -201,8 +203,8 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
 // waves to cover latencies with.
 template <int DK, int DV, int C, int CS>
 __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())) void COTTN_SYM(fwd_causal_scan)(
-    const e16_t* __restrict__ Q, const e16_t* __restrict__ K, const e16_t* __restrict__ V,
-    const float* __restrict__ s, e16_t* __restrict__ O, float* __restrict__ state_out,
+    const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
+    const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
     const float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
     int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
     int stream_q) {
@@ -214,13 +216,13 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   using StageV = TileStage<DV, C, Cfg::NT * CS>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
   constexpr bool OWN_STAGE = CS > 1 || Cfg::OWN_STAGE;
-  __shared__ __attribute__((aligned(16))) e16_t Qs[Cfg::TILEK];   // raw q rows
-  __shared__ __attribute__((aligned(16))) e16_t Ks[Cfg::TILEK];   // kh = r_j k_j
-  __shared__ __attribute__((aligned(16))) e16_t Vs[Cfg::TILEV];   // raw v rows
-  __shared__ __attribute__((aligned(16))) e16_t Sl[Cfg::STATE];   // state, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // raw q rows
+  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // kh = r_j k_j
+  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // raw v rows
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // state, [d_key][d_value]
   // with two waves on a row group the q rows stay live in the other wave, and with outputs
   // wider than the queries they do not fit the q rows: own staging tile
-  __shared__ __attribute__((aligned(16))) e16_t Os[OWN_STAGE ? Cfg::TILEV : 8];
+  __shared__ __attribute__((aligned(16))) elem_t Os[OWN_STAGE ? Cfg::TILEV : 8];
   __shared__ float rq[C];
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, seq_len, s_per_unit, stream_q);
@@ -229,10 +231,10 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const int rg = w % RG, cp = w / RG;  // row group, column part
-  const e16_t* Qu = Q + size_t(unit) * N * DK;
-  const e16_t* Ku = K + size_t(unit) * N * DK;
-  const e16_t* Vu = V + size_t(unit) * N * DV;
-  e16_t* Ou = O + size_t(unit) * N * DV;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Ku = K + size_t(unit) * N * DK;
+  const elem_t* Vu = V + size_t(unit) * N * DV;
+  elem_t* Ou = O + size_t(unit) * N * DV;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
@@ -286,7 +288,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   RowPieces<DV, NOT> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV, NOT>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
-  e16_t* stage = OWN_STAGE ? Os + 16 * rg * TPV : Qs + 16 * rg * TPK;
+  elem_t* stage = OWN_STAGE ? Os + 16 * rg * TPV : Qs + 16 * rg * TPK;
   const int col0 = 16 * NOT * cp;  // first output column of this wave
   for (int row0 = row_begin; row0 < row_end; row0 += C) {
     // ---- publish the state (bf16) and this chunk's tiles
@@ -295,11 +297,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y) {
-          uint2 pk;
-          pk.x = pack2(sacc[x][y][0], sacc[x][y][1]);
-          pk.y = pack2(sacc[x][y][2], sacc[x][y][3]);
-          *reinterpret_cast<uint2*>(Sl + (16 * ST::col_tile(rg, cp, x) + r) * SP +
-                                    16 * ST::row_tile(rg, cp, y) + 4 * q4) = pk;
+          store4(Sl + (16 * ST::col_tile(rg, cp, x) + r) * SP + 16 * ST::row_tile(rg, cp, y) + 4 * q4,
+                 sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
         }
     }
     {
@@ -324,7 +323,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     frag8 qf[Cfg::KSK];  // q rows of this wave: column-side operand of every product
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks)
-      qf[ks] = lds_row_frag(Qs + (16 * rg + r) * TPK + 32 * ks + 8 * q4);
+      qf[ks] = lds_row_frag(Qs + (16 * rg + r) * TPK + 32 * ks, q4);
     // oacc[nt][v] = O[query 16 rg + r][value col0 + 16 nt + 4 q4 + v] before the row factor
     f32x4 oacc[NOT];
 #pragma unroll
@@ -334,7 +333,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       frag8 sf[NOT];
 #pragma unroll
       for (int nt = 0; nt < NOT; ++nt)
-        sf[nt] = lds_col_frag(Sl, SP, 32 * ks + 8 * q4, 32 * ks + 8 * q4 + 4, col0 + 16 * nt, r);
+        sf[nt] = lds_col_frag_ks(Sl, SP, ks, q4, col0 + 16 * nt, r);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16(sf[nt], qf[ks], oacc[nt]);
@@ -353,7 +352,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
 #pragma unroll
       for (int x = 0; x < ST::NCT; ++x)
         kcol[x] = lds_col_frag(Ks, TPK, t0, t1, 16 * ST::col_tile(rg, cp, x), r);
-      if (!ST::ROW_OPERAND_IS_OUTPUT_V) {
+      if (!ST::ROW_OPERAND_IS_RESULT_COLUMN) {
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y)
           vrow[y] = lds_col_frag(Vs, TPV, t0, t1, 16 * ST::row_tile(rg, cp, y), r);
@@ -363,11 +362,11 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSK; ++ks)
-            kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + 32 * ks + 8 * q4);
+            kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
       }
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
-        u32x4 pw;
+        frag8 pf;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           const int jt = 2 * p + half;
@@ -375,16 +374,10 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSK; ++ks) pacc = mma16(kr[half][ks], qf[ks], pacc);
           // pacc[v] = q_(16 rg + r) . k_(16jt + 4*q4 + v); keep key <= query
-          float kept[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const bool keep = (jt < rg) || (jt == rg && 4 * q4 + v <= r);
-            kept[v] = keep ? pacc[v] : 0.f;
-          }
-          pw[2 * half + 0] = pack2(kept[0], kept[1]);
-          pw[2 * half + 1] = pack2(kept[2], kept[3]);
+          const bool full = jt < rg, diag = jt == rg;
+          put_half(pf, half, pacc, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
+                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
         }
-        const frag8 pf = __builtin_bit_cast(frag8, pw);
 #pragma unroll
         for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16(vc[nt], pf, oacc[nt]);
       }
@@ -394,7 +387,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int y = 0; y < ST::NRT; ++y)
 #pragma unroll
           for (int x = 0; x < ST::NCT; ++x)
-            sacc[x][y] = mma16(ST::ROW_OPERAND_IS_OUTPUT_V ? vc[y] : vrow[y], kcol[x], sacc[x][y]);
+            sacc[x][y] = mma16(ST::ROW_OPERAND_IS_RESULT_COLUMN ? vc[y] : vrow[y], kcol[x], sacc[x][y]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -410,7 +403,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     store_row_pieces<DV, NOT>(finished, Ou, last + 16 * rg, row_end, l, col0);
   }
 
-  if (seq_len != nullptr) zero_rows_e16<DV>(Ou, row_end, seg_end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
 
   if (state_out != nullptr && g == G - 1 && ST::active(rg, cp)) {
     float* out = state_out + size_t(unit) * DK * DV;
@@ -425,11 +418,12 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
 
 template <int DK, int DV, int C>
 hipError_t run_fwd_causal(const CausalArgs& a) {
+  constexpr int CS = FwdSplit<DK, DV, C>::CS;
   using Cfg = FwdCfg<DK, DV, C>;
   const int units = a.B * a.H;
-  const e16_t* Q = static_cast<const e16_t*>(a.Q);
-  const e16_t* K = static_cast<const e16_t*>(a.K);
-  const e16_t* V = static_cast<const e16_t*>(a.V);
+  const elem_t* Q = static_cast<const elem_t*>(a.Q);
+  const elem_t* K = static_cast<const elem_t*>(a.K);
+  const elem_t* V = static_cast<const elem_t*>(a.V);
   float* ws = static_cast<float*>(a.workspace);  // [units][G] states of DK x DV (tiled) when G > 1
   const float inv_eps = 1.0f / a.eps;
   hipError_t err = hipSuccess;
@@ -443,14 +437,13 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
       if (err != hipSuccess) return err;
     }
   }
-  constexpr int CS = FwdSplit<DK, DV, C>::CS;
   // Q rows are read once here.  When the call's four tensors exceed the 256 MB last-level cache
   // nothing of them survives until a backward call either, and loading them non-temporally
   // keeps the K, V rows the totals kernel left in the L2 in place (long context: scan 98 ->
   // 87 us); below that size a backward that follows finds the rows cached, and plain loads win.
-  const bool stream_q = 2.0 * units * double(a.N) * (DK + DV) * sizeof(e16_t) > 256.0 * 1024 * 1024;
+  const bool stream_q = 2.0 * units * double(a.N) * (DK + DV) * ELEM > 256.0 * 1024 * 1024;
   return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), COTTN_SYM(fwd_causal_scan)<DK, DV, C, CS>, dim3(units * a.G),
-                       dim3(Cfg::NT * CS), 0, a.stream, Q, K, V, a.s, static_cast<e16_t*>(a.O), a.state,
+                       dim3(Cfg::NT * CS), 0, a.stream, Q, K, V, a.s, static_cast<elem_t*>(a.O), a.state,
                        a.G > 1 ? ws : nullptr, a.state_in, a.H, a.N, a.G, a.seg_rows, inv_eps,
                        sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0);
 }
@@ -459,15 +452,17 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
 
 template <int DK, int DV, bool TILED>
 static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
-  const e16_t* X = static_cast<const e16_t*>(t.X);
-  const e16_t* Y = static_cast<const e16_t*>(t.Y);
+  const elem_t* X = static_cast<const elem_t*>(t.X);
+  const elem_t* Y = static_cast<const elem_t*>(t.Y);
   const float inv_eps = 1.0f / t.eps;
   // The totals kernel takes 128-row tiles when the segment is that long: a 512-thread
   // workgroup has all of its loads in flight at once instead of paying one memory latency per
   // 64-row chunk, and several workgroups still fit a compute unit (two 256-row tiles of the
-  // operand-tile pitch would leave room for one: measured 0.6 us slower on the GPT shape).
+  // operand-tile pitch would leave room for one: measured 0.6 us slower on the GPT shape;
+  // fp32 tiles of wide heads fit twice only with 64 rows).
   const dim3 grid(t.units * t.G);
-  if (t.seg_rows >= 128)
+  constexpr bool TALL = ELEM * 128 * (lds_pitch(DK) + lds_pitch(DV)) <= 80 * 1024;
+  if (TALL && t.seg_rows >= 128)
     return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 128, TILED>, grid, dim3(512),
                          0, t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps,
                          t.seq_len, t.H);
@@ -500,7 +495,7 @@ hipError_t COTTN_SYM(launch_fwd_segment_totals)(const CausalArgs& a, float* dst)
   return COTTN_SYM(launch_segment_totals)(t);
 }
 
-#ifndef COTTN_ELEM_F16  // not specific to the element type: defined once, by the bf16 build
+#if !defined(COTTN_ELEM_F16) && !defined(COTTN_ELEM_F32)  // not specific to the element type
 hipError_t launch_fwd_state_carry(float* seg_state, int units, int G, int elems, hipStream_t st) {
   const long total = long(units) * elems;
   return launch_kernel("fwd_state_carry", fwd_state_carry, dim3(unsigned((total / 4 + 255) / 256)),
@@ -509,6 +504,20 @@ hipError_t launch_fwd_state_carry(float* seg_state, int units, int G, int elems,
 #endif
 
 hipError_t COTTN_SYM(fwd_causal)(const CausalArgs& a) {
+#ifdef COTTN_ELEM_F32
+  switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
+    case 32032032: return run_fwd_causal<32, 32, 32>(a);
+    case 32064032: return run_fwd_causal<32, 64, 32>(a);
+    case 32128032: return run_fwd_causal<32, 128, 32>(a);
+    case 64032032: return run_fwd_causal<64, 32, 32>(a);
+    case 64064032: return run_fwd_causal<64, 64, 32>(a);
+    case 64128032: return run_fwd_causal<64, 128, 32>(a);
+    case 128032032: return run_fwd_causal<128, 32, 32>(a);
+    case 128064032: return run_fwd_causal<128, 64, 32>(a);
+    case 128128032: return run_fwd_causal<128, 128, 32>(a);
+    default: return hipErrorInvalidValue;
+  }
+#else
   // d_key != d_value: chunks of 64 rows
   switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
     case 32032064: return run_fwd_causal<32, 32, 64>(a);
@@ -526,6 +535,7 @@ hipError_t COTTN_SYM(fwd_causal)(const CausalArgs& a) {
     case 128064064: return run_fwd_causal<128, 64, 64>(a);
     default: return hipErrorInvalidValue;
   }
+#endif
 }
 
 }  // namespace cottn

@@ -63,15 +63,16 @@ hipError_t fwd_bidir_f32(const CausalArgs& a);
 hipError_t bwd_bidir_f32(const CausalArgs& a);
 hipError_t step_any(const StepArgs& a, int dtype);
 
-// small fp32 state kernels shared by the 16-bit and fp32 paths (defined next to their kernels)
+// small fp32 state kernels shared by all element types (defined next to their kernels)
 hipError_t launch_fwd_state_carry(float* seg_state, int units, int G, int elems, hipStream_t st);
 // either array may be null: then only the other one is carried
 hipError_t launch_bwd_state_carry(float* fwd_tot, float* rev_tot, int units, int G, int elems,
                                   hipStream_t st);
-// 16-bit paths: segment totals of Kh^T V for all segments but the last, [units][G][d][d] fp32 in `dst`
+// segment totals of Kh^T V for all segments but the last, [units][G][d][d] fp32 in `dst`
 // (the first kernel of the causal forward, also used by a backward without saved states)
 hipError_t launch_fwd_segment_totals_bf16(const CausalArgs& a, float* dst);
 hipError_t launch_fwd_segment_totals_f16(const CausalArgs& a, float* dst);
+hipError_t launch_fwd_segment_totals_f32(const CausalArgs& a, float* dst);
 
 // The same kernel in general: dst[unit][g] = sum over the rows of segment g of N(X)^T Y
 // (dk x dv) for g < n_compute (G slots per unit).
@@ -87,11 +88,9 @@ struct SegmentTotalsArgs {
 };
 hipError_t launch_segment_totals_bf16(const SegmentTotalsArgs& t);
 hipError_t launch_segment_totals_f16(const SegmentTotalsArgs& t);
-// ds[h] = sum over batches b and j < n of partial[(b H + h) n + j]; per_unit: ds[b][h] instead
-hipError_t launch_reduce_ds(const float* partial, float* ds, int B, int H, int n, int per_unit,
-                            hipStream_t st);
-hipError_t launch_bidir_combine(float* totals, size_t pair_stride, int n_pairs, int units, int G,
-                                int elems, float* state, float* ds_partial, hipStream_t st);
+hipError_t launch_segment_totals_f32(const SegmentTotalsArgs& t);
+hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, float* state,
+                                hipStream_t st);
 
 // the stabiliser map of Sec. 3.3 and its gradient (scale.hip)
 hipError_t launch_scale_from_m(const float* m, float* s, int H, float n, hipStream_t st);

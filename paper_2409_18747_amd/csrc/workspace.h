@@ -17,8 +17,8 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
 inline size_t round_up_256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace layouts (all fp32; a state is dk x dv: row-major [d_key][d_value] on the
-// bidirectional and fp32 paths; the 16-bit causal kernels, which alone read what they write
-// here, keep each state in 16x16 tiles of 256 consecutive floats in accumulator-register order,
+// bidirectional path; the causal kernels, which alone read what they write here, keep each
+// state in 16x16 tiles of 256 consecutive floats in accumulator-register order,
 // device_common.h: tiled_state_offset):
 //   causal forward   G > 1: [units][G][dk][dv]   segment totals, turned in place into the
 //                            state at each segment start
@@ -26,9 +26,8 @@ inline size_t round_up_256(size_t x) { return (x + 255) & ~size_t(255); }
 //                            the reverse-time states; always: [units][G] partial sums of ds
 //   bidirectional forward : [units][G][dk][dv]   segment totals, slot 0 becomes the full state
 //   bidirectional backward: two arrays [units][G][dk][dv], totals of Kh^T V and of Qh^T dO,
-//                            slot 0 becomes the full matrix when the combine kernel runs; per
-//                            unit max(G, dk*dv/256) partial sums of ds (the totals kernel
-//                            leaves G, the combine kernel dk*dv/256)
+//                            slot 0 becomes the full matrix when the combine kernel runs; then
+//                            [units][G] partial sums of ds (room for dk*dv/256 where that is more)
 inline size_t state_array_bytes(int B, int H, int dk, int dv, int G) {
   return round_up_256(size_t(B) * H * G * dk * dv * sizeof(float));
 }
