@@ -39,6 +39,66 @@ bool dims_ok(int B, int H, int N, int dk, int dv) {
   return true;
 }
 
+constexpr int kComputeUnits = 256;
+
+// Workgroups of the causal scans that a compute unit holds at once (LDS and registers).
+int scan_workgroups_per_cu(int C, int dtype, int dk, int dv) {
+  if (C > 64) return 1;
+  const int big = dk > dv ? dk : dv, small = dk > dv ? dv : dk;
+  if (dtype == COTTN_F32) return big == 32 ? 3 : big == 128 && small >= 64 ? 1 : 2;
+  return big == 32 ? 4 : small == 128 ? 1 : 2;
+}
+
+// Segments per (batch, head) for the causal calls: the split with the least time by a model of
+// the scans.  A workgroup walks `steps` chunks and pays about two more to start (first rows,
+// stored states); all start together, so a launch lasts as long as the compute unit with the
+// most workgroups, which holds `per_cu` at a time; a step takes 1 with two workgroups on the
+// compute unit and 0.75 alone (B8 H12 N1024 d64, dQ scan: 13.3 us with one per unit, 17.1 with
+// two).  More than one segment costs the totals kernel, and each segment's totals have to be
+// added up, by the workgroups or by a carry launch.  What the model buys over a fixed number of
+// workgroups is that no compute unit ends up with one more than the others: B4 H12 N1024 d128
+// fp32 8 segments (384 workgroups, one per compute unit at a time) 346 us, 5 (240) 279 us; B5 H12
+// N5000 d32 7 segments 74 us, 8 60 us; B1 H16 N8192 d64 22 segments 78 us, 16 68 us.
+long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv) {
+  const int per_cu = scan_workgroups_per_cu(C, dtype, dk, dv);
+  double best = 0.0;
+  long best_g = 1;
+  for (long steps = n_chunks; steps >= 1; --steps) {
+    // (only the counts that give different splits: about 2 sqrt(n_chunks) of them)
+    const long g = (n_chunks + steps - 1) / steps;
+    steps = (n_chunks + g - 1) / g;
+    const long on_cu = (units * g + kComputeUnits - 1) / kComputeUnits;
+    const auto step_time = [](long n) { return 0.5 + 0.25 * double(n); };
+    const double rounds = double(on_cu / per_cu) * step_time(per_cu) +
+                          (on_cu % per_cu ? step_time(on_cu % per_cu) : 0.0);
+    double cost = rounds * double(steps + 2);
+    if (g > 1) cost += sum_totals_in_place(int(g), dk, dv) ? 1.5 + 0.1 * double(g) : 4.0 + 0.05 * double(g);
+    if (g == 1 || cost < best) {
+      best = cost;
+      best_g = g;
+    }
+    if (units * g > 16L * kComputeUnits) break;   // finer only adds rounds
+  }
+  return best_g;
+}
+
+// Segments per (batch, head) for the bidirectional calls.  Their kernels have no chain to
+// shorten and little to set up: three workgroups per compute unit measured best (B32 H12 N512:
+// 59.2 us per forward + backward with 2 segments, 60.7 with 1), in at most four segments, whose
+// totals are soon added up; at 128 x 128 one (the dQ sweep fills the LDS of a compute unit: B8
+// H12 N1024 2 segments 97 us, 3 segments 116).  Few units with long sequences are cut further,
+// until (nearly) every compute unit has a workgroup and none has two: B1 H2 N65536 128
+// segments 76 us, 64 segments 95; B1 H12 N8192 d128 19 segments 122 us, 22 segments 151.
+long bidir_segments(long units, long n_chunks, int dk, int dv) {
+  long want = dk == 128 && dv == 128 ? kComputeUnits / units : (3 * kComputeUnits + units - 1) / units;
+  if (want > 4) want = 4;
+  if (units * want < kComputeUnits && n_chunks >= 8 * want) {
+    want = kComputeUnits / units;
+    if (want > n_chunks / 2) want = n_chunks / 2;   // at least two chunks each
+  }
+  return want;
+}
+
 }  // namespace
 
 // Split of one (batch, head) sequence into segments; see workspace.h.
@@ -59,32 +119,10 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   }
   const long units = long(B) * H;
   const long n_chunks = (long(N) + C - 1) / C;
-  long want;
-  if (g_tuned_segments > 0) {
-    want = g_tuned_segments;
-  } else {
-    if (dtype != COTTN_F32 && dk == 128 && dv == 128) {
-      // one workgroup fills the LDS of a compute unit at d = 128: a second round of
-      // workgroups costs more than shorter segments gain, so never more than one per unit
-      // (measured on B8 H12 N1024: 2 segments 143 us, 4 segments 178 us per step)
-      want = 256 / units;
-    } else {
-      // about one and a half workgroups per compute unit: measured best for the scan kernels
-      // (more segments shorten the serial chain but add totals to reduce and to add up)
-      const long target = 384;
-      want = (target + units - 1) / units;
-      // the bidirectional kernels have no chain to shorten and little to set up: three
-      // workgroups per compute unit measured best there (B32 H12 N512: 59.2 us per forward +
-      // backward with 2 segments, 60.7 with 1), as long as the kernels still add up the
-      // segment totals themselves
-      if (op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR) {
-        want = (768 + units - 1) / units;
-        if (want > kMaxSegmentsSummedInScan) want = kMaxSegmentsSummedInScan;
-      }
-      // long serial chains (16 chunks or more per segment) are bound by the memory path, not
-      // by the prologue: there two workgroups on every compute unit measured best
-      if (n_chunks >= 16 * want) want = (512 + units - 1) / units;
-    }
+  long want = g_tuned_segments;
+  if (want <= 0) {
+    const bool bidir = op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR;
+    want = bidir ? bidir_segments(units, n_chunks, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
   }
   if (want > n_chunks) want = n_chunks;
   if (want < 1) want = 1;
@@ -407,7 +445,7 @@ int bwd_bidir_any(const void* Q, const void* K, const void* V, const float* s, c
   a.workspace = workspace; a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
   a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
   a.eps = eps; a.stream = stream;
-  if (fwd_workspace != nullptr && plan.G <= kMaxSegmentsSummedInScan) {
+  if (fwd_workspace != nullptr && sum_totals_in_place(plan.G, dk, dv)) {
     SeqPlan fwd_plan;
     if (make_plan(COTTN_OP_FWD_BIDIR, B, H, N, dk, dv, 0, dtype, &fwd_plan) && fwd_plan.C == plan.C &&
         fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows) {

@@ -68,7 +68,14 @@ __global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals,
   const int e = blk * 256 + threadIdx.x;
   float* p = totals + size_t(unit) * G * elems;
   float a = 0.f;
-  for (int g = 0; g < G; ++g) a += p[size_t(g) * elems + e];
+  constexpr int BATCH = 16;   // loads in flight per thread
+  for (int g0 = 0; g0 < G; g0 += BATCH) {
+    float t[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) t[i] = g0 + i < G ? p[size_t(g0 + i) * elems + e] : 0.f;
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) a += t[i];
+  }
   p[e] = a;
   if (state != nullptr) state[size_t(unit) * elems + e] = a;
 }
@@ -78,15 +85,37 @@ __global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals,
 template <int DK, int DV, int NT, int SP>
 __device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __restrict__ src,
                                                     int n_sum, float* __restrict__ copy) {
-  for (int e = 4 * threadIdx.x; e < DK * DV; e += 4 * NT) {
-    f32x4 a = *reinterpret_cast<const f32x4*>(src + e);
-    for (int j = 1; j < n_sum; ++j) {
-      const f32x4 b = *reinterpret_cast<const f32x4*>(src + size_t(j) * DK * DV + e);
+  // up to 16 of a thread's loads are in flight before the first is waited for: PIECES pieces of
+  // BATCH matrices (a batch that reaches beyond the last matrix re-reads it and drops it)
+  constexpr int PIECES = DK * DV / (4 * NT) < 4 ? DK * DV / (4 * NT) : 4, BATCH = 16 / PIECES < 4 ? 16 / PIECES : 4;
+  static_assert(DK * DV % (4 * NT * PIECES) == 0, "whole passes of the workgroup");
+  for (int e0 = 4 * threadIdx.x; e0 < DK * DV; e0 += 4 * NT * PIECES) {
+    f32x4 sum[PIECES];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) a[v] += b[v];
+    for (int i = 0; i < PIECES; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j0 = 0; j0 < n_sum; j0 += BATCH) {
+      f32x4 t[BATCH][PIECES];
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b)
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i)
+          t[b][i] = *reinterpret_cast<const f32x4*>(src + size_t(min(j0 + b, n_sum - 1)) * DK * DV + e0 +
+                                                    4 * NT * i);
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) {
+        const bool keep = j0 + b < n_sum;
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sum[i][v] += keep ? t[b][i][v] : 0.f;
+      }
     }
-    if (copy != nullptr) *reinterpret_cast<f32x4*>(copy + e) = a;
-    store4(dst + (e / DV) * SP + e % DV, a[0], a[1], a[2], a[3]);
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int e = e0 + 4 * NT * i;
+      if (copy != nullptr) *reinterpret_cast<f32x4*>(copy + e) = sum[i];
+      store4(dst + (e / DV) * SP + e % DV, sum[i][0], sum[i][1], sum[i][2], sum[i][3]);
+    }
   }
 }
 
@@ -462,7 +491,7 @@ hipError_t run_fwd_bidir(const CausalArgs& a) {
   hipError_t err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, totals));
   if (err != hipSuccess) return err;
   // few segments: the apply workgroups add the totals up themselves (and write `state`)
-  const bool sum_in_apply = a.G <= kMaxSegmentsSummedInScan;
+  const bool sum_in_apply = sum_totals_in_place(a.G, DK, DV);
   if (!sum_in_apply) {
     err = launch_bidir_combine(totals, units, a.G, DK * DV, a.state, a.stream);
     if (err != hipSuccess) return err;
@@ -486,7 +515,7 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
   float* ds_partial = reinterpret_cast<float*>(ws + 2 * state_array_bytes(a.B, a.H, DK, DV, a.G));
   // few segments: the sweeps add the segment totals up themselves while staging them; many:
   // the combine kernel leaves the sum in slot 0
-  const bool few = a.G <= kMaxSegmentsSummedInScan;
+  const bool few = sum_totals_in_place(a.G, DK, DV);
   hipError_t err;
   // S = Kh^T V: the totals the forward left behind (slot 0 is their sum already when the
   // forward ran the combine kernel), or reduced here

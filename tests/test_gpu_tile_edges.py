@@ -40,3 +40,14 @@ def test_16bit_wide_rectangles(cottn, oracle, dtype, dk, dv):
     for i, N in enumerate(ROWS):
         run_shape(cottn, oracle, True, 2, 2, N, dk, dv, dtype, seed=1300 + dk + N,
                   segments=[0, 1, 2][i % 3], saved=i % 2 == 1)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d,segments", [(64, 5), (64, 24), (64, 25), (128, 10), (128, 11), (32, 17)])
+def test_segment_totals_added_in_place_or_carried(cottn, oracle, causal, d, segments):
+    """Up to a number of segments the kernels add the segment totals up themselves, beyond it a
+    launch of its own does: both sides of the line, and batches of totals that do not divide."""
+    N = 64 * segments - 10
+    run_shape(cottn, oracle, causal, 1, 2, N, d, d, "bf16", seed=1400 + d + segments, segments=segments, saved=True)
+    run_shape(cottn, oracle, causal, 1, 1, 32 * segments - 5, d, d, "f32", seed=1500 + d + segments,
+              segments=segments, saved=False)
