@@ -77,6 +77,9 @@ struct BwdCfg {
       lds_pitch(DK) > TPV ||
       (CS == 1 && LDS_BYTES + ELEM * TILEK <= 160 * 1024 &&
        (160 * 1024) / (LDS_BYTES + ELEM * TILEK) == WG_PER_CU);
+  // the masked tiles are formed before the other operands of a 32-token step are read, which
+  // keeps 32 registers fewer in use at a time
+  static constexpr bool MASKED_FIRST = DK == 128 && DV == 128 && CS == 2;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -92,8 +95,12 @@ struct BwdCfg {
 // and results per wave, 32-row steps keep the workgroup at four waves and two to a compute
 // unit: dQ / dK/dV scan at B4 H12 N2048 64 x 128 59 / 55 -> 24 / 26 us, 128 x 64 36 / 38 -> 27 /
 // 27 us.  Square and 32-wide shapes are slower that way (64 x 64 by 3 %, 32 x 32 by 30 %:
-// shorter steps, the masked tiles formed twice), and at 128 x 128 the states alone are 128
-// registers, so that half the budget spills (41 / 48 -> 120 us).
+// shorter steps, the masked tiles formed twice).  At 128 x 128 one workgroup fills the LDS of a
+// compute unit, and four waves on it wait for LDS reads with nothing to switch to: 64-row steps
+// with two waves per row group, eight waves in all (B8 H12 N1024 40 / 48 -> 37 / 41 us, B4 H12
+// N2048 38 / 45 -> 34 / 38 us).  That takes the masked tiles out of the large groups of LDS reads
+// (MASKED_FIRST): with everything read at once 9 and 18 registers spill, a spilled register comes
+// back behind the rows prefetched for the next step, and the scans take 43 / 52 us.
 //
 // fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four.  An
 // fp32 MFMA has a sixteenth of the bf16 rate, so these kernels sit near the matrix units' time
@@ -103,7 +110,7 @@ struct BwdCfg {
 // regrouping: 120 and 160 us).
 template <int DK, int DV, int C> struct BwdSplit {
   static constexpr bool WIDE = DK != DV && DK >= 64 && DV >= 64;
-  static constexpr int CR = WIDE ? 32 : C, CS = ELEM_IS_F32 || WIDE ? 2 : 1;
+  static constexpr int CR = WIDE ? 32 : C, CS = ELEM_IS_F32 || WIDE || (DK == 128 && DV == 128) ? 2 : 1;
 };
 
 // ---------------------------------------------------------------------------------------
@@ -281,7 +288,35 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     for (int p = 0; p < Cfg::NP; ++p) {
       const bool diag_or_below = 2 * p <= rg;
       const int t0 = 32 * p + 4 * q4, t1 = 32 * p + 16 + 4 * q4;  // token order of the A slots
-      frag8 kc[NKT], vcol[AT::NCT], krow[AT::NRT], vr[2][Cfg::KSV];
+      frag8 af;
+      frag8 vr[2][Cfg::KSV];
+      const auto read_values = [&] {
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+          for (int ks = 0; ks < Cfg::KSV; ++ks)
+            vr[half][ks] = lds_row_frag(Vs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
+      };
+      const auto form_masked = [&] {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int jt = 2 * p + half;
+          f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(vr[half][ks], gf[ks], t);
+          // t[v] = dO_(16 rg + r) . v_(16jt + 4 q4 + v); keep key <= query
+          const bool full = jt < rg, diag = jt == rg;
+          put_half(af, half, t, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
+                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
+        }
+      };
+      if (Cfg::MASKED_FIRST && diag_or_below) {
+        read_values();
+        __builtin_amdgcn_sched_barrier(0);
+        form_masked();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      frag8 kc[NKT], vcol[AT::NCT], krow[AT::NRT];
       frag8 qcol[RT::NCT], grow[RT::NRT];
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt) kc[nt] = lds_col_frag(Ks, TPK, t0, t1, colk + 16 * nt, r);
@@ -301,27 +336,10 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int y = 0; y < RT::NRT; ++y)
           grow[y] = lds_col_frag(Gs, TPV, t0, t1, 16 * RT::row_tile(rg, cp, y), r);
       }
-      if (diag_or_below) {
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks)
-            vr[half][ks] = lds_row_frag(Vs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
-      }
+      if (!Cfg::MASKED_FIRST && diag_or_below) read_values();
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
-        frag8 af;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int jt = 2 * p + half;
-          f32x4 t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(vr[half][ks], gf[ks], t);
-          // t[v] = dO_(16 rg + r) . v_(16jt + 4 q4 + v); keep key <= query
-          const bool full = jt < rg, diag = jt == rg;
-          put_half(af, half, t, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
-                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
-        }
+        if (!Cfg::MASKED_FIRST) form_masked();
 #pragma unroll
         for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(kc[nt], af, dq[nt]);
       }
@@ -605,33 +623,49 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       }
       if (diag_or_above) {
         frag8 qr[2][Cfg::KSK], gr[2][Cfg::KSV], qc[NKT];
+        frag8 pf, af;
+        // query tile it against key row 16 rg + r: keep key <= query
+        const auto put_masked = [&](frag8& f, int half, f32x4 t) {
+          const int it = 2 * p + half;
+          const bool full = it > rg, diag = it == rg;
+          put_half(f, half, t, full || (diag && r <= 4 * q4 + 0), full || (diag && r <= 4 * q4 + 1),
+                   full || (diag && r <= 4 * q4 + 2), full || (diag && r <= 4 * q4 + 3));
+        };
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSK; ++ks)
             qr[half][ks] = lds_row_frag(Qs + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
+        if (Cfg::MASKED_FIRST) {  // P is done before the rows of A are read
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            f32x4 tp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < Cfg::KSK; ++ks) tp = mma16(qr[half][ks], kf[ks], tp);
+            put_masked(pf, half, tp);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSV; ++ks)
             gr[half][ks] = lds_row_frag(Gs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
-        }
 #pragma unroll
         for (int nt = 0; nt < NKT; ++nt) qc[nt] = lds_col_frag(Qs, TPK, t0, t1, colk + 16 * nt, r);
         __builtin_amdgcn_sched_barrier(0);
-        frag8 pf, af;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-          const int it = 2 * p + half;
           f32x4 tp = {0.f, 0.f, 0.f, 0.f}, ta = {0.f, 0.f, 0.f, 0.f};
+          if (!Cfg::MASKED_FIRST) {
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSK; ++ks) tp = mma16(qr[half][ks], kf[ks], tp);
+            for (int ks = 0; ks < Cfg::KSK; ++ks) tp = mma16(qr[half][ks], kf[ks], tp);
+          }
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSV; ++ks) ta = mma16(gr[half][ks], vf[ks], ta);
-          // t*[v]: query 16 it + 4 q4 + v, key 16 rg + r; keep key <= query
-          const bool full = it > rg, diag = it == rg;
-          const bool k0 = full || (diag && r <= 4 * q4 + 0), k1 = full || (diag && r <= 4 * q4 + 1),
-                     k2 = full || (diag && r <= 4 * q4 + 2), k3 = full || (diag && r <= 4 * q4 + 3);
-          put_half(pf, half, tp, k0, k1, k2, k3);
-          put_half(af, half, ta, k0, k1, k2, k3);
+          if (!Cfg::MASKED_FIRST) put_masked(pf, half, tp);
+          put_masked(af, half, ta);
         }
 #pragma unroll
         for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);

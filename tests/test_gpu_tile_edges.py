@@ -42,6 +42,14 @@ def test_16bit_wide_rectangles(cottn, oracle, dtype, dk, dv):
                   segments=[0, 1, 2][i % 3], saved=i % 2 == 1)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_16bit_widest(cottn, oracle, dtype):
+    """128 x 128: 64-row steps with two waves per row group."""
+    for i, N in enumerate(ROWS):
+        run_shape(cottn, oracle, True, 2, 2, N, 128, 128, dtype, seed=1350 + N,
+                  segments=[0, 1, 2][i % 3], saved=i % 2 == 1)
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d,segments", [(64, 5), (64, 24), (64, 25), (128, 10), (128, 11), (32, 17)])
 def test_segment_totals_added_in_place_or_carried(cottn, oracle, causal, d, segments):
