@@ -77,13 +77,16 @@ struct BwdCfg {
       lds_pitch(DK) > TPV ||
       (CS == 1 && LDS_BYTES + ELEM * TILEK <= 160 * 1024 &&
        (160 * 1024) / (LDS_BYTES + ELEM * TILEK) == WG_PER_CU);
-  // the masked tiles are formed before the other operands of a 32-token step are read, which
-  // keeps 32 registers fewer in use at a time
-  static constexpr bool MASKED_FIRST = DK == 128 && DV == 128 && CS == 2;
+  // The operands of a 32-token step are read in several groups (masked tiles first), each used
+  // up before the next is read, instead of all at once: fewer registers in use at a time.  For
+  // 128 x 128, where everything at once does not fit, and for fp32, whose MFMAs take so long
+  // that one group's reads hide behind the other wave's products.
+  static constexpr bool PHASED = CS == 2 && (ELEM_IS_F32 || (DK == 128 && DV == 128));
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
-  static constexpr int WAVES_PER_EU = NW / 4 > 2 ? NW / 4 : (WAVES_RAW > 2 ? 2 : WAVES_RAW);
+  static constexpr int WAVES_PER_EU =
+      NW / 4 > 2 ? NW / 4 : (WAVES_RAW > 2 ? 2 : WAVES_RAW);
 };
 
 // Rows a kernel takes at a time (CR, a divisor of the chunk: the regrouping is exact for any)
@@ -98,16 +101,17 @@ struct BwdCfg {
 // shorter steps, the masked tiles formed twice).  At 128 x 128 one workgroup fills the LDS of a
 // compute unit, and four waves on it wait for LDS reads with nothing to switch to: 64-row steps
 // with two waves per row group, eight waves in all (B8 H12 N1024 40 / 48 -> 37 / 41 us, B4 H12
-// N2048 38 / 45 -> 34 / 38 us).  That takes the masked tiles out of the large groups of LDS reads
-// (MASKED_FIRST): with everything read at once 9 and 18 registers spill, a spilled register comes
-// back behind the rows prefetched for the next step, and the scans take 43 / 52 us.
+// N2048 38 / 45 -> 33 / 38 us).  That takes smaller groups of LDS reads (PHASED): with everything
+// read at once 9 and 18 registers spill, a spilled register comes back behind the rows
+// prefetched for the next step, and the scans take 43 / 52 us.
 //
 // fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four.  An
 // fp32 MFMA has a sixteenth of the bf16 rate, so these kernels sit near the matrix units' time
 // (B8 H12 N1024 d64: dQ 20 us and dK/dV 24 us of MFMA at the 153 TFLOP/s a large fp32 product
 // reaches) where their 16-bit twins wait for latencies; 32 rows instead of 64 save a fifth of
-// the masked products.  Measured there: dQ 57 us, dK/dV 67 us (vector-ALU kernels of the same
-// regrouping: 120 and 160 us).
+// the masked products.  Measured there: dQ 47 us, dK/dV 57 us (51 and 60 with the operands of a
+// step read at once; vector-ALU kernels of the same regrouping: 106 and 142 us).  A third workgroup
+// on the compute unit (168 registers) spills and is slower.
 template <int DK, int DV, int C> struct BwdSplit {
   static constexpr bool WIDE = DK != DV && DK >= 64 && DV >= 64;
   static constexpr int CR = WIDE ? 32 : C, CS = ELEM_IS_F32 || WIDE || (DK == 128 && DV == 128) ? 2 : 1;
@@ -310,14 +314,23 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
                    full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
         }
       };
-      if (Cfg::MASKED_FIRST && diag_or_below) {
+      frag8 qcol[RT::NCT], grow[RT::NRT];
+      const bool rev_here = with_rev && RT::active(rg, cp);
+      const auto read_reverse = [&] {
+#pragma unroll
+        for (int x = 0; x < RT::NCT; ++x)
+          qcol[x] = lds_col_frag(Qs, TPK, t0, t1, 16 * RT::col_tile(rg, cp, x), r);
+#pragma unroll
+        for (int y = 0; y < RT::NRT; ++y)
+          grow[y] = lds_col_frag(Gs, TPV, t0, t1, 16 * RT::row_tile(rg, cp, y), r);
+      };
+      if (Cfg::PHASED && diag_or_below) {
         read_values();
         __builtin_amdgcn_sched_barrier(0);
         form_masked();
         __builtin_amdgcn_sched_barrier(0);
       }
       frag8 kc[NKT], vcol[AT::NCT], krow[AT::NRT];
-      frag8 qcol[RT::NCT], grow[RT::NRT];
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt) kc[nt] = lds_col_frag(Ks, TPK, t0, t1, colk + 16 * nt, r);
 #pragma unroll
@@ -328,18 +341,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int y = 0; y < AT::NRT; ++y)
           krow[y] = lds_col_frag(Ks, TPK, t0, t1, 16 * AT::row_tile(rg, cp, y), r);
       }
-      if (with_rev && RT::active(rg, cp)) {
-#pragma unroll
-        for (int x = 0; x < RT::NCT; ++x)
-          qcol[x] = lds_col_frag(Qs, TPK, t0, t1, 16 * RT::col_tile(rg, cp, x), r);
-#pragma unroll
-        for (int y = 0; y < RT::NRT; ++y)
-          grow[y] = lds_col_frag(Gs, TPV, t0, t1, 16 * RT::row_tile(rg, cp, y), r);
+      if (!Cfg::PHASED) {
+        if (rev_here) read_reverse();
+        if (diag_or_below) read_values();
       }
-      if (!Cfg::MASKED_FIRST && diag_or_below) read_values();
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
-        if (!Cfg::MASKED_FIRST) form_masked();
+        if (!Cfg::PHASED) form_masked();
 #pragma unroll
         for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(kc[nt], af, dq[nt]);
       }
@@ -351,8 +359,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
           for (int x = 0; x < AT::NCT; ++x)
             sacc[x][y] = mma16(vcol[x], AT::ROW_OPERAND_IS_RESULT_COLUMN ? kc[y] : krow[y], sacc[x][y]);
       }
+      if (Cfg::PHASED) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (rev_here) read_reverse();
+        __builtin_amdgcn_sched_barrier(0);
+      }
       // reverse total: R^T += dO^T qh over the same tokens
-      if (with_rev && RT::active(rg, cp)) {
+      if (rev_here) {
 #pragma unroll
         for (int y = 0; y < RT::NRT; ++y)
 #pragma unroll
@@ -601,6 +614,55 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     for (int p = 0; p < Cfg::NP; ++p) {
       const bool diag_or_above = 2 * p + 1 >= rg;
       const int t0 = 32 * p + 4 * q4, t1 = 32 * p + 16 + 4 * q4;  // token order of the slots
+      frag8 qr[2][Cfg::KSK], gr[2][Cfg::KSV], qc[NKT];
+      frag8 pf, af;
+      const auto read_queries = [&](int half) {
+#pragma unroll
+        for (int ks = 0; ks < Cfg::KSK; ++ks)
+          qr[half][ks] = lds_row_frag(Qs + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
+      };
+      const auto read_out_grads = [&](int half) {
+#pragma unroll
+        for (int ks = 0; ks < Cfg::KSV; ++ks)
+          gr[half][ks] = lds_row_frag(Gs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
+      };
+      const auto read_query_columns = [&] {
+#pragma unroll
+        for (int nt = 0; nt < NKT; ++nt) qc[nt] = lds_col_frag(Qs, TPK, t0, t1, colk + 16 * nt, r);
+      };
+      // tile of query tile 2p + half and this wave's keys; t[v]: query 16 it + 4 q4 + v, key
+      // 16 rg + r; keep key <= query
+      const auto put_masked = [&](frag8& f, int half, f32x4 t) {
+        const int it = 2 * p + half;
+        const bool full = it > rg, diag = it == rg;
+        put_half(f, half, t, full || (diag && r <= 4 * q4 + 0), full || (diag && r <= 4 * q4 + 1),
+                 full || (diag && r <= 4 * q4 + 2), full || (diag && r <= 4 * q4 + 3));
+      };
+      const auto form_p = [&](int half) {
+        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < Cfg::KSK; ++ks) t = mma16(qr[half][ks], kf[ks], t);
+        return t;
+      };
+      const auto form_a = [&](int half) {
+        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(gr[half][ks], vf[ks], t);
+        return t;
+      };
+      if (Cfg::PHASED && diag_or_above) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          read_queries(half);
+          __builtin_amdgcn_sched_barrier(0);
+          put_masked(pf, half, form_p(half));
+          __builtin_amdgcn_sched_barrier(0);
+          read_out_grads(half);
+          __builtin_amdgcn_sched_barrier(0);
+          put_masked(af, half, form_a(half));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
       frag8 gc[NVT], qcol[AT::NCT], grow[AT::NRT];
 #pragma unroll
       for (int nt = 0; nt < NVT; ++nt) gc[nt] = lds_col_frag(Gs, TPV, t0, t1, colv + 16 * nt, r);
@@ -622,53 +684,29 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
             racc[x][y] = mma16(AT::ROW_OPERAND_IS_RESULT_COLUMN ? gc[y] : grow[y], qcol[x], racc[x][y]);
       }
       if (diag_or_above) {
-        frag8 qr[2][Cfg::KSK], gr[2][Cfg::KSV], qc[NKT];
-        frag8 pf, af;
-        // query tile it against key row 16 rg + r: keep key <= query
-        const auto put_masked = [&](frag8& f, int half, f32x4 t) {
-          const int it = 2 * p + half;
-          const bool full = it > rg, diag = it == rg;
-          put_half(f, half, t, full || (diag && r <= 4 * q4 + 0), full || (diag && r <= 4 * q4 + 1),
-                   full || (diag && r <= 4 * q4 + 2), full || (diag && r <= 4 * q4 + 3));
-        };
+        if (Cfg::PHASED) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+          for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
+          __builtin_amdgcn_sched_barrier(0);
+          read_query_columns();
+          __builtin_amdgcn_sched_barrier(0);
+        } else {
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSK; ++ks)
-            qr[half][ks] = lds_row_frag(Qs + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
-        if (Cfg::MASKED_FIRST) {  // P is done before the rows of A are read
+          for (int half = 0; half < 2; ++half) {
+            read_queries(half);
+            read_out_grads(half);
+          }
+          read_query_columns();
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int half = 0; half < 2; ++half) {
-            f32x4 tp = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < Cfg::KSK; ++ks) tp = mma16(qr[half][ks], kf[ks], tp);
+            const f32x4 tp = form_p(half), ta = form_a(half);
             put_masked(pf, half, tp);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks)
-            gr[half][ks] = lds_row_frag(Gs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
-#pragma unroll
-        for (int nt = 0; nt < NKT; ++nt) qc[nt] = lds_col_frag(Qs, TPK, t0, t1, colk + 16 * nt, r);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          f32x4 tp = {0.f, 0.f, 0.f, 0.f}, ta = {0.f, 0.f, 0.f, 0.f};
-          if (!Cfg::MASKED_FIRST) {
-#pragma unroll
-            for (int ks = 0; ks < Cfg::KSK; ++ks) tp = mma16(qr[half][ks], kf[ks], tp);
+            put_masked(af, half, ta);
           }
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks) ta = mma16(gr[half][ks], vf[ks], ta);
-          if (!Cfg::MASKED_FIRST) put_masked(pf, half, tp);
-          put_masked(af, half, ta);
+          for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
         }
-#pragma unroll
-        for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
 #pragma unroll
         for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16(qc[nt], af, dk[nt]);
       }

@@ -41,20 +41,22 @@ struct TileStage {
   __device__ __forceinline__ void fetch(const elem_t* __restrict__ base, int row0, int n_rows,
                                         bool stream = false) {
     const int tid = threadIdx.x;
-    const int col = (tid % LPR) * EPP;
-    const elem_t* p0 = base + size_t(row0) * D + (tid / LPR) * D + col;
+    // a base that is the same for all lanes plus a 32-bit lane offset that is the same for all
+    // tiles: the addresses then take scalar registers and one vector register
+    const elem_t* rows = base + size_t(row0) * D;
+    const unsigned lane = unsigned((tid / LPR) * D + (tid % LPR) * EPP);
     if (C % RPP == 0 && row0 + C <= n_rows) {
       // whole tile in range (workgroup-uniform): plain loads at constant strides
 #pragma unroll
       for (int p = 0; p < PASSES; ++p)
-        regs[p] = load_rows(p0 + p * RPP * D, stream);
+        regs[p] = load_rows(rows + p * RPP * D + lane, stream);
       return;
     }
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
       uint4 v = {0u, 0u, 0u, 0u};
-      if (lr < C && row0 + lr < n_rows) v = load_rows(p0 + p * RPP * D, stream);
+      if (lr < C && row0 + lr < n_rows) v = load_rows(rows + p * RPP * D + lane, stream);
       regs[p] = v;
     }
   }
@@ -225,13 +227,13 @@ __device__ __forceinline__ void store_row_pieces(const RowPieces<D, NTILES>& p,
                                                  elem_t* __restrict__ dst, int first_row,
                                                  int row_end, int l, int col0 = 0) {
   using RP = RowPieces<D, NTILES>;
+  elem_t* rows = dst + size_t(first_row) * D + col0;   // uniform over the wave
 #pragma unroll
   for (int j = 0; j < RP::PER_LANE; ++j) {
     const int i = l + 64 * j;
-    const int lr = i / RP::PPR, col = col0 + (i % RP::PPR) * EPP;
-    const int row = first_row + lr;
-    if ((RP::PIECES % 64 == 0 || i < RP::PIECES) && row < row_end)
-      store_streaming(dst + size_t(row) * D + col, p.v[j]);
+    const int lr = i / RP::PPR;
+    if ((RP::PIECES % 64 == 0 || i < RP::PIECES) && first_row + lr < row_end)
+      store_streaming(rows + unsigned(lr * D + (i % RP::PPR) * EPP), p.v[j]);
   }
 }
 
