@@ -82,6 +82,8 @@ struct BwdCfg {
   // 128 x 128, where everything at once does not fit, and for fp32, whose MFMAs take so long
   // that one group's reads hide behind the other wave's products.
   static constexpr bool PHASED = CS == 2 && (ELEM_IS_F32 || (DK == 128 && DV == 128));
+  // masked tiles formed by the two waves of a row group together (MaskedExchange); 32-row chunks
+  static constexpr bool SHARE_MASKED = ELEM_IS_F32 && CS == 2 && C == 32;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -107,10 +109,12 @@ struct BwdCfg {
 //
 // fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four.  An
 // fp32 MFMA has a sixteenth of the bf16 rate, so these kernels sit near the matrix units' time
-// (B8 H12 N1024 d64: dQ 20 us and dK/dV 24 us of MFMA at the 153 TFLOP/s a large fp32 product
+// (B8 H12 N1024 d64: dQ 20 us and dK/dV 23 us of MFMA at the 154 TFLOP/s a large fp32 product
 // reaches) where their 16-bit twins wait for latencies; 32 rows instead of 64 save a fifth of
-// the masked products.  Measured there: dQ 47 us, dK/dV 57 us (51 and 60 with the operands of a
-// step read at once; vector-ALU kernels of the same regrouping: 106 and 142 us).  A third workgroup
+// the masked products, and the two waves of a row group form them together and only where
+// something is visible (MaskedExchange; 6 of 18 and 8 of 24 products of a wave before that were
+// masked ones).  Measured there: dQ 45 us, dK/dV 52 us (47 and 57 with every wave forming all of its
+// group's tiles, 51 and 60 with the operands of a step read at once besides).  A third workgroup
 // on the compute unit (168 registers) spills and is slower.
 template <int DK, int DV, int C> struct BwdSplit {
   static constexpr bool WIDE = DK != DV && DK >= 64 && DV >= 64;
@@ -168,6 +172,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   __shared__ float rq[C];
   __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
   __shared__ float ds_wave[Cfg::NW];
+  // A tiles of the two key halves: in the staging tile where there is one (it is written a
+  // barrier after the last of them is read), so that 128 x 32 keeps two workgroups
+  constexpr bool IN_STAGE = Cfg::SHARE_MASKED && Cfg::DQ_OWN_STAGE;
+  using Masked = MaskedExchange<Cfg::SHARE_MASKED ? 2 : 0>;
+  static_assert(!IN_STAGE || sizeof(Masked) <= sizeof(elem_t) * Cfg::TILEK, "the tiles fit the staging tile");
+  __shared__ __attribute__((aligned(16))) char masked_lds[Cfg::SHARE_MASKED && !IN_STAGE ? sizeof(Masked) : 16];
+  Masked& masked = *reinterpret_cast<Masked*>(IN_STAGE ? reinterpret_cast<char*>(Os) : masked_lds);
 
   fetch_argument_now(Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G, seg_rows,
                      inv_eps, sum_totals, seq_len, s_per_unit, state_in);
@@ -175,7 +186,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const int rg = w % Cfg::RG, cp = w / Cfg::RG;   // row group, column part
+  const int rg = row_group<Cfg::RG, CS>(w), cp = w / Cfg::RG;   // row group, column part
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
@@ -265,6 +276,15 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       store_row_pieces<DK, NKT>(finished, dQu, row0 - C + 16 * rg, row_end, l, colk);
     __syncthreads();
 
+    if constexpr (Cfg::SHARE_MASKED) {
+      // this wave's half of the features of the masked tiles (key half 1 is masked for rg = 0)
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        if (half <= rg)
+          masked.put(half, w, l, row_products<Cfg::KSV>(Vs + (16 * half + r) * TPV, Gs + (16 * rg + r) * TPV,
+                                                        16 * Cfg::KSV * cp, q4));
+    }
+
     // earlier chunks: dqh^T += S dO^T (contraction over d_value = along the rows of St)
     frag8 gf[Cfg::KSV];  // dO rows of this wave: column-side operand of every product
 #pragma unroll
@@ -306,8 +326,12 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int half = 0; half < 2; ++half) {
           const int jt = 2 * p + half;
           f32x4 t = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (Cfg::SHARE_MASKED) {
+            if (half <= rg) t = masked.get(half, w, l);
+          } else {
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(vr[half][ks], gf[ks], t);
+            for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(vr[half][ks], gf[ks], t);
+          }
           // t[v] = dO_(16 rg + r) . v_(16jt + 4 q4 + v); keep key <= query
           const bool full = jt < rg, diag = jt == rg;
           put_half(af, half, t, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
@@ -324,8 +348,9 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int y = 0; y < RT::NRT; ++y)
           grow[y] = lds_col_frag(Gs, TPV, t0, t1, 16 * RT::row_tile(rg, cp, y), r);
       };
+      if (Cfg::SHARE_MASKED) __syncthreads();  // the partial tiles of the other waves are there
       if (Cfg::PHASED && diag_or_below) {
-        read_values();
+        if (!Cfg::SHARE_MASKED) read_values();
         __builtin_amdgcn_sched_barrier(0);
         form_masked();
         __builtin_amdgcn_sched_barrier(0);
@@ -348,8 +373,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
         if (!Cfg::PHASED) form_masked();
+        if (Cfg::SHARE_MASKED && rg == 0) {
 #pragma unroll
-        for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(kc[nt], af, dq[nt]);
+          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16_half(kc[nt], af, dq[nt], 0);
+        } else {
+#pragma unroll
+          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(kc[nt], af, dq[nt]);
+        }
       }
       // state update: S += kh^T v over these 32 tokens
       if (AT::active(rg, cp)) {
@@ -449,6 +479,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   __shared__ __attribute__((aligned(16))) elem_t Rl[DK * Cfg::SPV];  // reverse state, [d_key][d_value]
   __shared__ float rk[C];
   __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
+  // P tiles of the two query halves, then the A tiles
+  __shared__ MaskedExchange<Cfg::SHARE_MASKED ? 4 : 0> masked;
 
   fetch_argument_now(Q, K, V, dO, s, dK, dV, rev_states, ds_partial, ds, B, H, N, G, seg_rows,
                      inv_eps, sum_totals, seq_len, s_per_unit, rev_in, rev_out);
@@ -456,7 +488,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const int rg = w % Cfg::RG, cp = w / Cfg::RG;   // row group, column part
+  const int rg = row_group<Cfg::RG, CS>(w), cp = w / Cfg::RG;   // row group, column part
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
@@ -560,6 +592,18 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     }
     __syncthreads();
 
+    if constexpr (Cfg::SHARE_MASKED) {
+      // this wave's half of the features of the masked tiles (query half 0 is masked for rg = 1)
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        if (half >= rg) {
+          masked.put(half, w, l, row_products<Cfg::KSK>(Qs + (16 * half + r) * TPK, Ks + (16 * rg + r) * TPK,
+                                                        16 * Cfg::KSK * cp, q4));
+          masked.put(2 + half, w, l, row_products<Cfg::KSV>(Gs + (16 * half + r) * TPV, Vs + (16 * rg + r) * TPV,
+                                                            16 * Cfg::KSV * cp, q4));
+        }
+    }
+
     frag8 kf[Cfg::KSK], vf[Cfg::KSV];  // this wave's key rows and value rows (column side)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks)
@@ -650,7 +694,20 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int ks = 0; ks < Cfg::KSV; ++ks) t = mma16(gr[half][ks], vf[ks], t);
         return t;
       };
-      if (Cfg::PHASED && diag_or_above) {
+      if constexpr (Cfg::SHARE_MASKED) {
+        __syncthreads();  // the partial tiles of the other waves are there
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          f32x4 tp = {0.f, 0.f, 0.f, 0.f}, ta = {0.f, 0.f, 0.f, 0.f};
+          if (half >= rg) {
+            tp = masked.get(half, w, l);
+            ta = masked.get(2 + half, w, l);
+          }
+          put_masked(pf, half, tp);
+          put_masked(af, half, ta);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      } else if (Cfg::PHASED && diag_or_above) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           read_queries(half);
@@ -685,8 +742,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       }
       if (diag_or_above) {
         if (Cfg::PHASED) {
+          if (Cfg::SHARE_MASKED && rg == 1) {
 #pragma unroll
-          for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
+            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_half(gc[nt], pf, dv[nt], 1);
+          } else {
+#pragma unroll
+            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
+          }
           __builtin_amdgcn_sched_barrier(0);
           read_query_columns();
           __builtin_amdgcn_sched_barrier(0);
@@ -707,8 +769,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 #pragma unroll
           for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
         }
+        if (Cfg::SHARE_MASKED && rg == 1) {
 #pragma unroll
-        for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16(qc[nt], af, dk[nt]);
+          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16_half(qc[nt], af, dk[nt], 1);
+        } else {
+#pragma unroll
+          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16(qc[nt], af, dk[nt]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }

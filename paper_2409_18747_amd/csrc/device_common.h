@@ -97,6 +97,39 @@ __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
 __device__ __forceinline__ int slot_lo(int g) { return ELEM_IS_F32 ? 4 * g : 8 * g; }
 __device__ __forceinline__ int slot_hi(int g) { return ELEM_IS_F32 ? 16 + 4 * g : 8 * g + 4; }
 
+// fp32 only: the same product over half of the k slots, the `half`-th four elements of every
+// lane's fragments (what the other half would contract is known to be zero).
+__device__ __forceinline__ f32x4 mma16_half(frag8 a, frag8 b, f32x4 acc, int half) {
+#ifdef COTTN_ELEM_F32
+  if (half == 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int j = 4; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+  }
+#endif
+  return acc;
+}
+
+// fp32 only: the dot products of 16 rows at x (rows down the result tile) with 16 rows at y (rows
+// along it), over columns first_col .. first_col + 16 BLOCKS - 1 of both.  x, y: this lane's
+// row (lane % 16 of the 16), g: lane / 16.
+template <int BLOCKS>
+__device__ __forceinline__ f32x4 row_products(const elem_t* x, const elem_t* y, int first_col, int g) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#ifdef COTTN_ELEM_F32
+#pragma unroll
+  for (int i = 0; i < BLOCKS; ++i) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(x + first_col + 16 * i + 4 * g);
+    const f32x4 b = *reinterpret_cast<const f32x4*>(y + first_col + 16 * i + 4 * g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+  }
+#endif
+  return acc;
+}
+
 // Operand fragment whose k index runs along an LDS row; p: the row at the first of the 32
 // columns, g: lane / 16.
 __device__ __forceinline__ frag8 lds_row_frag(const elem_t* p, int g) {

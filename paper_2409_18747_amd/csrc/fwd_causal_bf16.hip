@@ -85,9 +85,10 @@ struct FwdCfg {
 // two variants time the same and the smaller workgroup is kept.
 template <int DK, int DV, int C> struct FwdSplit { static constexpr int CS = ELEM_IS_F32 ? 2 : 1; };
 template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
-// (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four;
-// B8 H12 N1024 d64 44 us, of which 14 us is MFMA time and 20 us the rows' way through HBM; the
-// vector-ALU kernel it replaces took 91 us)
+// (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four.  The
+// masked tile is formed by the two waves together, half of the features each, and not where
+// nothing of it is visible: an eighth of the products less.  B8 H12 N1024 d64 37 -> 34 us, of
+// which 15 us is MFMA time and 20 us the rows' way through HBM; d128 131 -> 122 us)
 
 // ---------------------------------------------------------------------------------------
 // Kernel 1: T[unit][g] = sum over the rows of segment g of kh^T v   (fp32, d_key x d_value;
@@ -224,13 +225,15 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   // wider than the queries they do not fit the q rows: own staging tile
   __shared__ __attribute__((aligned(16))) elem_t Os[OWN_STAGE ? Cfg::TILEV : 8];
   __shared__ float rq[C];
+  constexpr bool SHARE_MASKED = ELEM_IS_F32 && CS == 2 && C == 32;
+  __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, seq_len, s_per_unit, stream_q);
   int unit, g;
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
-  const int rg = w % RG, cp = w / RG;  // row group, column part
+  const int rg = row_group<RG, CS>(w), cp = w / RG;  // row group, column part
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
@@ -319,6 +322,15 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       store_row_pieces<DV, NOT>(finished, Ou, row0 - C + 16 * rg, row_end, l, col0);
     __syncthreads();
 
+    if constexpr (SHARE_MASKED) {
+      // this wave's half of the features of the masked tiles (key half 1 is masked for rg = 0)
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        if (half <= rg)
+          masked.put(half, w, l, row_products<Cfg::KSK>(Ks + (16 * half + r) * TPK, Qs + (16 * rg + r) * TPK,
+                                                        16 * Cfg::KSK * cp, q4));
+    }
+
     // ---- inter-chunk part: O^T += S^T Q^T (contraction over d_key = rows of Sl)
     frag8 qf[Cfg::KSK];  // q rows of this wave: column-side operand of every product
 #pragma unroll
@@ -357,13 +369,14 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int y = 0; y < ST::NRT; ++y)
           vrow[y] = lds_col_frag(Vs, TPV, t0, t1, 16 * ST::row_tile(rg, cp, y), r);
       }
-      if (diag_or_below) {
+      if (diag_or_below && !SHARE_MASKED) {
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSK; ++ks)
             kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
       }
+      if (SHARE_MASKED) __syncthreads();  // the partial tiles of the other waves are there
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
         frag8 pf;
@@ -371,15 +384,24 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int half = 0; half < 2; ++half) {
           const int jt = 2 * p + half;
           f32x4 pacc = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (SHARE_MASKED) {
+            if (half <= rg) pacc = masked.get(half, w, l);
+          } else {
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSK; ++ks) pacc = mma16(kr[half][ks], qf[ks], pacc);
+            for (int ks = 0; ks < Cfg::KSK; ++ks) pacc = mma16(kr[half][ks], qf[ks], pacc);
+          }
           // pacc[v] = q_(16 rg + r) . k_(16jt + 4*q4 + v); keep key <= query
           const bool full = jt < rg, diag = jt == rg;
           put_half(pf, half, pacc, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
                    full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
         }
+        if (SHARE_MASKED && rg == 0) {
 #pragma unroll
-        for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16(vc[nt], pf, oacc[nt]);
+          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16_half(vc[nt], pf, oacc[nt], 0);
+        } else {
+#pragma unroll
+          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16(vc[nt], pf, oacc[nt]);
+        }
       }
       // state update S^T += v^T kh over these 32 tokens
       if (ST::active(rg, cp)) {

@@ -151,6 +151,28 @@ struct SplitTiles {
   }
 };
 
+// fp32, two waves on each of the two row groups of a 32-row chunk: both need the group's masked
+// tiles, and an fp32 MFMA is slow enough that forming them twice shows (8 of the 24 products a
+// wave has in a chunk of the dK/dV scan at d = 64).  Each wave contracts half of the features and
+// passes its partial tile on through LDS: slot = one per tile of the group.
+template <int TILES>
+struct MaskedExchange {
+  f32x4 part[TILES][4][64];   // [tile][wave][lane]
+  __device__ __forceinline__ void put(int tile, int w, int l, f32x4 t) { part[tile][w][l] = t; }
+  // both halves of the features (waves w and w ^ 2 serve the same row group)
+  __device__ __forceinline__ f32x4 get(int tile, int w, int l) const {
+    return part[tile][w & 1][l] + part[tile][w | 2][l];
+  }
+};
+
+// Row group and column part of a wave.  With the masked tiles of a chunk skipped where nothing is
+// visible, one of the two row groups of the fp32 scans has less to do; wave w runs on SIMD w % 4,
+// so every second round of workgroups (256 compute units) swaps the groups.
+template <int RG, int CS>
+__device__ __forceinline__ int row_group(int w) {
+  return ELEM_IS_F32 && RG == 2 ? (w + (blockIdx.x >> 8)) % RG : w % RG;
+}
+
 // acc += the wave's tiles of the stored states first..last, `load(state, x, y)` returning
 // tile (x, y) of one of them.  States are taken BATCH at a time with every load of a batch
 // issued before the first addition, so a batch costs one memory latency, not one per state.
