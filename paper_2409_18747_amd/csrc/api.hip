@@ -119,9 +119,10 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   }
   const long units = long(B) * H;
   const long n_chunks = (long(N) + C - 1) / C;
+  const bool bidir = op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR;
   long want = g_tuned_segments;
+  plan->by_unit = want <= 0 && bidir && bidir_by_unit(units, N, dtype == COTTN_F32, dk, dv);
   if (want <= 0) {
-    const bool bidir = op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR;
     want = bidir ? bidir_segments(units, n_chunks, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
   }
   if (want > n_chunks) want = n_chunks;
@@ -130,8 +131,9 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   const long G = n_chunks > 0 ? (n_chunks + chunks_per_seg - 1) / chunks_per_seg : 1;
   if (units * G > 2147483647L / 4) return false;
   plan->C = C;
-  plan->G = int(G);
-  plan->seg_rows = int(chunks_per_seg * C);
+  plan->split = int(G);
+  plan->G = plan->by_unit ? 1 : int(G);
+  plan->seg_rows = int((plan->by_unit ? n_chunks : chunks_per_seg) * C);
   return true;
 }
 
@@ -212,7 +214,7 @@ int cottn_segments_dkdv(int op, int B, int H, int N, int dk, int dv, int chunk, 
   if (op < COTTN_OP_FWD_CAUSAL || op > COTTN_OP_BWD_BIDIR) return 0;
   SeqPlan plan;
   if (!make_plan(op, B, H, N, dk, dv, chunk, dtype, &plan)) return 0;
-  return plan.G;
+  return plan.split;
 }
 
 int cottn_segments(int op, int B, int H, int N, int d, int chunk, int dtype) {
@@ -420,6 +422,7 @@ int fwd_bidir_any(const void* Q, const void* K, const void* V, const float* s, c
   a.Q = Q; a.K = K; a.V = V; a.s = s; a.O = O; a.state = state; a.workspace = workspace;
   a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
   a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
+  a.by_unit = plan.by_unit;
   a.eps = eps; a.stream = stream;
   return map_hip(dtype == COTTN_BF16 ? fwd_bidir_bf16(a) : dtype == COTTN_F16 ? fwd_bidir_f16(a) : fwd_bidir_f32(a));
 }
@@ -444,6 +447,7 @@ int bwd_bidir_any(const void* Q, const void* K, const void* V, const float* s, c
   a.Q = Q; a.K = K; a.V = V; a.s = s; a.dO = dO; a.dQ = dQ; a.dK = dK; a.dV = dV; a.ds = ds;
   a.workspace = workspace; a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
   a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
+  a.by_unit = plan.by_unit;
   a.eps = eps; a.stream = stream;
   if (fwd_workspace != nullptr && sum_totals_in_place(plan.G, dk, dv)) {
     SeqPlan fwd_plan;

@@ -20,6 +20,7 @@
 //             number as <S, G>); second sweep (K, V -> dK, dV) applies G.  Every row of the
 //             seven tensors is moved once.  A backward that was not handed the forward's
 //             totals reduces Kh^T V first;
+//   by unit   16-bit rows, short sequences or many of them: the two launches of a call are one.
 //   combine   only with many segments: sums the segment totals per (batch, head) into slot 0;
 //             with few, the kernels add the totals up themselves while staging them.
 //
@@ -87,8 +88,9 @@ __device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __
                                                     int n_sum, float* __restrict__ copy) {
   // up to 16 of a thread's loads are in flight before the first is waited for: PIECES pieces of
   // BATCH matrices (a batch that reaches beyond the last matrix re-reads it and drops it)
-  constexpr int PIECES = DK * DV / (4 * NT) < 4 ? DK * DV / (4 * NT) : 4, BATCH = 16 / PIECES < 4 ? 16 / PIECES : 4;
-  static_assert(DK * DV % (4 * NT * PIECES) == 0, "whole passes of the workgroup");
+  constexpr int PASSES = DK * DV / (4 * NT), PIECES = PASSES < 1 ? 1 : PASSES < 4 ? PASSES : 4;
+  constexpr int BATCH = 16 / PIECES < 4 ? 16 / PIECES : 4;
+  static_assert(PASSES % PIECES == 0, "whole passes of the workgroup (or less than one)");
   for (int e0 = 4 * threadIdx.x; e0 < DK * DV; e0 += 4 * NT * PIECES) {
     f32x4 sum[PIECES];
 #pragma unroll
@@ -119,41 +121,17 @@ __device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __
   }
 }
 
-// O rows of one segment: O_i = s r_i (q_i S), accumulated as O^T = S^T Q^T.  `totals` holds
-// n_sum stored matrices per unit at a stride of `slots` matrices; the workgroup of segment 0
-// writes their sum to `state` when that is asked for.
+// O_i = s r_i (q_i S) for the rows row_begin .. row_end - 1 of one unit, with S in Sl (not yet
+// behind a barrier); the first C rows have been fetched.  Own: staging tile, or null.
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
-    const elem_t* __restrict__ Q, const float* __restrict__ s, elem_t* __restrict__ O,
-    const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, int H, int N,
-    int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+__device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst, elem_t* Qs, const elem_t* Sl,
+                                           elem_t* Os, float* rq, const elem_t* __restrict__ Qu,
+                                           elem_t* __restrict__ Ou, float scale, int row_begin, int row_end,
+                                           float inv_eps, int w, int l) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
   constexpr int TP = Cfg::TPK, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];  // raw q
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];  // [d_key][d_value]
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? Cfg::TILEV : 8];
-  __shared__ float rq[C];
-
-  fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
-                     s_per_unit);
-  int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
-  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
-            r = l % 16, q4 = l / 16;
-  const elem_t* Qu = Q + size_t(unit) * N * DK;
-  elem_t* Ou = O + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
-  const int row_begin = g * seg_rows;
-  const int seg_end = min(N, row_begin + seg_rows);
-  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
-
-  Stage qst;
-  qst.fetch(Qu, row_begin, row_end);
-  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, totals + size_t(unit) * slots * DK * DV, n_sum,
-                                  (state != nullptr && g == 0) ? state + size_t(unit) * DK * DV
-                                                               : nullptr);
-
+  const int r = l % 16, q4 = l / 16;
   RowPieces<DV> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
@@ -195,63 +173,60 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
     const int last = row_begin + (row_end - row_begin - 1) / C * C;
     store_row_pieces<DV>(finished, Ou, last + 16 * w, row_end, l);
   }
-  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
 }
 
-// Backward, first sweep: dQ rows of one segment and the segment's total of Qh^T dO.  It needs
-// only S = Kh^T V, which the forward already reduced, so the rows of Q and dO are read once,
-// here, for both dQ and the matrix G that the second sweep applies:
-//   dqh^T = S dO^T (over d_value),  dq_i = s r_i (dqh_i - qh_i (qh_i . dqh_i)),
-//   G_segment = sum over the rows of qh_i^T dO_i,  ds share = sum of qh_i . dqh_i.
-// Q is stored in LDS as qh = r_i q_i: it is contracted over the tokens in G, and the chain
-// rule wants the normalised row anyway.  Every wave reads all rows of both tiles (the total
-// contracts them over the tokens), so finished dQ rows are staged in a tile of their own where
-// that fits.
+// O rows of one segment: O_i = s r_i (q_i S), accumulated as O^T = S^T Q^T.  `totals` holds
+// n_sum stored matrices per unit at a stride of `slots` matrices; the workgroup of segment 0
+// writes their sum to `state` when that is asked for.
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
-    const elem_t* __restrict__ Q, const elem_t* __restrict__ dO, const float* __restrict__ s,
-    elem_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
-    float* __restrict__ g_totals, float* __restrict__ ds_partial, int H, int N, int G,
-    int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+__global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
+    const elem_t* __restrict__ Q, const float* __restrict__ s, elem_t* __restrict__ O,
+    const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, int H, int N,
+    int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
-  using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
-  using StageK = TileStage<DK, C, Cfg::NT>;
-  using StageV = TileStage<DV, C, Cfg::NT>;
-  constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
+  using Stage = TileStage<DK, C, Cfg::NT>;
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];  // raw q
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];  // [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? Cfg::TILEV : 8];
   __shared__ float rq[C];
-  __shared__ float ds_wave[Cfg::NW];
 
-  fetch_argument_now(Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows,
-                     inv_eps, seq_len, s_per_unit);
+  fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
+                     s_per_unit);
   int unit, g;
   unit_and_segment(blockIdx.x, G, unit, g);
-  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
-            r = l % 16, q4 = l / 16;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
   const elem_t* Qu = Q + size_t(unit) * N * DK;
-  const elem_t* Gu = dO + size_t(unit) * N * DV;
-  elem_t* dQu = dQ + size_t(unit) * N * DK;
+  elem_t* Ou = O + size_t(unit) * N * DV;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
 
-  StageK qst;
-  StageV gst;
+  Stage qst;
   qst.fetch(Qu, row_begin, row_end);
-  gst.fetch(Gu, row_begin, row_end);
-  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
+  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, totals + size_t(unit) * slots * DK * DV, n_sum,
+                                  (state != nullptr && g == 0) ? state + size_t(unit) * DK * DV
+                                                               : nullptr);
 
-  // racc[x][y]: element [v] of lane (r, q4) is G[key 16 ct + r][value 16 rt + 4 q4 + v]
-  f32x4 racc[RT::NCT][RT::NRT];
-#pragma unroll
-  for (int x = 0; x < RT::NCT; ++x)
-#pragma unroll
-    for (int y = 0; y < RT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float ds_lane = 0.f;
+  apply_rows<DK, DV, C>(qst, Qs, Sl, Cfg::FWD_OWN_STAGE ? Os : nullptr, rq, Qu, Ou, scale, row_begin, row_end,
+                        inv_eps, w, l);
+  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
+}
+
+// dQ rows row_begin .. row_end - 1 of one unit, with S in Sl (not yet behind a barrier); the first C
+// rows have been fetched.  Adds the rows' Qh^T dO to racc (element [v] of lane (r, q4) is
+// G[key 16 ct + r][value 16 rt + 4 q4 + v]) and their qh . dqh to ds_lane of the first lane row.
+template <int DK, int DV, int C, class RT = AccTiles<DV, DK, C / 16>>
+__device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst,
+                                        TileStage<DV, C, BiCfg<DK, DV, C>::NT>& gst,
+                                        f32x4 (&racc)[RT::NCT][RT::NRT], float& ds_lane, elem_t* Qs, elem_t* Gs,
+                                        elem_t* Os, const elem_t* Sl, float* rq, const elem_t* __restrict__ Qu,
+                                        const elem_t* __restrict__ Gu, elem_t* __restrict__ dQu, float scale,
+                                        int row_begin, int row_end, float inv_eps, int w, int l) {
+  using Cfg = BiCfg<DK, DV, C>;
+  using StageK = TileStage<DK, C, Cfg::NT>;
+  constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
+  const int r = l % 16, q4 = l / 16;
   RowPieces<DK> finished;  // dQ rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DK>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
@@ -320,6 +295,63 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
     const int last = row_begin + (row_end - row_begin - 1) / C * C;
     store_row_pieces<DK>(finished, dQu, last + 16 * w, row_end, l);
   }
+}
+
+// Backward, first sweep: dQ rows of one segment and the segment's total of Qh^T dO.  It needs
+// only S = Kh^T V, which the forward already reduced, so the rows of Q and dO are read once,
+// here, for both dQ and the matrix G that the second sweep applies:
+//   dqh^T = S dO^T (over d_value),  dq_i = s r_i (dqh_i - qh_i (qh_i . dqh_i)),
+//   G_segment = sum over the rows of qh_i^T dO_i,  ds share = sum of qh_i . dqh_i.
+// Q is stored in LDS as qh = r_i q_i: it is contracted over the tokens in G, and the chain
+// rule wants the normalised row anyway.  Every wave reads all rows of both tiles (the total
+// contracts them over the tokens), so finished dQ rows are staged in a tile of their own where
+// that fits.
+template <int DK, int DV, int C>
+__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
+    const elem_t* __restrict__ Q, const elem_t* __restrict__ dO, const float* __restrict__ s,
+    elem_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
+    float* __restrict__ g_totals, float* __restrict__ ds_partial, int H, int N, int G,
+    int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+  using Cfg = BiCfg<DK, DV, C>;
+  using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
+  using StageK = TileStage<DK, C, Cfg::NT>;
+  using StageV = TileStage<DV, C, Cfg::NT>;
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh = r_i q_i
+  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
+  __shared__ float rq[C];
+  __shared__ float ds_wave[Cfg::NW];
+
+  fetch_argument_now(Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows,
+                     inv_eps, seq_len, s_per_unit);
+  int unit, g;
+  unit_and_segment(blockIdx.x, G, unit, g);
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
+            r = l % 16, q4 = l / 16;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Gu = dO + size_t(unit) * N * DV;
+  elem_t* dQu = dQ + size_t(unit) * N * DK;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_begin = g * seg_rows;
+  const int seg_end = min(N, row_begin + seg_rows);
+  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
+
+  StageK qst;
+  StageV gst;
+  qst.fetch(Qu, row_begin, row_end);
+  gst.fetch(Gu, row_begin, row_end);
+  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
+
+  // racc[x][y]: element [v] of lane (r, q4) is G[key 16 ct + r][value 16 rt + 4 q4 + v]
+  f32x4 racc[RT::NCT][RT::NRT];
+#pragma unroll
+  for (int x = 0; x < RT::NCT; ++x)
+#pragma unroll
+    for (int y = 0; y < RT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ds_lane = 0.f;
+  dq_rows<DK, DV, C>(qst, gst, racc, ds_lane, Qs, Gs, Cfg::DQ_OWN_STAGE ? Os : nullptr, Sl, rq, Qu, Gu, dQu, scale,
+                     row_begin, row_end, inv_eps, w, l);
   if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, seg_end);  // rows that do not exist
 
   if (RT::active(w)) {
@@ -343,58 +375,19 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   }
 }
 
-// Backward, second sweep: dK and dV rows of one segment from G = Qh^T dO (the sum of the n_sum
-// stored matrices at g_totals); the first H workgroups also finish ds from the n_ds partial
-// sums per (batch, head) that the first sweep left.  Accumulated transposed:
-//   dkh^T = G V^T (over d_value),  (k G)^T = G^T k^T (over d_key),
-//   dk_j = s r_j (dkh_j - kh_j (kh_j . dkh_j)),  dv_j = s r_j (k_j G).
+// dK and dV rows row_begin .. row_end - 1 of one unit, with G in Gl (not yet behind a barrier);
+// the first C rows have been fetched.
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
-    const elem_t* __restrict__ K, const elem_t* __restrict__ V, const float* __restrict__ s,
-    elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
-    int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, int H,
-    int N, int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+__device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& kst,
+                                          TileStage<DV, C, BiCfg<DK, DV, C>::NT>& vst, elem_t* Ks, elem_t* Vs,
+                                          const elem_t* Gl, float* rk, const elem_t* __restrict__ Ku,
+                                          const elem_t* __restrict__ Vu, elem_t* __restrict__ dKu,
+                                          elem_t* __restrict__ dVu, float scale, int row_begin, int row_end,
+                                          float inv_eps, int w, int l) {
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
-  using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
-  __shared__ __attribute__((aligned(16))) elem_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
-  __shared__ float rk[C];
-
-  fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
-                     seg_rows, inv_eps, seq_len, s_per_unit);
-  int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
-  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
-            r = l % 16, q4 = l / 16;
-  const elem_t* Ku = K + size_t(unit) * N * DK;
-  const elem_t* Vu = V + size_t(unit) * N * DV;
-  elem_t* dKu = dK + size_t(unit) * N * DK;
-  elem_t* dVu = dV + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
-  const int row_begin = g * seg_rows;
-  const int seg_end = min(N, row_begin + seg_rows);
-  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
-
-  StageK kst;
-  StageV vst;
-  kst.fetch(Ku, row_begin, row_end);
-  vst.fetch(Vu, row_begin, row_end);
-
-  // ds[h] = sum of the shares of all batches (ds[b][h], one batch, with a scale per unit)
-  if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
-    float t = 0.f;
-    const int n = s_per_unit ? n_ds : B * n_ds;
-    for (int i = l; i < n; i += 64)
-      t += s_per_unit ? ds_partial[size_t(blockIdx.x) * n_ds + i]
-                      : ds_partial[(size_t(i / n_ds) * H + blockIdx.x) * n_ds + (i % n_ds)];
-    t = group_sum<64>(t);
-    if (l == 0) ds[blockIdx.x] = t;
-  }
-  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Gl, g_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
-
+  const int r = l % 16, q4 = l / 16;
   RowPieces<DK> done_k;  // rows of the previous chunk, stored one chunk late
   RowPieces<DV> done_v;
 #pragma unroll
@@ -467,11 +460,207 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     store_row_pieces<DK>(done_k, dKu, last + 16 * w, row_end, l);
     store_row_pieces<DV>(done_v, dVu, last + 16 * w, row_end, l);
   }
+}
+
+// Backward, second sweep: dK and dV rows of one segment from G = Qh^T dO (the sum of the n_sum
+// stored matrices at g_totals); the first H workgroups also finish ds from the n_ds partial
+// sums per (batch, head) that the first sweep left.  Accumulated transposed:
+//   dkh^T = G V^T (over d_value),  (k G)^T = G^T k^T (over d_key),
+//   dk_j = s r_j (dkh_j - kh_j (kh_j . dkh_j)),  dv_j = s r_j (k_j G).
+template <int DK, int DV, int C>
+__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
+    const elem_t* __restrict__ K, const elem_t* __restrict__ V, const float* __restrict__ s,
+    elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
+    int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, int H,
+    int N, int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+  using Cfg = BiCfg<DK, DV, C>;
+  using StageK = TileStage<DK, C, Cfg::NT>;
+  using StageV = TileStage<DV, C, Cfg::NT>;
+  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // raw k
+  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
+  __shared__ __attribute__((aligned(16))) elem_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
+  __shared__ float rk[C];
+
+  fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
+                     seg_rows, inv_eps, seq_len, s_per_unit);
+  int unit, g;
+  unit_and_segment(blockIdx.x, G, unit, g);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
+  const elem_t* Ku = K + size_t(unit) * N * DK;
+  const elem_t* Vu = V + size_t(unit) * N * DV;
+  elem_t* dKu = dK + size_t(unit) * N * DK;
+  elem_t* dVu = dV + size_t(unit) * N * DV;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_begin = g * seg_rows;
+  const int seg_end = min(N, row_begin + seg_rows);
+  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
+
+  StageK kst;
+  StageV vst;
+  kst.fetch(Ku, row_begin, row_end);
+  vst.fetch(Vu, row_begin, row_end);
+
+  // ds[h] = sum of the shares of all batches (ds[b][h], one batch, with a scale per unit)
+  if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
+    float t = 0.f;
+    const int n = s_per_unit ? n_ds : B * n_ds;
+    for (int i = l; i < n; i += 64)
+      t += s_per_unit ? ds_partial[size_t(blockIdx.x) * n_ds + i]
+                      : ds_partial[(size_t(i / n_ds) * H + blockIdx.x) * n_ds + (i % n_ds)];
+    t = group_sum<64>(t);
+    if (l == 0) ds[blockIdx.x] = t;
+  }
+  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Gl, g_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
+
+  dkdv_rows<DK, DV, C>(kst, vst, Ks, Vs, Gl, rk, Ku, Vu, dKu, dVu, scale, row_begin, row_end, inv_eps, w, l);
   if (seq_len != nullptr) {  // rows that do not exist
     zero_rows<DK>(dKu, row_end, seg_end);
     zero_rows<DV>(dVu, row_end, seg_end);
   }
 }
+
+// ---------------------------------------------------------------------------------------
+// 16-bit rows, short sequences or many of them (launch.h: bidir_by_unit): a whole (batch, head) per
+// workgroup, forward and backward in one launch each.  Split over launches such a call is in large
+// part launches, first loads and the matrix on its way through the workspace into every workgroup
+// (16 KB of fp32 for each segment's 64 x 64 total, 32 KB of rows behind it).  128-row steps and eight
+// waves keep the walk short; B16 H12 N389 f16 with lengths from a quarter of N up: forward 14.7 -> 10.6
+// us, backward 21.4 -> 17.9; B32 H12 N512 bf16 22 -> 18.5 and 36 -> 32 us, 5.4 TB/s of its rows.
+#ifndef COTTN_ELEM_F32
+constexpr int UNIT_ROWS = 128;
+
+// Forward: S = Kh^T V over the sequence in the accumulators, published to LDS (and to the workspace,
+// for the backward), then applied to the Q rows.
+template <int DK, int DV, int C>
+__global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
+    const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
+    const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ totals,
+    float* __restrict__ state, int H, int N, float inv_eps, const int* __restrict__ seq_len,
+    int s_per_unit) {
+  using Cfg = BiCfg<DK, DV, C>;
+  using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
+  constexpr int SP = Cfg::SP;
+  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // kh, then raw q
+  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // v, then finished rows
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // [d_key][d_value]
+  __shared__ float rq[C];
+
+  fetch_argument_now(Q, K, V, s, O, totals, state, H, N, inv_eps, seq_len, s_per_unit);
+  const int unit = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, r = l % 16, q4 = l / 16;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Ku = K + size_t(unit) * N * DK;
+  const elem_t* Vu = V + size_t(unit) * N * DV;
+  elem_t* Ou = O + size_t(unit) * N * DV;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_end = valid_rows(seq_len, unit, H, N);
+
+  f32x4 acc[ST::NCT][ST::NRT];   // layout: add_rows_to_state
+#pragma unroll
+  for (int x = 0; x < ST::NCT; ++x)
+#pragma unroll
+    for (int y = 0; y < ST::NRT; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  TileStage<DK, C, Cfg::NT> kst, qst;
+  TileStage<DV, C, Cfg::NT> vst;
+  kst.fetch(Ku, 0, row_end);
+  vst.fetch(Vu, 0, row_end);
+  qst.fetch(Qu, 0, row_end);
+  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, 0, row_end, inv_eps, w, l);
+  if (ST::active(w)) {
+#pragma unroll
+    for (int x = 0; x < ST::NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < ST::NRT; ++y) {
+        const int key = 16 * ST::row_tile(w, y) + r, value = 16 * ST::col_tile(w, x) + 4 * q4;
+        store4(Sl + key * SP + value, acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
+        const size_t at = size_t(unit) * DK * DV + key * DV + value;
+        store_state_words(totals + at, acc[x][y]);
+        if (state != nullptr) *reinterpret_cast<f32x4*>(state + at) = acc[x][y];
+      }
+  }
+  __syncthreads();  // every wave is done with the K and V tiles
+  apply_rows<DK, DV, C>(qst, Ks, Sl, Cfg::FWD_OWN_STAGE ? Vs : nullptr, rq, Qu, Ou, scale, 0, row_end, inv_eps, w, l);
+  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, N);  // rows that do not exist
+}
+
+// Backward: the dQ sweep with G = Qh^T dO in the accumulators, G published to LDS in the place of S,
+// then the dK/dV sweep.  The unit's share of ds goes to ds_out[unit]: ds itself where a scale belongs
+// to one unit, else a partial sum for bidir_sum_ds.
+template <int DK, int DV, int C>
+__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
+    const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
+    const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
+    elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ s_totals,
+    float* __restrict__ ds_out, int H, int N, float inv_eps, const int* __restrict__ seq_len,
+    int s_per_unit) {
+  using Cfg = BiCfg<DK, DV, C>;
+  using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
+  constexpr int SP = Cfg::SP;
+  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh, then raw k
+  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO, then v
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
+  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, then Qh^T dO, [d_key][d_value]
+  __shared__ float rq[C];
+  __shared__ float ds_wave[Cfg::NW];
+
+  fetch_argument_now(Q, K, V, dO, s, dQ, dK, dV, s_totals, ds_out, H, N, inv_eps, seq_len, s_per_unit);
+  const int unit = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, r = l % 16, q4 = l / 16;
+  const size_t k_rows = size_t(unit) * N * DK, v_rows = size_t(unit) * N * DV;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_end = valid_rows(seq_len, unit, H, N);
+
+  TileStage<DK, C, Cfg::NT> qst, kst;
+  TileStage<DV, C, Cfg::NT> gst, vst;
+  qst.fetch(Q + k_rows, 0, row_end);
+  gst.fetch(dO + v_rows, 0, row_end);
+  stage_summed_matrix<DK, DV, Cfg::NT, SP>(Sl, s_totals + size_t(unit) * DK * DV, 1, nullptr);
+  f32x4 racc[RT::NCT][RT::NRT];
+#pragma unroll
+  for (int x = 0; x < RT::NCT; ++x)
+#pragma unroll
+    for (int y = 0; y < RT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ds_lane = 0.f;
+  dq_rows<DK, DV, C>(qst, gst, racc, ds_lane, Qs, Gs, Cfg::DQ_OWN_STAGE ? Os : nullptr, Sl, rq, Q + k_rows,
+                     dO + v_rows, dQ + k_rows, scale, 0, row_end, inv_eps, w, l);
+  kst.fetch(K + k_rows, 0, row_end);
+  vst.fetch(V + v_rows, 0, row_end);
+  if (seq_len != nullptr) zero_rows<DK>(dQ + k_rows, row_end, N);  // rows that do not exist
+
+  ds_lane = group_sum<64>(ds_lane);   // lanes of the first lane row hold the row sums
+  if (l == 0) ds_wave[w] = ds_lane;
+  __syncthreads();  // (also where the sequence is empty and Sl has only just been staged)
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < Cfg::NW; ++i) t += ds_wave[i];
+    ds_out[unit] = t;
+  }
+  if (RT::active(w)) {
+#pragma unroll
+    for (int x = 0; x < RT::NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < RT::NRT; ++y)
+        store4(Sl + (16 * RT::col_tile(w, x) + r) * SP + 16 * RT::row_tile(w, y) + 4 * q4, racc[x][y][0],
+               racc[x][y][1], racc[x][y][2], racc[x][y][3]);
+  }
+  dkdv_rows<DK, DV, C>(kst, vst, Qs, Gs, Sl, rq, K + k_rows, V + v_rows, dK + k_rows, dV + v_rows, scale, 0, row_end,
+                       inv_eps, w, l);
+  if (seq_len != nullptr) {  // rows that do not exist
+    zero_rows<DK>(dK + k_rows, row_end, N);
+    zero_rows<DV>(dV + v_rows, row_end, N);
+  }
+}
+
+// ds[h] = sum over the batch of the units' shares (one wave per head)
+__global__ __launch_bounds__(64) void bidir_sum_ds(const float* __restrict__ ds_partial, float* __restrict__ ds,
+                                                   int B, int H) {
+  float t = 0.f;
+  for (int b = threadIdx.x; b < B; b += 64) t += ds_partial[size_t(b) * H + blockIdx.x];
+  t = group_sum<64>(t);
+  if (threadIdx.x == 0) ds[blockIdx.x] = t;
+}
+#endif  // COTTN_ELEM_F32
 
 SegmentTotalsArgs totals_args(const CausalArgs& a, const void* X, const void* Y, float* dst) {
   SegmentTotalsArgs t{};
@@ -488,6 +677,13 @@ hipError_t run_fwd_bidir(const CausalArgs& a) {
   using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   float* totals = static_cast<float*>(a.workspace);
+#ifndef COTTN_ELEM_F32
+  if (a.by_unit)
+    return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, UNIT_ROWS>, dim3(units),
+                         dim3(UNIT_ROWS * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+                         static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
+                         static_cast<elem_t*>(a.O), totals, a.state, a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
+#endif
   hipError_t err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, totals));
   if (err != hipSuccess) return err;
   // few segments: the apply workgroups add the totals up themselves (and write `state`)
@@ -529,6 +725,20 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
     }
     s_src = s_totals;
   }
+#ifndef COTTN_ELEM_F32
+  if (a.by_unit) {
+    // with a scale per unit, or one batch, a unit's share of ds is ds
+    const bool whole = a.s_per_unit || a.B == 1;
+    err = launch_kernel(COTTN_SYM_STR(bwd_bidir_unit), COTTN_SYM(bwd_bidir_unit)<DK, DV, UNIT_ROWS>, dim3(units),
+                        dim3(UNIT_ROWS * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+                        static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V),
+                        static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ),
+                        static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), s_src, whole ? a.ds : ds_partial,
+                        a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
+    if (err != hipSuccess || whole) return err;
+    return launch_kernel("bidir_sum_ds", bidir_sum_ds, dim3(a.H), dim3(64), 0, a.stream, ds_partial, a.ds, a.B, a.H);
+  }
+#endif
   err = launch_kernel(COTTN_SYM_STR(bwd_bidir_dq), COTTN_SYM(bwd_bidir_dq)<DK, DV, C>, dim3(units * a.G),
                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q),
                       static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ), s_src, a.G,

@@ -123,10 +123,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   const int row_begin = g * seg_rows;
   const int row_end = min(valid_rows(seq_len, unit, H, N), row_begin + seg_rows);
 
-  // acc[x][y] = S tile (key tile row_tile(y), value tile col_tile(x)), held with the keys
-  // along the lanes: element [v] of lane (r, q4) is S[16 kt + r][16 vt + 4 q4 + v], the
-  // orientation the forward and the dQ scan keep their running state in
-  f32x4 acc[ST::NCT][ST::NRT];
+  f32x4 acc[ST::NCT][ST::NRT];   // layout: add_rows_to_state
 #pragma unroll
   for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
@@ -136,36 +133,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   StageV vst;
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
-  for (int row0 = row_begin; row0 < row_end; row0 += C) {
-    float rk[StageK::PASSES];
-    kst.row_rinv(inv_eps, rk);
-    __syncthreads();  // previous chunk's reads of Ks/Vs are done
-    kst.commit_scaled(Ks, rk);
-    vst.commit_plain(Vs);
-    if (row0 + C < row_end) {
-      kst.fetch(Ku, row0 + C, row_end);
-      vst.fetch(Vu, row0 + C, row_end);
-    }
-    __syncthreads();
-    if (ST::active(w)) {
-#pragma unroll
-      for (int p = 0; p < Cfg::NP; ++p) {
-        frag8 bv[ST::NCT], ak[ST::NRT];
-#pragma unroll
-        for (int x = 0; x < ST::NCT; ++x)
-          bv[x] = lds_col_frag_ks(Vs, Cfg::TPV, p, q4, 16 * ST::col_tile(w, x), r);
-#pragma unroll
-        for (int y = 0; y < ST::NRT; ++y)
-          ak[y] = lds_col_frag_ks(Ks, Cfg::TPK, p, q4, 16 * ST::row_tile(w, y), r);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int y = 0; y < ST::NRT; ++y)
-#pragma unroll
-          for (int x = 0; x < ST::NCT; ++x) acc[x][y] = mma16(bv[x], ak[y], acc[x][y]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
+  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, row_begin, row_end, inv_eps, w, l);
   if (ST::active(w)) {
     float* out = seg_state + (size_t(unit) * n_slots + g) * DK * DV;
 #pragma unroll

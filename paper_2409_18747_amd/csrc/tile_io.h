@@ -202,6 +202,50 @@ __device__ __forceinline__ void add_stored_states(f32x4 (&acc)[NCT][NRT], int fi
   }
 }
 
+// acc += kh^T v over rows row_begin .. row_end - 1 of one unit, C rows at a time; the first C rows
+// of K and V have been fetched.  acc[x][y] = S tile (key tile row_tile(y), value tile col_tile(x)),
+// held with the keys along the lanes: element [v] of lane (r, q4) is S[16 kt + r][16 vt + 4 q4 + v],
+// the orientation the forward and the dQ scan keep their running state in.  Ends with the tiles
+// still being read: a barrier has to follow before they are written again.
+template <int DK, int DV, int C, int NT, class ST = AccTiles<DK, DV, NT / 64>>
+__device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT], TileStage<DK, C, NT>& kst,
+                                                  TileStage<DV, C, NT>& vst, elem_t* Ks, elem_t* Vs,
+                                                  const elem_t* __restrict__ Ku, const elem_t* __restrict__ Vu,
+                                                  int row_begin, int row_end, float inv_eps, int w, int l) {
+  constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);
+  const int r = l % 16, q4 = l / 16;
+  for (int row0 = row_begin; row0 < row_end; row0 += C) {
+    float rk[TileStage<DK, C, NT>::PASSES];
+    kst.row_rinv(inv_eps, rk);
+    __syncthreads();  // previous chunk's reads of Ks/Vs are done
+    kst.commit_scaled(Ks, rk);
+    vst.commit_plain(Vs);
+    if (row0 + C < row_end) {
+      kst.fetch(Ku, row0 + C, row_end);
+      vst.fetch(Vu, row0 + C, row_end);
+    }
+    __syncthreads();
+    if (ST::active(w)) {
+#pragma unroll
+      for (int p = 0; p < C / 32; ++p) {
+        frag8 bv[ST::NCT], ak[ST::NRT];
+#pragma unroll
+        for (int x = 0; x < ST::NCT; ++x)
+          bv[x] = lds_col_frag_ks(Vs, TPV, p, q4, 16 * ST::col_tile(w, x), r);
+#pragma unroll
+        for (int y = 0; y < ST::NRT; ++y)
+          ak[y] = lds_col_frag_ks(Ks, TPK, p, q4, 16 * ST::row_tile(w, y), r);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int y = 0; y < ST::NRT; ++y)
+#pragma unroll
+          for (int x = 0; x < ST::NCT; ++x) acc[x][y] = mma16(bv[x], ak[y], acc[x][y]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+
 // A wave's finished result block (16 rows x NTILES*16 columns, by default all D columns) as
 // whole 16-byte pieces of rows, one or more per lane, ready for coalesced global stores.
 template <int D, int NTILES = D / 16>

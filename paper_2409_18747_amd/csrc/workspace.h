@@ -10,6 +10,10 @@ struct SeqPlan {
   int C;
   int G;
   int seg_rows;
+  // a bidirectional call that takes a whole (batch, head) per workgroup (bidir_by_unit): one
+  // segment, in place of the `split` it would have been cut into
+  bool by_unit;
+  int split;
 };
 
 bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype, SeqPlan* plan);

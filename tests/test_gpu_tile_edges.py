@@ -50,6 +50,19 @@ def test_16bit_widest(cottn, oracle, dtype):
                   segments=[0, 1, 2][i % 3], saved=i % 2 == 1)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("dk,dv", DIMS)
+def test_bidirectional_by_unit(cottn, oracle, dtype, dk, dv):
+    """A (batch, head) per workgroup in 128-row steps: edges of a step, and the most rows for few, for
+    many (160) and for very many (192) of them."""
+    wide = dk == 128 and dv == 128
+    for i, (B, H, N) in enumerate([(2, 2, 1), (2, 3, 127), (2, 2, 128), (8, 8, 129) if wide else (1, 2, 129),
+                                   (8, 8, 256) if wide else (2, 2, 256), (20, 8, 257), (16, 12, 513)]):
+        if N > 256 and (dk, dv) not in ((32, 32), (64, 64)):
+            continue
+        run_shape(cottn, oracle, False, B, H, N, dk, dv, dtype, seed=1600 + dk + dv + N, saved=i % 2 == 1)
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d,segments", [(64, 5), (64, 24), (64, 25), (128, 10), (128, 11), (32, 17)])
 def test_segment_totals_added_in_place_or_carried(cottn, oracle, causal, d, segments):
