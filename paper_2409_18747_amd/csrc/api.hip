@@ -83,18 +83,24 @@ long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv
 }
 
 // Segments per (batch, head) for the bidirectional calls.  Their kernels have no chain to
-// shorten and little to set up: three workgroups per compute unit measured best (B32 H12 N512:
-// 59.2 us per forward + backward with 2 segments, 60.7 with 1), in at most four segments, whose
-// totals are soon added up; at 128 x 128 one (the dQ sweep fills the LDS of a compute unit: B8
-// H12 N1024 2 segments 97 us, 3 segments 116).  Few units with long sequences are cut further,
+// shorten and little to set up: about three workgroups per compute unit measured best (B24 H8 N3000
+// d64, forward + backward: 154 us with 4 segments, 164 with 2), in at most four segments, whose
+// totals are soon added up.  Two fit a compute unit at a time, so 193 to 256 units take two
+// segments (B32 H8 N2048: 134 us, 150 us with 3).  At 128 x 128 one workgroup fills a compute
+// unit (B8 H12 N1024 2 segments 91 us, 3 segments 116), and so it does in the dQ sweep of 16-bit
+// rows with 128 and 64 or 128 and 32 columns (B16 H8 N1024 64 x 128 2 segments 63 us, 4 segments
+// 74; from 129 units on, where that leaves one, four are the better again).  Few units with long sequences are cut further,
 // until (nearly) every compute unit has a workgroup and none has two: B1 H2 N65536 128
-// segments 76 us, 64 segments 95; B1 H12 N8192 d128 19 segments 122 us, 22 segments 151.
-long bidir_segments(long units, long n_chunks, int dk, int dv) {
-  long want = dk == 128 && dv == 128 ? kComputeUnits / units : (3 * kComputeUnits + units - 1) / units;
+// segments 69 us (64 segments, with 64-row steps, 95); B1 H12 N8192 16 segments 42 us, 32 segments 53.
+long bidir_segments(long units, long N, bool f32, int dk, int dv) {
+  const bool one_per_cu = (dk == 128 && dv == 128) ||
+                          (!f32 && units <= kComputeUnits / 2 && (dk == 128 || (dk == 64 && dv == 128)));
+  long want = one_per_cu ? kComputeUnits / units : (3 * kComputeUnits + units - 1) / units;
+  if (units > 192 && units <= 256 && want > 2) want = 2;
   if (want > 4) want = 4;
-  if (units * want < kComputeUnits && n_chunks >= 8 * want) {
+  if (units * want < kComputeUnits && N > 512 * want - 64) {
     want = kComputeUnits / units;
-    if (want > n_chunks / 2) want = n_chunks / 2;   // at least two chunks each
+    if (want > N / 128) want = N / 128;   // at least 128 rows each
   }
   return want;
 }
@@ -114,16 +120,16 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   } else {
     C = chunk == 0 ? 32 : chunk;
     if (C != 32) return false;
-    // (the bidirectional kernels have no quadratic part inside a chunk and take 64 rows a time)
-    if (op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR) C = 64;
   }
+  // (the bidirectional kernels have no quadratic part inside a chunk)
+  if (op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR) C = bidir_step_rows(dtype == COTTN_F32);
   const long units = long(B) * H;
   const long n_chunks = (long(N) + C - 1) / C;
   const bool bidir = op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR;
   long want = g_tuned_segments;
   plan->by_unit = want <= 0 && bidir && bidir_by_unit(units, N, dtype == COTTN_F32, dk, dv);
   if (want <= 0) {
-    want = bidir ? bidir_segments(units, n_chunks, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
+    want = bidir ? bidir_segments(units, N, dtype == COTTN_F32, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
   }
   if (want > n_chunks) want = n_chunks;
   if (want < 1) want = 1;

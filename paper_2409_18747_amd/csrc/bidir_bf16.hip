@@ -527,8 +527,6 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
 // waves keep the walk short; B16 H12 N389 f16 with lengths from a quarter of N up: forward 14.7 -> 10.6
 // us, backward 21.4 -> 17.9; B32 H12 N512 bf16 22 -> 18.5 and 36 -> 32 us, 5.4 TB/s of its rows.
 #ifndef COTTN_ELEM_F32
-constexpr int UNIT_ROWS = 128;
-
 // Forward: S = Kh^T V over the sequence in the accumulators, published to LDS (and to the workspace,
 // for the backward), then applied to the Q rows.
 template <int DK, int DV, int C>
@@ -673,14 +671,14 @@ SegmentTotalsArgs totals_args(const CausalArgs& a, const void* X, const void* Y,
 
 template <int DK, int DV>
 hipError_t run_fwd_bidir(const CausalArgs& a) {
-  constexpr int C = 64;
+  constexpr int C = bidir_step_rows(ELEM_IS_F32);
   using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   float* totals = static_cast<float*>(a.workspace);
 #ifndef COTTN_ELEM_F32
   if (a.by_unit)
-    return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, UNIT_ROWS>, dim3(units),
-                         dim3(UNIT_ROWS * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+    return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, C>, dim3(units),
+                         dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
                          static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
                          static_cast<elem_t*>(a.O), totals, a.state, a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
 #endif
@@ -701,7 +699,7 @@ hipError_t run_fwd_bidir(const CausalArgs& a) {
 
 template <int DK, int DV>
 hipError_t run_bwd_bidir(const CausalArgs& a) {
-  constexpr int C = 64;
+  constexpr int C = bidir_step_rows(ELEM_IS_F32);
   using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   char* ws = static_cast<char*>(a.workspace);
@@ -729,8 +727,8 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
   if (a.by_unit) {
     // with a scale per unit, or one batch, a unit's share of ds is ds
     const bool whole = a.s_per_unit || a.B == 1;
-    err = launch_kernel(COTTN_SYM_STR(bwd_bidir_unit), COTTN_SYM(bwd_bidir_unit)<DK, DV, UNIT_ROWS>, dim3(units),
-                        dim3(UNIT_ROWS * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+    err = launch_kernel(COTTN_SYM_STR(bwd_bidir_unit), COTTN_SYM(bwd_bidir_unit)<DK, DV, C>, dim3(units),
+                        dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
                         static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V),
                         static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ),
                         static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), s_src, whole ? a.ds : ds_partial,

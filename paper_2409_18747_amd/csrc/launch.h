@@ -48,19 +48,26 @@ constexpr bool sum_totals_in_place(int G, int dk, int dv) {
   return G <= 24 && long(G - 1) * dk * dv * 4 <= 600 * 1024;
 }
 
+// Rows a step of the bidirectional kernels takes (a wave per 16 of them).  16-bit: 128; with 64 a
+// workgroup has four waves to cover latencies with and twice the barriers (forward + backward, 64 ->
+// 128 rows: B4 H8 N4096 d64 50 -> 42 us, B16 H8 N4096 138 -> 132 us, B1 H8 N16384 d32 45 -> 38 us, B2 H8
+// N1000 d128 53 -> 46 us, B16 H16 N4096 d128 634 -> 631 us).  fp32 tiles of 128 rows and 128 columns
+// would not fit the LDS.
+constexpr int bidir_step_rows(bool f32) { return f32 ? 64 : 128; }
+
 // Whether a bidirectional call with 16-bit rows takes a whole (batch, head) per workgroup, forward and
 // backward in one launch each (bidir_bf16.hip: fwd_bidir_unit, bwd_bidir_unit), or splits the sequence
 // over workgroups and the work over two launches each.  A unit's rows are walked one step after the
 // other, so either they are few or the units alone have to fill the compute units.  Forward +
-// backward, split / by unit: 8 units of 120 rows 22 / 20 us, of 250 rows at 128 x 128 31 / 34; 32 units
-// of 200 rows d64 26 / 22 us; 128 units of 512 rows d64 29.9 / 30.3 us, 160 units 34.9 / 32.4, 384 units
-// 58 / 53; 160 units of 1024 rows 52.6 / 54.1 us, 192 units 59 / 56, 512 units 142 / 121, at 32 x 32 192
+// backward, split / by unit: 8 units of 120 rows 22 / 20 us, of 250 rows at 128 x 128 32 / 33; 32 units
+// of 200 rows d64 26 / 22 us; 128 units of 500 rows d64 28 / 30 us, 160 units of 512 37 / 32, 384 units
+// 58 / 53; 160 units of 1024 rows 52.6 / 54.1 us, 192 units 59 / 54, 384 units 98 / 93, at 32 x 32 192
 // units 29 / 33; 272 units of 1500 rows 118 / 119 us, 320 units of 2048 rows 187 / 194 us.  (fp32 steps
 // last longer, and only 224 to 256 units gain: always split.)
 constexpr bool bidir_by_unit(long units, int N, bool f32, int dk, int dv) {
   if (f32) return false;
   if (N <= 128) return true;
-  if (N <= 256) return dk < 128 || dv < 128 || units >= 64;
+  if (N <= 256) return dk < 128 || dv < 128 || units >= 96;
   if (N <= 512) return units >= 160;
   return N <= 1536 && units >= 192 && (dk > 32 || dv > 32);
 }
