@@ -277,7 +277,7 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
 #pragma unroll
         for (int y = 0; y < RT::NRT; ++y)
 #pragma unroll
-          for (int x = 0; x < RT::NCT; ++x) racc[x][y] = mma16(grow[y], qcol[x], racc[x][y]);
+          for (int x = 0; x < RT::NCT; ++x) racc[x][y] = mma16_add(grow[y], qcol[x], racc[x][y]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }

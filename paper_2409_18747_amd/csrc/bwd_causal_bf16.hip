@@ -375,10 +375,10 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         if (!Cfg::PHASED) form_masked();
         if (Cfg::SHARE_MASKED && rg == 0) {
 #pragma unroll
-          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16_half(kc[nt], af, dq[nt], 0);
+          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16_half_add(kc[nt], af, dq[nt], 0);
         } else {
 #pragma unroll
-          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(kc[nt], af, dq[nt]);
+          for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16_add(kc[nt], af, dq[nt]);
         }
       }
       // state update: S += kh^T v over these 32 tokens
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int y = 0; y < AT::NRT; ++y)
 #pragma unroll
           for (int x = 0; x < AT::NCT; ++x)
-            sacc[x][y] = mma16(vcol[x], AT::ROW_OPERAND_IS_RESULT_COLUMN ? kc[y] : krow[y], sacc[x][y]);
+            sacc[x][y] = mma16_add(vcol[x], AT::ROW_OPERAND_IS_RESULT_COLUMN ? kc[y] : krow[y], sacc[x][y]);
       }
       if (Cfg::PHASED) {
         __builtin_amdgcn_sched_barrier(0);
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 #pragma unroll
         for (int y = 0; y < RT::NRT; ++y)
 #pragma unroll
-          for (int x = 0; x < RT::NCT; ++x) racc[x][y] = mma16(grow[y], qcol[x], racc[x][y]);
+          for (int x = 0; x < RT::NCT; ++x) racc[x][y] = mma16_add(grow[y], qcol[x], racc[x][y]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -738,16 +738,16 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int y = 0; y < AT::NRT; ++y)
 #pragma unroll
           for (int x = 0; x < AT::NCT; ++x)
-            racc[x][y] = mma16(AT::ROW_OPERAND_IS_RESULT_COLUMN ? gc[y] : grow[y], qcol[x], racc[x][y]);
+            racc[x][y] = mma16_add(AT::ROW_OPERAND_IS_RESULT_COLUMN ? gc[y] : grow[y], qcol[x], racc[x][y]);
       }
       if (diag_or_above) {
         if (Cfg::PHASED) {
           if (Cfg::SHARE_MASKED && rg == 1) {
 #pragma unroll
-            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_half(gc[nt], pf, dv[nt], 1);
+            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_half_add(gc[nt], pf, dv[nt], 1);
           } else {
 #pragma unroll
-            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
+            for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_add(gc[nt], pf, dv[nt]);
           }
           __builtin_amdgcn_sched_barrier(0);
           read_query_columns();
@@ -767,14 +767,14 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
             put_masked(af, half, ta);
           }
 #pragma unroll
-          for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16(gc[nt], pf, dv[nt]);
+          for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_add(gc[nt], pf, dv[nt]);
         }
         if (Cfg::SHARE_MASKED && rg == 1) {
 #pragma unroll
-          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16_half(qc[nt], af, dk[nt], 1);
+          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16_half_add(qc[nt], af, dk[nt], 1);
         } else {
 #pragma unroll
-          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16(qc[nt], af, dk[nt]);
+          for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16_add(qc[nt], af, dk[nt]);
         }
       }
       __builtin_amdgcn_sched_barrier(0);

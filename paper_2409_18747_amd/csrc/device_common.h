@@ -97,9 +97,20 @@ __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
 __device__ __forceinline__ int slot_lo(int g) { return ELEM_IS_F32 ? 4 * g : 8 * g; }
 __device__ __forceinline__ int slot_hi(int g) { return ELEM_IS_F32 ? 16 + 4 * g : 8 * g + 4; }
 
-// fp32 only: the same product over half of the k slots, the `half`-th four elements of every
+// The products over 32 tokens added to a sum that is longer.  fp32: formed on their own and added
+// as one addend, so that the sum is rounded once per 32 tokens and not once per four (causal, N =
+// 4000, d = 32: error against 64 bits 3.7e-7 -> 1.9e-7; B8 H12 N1024 d64 151 us either way; 16-bit operands are off by 2^-9 or
+// 2^-12 each, and their sums take the products directly).
+__device__ __forceinline__ f32x4 mma16_add(frag8 a, frag8 b, f32x4 sum) {
+  if (!ELEM_IS_F32) return mma16(a, b, sum);
+  const f32x4 t = mma16(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
+  return f32x4{sum[0] + t[0], sum[1] + t[1], sum[2] + t[2], sum[3] + t[3]};
+}
+
+// fp32 only: the same over half of the k slots, the `half`-th four elements of every
 // lane's fragments (what the other half would contract is known to be zero).
-__device__ __forceinline__ f32x4 mma16_half(frag8 a, frag8 b, f32x4 acc, int half) {
+__device__ __forceinline__ f32x4 mma16_half_add(frag8 a, frag8 b, f32x4 sum, int half) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #ifdef COTTN_ELEM_F32
   if (half == 0) {
 #pragma unroll
@@ -109,7 +120,7 @@ __device__ __forceinline__ f32x4 mma16_half(frag8 a, frag8 b, f32x4 acc, int hal
     for (int j = 4; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
   }
 #endif
-  return acc;
+  return f32x4{sum[0] + acc[0], sum[1] + acc[1], sum[2] + acc[2], sum[3] + acc[3]};
 }
 
 // fp32 only: the dot products of 16 rows at x (rows down the result tile) with 16 rows at y (rows

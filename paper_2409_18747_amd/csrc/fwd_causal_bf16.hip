@@ -365,10 +365,10 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         }
         if (SHARE_MASKED && rg == 0) {
 #pragma unroll
-          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16_half(vc[nt], pf, oacc[nt], 0);
+          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16_half_add(vc[nt], pf, oacc[nt], 0);
         } else {
 #pragma unroll
-          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16(vc[nt], pf, oacc[nt]);
+          for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16_add(vc[nt], pf, oacc[nt]);
         }
       }
       // state update S^T += v^T kh over these 32 tokens
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int y = 0; y < ST::NRT; ++y)
 #pragma unroll
           for (int x = 0; x < ST::NCT; ++x)
-            sacc[x][y] = mma16(ST::ROW_OPERAND_IS_RESULT_COLUMN ? vc[y] : vrow[y], kcol[x], sacc[x][y]);
+            sacc[x][y] = mma16_add(ST::ROW_OPERAND_IS_RESULT_COLUMN ? vc[y] : vrow[y], kcol[x], sacc[x][y]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }

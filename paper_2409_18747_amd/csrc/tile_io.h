@@ -239,7 +239,7 @@ __device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT]
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y)
 #pragma unroll
-          for (int x = 0; x < ST::NCT; ++x) acc[x][y] = mma16(bv[x], ak[y], acc[x][y]);
+          for (int x = 0; x < ST::NCT; ++x) acc[x][y] = mma16_add(bv[x], ak[y], acc[x][y]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
