@@ -53,8 +53,8 @@ int scan_workgroups_per_cu(int C, int dtype, int dk, int dv) {
 // the scans.  A workgroup walks `steps` chunks and pays about two more to start (first rows,
 // stored states); all start together, so a launch lasts as long as the compute unit with the
 // most workgroups, which holds `per_cu` at a time; a step takes 1 with two workgroups on the
-// compute unit and 0.75 alone (B8 H12 N1024 d64, dQ scan: 13.3 us with one per unit, 17.1 with
-// two).  More than one segment costs the totals kernel, and each segment's totals have to be
+// compute unit and 0.8 alone (B8 H12 N1024 d64, dQ scan: 13.3 us with one per unit, 17.1 with
+// two; B17 H8 N413 d64, forward + backward: 3 segments 38 us, one 46).  More than one segment costs the totals kernel, and each segment's totals have to be
 // added up, by the workgroups or by a carry launch.  What the model buys over a fixed number of
 // workgroups is that no compute unit ends up with one more than the others: B4 H12 N1024 d128
 // fp32 8 segments (384 workgroups, one per compute unit at a time) 346 us, 5 (240) 279 us; B5 H12
@@ -68,11 +68,11 @@ long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv
     const long g = (n_chunks + steps - 1) / steps;
     steps = (n_chunks + g - 1) / g;
     const long on_cu = (units * g + kComputeUnits - 1) / kComputeUnits;
-    const auto step_time = [](long n) { return 0.5 + 0.25 * double(n); };
+    const auto step_time = [](long n) { return 0.6 + 0.2 * double(n); };
     const double rounds = double(on_cu / per_cu) * step_time(per_cu) +
                           (on_cu % per_cu ? step_time(on_cu % per_cu) : 0.0);
     double cost = rounds * double(steps + 2);
-    if (g > 1) cost += sum_totals_in_place(int(g), dk, dv) ? 1.5 + 0.1 * double(g) : 4.0 + 0.05 * double(g);
+    if (g > 1) cost += sum_totals_in_place(int(g), dk, dv) ? 0.9 + 0.1 * double(g) : 4.0 + 0.05 * double(g);
     if (g == 1 || cost < best) {
       best = cost;
       best_g = g;
