@@ -315,6 +315,12 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
+// Puts the calling thread's segment override back when a call that sets one of its own returns.
+struct SegmentsForCall {
+  const int before = g_tuned_segments;
+  ~SegmentsForCall() { g_tuned_segments = before; }
+};
+
 int static_workspace(void** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return COTTN_E_HIP;
@@ -339,7 +345,19 @@ int cottn_fwd_causal_static(const void* Q, const void* K, const void* V, const f
   if (st != COTTN_OK) return st;
   SeqPlan plan;
   if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
-  const size_t need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
+  size_t need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
+  // a split whose states do not fit the array gives way to one of about 384 workgroups (512 for
+  // long segments, 256 at 16-bit d = 128), for this call
+  const SegmentsForCall restore;
+  if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES) && g_tuned_segments <= 0) {
+    const long units = long(B) * H;
+    long want = dtype != COTTN_F32 && d == 128 ? kComputeUnits / units : (384 + units - 1) / units;
+    if (want < 1) want = 1;
+    if (!(dtype != COTTN_F32 && d == 128) && N > 16 * want * plan.C - plan.C) want = (512 + units - 1) / units;
+    g_tuned_segments = int(want);
+    if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
+    need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
+  }
   if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES)) return COTTN_E_WORKSPACE;
   void* ws = nullptr;
   if (need > 0 && (st = static_workspace(&ws)) != COTTN_OK) return st;

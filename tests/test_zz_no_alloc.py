@@ -45,3 +45,21 @@ def test_two_calls_in_a_row_second_smaller():
     one_call(cottn, 1, 2, 8192, 64, "bf16", seed=73)
     one_call(cottn, 1, 3, 700, 32, "f16", seed=74, with_state=False)
     one_call(cottn, 2, 2, 300, 64, "f32", seed=75)
+
+
+def test_split_gives_way_to_the_array():
+    """A shape whose usual split needs more than the array: the call takes a coarser one.  The same
+    sums in another grouping: operands are rounded to 2^-11, results differ by less than the suite's
+    fp16 bound."""
+    import torch
+    import paper_2409_18747_amd.binding as cottn
+    B, H, N, d = 32, 5, 1988, 128
+    assert cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, H, N, d, 0, cottn.COTTN_F16) > cottn.STATIC_WORKSPACE_BYTES
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    Q, K, V = (torch.randn(B, H, N, d, device="cuda", generator=gen).half() for _ in range(3))
+    s = torch.ones(H, device="cuda")
+    O = torch.full_like(Q, float("nan"))
+    cottn.cottn_fwd_causal_static(Q, K, V, s, O)
+    ref = cottn.cottn_fwd_causal(Q, K, V, s)
+    assert float((O.float() - ref.float()).abs().max() / ref.float().abs().max()) <= 2.5e-3
+    assert cottn.cottn_segments(cottn.OP_FWD_CAUSAL, B, H, N, d, 0, cottn.COTTN_F16) > 1  # nothing stays set
