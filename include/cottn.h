@@ -83,7 +83,10 @@ typedef enum {
 } cottn_op;
 
 /* Bytes of workspace the given operation needs for these arguments (0 for COTTN_OP_STEP).
- * Returns (size_t)-1 if the arguments are not supported.  Host only; touches no GPU. */
+ * Returns (size_t)-1 if the arguments are not supported.  Host only; touches no GPU.
+ * A causal call keeps one fp32 state per segment (the backward two), and the library cuts a sequence
+ * into segments only where the B*H units leave compute units idle: fewer than 512 + B*H segments in
+ * all (1024 + B*H for fp32 32 x 32), 64 MB of states at most. */
 size_t cottn_workspace_bytes(int op, int B, int H, int N, int d, int chunk, int dtype);
 
 /* Number of sequence segments per (batch, head) the library will scan in parallel for
@@ -116,8 +119,9 @@ int cottn_fwd_causal(const void* Q, const void* K, const void* V, const float* s
  * hipMalloc.  Same arguments, results and errors as cottn_fwd_causal without the two workspace
  * arguments: the segment states live in a COTTN_STATIC_WORKSPACE_BYTES array inside the
  * library's own device code (each GPU the library runs on holds it until the process ends).
- * Shapes whose cottn_workspace_bytes(COTTN_OP_FWD_CAUSAL, ...) exceeds that size are rejected
- * with COTTN_E_WORKSPACE before anything is enqueued.  The call allocates and frees nothing
+ * Where the library's own split needs more than that, the call takes the finest split that fits;
+ * a split set by cottn_tune_segments that does not fit is rejected with COTTN_E_WORKSPACE before
+ * anything is enqueued.  The call allocates and frees nothing
  * (the array's address is looked up once per device, on the first call with that device
  * current; hip_stream must belong to the current device).  Every call on a GPU uses that
  * GPU's one array: calls that may overlap on one GPU (different streams, different threads)

@@ -41,43 +41,82 @@ bool dims_ok(int B, int H, int N, int dk, int dv) {
 
 constexpr int kComputeUnits = 256;
 
-// Workgroups of the causal scans that a compute unit holds at once (LDS and registers).
-int scan_workgroups_per_cu(int C, int dtype, int dk, int dv) {
-  if (C > 64) return 1;
-  const int big = dk > dv ? dk : dv, small = dk > dv ? dv : dk;
-  if (dtype == COTTN_F32) return big == 32 ? 3 : big == 128 && small >= 64 ? 1 : 2;
-  return big == 32 ? 4 : small == 128 ? 1 : 2;
+// Segments per (batch, head) for the causal calls.  The usual split: about one and a half workgroups
+// per compute unit (384), two for long chains (16 chunks or more per segment), never more than one
+// at 16-bit 128 x 128, where a workgroup fills a compute unit's LDS.
+long usual_causal_segments(long units, long n_chunks, int dtype, int dk, int dv) {
+  long want;
+  if (dtype != COTTN_F32 && dk == 128 && dv == 128) {
+    want = kComputeUnits / units;
+  } else {
+    want = (384 + units - 1) / units;
+    if (n_chunks >= 16 * want) want = (512 + units - 1) / units;
+  }
+  want = want > n_chunks ? n_chunks : want < 1 ? 1 : want;
+  const long steps = n_chunks > 0 ? (n_chunks + want - 1) / want : 1;
+  return n_chunks > 0 ? (n_chunks + steps - 1) / steps : 1;
 }
 
-// Segments per (batch, head) for the causal calls: the split with the least time by a model of
-// the scans.  A workgroup walks `steps` chunks and pays about two more to start (first rows,
-// stored states); all start together, so a launch lasts as long as the compute unit with the
-// most workgroups, which holds `per_cu` at a time; a step takes 1 with two workgroups on the
-// compute unit and 0.8 alone (B8 H12 N1024 d64, dQ scan: 13.3 us with one per unit, 17.1 with
-// two; B17 H8 N413 d64, forward + backward: 3 segments 38 us, one 46).  More than one segment costs the totals kernel, and each segment's totals have to be
-// added up, by the workgroups or by a carry launch.  What the model buys over a fixed number of
-// workgroups is that no compute unit ends up with one more than the others: B4 H12 N1024 d128
-// fp32 8 segments (384 workgroups, one per compute unit at a time) 346 us, 5 (240) 279 us; B5 H12
-// N5000 d32 7 segments 74 us, 8 60 us; B1 H16 N8192 d64 22 segments 78 us, 16 68 us.
+// What a forward and its backward take with g segments, in microseconds, by a model of the kernels.
+// A chunk step of the three scans takes `step`, as the rows are wide, and more with a second
+// workgroup on the compute unit; a workgroup walks its steps and pays about two more to start (first
+// rows, stored states), and the compute unit with the most workgroups, of which it runs `at_once` at
+// a time, ends last.  More than one segment costs the totals kernel, and the segments' totals have
+// to be added up, by every workgroup (three scans read them) or by two carry launches.  Fitted to the
+// times of 3700 shapes (1 to 1280 units of 128 to 65536 rows, all pairs of widths, the splits that put
+// up to 1300 workgroups on the chip): off by 8 to 12 %.
+double causal_call_us(long units, long n_chunks, long g, int dtype, int dk, int dv) {
+  const bool f32 = dtype == COTTN_F32;
+  const long steps = (n_chunks + g - 1) / g, on_cu = (units * g + kComputeUnits - 1) / kComputeUnits;
+  const long at_once = dk == 32 && dv == 32 ? 4 : 2;
+  const double step = (f32 ? 0.085 : 0.041) * (dk + dv), next_one = f32 ? 0.63 : 0.37;
+  const auto together = [&](long n) { return n > 0 ? 1.0 + next_one * double(n - 1) : 0.0; };
+  double us = step * double(steps + 1.8) * (double(on_cu / at_once) * together(at_once) + together(on_cu % at_once));
+  if (g > 1) {
+    const double state = double(dk) * dv * 4.0 / 1024.0 + 3.7;   // KB, and what a small one costs besides
+    us += 5.2 + 0.2 * step * double(steps * on_cu);
+    us += causal_totals_in_place(units, int(g), dk, dv) ? 0.036 * state * double(g - 1) : 8.8 + 0.02 * state * double(g);
+  }
+  return us;
+}
+
+// The split with the least time by the model, if that promises 8 % over the usual one (what the model
+// is off by), among those with up to two workgroups per compute unit (four of fp32 32 x 32, which
+// fit).  More gain the backward little and cost the forward, which runs three workgroups or more at
+// once, a second round (768 units of 1024 rows at 64 x 64: 2 segments 86 / 291 us for the forward /
+// with its backward, 1 segment 64 / 275).  Forward / with backward at 64 x 64, usual -> chosen: 64 units
+// of 2048 rows 6 -> 8 segments 24 / 66 -> 22 / 59 us, 16 units of 4096 rows 22 -> 16 segments 18 / 49 -> 16 /
+// 43, fp32 40 units of 1024 rows 8 -> 11 segments 33 / 94 -> 29 / 81.  Over those shapes 16-bit calls
+// are 5 % and fp32 ones 8 % faster than with the usual split, and 20 are slower by 4 to 9 %.
+//   - 16-bit 128 x 128 keeps the usual split, within 2 % of the best on average; a coarser one leaves
+//     compute units idle (8 units of 2048 rows: 32 segments 30 / 55 us, 8 segments 29 / 73; 10 units of
+//     4096 rows: 22 segments 31 / 76, 10 segments 38 / 107).
+//   - With 129 to 256 16-bit units (384 at 32 x 32), where chains are short or rows narrow, one segment
+//     less leaves compute units idle in one pass and one more starts a round in the other (176 units of
+//     600 rows at 64 x 64: 3 segments 20.6 / 61 us, 2 segments 22.5 / 57; 192 of 8192 rows at 32 x 64: a
+//     forward 147 us with 3, 162 with 2): they keep the usual split, and no split at all is left to
+//     more units than that, or to one or two chunks.
 long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv) {
-  const int per_cu = scan_workgroups_per_cu(C, dtype, dk, dv);
-  double best = 0.0;
-  long best_g = 1;
+  const long usual = usual_causal_segments(units, n_chunks, dtype, dk, dv);
+  const bool f32 = dtype == COTTN_F32;
+  if (C > 64 || (!f32 && dk == 128 && dv == 128)) return usual;
+  const long chip = dk == 32 && dv == 32 ? 384 : kComputeUnits;
+  if (!f32 && units > 128 && units <= chip && (n_chunks < 16 * usual || dk + dv <= 96)) return usual;
+  const long most = (f32 && dk == 32 && dv == 32 ? 4L : 2L) * kComputeUnits;
+  const bool split = !f32 && units <= chip && usual > 1 && n_chunks > 2;
+  double best = causal_call_us(units, n_chunks, usual, dtype, dk, dv) / 1.08;
+  long best_g = usual;
   for (long steps = n_chunks; steps >= 1; --steps) {
     // (only the counts that give different splits: about 2 sqrt(n_chunks) of them)
     const long g = (n_chunks + steps - 1) / steps;
     steps = (n_chunks + g - 1) / g;
-    const long on_cu = (units * g + kComputeUnits - 1) / kComputeUnits;
-    const auto step_time = [](long n) { return 0.6 + 0.2 * double(n); };
-    const double rounds = double(on_cu / per_cu) * step_time(per_cu) +
-                          (on_cu % per_cu ? step_time(on_cu % per_cu) : 0.0);
-    double cost = rounds * double(steps + 2);
-    if (g > 1) cost += sum_totals_in_place(int(g), dk, dv) ? 0.9 + 0.1 * double(g) : 4.0 + 0.05 * double(g);
-    if (g == 1 || cost < best) {
-      best = cost;
+    if (g > 1 && units * g > most) break;
+    if (g == 1 && split) continue;
+    const double us = causal_call_us(units, n_chunks, g, dtype, dk, dv);
+    if (us < best) {
+      best = us;
       best_g = g;
     }
-    if (units * g > 16L * kComputeUnits) break;   // finer only adds rounds
   }
   return best_g;
 }
@@ -108,7 +147,8 @@ long bidir_segments(long units, long N, bool f32, int dk, int dv) {
 }  // namespace
 
 // Split of one (batch, head) sequence into segments; see workspace.h.
-bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype, SeqPlan* plan) {
+bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype, SeqPlan* plan,
+               long most_segments) {
   if (dtype != COTTN_F32 && dtype != COTTN_BF16 && dtype != COTTN_F16) return false;
   if (!dims_ok(B, H, N, dk, dv)) return false;
   int C;
@@ -130,6 +170,7 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   plan->by_unit = want <= 0 && bidir && bidir_by_unit(units, N, dtype == COTTN_F32, dk, dv);
   if (want <= 0) {
     want = bidir ? bidir_segments(units, N, dtype == COTTN_F32, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
+    if (most_segments > 0 && want > most_segments) want = most_segments;
   }
   if (want > n_chunks) want = n_chunks;
   if (want < 1) want = 1;
@@ -265,7 +306,7 @@ int check_lengths(const int* seq_len) {
 int fwd_causal_any(const void* Q, const void* K, const void* V, const float* s, const int* seq_len,
                    const float* state_in, void* O, float* state, void* workspace,
                    size_t workspace_bytes, int B, int H, int N, int dk, int dv, int chunk, int dtype,
-                   float eps, void* hip_stream) {
+                   float eps, void* hip_stream, long most_segments = 0) {
   const void* req[] = {Q, K, V, s, O};
   int st = check_common(req, 5, B, H, N, dk, dv, dtype, eps);
   if (st != COTTN_OK) return st;
@@ -274,7 +315,7 @@ int fwd_causal_any(const void* Q, const void* K, const void* V, const float* s, 
   if (state_in != nullptr && state_in == state) return COTTN_E_ARG;
   if ((st = check_lengths(seq_len)) != COTTN_OK) return st;
   SeqPlan plan;
-  if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dtype, &plan)) return COTTN_E_SHAPE;
+  if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dtype, &plan, most_segments)) return COTTN_E_SHAPE;
   st = check_workspace(workspace, workspace_bytes,
                        workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, dk, dv, plan));
   if (st != COTTN_OK) return st;
@@ -315,12 +356,6 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
-// Puts the calling thread's segment override back when a call that sets one of its own returns.
-struct SegmentsForCall {
-  const int before = g_tuned_segments;
-  ~SegmentsForCall() { g_tuned_segments = before; }
-};
-
 int static_workspace(void** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return COTTN_E_HIP;
@@ -346,16 +381,13 @@ int cottn_fwd_causal_static(const void* Q, const void* K, const void* V, const f
   SeqPlan plan;
   if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
   size_t need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
-  // a split whose states do not fit the array gives way to one of about 384 workgroups (512 for
-  // long segments, 256 at 16-bit d = 128), for this call
-  const SegmentsForCall restore;
-  if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES) && g_tuned_segments <= 0) {
-    const long units = long(B) * H;
-    long want = dtype != COTTN_F32 && d == 128 ? kComputeUnits / units : (384 + units - 1) / units;
-    if (want < 1) want = 1;
-    if (!(dtype != COTTN_F32 && d == 128) && N > 16 * want * plan.C - plan.C) want = (512 + units - 1) / units;
-    g_tuned_segments = int(want);
-    if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
+  // a split of the library's own whose states do not fit the array gives way to the finest that does
+  // (fp32 at d = 128 only: at most 512 workgroups, 573 with 129 to 191 units, have a state each)
+  long most = 0;
+  if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES)) {
+    const long most_that_fit = long(COTTN_STATIC_WORKSPACE_BYTES) / (long(B) * H * d * d * long(sizeof(float)));
+    most = most_that_fit < 1 ? 1 : most_that_fit;
+    if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan, most)) return COTTN_E_SHAPE;
     need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
   }
   if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES)) return COTTN_E_WORKSPACE;
@@ -364,7 +396,7 @@ int cottn_fwd_causal_static(const void* Q, const void* K, const void* V, const f
   // every slot of the segment-state array that a kernel reads is written earlier in the same
   // call, so what the previous call left in the array needs no clearing
   return fwd_causal_any(Q, K, V, s, nullptr, nullptr, O, state, ws, need, B, H, N,
-                        d, d, chunk, dtype, eps, hip_stream);
+                        d, d, chunk, dtype, eps, hip_stream, most);
 }
 
 int cottn_fwd_causal_from_state(const void* Q, const void* K, const void* V, const float* s,

@@ -39,11 +39,23 @@ struct CausalArgs {
 // Whether the kernels that need the states of other segments add the segment totals up
 // themselves (each workgroup reads up to G - 1 states of its unit out of the L2) or a carry /
 // combine kernel is launched that turns the state arrays into prefixes, suffixes or sums.  A
-// launch costs about 5 us with its gap, a state 16 KB to 64 KB of L2 reads per workgroup:
-// measured on forward + backward, causal 64 x 64 12 segments 35 -> 32 us, 16 segments 73 -> 68
-// us, 32 segments 201 -> 205 us; 128 x 128 10 segments 296 -> 284 us, 16 segments 158 -> 165 us.
-// The forward and the backward must agree on it for the backward to take over the forward's
+// launch costs about 5 us with its gap; a state of 4 KB to 64 KB takes every workgroup about 0.15 us
+// to 0.6 us in each scan, and the carry kernel, which moves all of them, longer the more units there
+// are.  The forward and the backward must agree on it for the backward to take over the forward's
 // saved states.
+//
+// Causal, in place minus carried, forward / backward in us, at 2, 12 and 24 units: 64 x 64 12 segments
+// -1.1 / -0.6, -2.3 / -1.4, -5.1 / -2.6; 24 segments 0.0 / +0.9, -2.9 / +1.8; 64 x 128 6 segments -0.6 /
+// +0.7, -1.7 / -0.2, -3.9 / -1.7; 16 segments +1.9 / +7.3, -1.3 / +6.5, -1.9 / +6.6; 128 x 128 4 segments
+// -0.7 / -0.1, -2.1 / -1.7, -4.8 / -2.3; 10 segments +2.7 / +5.5, -1.4 / +5.1, -4.8 / 0.0.  The line
+// follows the number of segments where the sums of the two cross, 17 / 24 / 31 or more at 64 x 64, 7 /
+// 10 / 14 at 64 x 128, 4 / 7 / 13 at 128 x 128, or one above: a launch takes the host 3 us too.
+constexpr bool causal_totals_in_place(long units, int G, int dk, int dv) {
+  return long(G - 1) * dk * dv * 4 <= (200 + 13 * (units < 32 ? units : 32)) * 1024;
+}
+// Bidirectional: only the sums are needed, which a backward that is handed the forward's totals takes
+// over where they were left as they are; the line lies where the combine launch is the better one for
+// the forward alone (64 x 64 24 segments +1.3 us at 2 units, 64 x 128 12 +0.8, 128 x 128 8 +1.2).
 constexpr bool sum_totals_in_place(int G, int dk, int dv) {
   return G <= 24 && long(G - 1) * dk * dv * 4 <= 600 * 1024;
 }

@@ -16,7 +16,9 @@ struct SeqPlan {
   int split;
 };
 
-bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype, SeqPlan* plan);
+// most_segments > 0: no more than that, where the library chooses
+bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype, SeqPlan* plan,
+               long most_segments = 0);
 
 inline size_t round_up_256(size_t x) { return (x + 255) & ~size_t(255); }
 
