@@ -91,9 +91,7 @@ size_t cottn_workspace_bytes(int op, int B, int H, int N, int d, int chunk, int 
 
 /* Number of sequence segments per (batch, head) the library will scan in parallel for
  * these arguments (1 = one serial chunk scan per (b, h)); 0 if unsupported.  Informational:
- * the chunked regrouping of the cumulative sum of eq. attn_2 is exact for any value.  (A
- * bidirectional call of short or of many 16-bit sequences runs unsplit, one workgroup per (b, h);
- * for it this is the split it would have otherwise.)
+ * the chunked regrouping of the cumulative sum of eq. attn_2 is exact for any value.
  * cottn_tune_segments(g) forces the value for later calls made by the CALLING THREAD (g <= 0
  * restores the built-in heuristic); it is a knob for tests and tuning runs and the only state
  * the library keeps between calls besides the profiling totals below.  A backward call that is

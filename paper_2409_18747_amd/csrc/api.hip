@@ -178,7 +178,6 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   const long G = n_chunks > 0 ? (n_chunks + chunks_per_seg - 1) / chunks_per_seg : 1;
   if (units * G > 2147483647L / 4) return false;
   plan->C = C;
-  plan->split = int(G);
   plan->G = plan->by_unit ? 1 : int(G);
   plan->seg_rows = int((plan->by_unit ? n_chunks : chunks_per_seg) * C);
   return true;
@@ -261,7 +260,7 @@ int cottn_segments_dkdv(int op, int B, int H, int N, int dk, int dv, int chunk, 
   if (op < COTTN_OP_FWD_CAUSAL || op > COTTN_OP_BWD_BIDIR) return 0;
   SeqPlan plan;
   if (!make_plan(op, B, H, N, dk, dv, chunk, dtype, &plan)) return 0;
-  return plan.split;
+  return plan.G;
 }
 
 int cottn_segments(int op, int B, int H, int N, int d, int chunk, int dtype) {

@@ -10,10 +10,7 @@ struct SeqPlan {
   int C;
   int G;
   int seg_rows;
-  // a bidirectional call that takes a whole (batch, head) per workgroup (bidir_by_unit): one
-  // segment, in place of the `split` it would have been cut into
-  bool by_unit;
-  int split;
+  bool by_unit;   // a bidirectional call that takes a whole (batch, head) per workgroup (bidir_by_unit), G = 1
 };
 
 // most_segments > 0: no more than that, where the library chooses

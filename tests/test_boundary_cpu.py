@@ -103,9 +103,8 @@ def test_workspace_sizes(lib):
 
 def test_heuristic_split_per_operation(lib):
     """The split the library chooses by itself: the causal forward and backward agree (the
-    backward takes the forward's states over only then), so do the bidirectional pair, and the
-    bidirectional calls, which have no chain of chunks to shorten, are cut finer but never into
-    more segments than their kernels add up themselves (four)."""
+    backward takes the forward's states over only then), and so do the bidirectional pair, whose
+    calls of short or of many 16-bit sequences run unsplit."""
     lib.cottn_tune_segments(0)
     for B, H, N, d in [(8, 12, 1024, 64), (32, 12, 512, 64), (1, 16, 65536, 64), (2, 3, 333, 32),
                        (8, 12, 1024, 128), (1, 1, 64, 64)]:
@@ -113,9 +112,26 @@ def test_heuristic_split_per_operation(lib):
         assert lib.cottn_segments(2, B, H, N, d, 0, BF16) == lib.cottn_segments(3, B, H, N, d, 0, BF16)
     assert lib.cottn_segments(0, 8, 12, 1024, 64, 0, BF16) == 4     # 384 workgroups
     assert lib.cottn_segments(0, 32, 12, 512, 64, 0, BF16) == 1     # 384 units fill the chip
-    assert lib.cottn_segments(2, 32, 12, 512, 64, 0, BF16) == 2     # 768 workgroups
-    assert lib.cottn_segments(2, 8, 12, 1024, 64, 0, BF16) == 4     # capped at four
+    assert lib.cottn_segments(2, 32, 12, 512, 64, 0, BF16) == 1     # a (batch, head) per workgroup
+    assert lib.cottn_segments(2, 32, 12, 512, 64, 0, F32) == 2      # 768 workgroups
+    assert lib.cottn_segments(2, 8, 12, 1024, 64, 0, BF16) == 4     # two to three workgroups per compute unit
+    assert lib.cottn_segments(2, 1, 2, 65536, 64, 0, BF16) == 128   # few units: one on every compute unit
     assert lib.cottn_segments(0, 1, 16, 65536, 64, 0, BF16) == 32   # long chains: 512 workgroups
+
+
+@pytest.mark.parametrize("B,H,N,d", [(32, 12, 512, 64), (2, 2, 100, 128), (12, 8, 200, 128), (1, 1, 256, 32), (24, 12, 1500, 64),
+                                     (8, 12, 1024, 64), (1, 2, 65536, 64), (4, 4, 700, 32)])
+def test_reported_segments_are_the_ones_that_run(lib, B, H, N, d):
+    """The bidirectional forward keeps one fp32 state per segment, by unit or split: the query answers for
+    the call that runs, and a call tuned to the answer has the same workspace."""
+    for dtype in (F32, BF16):
+        lib.cottn_tune_segments(0)
+        g = lib.cottn_segments(2, B, H, N, d, 0, dtype)
+        assert g == lib.cottn_segments(3, B, H, N, d, 0, dtype)
+        assert lib.cottn_workspace_bytes(2, B, H, N, d, 0, dtype) == B * H * g * d * d * 4
+        lib.cottn_tune_segments(g)
+        assert lib.cottn_workspace_bytes(2, B, H, N, d, 0, dtype) == B * H * g * d * d * 4
+        lib.cottn_tune_segments(0)
 
 
 F16 = 2
