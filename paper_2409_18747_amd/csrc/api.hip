@@ -164,7 +164,7 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   // (the bidirectional kernels have no quadratic part inside a chunk)
   if (op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR) C = bidir_step_rows(dtype == COTTN_F32);
   const long units = long(B) * H;
-  const long n_chunks = (long(N) + C - 1) / C;
+  long n_chunks = (long(N) + C - 1) / C;
   const bool bidir = op == COTTN_OP_FWD_BIDIR || op == COTTN_OP_BWD_BIDIR;
   long want = g_tuned_segments;
   plan->by_unit = want <= 0 && bidir && bidir_by_unit(units, N, dtype == COTTN_F32, dk, dv);
@@ -174,6 +174,11 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   }
   if (want > n_chunks) want = n_chunks;
   if (want < 1) want = 1;
+  if (bidir && !threads_fit(units * want, 4 * C)) {
+    C = 64;
+    plan->by_unit = false;
+    n_chunks = (long(N) + C - 1) / C;
+  }
   const long chunks_per_seg = n_chunks > 0 ? (n_chunks + want - 1) / want : 1;
   const long G = n_chunks > 0 ? (n_chunks + chunks_per_seg - 1) / chunks_per_seg : 1;
   if (units * G > 2147483647L / 4) return false;

@@ -669,18 +669,18 @@ SegmentTotalsArgs totals_args(const CausalArgs& a, const void* X, const void* Y,
   return t;
 }
 
-template <int DK, int DV>
-hipError_t run_fwd_bidir(const CausalArgs& a) {
-  constexpr int C = bidir_step_rows(ELEM_IS_F32);
+template <int DK, int DV, int C>
+hipError_t run_fwd_bidir_rows(const CausalArgs& a) {
   using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   float* totals = static_cast<float*>(a.workspace);
 #ifndef COTTN_ELEM_F32
-  if (a.by_unit)
-    return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, C>, dim3(units),
-                         dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
-                         static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
-                         static_cast<elem_t*>(a.O), totals, a.state, a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
+  if constexpr (C == bidir_step_rows(false))
+    if (a.by_unit)
+      return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, C>, dim3(units),
+                           dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+                           static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
+                           static_cast<elem_t*>(a.O), totals, a.state, a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
 #endif
   hipError_t err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, totals));
   if (err != hipSuccess) return err;
@@ -697,9 +697,8 @@ hipError_t run_fwd_bidir(const CausalArgs& a) {
                        a.seq_len, a.s_per_unit);
 }
 
-template <int DK, int DV>
-hipError_t run_bwd_bidir(const CausalArgs& a) {
-  constexpr int C = bidir_step_rows(ELEM_IS_F32);
+template <int DK, int DV, int C>
+hipError_t run_bwd_bidir_rows(const CausalArgs& a) {
   using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   char* ws = static_cast<char*>(a.workspace);
@@ -724,18 +723,19 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
     s_src = s_totals;
   }
 #ifndef COTTN_ELEM_F32
-  if (a.by_unit) {
-    // with a scale per unit, or one batch, a unit's share of ds is ds
-    const bool whole = a.s_per_unit || a.B == 1;
-    err = launch_kernel(COTTN_SYM_STR(bwd_bidir_unit), COTTN_SYM(bwd_bidir_unit)<DK, DV, C>, dim3(units),
-                        dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
-                        static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V),
-                        static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ),
-                        static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), s_src, whole ? a.ds : ds_partial,
-                        a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
-    if (err != hipSuccess || whole) return err;
-    return launch_kernel("bidir_sum_ds", bidir_sum_ds, dim3(a.H), dim3(64), 0, a.stream, ds_partial, a.ds, a.B, a.H);
-  }
+  if constexpr (C == bidir_step_rows(false))
+    if (a.by_unit) {
+      // with a scale per unit, or one batch, a unit's share of ds is ds
+      const bool whole = a.s_per_unit || a.B == 1;
+      err = launch_kernel(COTTN_SYM_STR(bwd_bidir_unit), COTTN_SYM(bwd_bidir_unit)<DK, DV, C>, dim3(units),
+                          dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
+                          static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V),
+                          static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ),
+                          static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), s_src, whole ? a.ds : ds_partial,
+                          a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
+      if (err != hipSuccess || whole) return err;
+      return launch_kernel("bidir_sum_ds", bidir_sum_ds, dim3(a.H), dim3(64), 0, a.stream, ds_partial, a.ds, a.B, a.H);
+    }
 #endif
   err = launch_kernel(COTTN_SYM_STR(bwd_bidir_dq), COTTN_SYM(bwd_bidir_dq)<DK, DV, C>, dim3(units * a.G),
                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q),
@@ -752,6 +752,25 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
                        static_cast<const elem_t*>(a.V), a.s, static_cast<elem_t*>(a.dK),
                        static_cast<elem_t*>(a.dV), g_totals, a.G, few ? a.G : 1, ds_partial, a.G, a.ds,
                        a.B, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps, a.seq_len, a.s_per_unit);
+}
+
+// The plan's rows per step: the usual ones, or 64 for very many sequences (launch.h: threads_fit), whose
+// states of more than 64 x 64 no card holds.
+template <int DK, int DV>
+hipError_t run_fwd_bidir(const CausalArgs& a) {
+  constexpr int C = bidir_step_rows(ELEM_IS_F32);
+  if (a.C == C) return run_fwd_bidir_rows<DK, DV, C>(a);
+  if constexpr (DK * DV <= 64 * 64)
+    if (a.C == 64) return run_fwd_bidir_rows<DK, DV, 64>(a);
+  return hipErrorInvalidValue;
+}
+template <int DK, int DV>
+hipError_t run_bwd_bidir(const CausalArgs& a) {
+  constexpr int C = bidir_step_rows(ELEM_IS_F32);
+  if (a.C == C) return run_bwd_bidir_rows<DK, DV, C>(a);
+  if constexpr (DK * DV <= 64 * 64)
+    if (a.C == 64) return run_bwd_bidir_rows<DK, DV, 64>(a);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

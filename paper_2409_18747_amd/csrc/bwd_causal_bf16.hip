@@ -818,9 +818,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   }
 }
 
-template <int DK, int DV, int C>
+template <int DK, int DV, int C, int CR = BwdSplit<DK, DV, C>::CR, int CS = BwdSplit<DK, DV, C>::CS>
 hipError_t run_bwd_causal(const CausalArgs& a) {
-  constexpr int CR = BwdSplit<DK, DV, C>::CR, CS = BwdSplit<DK, DV, C>::CS;
   using Cfg = BwdCfg<DK, DV, CR, CS>;
   const int units = a.B * a.H;
   const elem_t* Q = static_cast<const elem_t*>(a.Q);
@@ -906,7 +905,9 @@ hipError_t COTTN_SYM(bwd_causal)(const CausalArgs& a) {
     case 64064064: return run_bwd_causal<64, 64, 64>(a);
     case 64064128: return run_bwd_causal<64, 64, 128>(a);
     case 64064256: return run_bwd_causal<64, 64, 256>(a);
-    case 128128064: return run_bwd_causal<128, 128, 64>(a);
+    case 128128064:
+      return threads_fit(long(a.B) * a.H * a.G, 512) ? run_bwd_causal<128, 128, 64>(a)
+                                                     : run_bwd_causal<128, 128, 64, 64, 1>(a);
     case 32064064: return run_bwd_causal<32, 64, 64>(a);
     case 32128064: return run_bwd_causal<32, 128, 64>(a);
     case 64032064: return run_bwd_causal<64, 32, 64>(a);

@@ -67,6 +67,11 @@ constexpr bool sum_totals_in_place(int G, int dk, int dv) {
 // would not fit the LDS.
 constexpr int bidir_step_rows(bool f32) { return f32 ? 64 : 128; }
 
+// A launch takes fewer than 2^32 threads.  8 388 608 workgroups of 512 are one too many, of 256 they are
+// not: for so many (short) sequences the kernels of 512 threads give way to ones of 256, the
+// bidirectional ones to 64-row steps, the 128 x 128 backward scans to one wave per row group.
+constexpr bool threads_fit(long workgroups, int threads) { return workgroups * threads < (1L << 32); }
+
 // Whether a bidirectional call with 16-bit rows takes a whole (batch, head) per workgroup, forward and
 // backward in one launch each (bidir_bf16.hip: fwd_bidir_unit, bwd_bidir_unit), or splits the sequence
 // over workgroups and the work over two launches each.  A unit's rows are walked one step after the
