@@ -125,20 +125,28 @@ long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv
 // shorten and little to set up: about three workgroups per compute unit measured best (B24 H8 N3000
 // d64, forward + backward: 154 us with 4 segments, 164 with 2), in at most four segments, whose
 // totals are soon added up.  Two fit a compute unit at a time, so 193 to 256 units take two
-// segments (B32 H8 N2048: 134 us, 150 us with 3).  At 128 x 128 one workgroup fills a compute
-// unit (B8 H12 N1024 2 segments 91 us, 3 segments 116), and so it does in the dQ sweep of 16-bit
+// segments (B32 H8 N2048: 134 us, 150 us with 3), and with 342 units and more three are the start of a
+// third round, which long sequences feel (352 units of 8192 rows at 32 x 32: 2 segments 145 / 389 us
+// for the forward / with its backward, 3 segments 164 / 424).  At 128 x 128 one workgroup fills a
+// compute unit (B8 H12 N1024 2 segments 91 us, 3 segments 116), and so it does in the dQ sweep of 16-bit
 // rows with 128 and 64 or 128 and 32 columns (B16 H8 N1024 64 x 128 2 segments 63 us, 4 segments
-// 74; from 129 units on, where that leaves one, four are the better again).  Few units with long sequences are cut further,
-// until (nearly) every compute unit has a workgroup and none has two: B1 H2 N65536 128
-// segments 69 us (64 segments, with 64-row steps, 95); B1 H12 N8192 16 segments 42 us, 32 segments 53.
+// 74; from 129 units on, where that leaves one, four are the better again); a little more than one
+// for each takes two, which even the second round out (320 units of 2048 rows: 1 segment 200 / 572 us, 2
+// segments 168 / 490).  Few units with long sequences are cut further, until (nearly) every compute unit
+// has a workgroup and none has two: B1 H2 N65536 128 segments 69 us (64 segments, with 64-row steps, 95);
+// B1 H12 N8192 16 segments 42 us, 32 segments 53; two for the longest at 16-bit 32 x 32, of which it
+// runs four (24 units of 65536 rows: 10 segments 105 / 226 us, 20 segments 72 / 201).
 long bidir_segments(long units, long N, bool f32, int dk, int dv) {
-  const bool one_per_cu = (dk == 128 && dv == 128) ||
-                          (!f32 && units <= kComputeUnits / 2 && (dk == 128 || (dk == 64 && dv == 128)));
+  const bool widest = dk == 128 && dv == 128, narrowest = dk == 32 && dv == 32;
+  const bool one_per_cu = widest || (!f32 && units <= kComputeUnits / 2 && (dk == 128 || (dk == 64 && dv == 128)));
   long want = one_per_cu ? kComputeUnits / units : (3 * kComputeUnits + units - 1) / units;
   if (units > 192 && units <= 256 && want > 2) want = 2;
+  if (units > 341 && N >= 2048 && want > 2) want = 2;
+  if (!f32 && widest && units > 256 && units <= 320 && N > 1024) want = 2;
   if (want > 4) want = 4;
   if (units * want < kComputeUnits && N > 512 * want - 64) {
     want = kComputeUnits / units;
+    if (!f32 && narrowest && N > 4096 * want) want *= 2;
     if (want > N / 128) want = N / 128;   // at least 128 rows each
   }
   return want;

@@ -671,12 +671,16 @@ SegmentTotalsArgs totals_args(const CausalArgs& a, const void* X, const void* Y,
 
 template <int DK, int DV, int C>
 hipError_t run_fwd_bidir_rows(const CausalArgs& a) {
-  using Cfg = BiCfg<DK, DV, C>;
   const int units = a.B * a.H;
   float* totals = static_cast<float*>(a.workspace);
+  // 16-bit 128 x 128 beyond one workgroup per compute unit: one by unit fills a compute unit, and so the
+  // second round finds most of them idle; the totals and the apply kernel fit twice, the latter in
+  // 64-row steps (by unit or 128-row steps / so: 288 units of 777 rows 79.7 / 73.8 us, 320 of 2048 200 /
+  // 185, 896 of 513 151 / 142; up to 256 workgroups the other way round, 256 of 1024 rows 47.7 / 59.4).
+  const bool in_rounds = !ELEM_IS_F32 && DK == 128 && DV == 128 && long(units) * a.G > 256;
 #ifndef COTTN_ELEM_F32
   if constexpr (C == bidir_step_rows(false))
-    if (a.by_unit)
+    if (a.by_unit && !in_rounds)
       return launch_kernel(COTTN_SYM_STR(fwd_bidir_unit), COTTN_SYM(fwd_bidir_unit)<DK, DV, C>, dim3(units),
                            dim3(C * 4), 0, a.stream, static_cast<const elem_t*>(a.Q),
                            static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
@@ -690,11 +694,15 @@ hipError_t run_fwd_bidir_rows(const CausalArgs& a) {
     err = launch_bidir_combine(totals, units, a.G, DK * DV, a.state, a.stream);
     if (err != hipSuccess) return err;
   }
-  return launch_kernel(COTTN_SYM_STR(fwd_bidir_apply), COTTN_SYM(fwd_bidir_apply)<DK, DV, C>, dim3(units * a.G),
-                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q), a.s,
-                       static_cast<elem_t*>(a.O), totals, a.G, sum_in_apply ? a.G : 1,
-                       sum_in_apply ? a.state : nullptr, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps,
-                       a.seq_len, a.s_per_unit);
+  const auto apply = [&](auto kernel, int rows) {
+    return launch_kernel(COTTN_SYM_STR(fwd_bidir_apply), kernel, dim3(units * a.G), dim3(rows * 4), 0, a.stream,
+                         static_cast<const elem_t*>(a.Q), a.s, static_cast<elem_t*>(a.O), totals, a.G,
+                         sum_in_apply ? a.G : 1, sum_in_apply ? a.state : nullptr, a.H, a.N, a.G, a.seg_rows,
+                         1.0f / a.eps, a.seq_len, a.s_per_unit);
+  };
+  if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
+    if (in_rounds) return apply(COTTN_SYM(fwd_bidir_apply)<DK, DV, 64>, 64);
+  return apply(COTTN_SYM(fwd_bidir_apply)<DK, DV, C>, C);
 }
 
 template <int DK, int DV, int C>

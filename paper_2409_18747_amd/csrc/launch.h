@@ -79,14 +79,19 @@ constexpr bool threads_fit(long workgroups, int threads) { return workgroups * t
 // backward, split / by unit: 8 units of 120 rows 22 / 20 us, of 250 rows at 128 x 128 32 / 33; 32 units
 // of 200 rows d64 26 / 22 us; 128 units of 500 rows d64 28 / 30 us, 160 units of 512 37 / 32, 384 units
 // 58 / 53; 160 units of 1024 rows 52.6 / 54.1 us, 192 units 59 / 54, 384 units 98 / 93, at 32 x 32 192
-// units 29 / 33; 272 units of 1500 rows 118 / 119 us, 320 units of 2048 rows 187 / 194 us.  (fp32 steps
-// last longer, and only 224 to 256 units gain: always split.)
+// units 29 / 33; 272 units of 1500 rows 118 / 119 us, 320 units of 2048 rows 187 / 194 us.  Where two
+// rounds of workgroups leave most compute units idle in the second and sequences are long enough, the
+// split is the better one too: wide rows, of which one workgroup fills a compute unit (288 units of 1500
+// rows at 64 x 128 219 / 246 us, 272 of 777 at 128 x 32 92 / 104), and more than 512 units (576 of 1500
+// rows at 128 x 32 326 / 365).  (fp32 steps last longer, and only 224 to 256 units gain: always split.)
 constexpr bool bidir_by_unit(long units, int N, bool f32, int dk, int dv) {
   if (f32) return false;
   if (N <= 128) return true;
   if (N <= 256) return dk < 128 || dv < 128 || units >= 96;
   if (N <= 512) return units >= 160;
-  return N <= 1536 && units >= 192 && (dk > 32 || dv > 32);
+  if (N > 1536 || units < 192 || (dk == 32 && dv == 32)) return false;
+  if (N > 1024 && (units > 512 || (units > 256 && units < 448 && (dk == 128 || dv == 128)))) return false;
+  return !(dk == 128 && dv == 32 && units > 256 && units < 320);
 }
 
 struct StepArgs {
