@@ -42,6 +42,7 @@ def run_bidir(cottn, oracle, B, H, N, d, dtype, seed, segments=0, saved=False):
           (dtype, B, H, N, d, segments, saved, {k: "%.2e" % v for k, v in errs.items()}), flush=True)
     for name, e in errs.items():
         assert e <= TOL[dtype], (name, e)
+    return dQ, dK, dV, ds
 
 
 @pytest.mark.parametrize("N", [1, 17, 64, 65, 200, 512])
@@ -61,8 +62,14 @@ def test_bf16_totals_saved_by_forward(cottn, oracle, segments, d, N):
     run_bidir(cottn, oracle, 2, 3, N, d, "bf16", seed=41, segments=segments, saved=True)
 
 
-def test_f32_ignores_forward_workspace(cottn, oracle):
-    run_bidir(cottn, oracle, 1, 2, 150, 64, "f32", seed=42, segments=2, saved=True)
+@pytest.mark.parametrize("segments", [1, 2, 3])
+def test_f32_totals_saved_by_forward(cottn, oracle, segments):
+    """Gradients from the totals the forward left behind equal those of a backward that reduces them again."""
+    import torch
+    a = run_bidir(cottn, oracle, 1, 2, 150, 64, "f32", seed=42, segments=segments, saved=True)
+    b = run_bidir(cottn, oracle, 1, 2, 150, 64, "f32", seed=42, segments=segments, saved=False)
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
 
 
 def test_bf16_bert_shape_slice(cottn, oracle):

@@ -80,8 +80,15 @@ def test_bf16_states_saved_by_forward(cottn, oracle, segments, d, N):
         assert torch.equal(x, y)
 
 
-def test_f32_ignores_forward_workspace(cottn, oracle):
-    run_bwd(cottn, oracle, 1, 2, 200, 64, "f32", seed=5, segments=3, saved=True)
+@pytest.mark.parametrize("segments", [2, 3, 7])
+def test_f32_states_saved_by_forward(cottn, oracle, segments):
+    """The same for fp32, with totals added in place and (128 x 128 in 7 segments) carried."""
+    import torch
+    for d in (64, 128):
+        a = run_bwd(cottn, oracle, 1, 2, 230, d, "f32", seed=5, segments=segments, saved=True)
+        b = run_bwd(cottn, oracle, 1, 2, 230, d, "f32", seed=5, segments=segments, saved=False)
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
 
 
 def test_bf16_default_plan_gpt_shape(cottn, oracle):

@@ -77,8 +77,9 @@ def test_f16_and_saved_states(cottn, oracle, dk, dv):
 @pytest.mark.parametrize("dk,dv", SHAPES)
 def test_f32_shapes(cottn, oracle, causal, dk, dv):
     """The fp32 path at d_key != d_value: several chunks of 32, a ragged tail, several segments,
-    and a split the forward leaves nothing behind for (fp32 ignores a forward workspace)."""
+    states handed over, and a split the causal forward leaves nothing behind for."""
     run(cottn, oracle, causal, 2, 2, 150, dk, dv, "f32", seed=900 + dk + dv, segments=3)
+    run(cottn, oracle, causal, 1, 2, 150, dk, dv, "f32", seed=902 + dk + dv, segments=3, saved=True)
     run(cottn, oracle, causal, 1, 2, 45, dk, dv, "f32", seed=901 + dk + dv, segments=1, saved=True)
 
 
