@@ -66,3 +66,17 @@ def test_host_tensors_are_refused(cottn):
     q = torch.zeros(1, 2, 64, dtype=torch.bfloat16)
     with pytest.raises(ValueError, match="must live on the GPU"):
         cottn.cottn_step(q, q, q, torch.ones(2), torch.zeros(1, 2, 64, 64))
+
+
+@pytest.mark.parametrize("missing", [[], ["_raw_stream"], ["_current_device"]])
+def test_current_stream_with_and_without_the_handle_calls(cottn, monkeypatch, missing):
+    """torch builds that lack the calls for the bare handle get it from the Stream object."""
+    class Stream:
+        cuda_stream = 4242
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(cottn, "_raw_stream", lambda device: 1000 + device)
+    monkeypatch.setattr(cottn, "_current_device", lambda: 3)
+    for name in missing:
+        monkeypatch.setattr(cottn, name, None)
+    assert cottn._stream(None) == (4242 if missing else 1003)
+    assert cottn._stream(Stream) == 4242
