@@ -65,7 +65,7 @@ struct BwdCfg {
   static constexpr int KSK = DK / 32, KSV = DV / 32;
   static constexpr int NP = C / 32;
   static constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);   // operand tiles
-  static constexpr int SPK = lds_pitch(DK), SPV = lds_pitch(DV);   // state copies
+  static constexpr int SPV = lds_pitch(DV);   // state copies
   static constexpr int TILEK = C * TPK, TILEV = C * TPV;
   // the copy of the running state in elements, [d_key][d_value] in both scans
   static constexpr int STATE = DK * SPV;

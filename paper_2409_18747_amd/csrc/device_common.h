@@ -354,7 +354,6 @@ __device__ __forceinline__ void store_streaming(void* dst, uint4 v) {
 // workgroups of the same (batch, head) unit, which unit_and_segment() puts on this XCD: plain
 // stores leave the lines in this XCD's L2 for them (0.5 us of the 52 us step on B8 H12 N1024 d64
 // against non-temporal stores).
-__device__ __forceinline__ void store_state_word(float* dst, float v) { *dst = v; }
 __device__ __forceinline__ void store_state_words(float* dst, f32x4 v) {
   *reinterpret_cast<f32x4*>(dst) = v;
 }

@@ -30,7 +30,7 @@ inline size_t round_up_256(size_t x) { return (x + 255) & ~size_t(255); }
 //   bidirectional forward : [units][G][dk][dv]   segment totals, slot 0 becomes the full state
 //   bidirectional backward: two arrays [units][G][dk][dv], totals of Kh^T V and of Qh^T dO,
 //                            slot 0 becomes the full matrix when the combine kernel runs; then
-//                            [units][G] partial sums of ds (room for dk*dv/256 where that is more)
+//                            [units][G] partial sums of ds
 inline size_t state_array_bytes(int B, int H, int dk, int dv, int G) {
   return round_up_256(size_t(B) * H * G * dk * dv * sizeof(float));
 }
@@ -43,8 +43,7 @@ inline size_t workspace_bytes_for(int op, int B, int H, int dk, int dv, const Se
     case 0: return p.G > 1 ? state_array_bytes(B, H, dk, dv, p.G) : 0;
     case 1: return (p.G > 1 ? 2 * state_array_bytes(B, H, dk, dv, p.G) : 0) + ds_partials_bytes(B, H, p.G);
     case 2: return state_array_bytes(B, H, dk, dv, p.G);
-    case 3: return 2 * state_array_bytes(B, H, dk, dv, p.G) +
-                   ds_partials_bytes(B, H, p.G > dk * dv / 256 ? p.G : dk * dv / 256);
+    case 3: return 2 * state_array_bytes(B, H, dk, dv, p.G) + ds_partials_bytes(B, H, p.G);
     default: return 0;
   }
 }

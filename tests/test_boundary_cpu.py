@@ -298,7 +298,7 @@ def test_rectangular_head_dimensions_on_the_host(lib):
     assert wb(0, 8, 12, 1024, 64, 64, 0, BF16) == lib.cottn_workspace_bytes(0, 8, 12, 1024, 64, 0, BF16)
     assert wb(0, 8, 12, 1024, 32, 128, 0, BF16) == 8 * 12 * 4 * 32 * 128 * 4
     assert wb(1, 8, 12, 1024, 128, 64, 0, BF16) == 2 * 8 * 12 * 4 * 128 * 64 * 4 + 1536
-    assert wb(3, 2, 2, 512, 64, 32, 0, BF16) == 2 * 2 * 2 * 4 * 64 * 32 * 4 + 256   # ds partials: max(G, dk*dv/256) = 8 per unit
+    assert wb(3, 2, 2, 512, 64, 32, 0, BF16) == 2 * 2 * 2 * 4 * 64 * 32 * 4 + 256   # ds partials: G = 4 per unit
     assert lib.cottn_segments_dkdv(0, 8, 12, 1024, 64, 128, 0, BF16) == 4
     lib.cottn_tune_segments(0)
     assert wb(4, 256, 16, 1, 32, 128, 0, BF16) == 0             # decode needs none
