@@ -84,9 +84,9 @@ typedef enum {
 
 /* Bytes of workspace the given operation needs for these arguments (0 for COTTN_OP_STEP).
  * Returns (size_t)-1 if the arguments are not supported.  Host only; touches no GPU.
- * A causal call keeps one fp32 state per segment (the backward two), and the library cuts a sequence
- * into segments only where the B*H units leave compute units idle: fewer than 512 + B*H segments in
- * all (1024 + B*H for fp32 32 x 32), 64 MB of states at most. */
+ * A causal call keeps one fp32 state per segment (the backward two) where the library cuts a sequence
+ * into more than one, which it does only up to 640 segments in all (1024 for fp32 and for 32 x 32): 64
+ * MB of states at most. */
 size_t cottn_workspace_bytes(int op, int B, int H, int N, int d, int chunk, int dtype);
 
 /* Number of sequence segments per (batch, head) the library will scan in parallel for

@@ -41,79 +41,70 @@ bool dims_ok(int B, int H, int N, int dk, int dv) {
 
 constexpr int kComputeUnits = 256;
 
-// Segments per (batch, head) for the causal calls.  The usual split: about one and a half workgroups
-// per compute unit (384), two for long chains (16 chunks or more per segment), never more than one
-// at 16-bit 128 x 128, where a workgroup fills a compute unit's LDS.
-long usual_causal_segments(long units, long n_chunks, int dtype, int dk, int dv) {
-  long want;
-  if (dtype != COTTN_F32 && dk == 128 && dv == 128) {
-    want = kComputeUnits / units;
-  } else {
-    want = (384 + units - 1) / units;
-    if (n_chunks >= 16 * want) want = (512 + units - 1) / units;
-  }
-  want = want > n_chunks ? n_chunks : want < 1 ? 1 : want;
-  const long steps = n_chunks > 0 ? (n_chunks + want - 1) / want : 1;
-  return n_chunks > 0 ? (n_chunks + steps - 1) / steps : 1;
-}
-
-// What a forward and its backward take with g segments, in microseconds, by a model of the kernels.
-// A chunk step of the three scans takes `step`, as the rows are wide, and more with a second
-// workgroup on the compute unit; a workgroup walks its steps and pays about two more to start (first
-// rows, stored states), and the compute unit with the most workgroups, of which it runs `at_once` at
-// a time, ends last.  More than one segment costs the totals kernel, and the segments' totals have
-// to be added up, by every workgroup (three scans read them) or by two carry launches.  Fitted to the
-// times of 3700 shapes (1 to 1280 units of 128 to 65536 rows, all pairs of widths, the splits that put
-// up to 1300 workgroups on the chip): off by 8 to 12 %.
-double causal_call_us(long units, long n_chunks, long g, int dtype, int dk, int dv) {
-  const bool f32 = dtype == COTTN_F32;
+// What a causal forward and its backward take with g segments, in microseconds, by a model of the
+// kernels: the split is the one for which this is least.
+//   - A chunk step of the three scans takes `step`, as the rows are wide.  A workgroup walks its steps
+//     and pays over two more to start (first rows, stored states).  The compute unit with the most
+//     workgroups ends last; of `at_once` at a time each further one adds `next_one` of a step.  But the
+//     rows have to come through memory, 0.86 us for every MB of Q and V.
+//   - More than one segment costs the totals kernel, and the totals have to be added up, by every
+//     workgroup (three scans read them), or by carry launches, which walk the segments one batch of
+//     states after the other and move all of them.
+// Fitted to the times of 3700 shapes (1 to 1280 units of 128 to 65536 rows, all pairs of widths, the splits
+// that put up to 1300 workgroups on the chip) so that neither the forward alone nor the pair is far from
+// its best: the split chosen takes 0.6 % (geometric mean of the two) longer than the best one.
+double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int dk, int dv) {
+  const bool f32 = dtype == COTTN_F32, narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
+  const int big = dk > dv ? dk : dv, small = dk > dv ? dv : dk;
+  const long at_once = narrowest ? 4 : (f32 ? big == 128 && small >= 64 : widest) ? 1 : 2;
+  const double next_one = f32 ? (narrowest ? 0.2 : 0.38) : narrowest ? 0.05 : 0.24;
+  const double step = (f32 ? 0.07 : widest ? 0.0265 : 0.041) * (dk + dv);
   const long steps = (n_chunks + g - 1) / g, on_cu = (units * g + kComputeUnits - 1) / kComputeUnits;
-  const long at_once = dk == 32 && dv == 32 ? 4 : 2;
-  const double step = (f32 ? 0.085 : 0.041) * (dk + dv), next_one = f32 ? 0.63 : 0.37;
   const auto together = [&](long n) { return n > 0 ? 1.0 + next_one * double(n - 1) : 0.0; };
-  double us = step * double(steps + 1.8) * (double(on_cu / at_once) * together(at_once) + together(on_cu % at_once));
+  double us = step * (double(steps) + 2.2) * (double(on_cu / at_once) * together(at_once) + together(on_cu % at_once));
+  const double rows_us = 0.86e-6 * double(units) * double(N) * (dk + dv) * (f32 ? 4 : 2);
+  if (us < rows_us) us = rows_us;
   if (g > 1) {
-    const double state = double(dk) * dv * 4.0 / 1024.0 + 3.7;   // KB, and what a small one costs besides
-    us += 5.2 + 0.2 * step * double(steps * on_cu);
-    us += causal_totals_in_place(units, int(g), dk, dv) ? 0.036 * state * double(g - 1) : 8.8 + 0.02 * state * double(g);
+    const double state = double(dk) * dv * 4.0 / 1024.0;   // KB
+    us += 5.8 + 0.135 * step * double(steps * on_cu);
+    us += causal_totals_in_place(units, int(g), dk, dv) ? 0.026 * (state + 7.0) * double(g - 1)
+                                                        : 8.0 + 0.3 * double(g) + 0.001 * state * double(units * g);
   }
   return us;
 }
 
-// The split with the least time by the model, if that promises 8 % over the usual one (what the model
-// is off by), among those with up to two workgroups per compute unit (four of fp32 32 x 32, which
-// fit).  More gain the backward little and cost the forward, which runs three workgroups or more at
-// once, a second round (768 units of 1024 rows at 64 x 64: 2 segments 86 / 291 us for the forward /
-// with its backward, 1 segment 64 / 275).  Forward / with backward at 64 x 64, usual -> chosen: 64 units
-// of 2048 rows 6 -> 8 segments 24 / 66 -> 22 / 59 us, 16 units of 4096 rows 22 -> 16 segments 18 / 49 -> 16 /
-// 43, fp32 40 units of 1024 rows 8 -> 11 segments 33 / 94 -> 29 / 81.  Over those shapes 16-bit calls
-// are 5 % and fp32 ones 8 % faster than with the usual split, and 20 are slower by 4 to 9 %.
-//   - 16-bit 128 x 128 keeps the usual split, within 2 % of the best on average; a coarser one leaves
-//     compute units idle (8 units of 2048 rows: 32 segments 30 / 55 us, 8 segments 29 / 73; 10 units of
-//     4096 rows: 22 segments 31 / 76, 10 segments 38 / 107).
-//   - With 129 to 256 16-bit units (384 at 32 x 32), where chains are short or rows narrow, one segment
-//     less leaves compute units idle in one pass and one more starts a round in the other (176 units of
-//     600 rows at 64 x 64: 3 segments 20.6 / 61 us, 2 segments 22.5 / 57; 192 of 8192 rows at 32 x 64: a
-//     forward 147 us with 3, 162 with 2): they keep the usual split, and no split at all is left to
-//     more units than that, or to one or two chunks.
-long causal_segments(long units, long n_chunks, int C, int dtype, int dk, int dv) {
-  const long usual = usual_causal_segments(units, n_chunks, dtype, dk, dv);
-  const bool f32 = dtype == COTTN_F32;
-  if (C > 64 || (!f32 && dk == 128 && dv == 128)) return usual;
-  const long chip = dk == 32 && dv == 32 ? 384 : kComputeUnits;
-  if (!f32 && units > 128 && units <= chip && (n_chunks < 16 * usual || dk + dv <= 96)) return usual;
-  const long most = (f32 && dk == 32 && dv == 32 ? 4L : 2L) * kComputeUnits;
-  const bool split = !f32 && units <= chip && usual > 1 && n_chunks > 2;
-  double best = causal_call_us(units, n_chunks, usual, dtype, dk, dv) / 1.08;
-  long best_g = usual;
-  for (long steps = n_chunks; steps >= 1; --steps) {
+// Segments per (batch, head) for the causal calls: the least time by the model among the splits of up to
+// 640 workgroups (1024 for fp32, whose scans hold the longer steps, and for 32 x 32, of which a compute
+// unit runs four), or none.  Finer ones gain the backward little and cost the forward, which runs three
+// workgroups or more at once, a round (768 units of 1024 rows at 64 x 64: 2 segments 86 / 291 us for the
+// forward / with its backward, 1 segment 64 / 275).  Others of the measured, forward / with backward: 16-bit
+// 128 x 128 8 units of 2048 rows 32 segments 30 / 55 us, 16 27 / 51, 8 29 / 73; 288 units of 2048 rows 3
+// segments 198 / 655 us, 1 segment 196 / 785; 64 x 64 64 units of 2048 rows 6 segments 24 / 66, 8 22 / 59;
+// 176 units of 600 rows 3 segments 20.6 / 61, 1 segment 18.3 / 61; fp32 40 units of 1024 rows 8 segments
+// 33 / 94, 11 29 / 81.
+// No split at all leaves the backward waiting where units are few: up to 160 16-bit units of more than four
+// chunks (of 32 x 32 fewer than 384 of more than eight) take at least two segments, but at 128 x 128, where
+// one unit fills a compute unit (160 units of 300 rows at 64 x 32: 3 segments 9.5 / 26 us, 1 segment 8.6 /
+// 32; 352 units of 2048 rows at 32 x 32: 2 segments 41 / 125, 1 segment 38 / 145).
+// (Chunks of more than 64 rows, which are for experiments: one and a half workgroups per compute unit,
+// two for long chains.)
+long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk, int dv) {
+  if (C > 64) {
+    const long want = (384 + units - 1) / units;
+    return n_chunks >= 16 * want ? (512 + units - 1) / units : want;
+  }
+  const bool f32 = dtype == COTTN_F32, narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
+  const long most = f32 || narrowest ? 1024 : 640;
+  const bool cut = !f32 && !widest && ((n_chunks > 4 && units <= 160) || (narrowest && n_chunks > 8 && units < 384));
+  double best = causal_call_us(units, N, n_chunks, 1, dtype, dk, dv);
+  long best_g = 1;
+  for (long steps = n_chunks - 1; steps >= 1; --steps) {
     // (only the counts that give different splits: about 2 sqrt(n_chunks) of them)
     const long g = (n_chunks + steps - 1) / steps;
     steps = (n_chunks + g - 1) / g;
-    if (g > 1 && units * g > most) break;
-    if (g == 1 && split) continue;
-    const double us = causal_call_us(units, n_chunks, g, dtype, dk, dv);
-    if (us < best) {
+    if (units * g > most) break;
+    const double us = causal_call_us(units, N, n_chunks, g, dtype, dk, dv);
+    if (us < best || (cut && best_g == 1)) {
       best = us;
       best_g = g;
     }
@@ -177,7 +168,7 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   long want = g_tuned_segments;
   plan->by_unit = want <= 0 && bidir && bidir_by_unit(units, N, dtype == COTTN_F32, dk, dv);
   if (want <= 0) {
-    want = bidir ? bidir_segments(units, N, dtype == COTTN_F32, dk, dv) : causal_segments(units, n_chunks, C, dtype, dk, dv);
+    want = bidir ? bidir_segments(units, N, dtype == COTTN_F32, dk, dv) : causal_segments(units, N, n_chunks, C, dtype, dk, dv);
     if (most_segments > 0 && want > most_segments) want = most_segments;
   }
   if (want > n_chunks) want = n_chunks;
@@ -394,7 +385,7 @@ int cottn_fwd_causal_static(const void* Q, const void* K, const void* V, const f
   if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
   size_t need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
   // a split of the library's own whose states do not fit the array gives way to the finest that does
-  // (fp32 at d = 128 only: at most 512 workgroups, 573 with 129 to 191 units, have a state each)
+  // (d = 128: up to 640 workgroups, 1024 for fp32, have a state of 64 KB each)
   long most = 0;
   if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES)) {
     const long most_that_fit = long(COTTN_STATIC_WORKSPACE_BYTES) / (long(B) * H * d * d * long(sizeof(float)));

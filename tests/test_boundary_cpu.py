@@ -138,13 +138,16 @@ F16 = 2
 
 
 @pytest.mark.parametrize("units,N,d,dtype,segments", [
-    # 16-bit 128 x 128: a workgroup for every compute unit, none has two
-    (8, 2048, 128, BF16, 32), (10, 4096, 128, BF16, 22), (16, 2048, 128, F16, 16), (16, 4096, 128, BF16, 16),
-    (2, 8192, 128, BF16, 128), (1, 1024, 128, BF16, 16), (160, 4096, 128, BF16, 1), (320, 4096, 128, F16, 1),
+    # 16-bit 128 x 128: not so few segments that most of the chip idles
+    (8, 2048, 128, BF16, 16), (10, 4096, 128, BF16, 22), (16, 2048, 128, F16, 16), (16, 4096, 128, BF16, 16),
+    (2, 8192, 128, BF16, 43), (1, 1024, 128, BF16, 16), (160, 4096, 128, BF16, 3), (320, 4096, 128, F16, 2),
+    (400, 4096, 128, F16, 1),
     # units that fill the chip by themselves
     (216, 4738, 64, F16, 2), (512, 1024, 32, BF16, 1), (640, 2048, 64, BF16, 1), (768, 1024, 64, F16, 1),
-    # few units: not so few segments that most of the chip idles
-    (1, 2048, 64, BF16, 32), (4, 8192, 64, F16, 64), (64, 2048, 64, BF16, 8), (96, 1024, 64, F32, 5),
+    (256, 128, 64, BF16, 1),
+    # fewer units
+    (1, 2048, 64, BF16, 16), (4, 8192, 64, F16, 43), (64, 2048, 64, BF16, 8), (160, 300, 64, BF16, 3),
+    (352, 2048, 32, BF16, 2), (96, 1024, 64, F32, 5),
 ])
 def test_causal_split_of_a_shape(lib, units, N, d, dtype, segments):
     lib.cottn_tune_segments(0)
@@ -152,8 +155,8 @@ def test_causal_split_of_a_shape(lib, units, N, d, dtype, segments):
 
 
 def test_causal_split_is_bounded(lib):
-    """Fewer than 512 workgroups beyond the units themselves (1024 for fp32 32 x 32, 256 for 16-bit 128 x
-    128), and so at most 64 MB of states; the forward and the backward always agree."""
+    """A split has at most 640 workgroups (1024 for fp32 and 32 x 32), and so at most 64 MB of states; the
+    forward and the backward always agree."""
     lib.cottn_tune_segments(0)
     for units in [1, 2, 3, 7, 15, 24, 40, 63, 96, 100, 129, 144, 160, 176, 200, 256, 257, 320, 399, 511, 512, 700, 2049]:
         for N in [1, 64, 65, 300, 1024, 4738, 30000]:
@@ -161,8 +164,8 @@ def test_causal_split_is_bounded(lib):
                 for dtype in (F32, BF16):
                     g = lib.cottn_segments_dkdv(0, units, 1, N, dk, dv, 0, dtype)
                     assert g == lib.cottn_segments_dkdv(1, units, 1, N, dk, dv, 0, dtype)
-                    most = 1024 if dtype == F32 and dk == dv == 32 else 256 if dtype != F32 and dk == dv == 128 else 512
-                    assert g == 1 or units * g < most + units, (units, N, dk, dv, dtype, g)
+                    most = 1024 if dtype == F32 or dk == dv == 32 else 640
+                    assert g == 1 or units * g <= most, (units, N, dk, dv, dtype, g)
                     assert lib.cottn_workspace_bytes_dkdv(0, units, 1, N, dk, dv, 0, dtype) <= 64 << 20
 
 

@@ -74,7 +74,7 @@ def _sums_launched(cottn):
 
 
 # (d, segments, whether a launch of its own adds the totals up): both sides of each line, at two units
-@pytest.mark.parametrize("d,segments,launch", [(64, 5, False), (64, 15, False), (64, 16, True), (64, 25, True), (128, 4, False),
+@pytest.mark.parametrize("d,segments,launch", [(64, 5, False), (64, 18, False), (64, 19, True), (64, 25, True), (128, 4, False),
                                                (128, 5, True), (128, 11, True), (32, 17, False)])
 def test_causal_totals_added_in_place_or_carried(cottn, oracle, d, segments, launch):
     """Up to a number of segments the scans add the segment totals up themselves, beyond it a launch of
