@@ -52,7 +52,9 @@ constexpr int kComputeUnits = 256;
 //     states after the other and move all of them.
 // Fitted to the times of 3700 shapes (1 to 1280 units of 128 to 65536 rows, all pairs of widths, the splits
 // that put up to 1300 workgroups on the chip) so that neither the forward alone nor the pair is far from
-// its best: the split chosen takes 0.6 % (geometric mean of the two) longer than the best one.
+// its best: the split chosen takes 0.6 % (geometric mean of the two) longer than the best one.  At 16-bit 128 x
+// 128 the totals weigh more with the pair, which a fit to both alike cut too coarsely (14 units of 777 rows 5
+// segments 21 / 56 us, 13 segments 26 / 45; 2 units of 8192 rows 43 segments 29 / 68, 64 29 / 60).
 double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int dk, int dv) {
   const bool f32 = dtype == COTTN_F32, narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
   const int big = dk > dv ? dk : dv, small = dk > dv ? dv : dk;
@@ -67,8 +69,10 @@ double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int 
   if (g > 1) {
     const double state = double(dk) * dv * 4.0 / 1024.0;   // KB
     us += 5.8 + 0.135 * step * double(steps * on_cu);
-    us += causal_totals_in_place(units, int(g), dk, dv) ? 0.026 * (state + 7.0) * double(g - 1)
-                                                        : 8.0 + 0.3 * double(g) + 0.001 * state * double(units * g);
+    const bool wide = widest && !f32;
+    us += causal_totals_in_place(units, int(g), dk, dv, f32)
+              ? (wide ? 0.037 : 0.026) * (state + 7.0) * double(g - 1)
+              : (wide ? 9.0 + 0.2 * double(g) : 8.0 + 0.3 * double(g)) + 0.001 * state * double(units * g);
   }
   return us;
 }
@@ -76,16 +80,16 @@ double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int 
 // Segments per (batch, head) for the causal calls: the least time by the model among the splits of up to
 // 640 workgroups (1024 for fp32, whose scans hold the longer steps, and for 32 x 32, of which a compute
 // unit runs four), or none.  Finer ones gain the backward little and cost the forward, which runs three
-// workgroups or more at once, a round (768 units of 1024 rows at 64 x 64: 2 segments 86 / 291 us for the
-// forward / with its backward, 1 segment 64 / 275).  Others of the measured, forward / with backward: 16-bit
-// 128 x 128 8 units of 2048 rows 32 segments 30 / 55 us, 16 27 / 51, 8 29 / 73; 288 units of 2048 rows 3
-// segments 198 / 655 us, 1 segment 196 / 785; 64 x 64 64 units of 2048 rows 6 segments 24 / 66, 8 22 / 59;
-// 176 units of 600 rows 3 segments 20.6 / 61, 1 segment 18.3 / 61; fp32 40 units of 1024 rows 8 segments
-// 33 / 94, 11 29 / 81.
+// workgroups or more at once, a round (768 units of 1024 rows at 64 x 64: 2 segments 87 / 291 us for the
+// forward / with its backward, 1 segment 64 / 270).  Others of the measured, forward / with backward: 16-bit
+// 128 x 128 8 units of 2048 rows 32 segments 30 / 55 us, 16 27 / 51, 8 29 / 71; 64 x 64 64 units of 2048
+// rows 6 segments 24 / 66, 8 22 / 59; 176 units of 600 rows 3 segments 19.8 / 61, 2 22.0 / 58, 1 17.8 / 62;
+// fp32 40 units of 1024 rows 8 segments 33 / 94, 11 29 / 80.  Where the line costs most: 128 x 128 288 units
+// of 2048 rows 2 segments 204 / 703 us, 1 190 / 777, but 3, which it leaves out, 195 / 643.
 // No split at all leaves the backward waiting where units are few: up to 160 16-bit units of more than four
 // chunks (of 32 x 32 fewer than 384 of more than eight) take at least two segments, but at 128 x 128, where
-// one unit fills a compute unit (160 units of 300 rows at 64 x 32: 3 segments 9.5 / 26 us, 1 segment 8.6 /
-// 32; 352 units of 2048 rows at 32 x 32: 2 segments 41 / 125, 1 segment 38 / 145).
+// one unit fills a compute unit (160 units of 300 rows at 64 x 32: 3 segments 10.0 / 26 us, 1 segment 9.1
+// / 32; 352 units of 2048 rows at 32 x 32: 2 segments 41 / 125, 1 segment 37 / 136).
 // (Chunks of more than 64 rows, which are for experiments: one and a half workgroups per compute unit,
 // two for long chains.)
 long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk, int dv) {
@@ -114,19 +118,19 @@ long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk
 
 // Segments per (batch, head) for the bidirectional calls.  Their kernels have no chain to
 // shorten and little to set up: about three workgroups per compute unit measured best (B24 H8 N3000
-// d64, forward + backward: 154 us with 4 segments, 164 with 2), in at most four segments, whose
+// d64, forward + backward: 155 us with 4 segments, 169 with 2), in at most four segments, whose
 // totals are soon added up.  Two fit a compute unit at a time, so 193 to 256 units take two
-// segments (B32 H8 N2048: 134 us, 150 us with 3), and with 342 units and more three are the start of a
-// third round, which long sequences feel (352 units of 8192 rows at 32 x 32: 2 segments 145 / 389 us
-// for the forward / with its backward, 3 segments 164 / 424).  At 128 x 128 one workgroup fills a
-// compute unit (B8 H12 N1024 2 segments 91 us, 3 segments 116), and so it does in the dQ sweep of 16-bit
-// rows with 128 and 64 or 128 and 32 columns (B16 H8 N1024 64 x 128 2 segments 63 us, 4 segments
-// 74; from 129 units on, where that leaves one, four are the better again); a little more than one
-// for each takes two, which even the second round out (320 units of 2048 rows: 1 segment 200 / 572 us, 2
-// segments 168 / 490).  Few units with long sequences are cut further, until (nearly) every compute unit
-// has a workgroup and none has two: B1 H2 N65536 128 segments 69 us (64 segments, with 64-row steps, 95);
-// B1 H12 N8192 16 segments 42 us, 32 segments 53; two for the longest at 16-bit 32 x 32, of which it
-// runs four (24 units of 65536 rows: 10 segments 105 / 226 us, 20 segments 72 / 201).
+// segments (B32 H8 N2048: 137 us, 151 us with 3), and with 342 units and more three are the start of a
+// third round, which long sequences feel (352 units of 8192 rows at 32 x 32: 2 segments 146 / 391 us
+// for the forward / with its backward, 3 segments 164 / 422).  At 128 x 128 one workgroup fills a
+// compute unit (B8 H12 N1024 2 segments 90 us, 3 segments 114), and so it does in the dQ sweep of 16-bit
+// rows with 128 and 64 or 128 and 32 columns (B16 H8 N1024 64 x 128 2 segments 62 us, 4 segments
+// 73; from 129 units on, where that leaves one, four are the better again); a little more than one
+// for each takes two, which even the second round out (320 units of 2048 rows: 1 segment 185 / 560 us, 2
+// segments 174 / 485).  Few units with long sequences are cut further, until (nearly) every compute unit
+// has a workgroup and none has two: B1 H2 N65536 128 segments 74 us, 64 segments 84;
+// B1 H12 N8192 16 segments 43 us, 32 segments 53; two for the longest at 16-bit 32 x 32, of which it
+// runs four (24 units of 65536 rows: 10 segments 104 / 231 us, 20 segments 73 / 206).
 long bidir_segments(long units, long N, bool f32, int dk, int dv) {
   const bool widest = dk == 128 && dv == 128, narrowest = dk == 32 && dv == 32;
   const bool one_per_cu = widest || (!f32 && units <= kComputeUnits / 2 && (dk == 128 || (dk == 64 && dv == 128)));

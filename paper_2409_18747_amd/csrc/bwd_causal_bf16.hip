@@ -832,7 +832,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const dim3 grid(units * a.G), block(Cfg::NT);
   const float inv_eps = 1.0f / a.eps;
   // few segments: no carry launches, the scan workgroups add up the totals they need
-  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV);
+  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
   hipError_t err;
   if (a.G > 1) {
     // Forward-time states: taken over from the forward call when it left them behind (raw

@@ -418,7 +418,7 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   const float inv_eps = 1.0f / a.eps;
   hipError_t err = hipSuccess;
   // few segments: no carry launch, each scan workgroup adds up the totals before its segment
-  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV);
+  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
   if (a.G > 1) {
     err = COTTN_SYM(launch_fwd_segment_totals)(a, ws);
     if (err != hipSuccess) return err;

@@ -49,10 +49,14 @@ struct CausalArgs {
 // +0.7, -1.7 / -0.2, -3.9 / -1.7; 16 segments +1.9 / +7.3, -1.3 / +6.5, -1.9 / +6.6; 128 x 128 4 segments
 // -0.7 / -0.1, -2.1 / -1.7, -4.8 / -2.3; 10 segments +2.7 / +5.5, -1.4 / +5.1, -4.8 / 0.0.  The line
 // follows the number of segments where the sums of the two cross, 18 / 24 / 31 or more at 64 x 64, 7 /
-// 10 / 14 at 64 x 128, 4 / 7 / 13 at 128 x 128, or one above: a launch takes the host 3 us too.
-constexpr bool causal_totals_in_place(long units, int G, int dk, int dv) {
+// 10 / 14 at 64 x 128, 4 / 7 / 13 at 128 x 128, or one above: a launch takes the host 3 us too.  At 128 x
+// 128 16-bit rows keep to 4 / 6 / 9: with more in place, 14 units of 1024 rows take 23 / 54 us for the forward
+// / with its backward instead of 24 / 50, though 24 units of 4738 rows take 47 / 128 instead of 51 / 136;
+// fp32 gains everywhere (24 units of 300 rows 30 / 71 instead of 39 / 75).
+constexpr bool causal_totals_in_place(long units, int G, int dk, int dv, bool f32) {
   const long few = units < 32 ? units : 32;
-  return long(G - 1) * dk * dv * 4 <= (dk * dv <= 64 * 64 ? 264 + 10 * few : 200 + 13 * few) * 1024;
+  const long kb = dk * dv <= 64 * 64 ? 264 + 10 * few : 200 + (f32 && dk * dv == 128 * 128 ? 24 : 13) * few;
+  return long(G - 1) * dk * dv * 4 <= kb * 1024;
 }
 // Bidirectional: only the sums are needed, which a backward that is handed the forward's totals takes
 // over where they were left as they are; the line lies where the combine launch is the better one for

@@ -140,7 +140,8 @@ F16 = 2
 @pytest.mark.parametrize("units,N,d,dtype,segments", [
     # 16-bit 128 x 128: not so few segments that most of the chip idles
     (8, 2048, 128, BF16, 16), (10, 4096, 128, BF16, 22), (16, 2048, 128, F16, 16), (16, 4096, 128, BF16, 16),
-    (2, 8192, 128, BF16, 43), (1, 1024, 128, BF16, 16), (160, 4096, 128, BF16, 3), (320, 4096, 128, F16, 2),
+    (2, 8192, 128, BF16, 64), (1, 1024, 128, BF16, 16), (14, 777, 128, BF16, 13),
+    (12, 1500, 128, F16, 12), (14, 1024, 128, BF16, 8), (160, 4096, 128, BF16, 3), (320, 4096, 128, F16, 2),
     (400, 4096, 128, F16, 1),
     # units that fill the chip by themselves
     (216, 4738, 64, F16, 2), (512, 1024, 32, BF16, 1), (640, 2048, 64, BF16, 1), (768, 1024, 64, F16, 1),

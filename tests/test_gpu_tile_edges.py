@@ -88,6 +88,16 @@ def test_causal_totals_added_in_place_or_carried(cottn, oracle, d, segments, lau
         assert _sums_launched(cottn) == launch
 
 
+@pytest.mark.parametrize("dtype,segments,launch", [("f32", 10, False), ("f32", 11, True), ("bf16", 7, False), ("f16", 8, True)])
+def test_causal_totals_of_sixteen_units(cottn, oracle, dtype, segments, launch):
+    """With the units the line of 128 x 128 moves further in fp32 than in 16 bits."""
+    rows = 32 if dtype == "f32" else 64
+    cottn.profile_start()
+    run_shape(cottn, oracle, True, 2, 8, rows * segments - 5, 128, 128, dtype, seed=1450 + segments, segments=segments,
+              saved=segments % 2 == 0)
+    assert _sums_launched(cottn) == launch
+
+
 @pytest.mark.parametrize("d,segments,launch", [(64, 5, False), (64, 24, False), (64, 25, True), (128, 10, False),
                                                (128, 11, True), (32, 17, False)])
 def test_bidirectional_totals_added_in_place_or_combined(cottn, oracle, d, segments, launch):
