@@ -51,11 +51,15 @@ struct BiCfg {
   static constexpr int STATE = DK * SP;
   // the forward stages finished output rows (DV wide) in the wave's own dead query rows when
   // those are wide enough, else in a tile of their own
-  static constexpr bool FWD_OWN_STAGE = lds_pitch(DV) > TPK;
+  static constexpr bool FWD_OWN_STAGE = ELEM * stage_pitch(DV) > LDS_ELEM * TPK;
   // the dQ sweep stages finished rows in a tile of their own when the LDS has room for it,
-  // otherwise behind a barrier in the dead dO tile (fp32 with wide heads)
+  // otherwise behind a barrier in the dead dO tile (fp32 with wide heads); SPLIT3: when that does
+  // not cost a workgroup, otherwise in the dead Q tile, whose rows are always wide enough
+  static constexpr int DQ_BYTES = LDS_ELEM * (TILEK + TILEV + STATE) + 8 * C;
+  static constexpr int DQ_STAGE_BYTES = ELEM * C * stage_tile_pitch(DK, C);
   static constexpr bool DQ_OWN_STAGE =
-      lds_pitch(DK) > TPV || ELEM * (2 * TILEK + TILEV + STATE) + 8 * C <= 160 * 1024;
+      SPLIT3 ? 160 * 1024 / (DQ_BYTES + DQ_STAGE_BYTES) == 160 * 1024 / DQ_BYTES
+             : ELEM * stage_pitch(DK) > LDS_ELEM * TPV || DQ_BYTES + DQ_STAGE_BYTES <= 160 * 1024;
 };
 
 // Slot 0 <- sum over g of the slots, one matrix element per thread (grid: elems/256 workgroups
@@ -84,7 +88,7 @@ __global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals,
 // dst (LDS, elements, row-major [DK][DV] with row pitch SP) <- sum of the first n_sum of the
 // [DK][DV] fp32 matrices at src; the fp32 sum also goes to `copy` when that is not null.
 template <int DK, int DV, int NT, int SP>
-__device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __restrict__ src,
+__device__ __forceinline__ void stage_summed_matrix(lds_t* dst, const float* __restrict__ src,
                                                     int n_sum, float* __restrict__ copy) {
   // up to 16 of a thread's loads are in flight before the first is waited for: PIECES pieces of
   // BATCH matrices (a batch that reaches beyond the last matrix re-reads it and drops it)
@@ -116,7 +120,7 @@ __device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __
     for (int i = 0; i < PIECES; ++i) {
       const int e = e0 + 4 * NT * i;
       if (copy != nullptr) *reinterpret_cast<f32x4*>(copy + e) = sum[i];
-      store4(dst + (e / DV) * SP + e % DV, sum[i][0], sum[i][1], sum[i][2], sum[i][3]);
+      store4_lds(dst + (e / DV) * SP + lds_col(e % DV), sum[i][0], sum[i][1], sum[i][2], sum[i][3]);
     }
   }
 }
@@ -124,7 +128,7 @@ __device__ __forceinline__ void stage_summed_matrix(elem_t* dst, const float* __
 // O_i = s r_i (q_i S) for the rows row_begin .. row_end - 1 of one unit, with S in Sl (not yet
 // behind a barrier); the first C rows have been fetched.  Own: staging tile, or null.
 template <int DK, int DV, int C>
-__device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst, elem_t* Qs, const elem_t* Sl,
+__device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst, lds_t* Qs, const lds_t* Sl,
                                            elem_t* Os, float* rq, const elem_t* __restrict__ Qu,
                                            elem_t* __restrict__ Ou, float scale, int row_begin, int row_end,
                                            float inv_eps, int w, int l) {
@@ -135,7 +139,8 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
   RowPieces<DV> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
-  elem_t* stage = Cfg::FWD_OWN_STAGE ? Os + 16 * w * Cfg::TPV : Qs + 16 * w * TP;
+  void* stage = Cfg::FWD_OWN_STAGE ? static_cast<void*>(Os + 16 * w * stage_tile_pitch(DV, C))
+                                   : static_cast<void*>(Qs + 16 * w * TP);
   for (int row0 = row_begin; row0 < row_end; row0 += C) {
     {
       float rqv[Stage::PASSES];
@@ -153,7 +158,7 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
     frag8 qf[Cfg::KSK], sf[Cfg::KSK][Cfg::DTV];
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks) {
-      qf[ks] = lds_row_frag(Qs + (16 * w + r) * TP + 32 * ks, q4);
+      qf[ks] = lds_row_frag(Qs + (16 * w + r) * TP + lds_col(32 * ks), q4);
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTV; ++nt)
         sf[ks][nt] = lds_col_frag_ks(Sl, SP, ks, q4, 16 * nt, r);
@@ -185,9 +190,9 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
     int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];  // raw q
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];  // [d_key][d_value]
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? Cfg::TILEV : 8];
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];  // raw q
+  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];  // [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? C * stage_tile_pitch(DV, C) : 8];
   __shared__ float rq[C];
 
   fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
@@ -219,8 +224,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
 template <int DK, int DV, int C, class RT = AccTiles<DV, DK, C / 16>>
 __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst,
                                         TileStage<DV, C, BiCfg<DK, DV, C>::NT>& gst,
-                                        f32x4 (&racc)[RT::NCT][RT::NRT], float& ds_lane, elem_t* Qs, elem_t* Gs,
-                                        elem_t* Os, const elem_t* Sl, float* rq, const elem_t* __restrict__ Qu,
+                                        f32x4 (&racc)[RT::NCT][RT::NRT], float& ds_lane, lds_t* Qs, lds_t* Gs,
+                                        elem_t* Os, const lds_t* Sl, float* rq, const elem_t* __restrict__ Qu,
                                         const elem_t* __restrict__ Gu, elem_t* __restrict__ dQu, float scale,
                                         int row_begin, int row_end, float inv_eps, int w, int l) {
   using Cfg = BiCfg<DK, DV, C>;
@@ -251,11 +256,11 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
     for (int nt = 0; nt < Cfg::DTK; ++nt) dq[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks) {
-      const frag8 gf = lds_row_frag(Gs + (16 * w + r) * TPV + 32 * ks, q4);
+      const frag8 gf = lds_row_frag(Gs + (16 * w + r) * TPV + lds_col(32 * ks), q4);
       frag8 srow[Cfg::DTK];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt)
-        srow[nt] = lds_row_frag(Sl + (16 * nt + r) * SP + 32 * ks, q4);
+        srow[nt] = lds_row_frag(Sl + (16 * nt + r) * SP + lds_col(32 * ks), q4);
       __builtin_amdgcn_sched_barrier(0);  // all LDS reads are issued before the first MFMA
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt) dq[nt] = mma16(srow[nt], gf, dq[nt]);
@@ -288,7 +293,10 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
     if (q4 == 0) ds_lane += rho;
     if (!Cfg::DQ_OWN_STAGE) __syncthreads();  // every wave is done with the dO tile
     gather_rows_transposed<DK>(dq, scale * ri,
-                               Cfg::DQ_OWN_STAGE ? Os + 16 * w * TPK : Gs + 16 * w * TPV, l, finished);
+                               Cfg::DQ_OWN_STAGE ? static_cast<void*>(Os + 16 * w * stage_tile_pitch(DK, C))
+                               : SPLIT3          ? static_cast<void*>(Qs + 16 * w * TPK)
+                                                 : static_cast<void*>(Gs + 16 * w * TPV),
+                               l, finished);
     __syncthreads();
   }
   if (row_begin < row_end) {
@@ -316,10 +324,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // qh = r_i q_i
+  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? C * stage_tile_pitch(DK, C) : 8];   // finished dQ rows
+  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
   __shared__ float rq[C];
   __shared__ float ds_wave[Cfg::NW];
 
@@ -379,8 +387,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
 // the first C rows have been fetched.
 template <int DK, int DV, int C>
 __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& kst,
-                                          TileStage<DV, C, BiCfg<DK, DV, C>::NT>& vst, elem_t* Ks, elem_t* Vs,
-                                          const elem_t* Gl, float* rk, const elem_t* __restrict__ Ku,
+                                          TileStage<DV, C, BiCfg<DK, DV, C>::NT>& vst, lds_t* Ks, lds_t* Vs,
+                                          const lds_t* Gl, float* rk, const elem_t* __restrict__ Ku,
                                           const elem_t* __restrict__ Vu, elem_t* __restrict__ dKu,
                                           elem_t* __restrict__ dVu, float scale, int row_begin, int row_end,
                                           float inv_eps, int w, int l) {
@@ -421,11 +429,11 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
     // G V^T contracts over d_value (row fragments of Gl along its rows)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks) {
-      const frag8 vf = lds_row_frag(Vs + (16 * w + r) * TPV + 32 * ks, q4);
+      const frag8 vf = lds_row_frag(Vs + (16 * w + r) * TPV + lds_col(32 * ks), q4);
       frag8 grow[Cfg::DTK];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt)
-        grow[nt] = lds_row_frag(Gl + (16 * nt + r) * SP + 32 * ks, q4);
+        grow[nt] = lds_row_frag(Gl + (16 * nt + r) * SP + lds_col(32 * ks), q4);
       __builtin_amdgcn_sched_barrier(0);  // all LDS reads are issued before the first MFMA
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTK; ++nt) dk[nt] = mma16(grow[nt], vf, dk[nt]);
@@ -434,7 +442,7 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
     // G^T k^T contracts over d_key (fragments down the rows of Gl)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks) {
-      const frag8 kf = lds_row_frag(Ks + (16 * w + r) * TPK + 32 * ks, q4);
+      const frag8 kf = lds_row_frag(Ks + (16 * w + r) * TPK + lds_col(32 * ks), q4);
       frag8 gcol[Cfg::DTV];
 #pragma unroll
       for (int nt = 0; nt < Cfg::DTV; ++nt)
@@ -476,9 +484,9 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
-  __shared__ __attribute__((aligned(16))) elem_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // raw k
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];
+  __shared__ __attribute__((aligned(16))) lds_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
   __shared__ float rk[C];
 
   fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
@@ -538,9 +546,9 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   using Cfg = BiCfg<DK, DV, C>;
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   constexpr int SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // kh, then raw q
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // v, then finished rows
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // kh, then raw q
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // v, then finished rows
+  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // [d_key][d_value]
   __shared__ float rq[C];
 
   fetch_argument_now(Q, K, V, s, O, totals, state, H, N, inv_eps, seq_len, s_per_unit);
@@ -594,10 +602,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
   using Cfg = BiCfg<DK, DV, C>;
   using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
   constexpr int SP = Cfg::SP;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh, then raw k
-  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO, then v
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];   // finished dQ rows
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // Kh^T V, then Qh^T dO, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // qh, then raw k
+  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO, then v
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? C * stage_tile_pitch(DK, C) : 8];   // finished dQ rows
+  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // Kh^T V, then Qh^T dO, [d_key][d_value]
   __shared__ float rq[C];
   __shared__ float ds_wave[Cfg::NW];
 
@@ -686,7 +694,7 @@ hipError_t run_fwd_bidir_rows(const CausalArgs& a) {
                            static_cast<const elem_t*>(a.K), static_cast<const elem_t*>(a.V), a.s,
                            static_cast<elem_t*>(a.O), totals, a.state, a.H, a.N, 1.0f / a.eps, a.seq_len, a.s_per_unit);
 #endif
-  hipError_t err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, totals));
+  hipError_t err = COTTN_ELEM_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, totals));
   if (err != hipSuccess) return err;
   // few segments: the apply workgroups add the totals up themselves (and write `state`)
   const bool sum_in_apply = sum_totals_in_place(a.G, DK, DV);
@@ -722,7 +730,7 @@ hipError_t run_bwd_bidir_rows(const CausalArgs& a) {
   // forward ran the combine kernel), or reduced here
   const float* s_src = a.saved_fwd_states;
   if (s_src == nullptr) {
-    err = COTTN_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, s_totals));
+    err = COTTN_ELEM_SYM(launch_segment_totals)(totals_args(a, a.K, a.V, s_totals));
     if (err != hipSuccess) return err;
     if (!few) {
       err = launch_bidir_combine(s_totals, units, a.G, DK * DV, nullptr, a.stream);
@@ -791,7 +799,16 @@ hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, floa
 }
 #endif
 
-#define COTTN_FOR_EACH_DK_DV(CALL)                                                              \
+#if defined(COTTN_F32_WHOLE)
+hipError_t fwd_bidir_f32w(const CausalArgs& a) { return run_fwd_bidir<128, 128>(a); }
+hipError_t bwd_bidir_f32w(const CausalArgs& a) { return run_bwd_bidir<128, 128>(a); }
+#else
+#ifdef COTTN_ELEM_F32   // the parts of its tiles and state do not fit the LDS
+#define COTTN_128_128(CALL, WHOLE) WHOLE(a)
+#else
+#define COTTN_128_128(CALL, WHOLE) CALL<128, 128>(a)
+#endif
+#define COTTN_FOR_EACH_DK_DV(CALL, WHOLE)                                                       \
   switch (a.dk * 1000 + a.dv) {                                                                 \
     case 32032: return CALL<32, 32>(a);                                                         \
     case 32064: return CALL<32, 64>(a);                                                         \
@@ -801,12 +818,13 @@ hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, floa
     case 64128: return CALL<64, 128>(a);                                                        \
     case 128032: return CALL<128, 32>(a);                                                       \
     case 128064: return CALL<128, 64>(a);                                                       \
-    case 128128: return CALL<128, 128>(a);                                                      \
+    case 128128: return COTTN_128_128(CALL, WHOLE);                                             \
     default: return hipErrorInvalidValue;                                                       \
   }
 
-hipError_t COTTN_SYM(fwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_fwd_bidir) }
+hipError_t COTTN_SYM(fwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_fwd_bidir, fwd_bidir_f32w) }
 
-hipError_t COTTN_SYM(bwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_bwd_bidir) }
+hipError_t COTTN_SYM(bwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_bwd_bidir, bwd_bidir_f32w) }
+#endif
 
 }  // namespace cottn

@@ -69,21 +69,23 @@ struct BwdCfg {
   static constexpr int TILEK = C * TPK, TILEV = C * TPV;
   // the copy of the running state in elements, [d_key][d_value] in both scans
   static constexpr int STATE = DK * SPV;
-  static constexpr int LDS_BYTES = ELEM * (2 * TILEK + 2 * TILEV + STATE) + 4 * C * CS + 4 * C + 64;
+  static constexpr int LDS_BYTES = LDS_ELEM * (2 * TILEK + 2 * TILEV + STATE) + 4 * C * CS + 4 * C + 64;
   static constexpr int WG_PER_CU = (160 * 1024) / LDS_BYTES;
   // the dQ kernel adds a staging tile when that does not lower the workgroups per compute
-  // unit, and must when the finished rows (DK wide) do not fit the rows of the dO tile
+  // unit, and must when the finished rows (DK wide) do not fit the rows of the dO tile (the parts of
+  // SPLIT3 rows leave room for them in the Q tile)
+  static constexpr int OP = stage_tile_pitch(DK, C);   // of that tile, in elem_t
   static constexpr bool DQ_OWN_STAGE =
-      lds_pitch(DK) > TPV ||
-      (CS == 1 && LDS_BYTES + ELEM * TILEK <= 160 * 1024 &&
-       (160 * 1024) / (LDS_BYTES + ELEM * TILEK) == WG_PER_CU);
+      (!SPLIT3 && ELEM * stage_pitch(DK) > LDS_ELEM * TPV) ||
+      (CS == 1 && LDS_BYTES + ELEM * C * OP <= 160 * 1024 &&
+       (160 * 1024) / (LDS_BYTES + ELEM * C * OP) == WG_PER_CU);
   // The operands of a 32-token step are read in several groups (masked tiles first), each used
   // up before the next is read, instead of all at once: fewer registers in use at a time.  For
-  // 128 x 128, where everything at once does not fit, and for fp32, whose MFMAs take so long
-  // that one group's reads hide behind the other wave's products.
+  // 128 x 128, where everything at once does not fit, and for fp32, whose products take so long
+  // that one group's reads hide behind the other wave's.
   static constexpr bool PHASED = CS == 2 && (ELEM_IS_F32 || (DK == 128 && DV == 128));
   // masked tiles formed by the two waves of a row group together (MaskedExchange); 32-row chunks
-  static constexpr bool SHARE_MASKED = ELEM_IS_F32 && CS == 2 && C == 32;
+  static constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -107,15 +109,17 @@ struct BwdCfg {
 // read at once 9 and 18 registers spill, a spilled register comes back behind the rows
 // prefetched for the next step, and the scans take 43 / 52 us.
 //
-// fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four.  An
-// fp32 MFMA has a sixteenth of the bf16 rate, so these kernels sit near the matrix units' time
-// (B8 H12 N1024 d64: dQ 20 us and dK/dV 23 us of MFMA at the 154 TFLOP/s a large fp32 product
-// reaches) where their 16-bit twins wait for latencies; 32 rows instead of 64 save a fifth of
-// the masked products, and the two waves of a row group form them together and only where
-// something is visible (MaskedExchange; 6 of 18 and 8 of 24 products of a wave before that were
-// masked ones).  Measured there: dQ 45 us, dK/dV 52 us (47 and 57 with every wave forming all of its
-// group's tiles, 51 and 60 with the operands of a step read at once besides).  A third workgroup
-// on the compute unit (168 registers) spills and is slower.
+// fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four, of which the
+// tiles and the state in parts (device_common.h: SPLIT3) leave room for two at 64 x 64.  B8 H12 N1024 d64:
+// dQ 46 -> 38 us, dK/dV 52 -> 44 us against the fp32 matrix instruction; the scans' rows take 25 and 30 us
+// through HBM.  The vector ALU bounds them: 5.5 instructions part an element, of the rows once and of the
+// state once a step.  64-row steps with eight waves, one workgroup to a compute unit, take 51 and 63
+// us; products of results straight into their sums (no instruction for the addition) 38 and 45, at
+// 1.2 times the error.
+// Where the whole fp32 kernels stand, an MFMA has a sixteenth of the bf16 rate: 32 rows instead of 64
+// save a fifth of the masked products, and the two waves of a row group form them together and only
+// where something is visible (MaskedExchange).  A third workgroup on the compute unit (168 registers)
+// spills and is slower.
 template <int DK, int DV, int C> struct BwdSplit {
   static constexpr bool WIDE = DK != DV && DK >= 64 && DV >= 64;
   static constexpr int CR = WIDE ? 32 : C, CS = ELEM_IS_F32 || WIDE || (DK == 128 && DV == 128) ? 2 : 1;
@@ -160,15 +164,15 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SPV;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // kh = r_j k_j
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // raw v
-  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) elem_t St[DK * Cfg::SPV];  // state, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // qh = r_i q_i
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // kh = r_j k_j
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v
+  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
+  __shared__ __attribute__((aligned(16))) lds_t St[DK * Cfg::SPV];  // state, [d_key][d_value]
   // Every wave reads all rows of all four tiles until the end of a chunk (the reverse total
   // contracts Qs and Gs over the tokens), so finished dQ rows are staged in a tile of their
-  // own when LDS has room for one; otherwise behind a barrier in the dead dO tile.
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? Cfg::TILEK : 8];
+  // own when LDS has room for one; otherwise behind a barrier in the dead dO (SPLIT3: Q) tile.
+  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? C * Cfg::OP : 8];
   __shared__ float rq[C];
   __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
   __shared__ float ds_wave[Cfg::NW];
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   // barrier after the last of them is read), so that 128 x 32 keeps two workgroups
   constexpr bool IN_STAGE = Cfg::SHARE_MASKED && Cfg::DQ_OWN_STAGE;
   using Masked = MaskedExchange<Cfg::SHARE_MASKED ? 2 : 0>;
-  static_assert(!IN_STAGE || sizeof(Masked) <= sizeof(elem_t) * Cfg::TILEK, "the tiles fit the staging tile");
+  static_assert(!IN_STAGE || sizeof(Masked) <= sizeof(Os), "the tiles fit the staging tile");
   __shared__ __attribute__((aligned(16))) char masked_lds[Cfg::SHARE_MASKED && !IN_STAGE ? sizeof(Masked) : 16];
   Masked& masked = *reinterpret_cast<Masked*>(IN_STAGE ? reinterpret_cast<char*>(Os) : masked_lds);
 
@@ -252,8 +256,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
         for (int y = 0; y < AT::NRT; ++y) {
-          store4(St + (16 * AT::row_tile(rg, cp, y) + r) * SP + 16 * AT::col_tile(rg, cp, x) + 4 * q4,
-                 sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
+          store4_lds(St + (16 * AT::row_tile(rg, cp, y) + r) * SP + lds_col(16 * AT::col_tile(rg, cp, x)) + 4 * q4,
+                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
         }
     }
     {
@@ -289,7 +293,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     frag8 gf[Cfg::KSV];  // dO rows of this wave: column-side operand of every product
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks)
-      gf[ks] = lds_row_frag(Gs + (16 * rg + r) * TPV + 32 * ks, q4);
+      gf[ks] = lds_row_frag(Gs + (16 * rg + r) * TPV + lds_col(32 * ks), q4);
     // dq[nt][v] = dqh[query 16 rg + r][key feature colk + 16 nt + 4 q4 + v]
     f32x4 dq[NKT];
 #pragma unroll
@@ -299,7 +303,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       frag8 sf[NKT];
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt)
-        sf[nt] = lds_row_frag(St + (colk + 16 * nt + r) * SP + 32 * ks, q4);
+        sf[nt] = lds_row_frag(St + (colk + 16 * nt + r) * SP + lds_col(32 * ks), q4);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16(sf[nt], gf[ks], dq[nt]);
@@ -319,7 +323,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSV; ++ks)
-            vr[half][ks] = lds_row_frag(Vs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
+            vr[half][ks] = lds_row_frag(Vs + (16 * (2 * p + half) + r) * TPV + lds_col(32 * ks), q4);
       };
       const auto form_masked = [&] {
 #pragma unroll
@@ -419,8 +423,10 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     if (q4 == 0 && cp == 0) ds_lane += rho;
     if (CS == 1 && !Cfg::DQ_OWN_STAGE) __syncthreads();  // every wave is done with the dO tile
     gather_rows_transposed<DK, NKT>(dq, scale * ri,
-                                    Cfg::DQ_OWN_STAGE ? Os + 16 * rg * TPK : Gs + 16 * rg * TPV, l,
-                                    finished, colk);
+                                    Cfg::DQ_OWN_STAGE ? static_cast<void*>(Os + 16 * rg * Cfg::OP)
+                                    : SPLIT3        ? static_cast<void*>(Qs + 16 * rg * TPK)
+                                                    : static_cast<void*>(Gs + 16 * rg * TPV),
+                                    l, finished, colk);
     __syncthreads();
   }
   if (row_begin < row_end) {
@@ -472,11 +478,11 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SPV;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // r_i q_i
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // raw v
-  __shared__ __attribute__((aligned(16))) elem_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) elem_t Rl[DK * Cfg::SPV];  // reverse state, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // r_i q_i
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // raw k
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v
+  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
+  __shared__ __attribute__((aligned(16))) lds_t Rl[DK * Cfg::SPV];  // reverse state, [d_key][d_value]
   __shared__ float rk[C];
   __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
   // P tiles of the two query halves, then the A tiles
@@ -566,8 +572,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
         for (int y = 0; y < AT::NRT; ++y) {
-          store4(Rl + (16 * AT::col_tile(rg, cp, x) + r) * SP + 16 * AT::row_tile(rg, cp, y) + 4 * q4,
-                 racc[x][y][0], racc[x][y][1], racc[x][y][2], racc[x][y][3]);
+          store4_lds(Rl + (16 * AT::col_tile(rg, cp, x) + r) * SP + lds_col(16 * AT::row_tile(rg, cp, y)) + 4 * q4,
+                     racc[x][y][0], racc[x][y][1], racc[x][y][2], racc[x][y][3]);
         }
     }
     {
@@ -607,10 +613,10 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     frag8 kf[Cfg::KSK], vf[Cfg::KSV];  // this wave's key rows and value rows (column side)
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks)
-      kf[ks] = lds_row_frag(Ks + (16 * rg + r) * TPK + 32 * ks, q4);
+      kf[ks] = lds_row_frag(Ks + (16 * rg + r) * TPK + lds_col(32 * ks), q4);
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSV; ++ks)
-      vf[ks] = lds_row_frag(Vs + (16 * rg + r) * TPV + 32 * ks, q4);
+      vf[ks] = lds_row_frag(Vs + (16 * rg + r) * TPV + lds_col(32 * ks), q4);
     // dk[nt][v] = dkh[key 16 rg + r][feature colk + 16 nt + 4 q4 + v]; dv likewise before s r_j
     f32x4 dk[NKT], dv[NVT];
 #pragma unroll
@@ -631,7 +637,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       if (ks < Cfg::KSV) {
 #pragma unroll
         for (int nt = 0; nt < NKT; ++nt)
-          rrow[nt] = lds_row_frag(Rl + (colk + 16 * nt + r) * SP + 32 * ks, q4);
+          rrow[nt] = lds_row_frag(Rl + (colk + 16 * nt + r) * SP + lds_col(32 * ks), q4);
       }
       __builtin_amdgcn_sched_barrier(0);
       if (ks < KS_BOTH && NKT == NVT) {
@@ -663,12 +669,12 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       const auto read_queries = [&](int half) {
 #pragma unroll
         for (int ks = 0; ks < Cfg::KSK; ++ks)
-          qr[half][ks] = lds_row_frag(Qs + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
+          qr[half][ks] = lds_row_frag(Qs + (16 * (2 * p + half) + r) * TPK + lds_col(32 * ks), q4);
       };
       const auto read_out_grads = [&](int half) {
 #pragma unroll
         for (int ks = 0; ks < Cfg::KSV; ++ks)
-          gr[half][ks] = lds_row_frag(Gs + (16 * (2 * p + half) + r) * TPV + 32 * ks, q4);
+          gr[half][ks] = lds_row_frag(Gs + (16 * (2 * p + half) + r) * TPV + lds_col(32 * ks), q4);
       };
       const auto read_query_columns = [&] {
 #pragma unroll
@@ -843,7 +849,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
     if (a.saved_fwd_states != nullptr) {
       fwd_states = a.saved_fwd_states;
     } else {
-      err = COTTN_SYM(launch_fwd_segment_totals)(a, own_fwd);
+      err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, own_fwd);
       if (err != hipSuccess) return err;
       if (!sum_in_scan) {
         err = launch_bwd_state_carry(own_fwd, nullptr, units, a.G, DK * DV, a.stream);
@@ -883,17 +889,22 @@ hipError_t launch_bwd_state_carry(float* fwd_tot, float* rev_tot, int units, int
 #endif
 
 hipError_t COTTN_SYM(bwd_causal)(const CausalArgs& a) {
-#ifdef COTTN_ELEM_F32
+#if defined(COTTN_F32_WHOLE)
+  switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
+    case 32128032: return run_bwd_causal<32, 128, 32>(a);
+    case 128032032: return run_bwd_causal<128, 32, 32>(a);
+    case 128128032: return run_bwd_causal<128, 128, 32>(a);
+    default: return hipErrorInvalidValue;
+  }
+#elif defined(COTTN_ELEM_F32)
   switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
     case 32032032: return run_bwd_causal<32, 32, 32>(a);
     case 32064032: return run_bwd_causal<32, 64, 32>(a);
-    case 32128032: return run_bwd_causal<32, 128, 32>(a);
+    case 32128032: case 128032032: case 128128032: return bwd_causal_f32w(a);   // device_common.h: SPLIT3
     case 64032032: return run_bwd_causal<64, 32, 32>(a);
     case 64064032: return run_bwd_causal<64, 64, 32>(a);
     case 64128032: return run_bwd_causal<64, 128, 32>(a);
-    case 128032032: return run_bwd_causal<128, 32, 32>(a);
     case 128064032: return run_bwd_causal<128, 64, 32>(a);
-    case 128128032: return run_bwd_causal<128, 128, 32>(a);
     default: return hipErrorInvalidValue;
   }
 #else

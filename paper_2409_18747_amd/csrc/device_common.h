@@ -2,41 +2,83 @@
 // fragment reads (plain and transposing), packing, lane reductions.
 // Nothing in here knows about attention.
 //
-// The MFMA kernels are written once for a floating-point element and compiled three times:
+// The MFMA kernels are written once for a floating-point element and compiled for three:
 // bfloat16 by default, IEEE half when the translation unit defines COTTN_ELEM_F16 before
 // including anything, fp32 with COTTN_ELEM_F32 (the *_f16.hip and *_f32.hip files do exactly
-// that and then include the kernel source).  COTTN_SYM(name) appends the element's suffix to
-// kernel and launcher names.
+// that and then include the kernel source).  fp32 comes in two ways, see SPLIT3 below.
+// COTTN_SYM(name) appends the element's suffix to kernel and launcher names.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace cottn {
 
-#if defined(COTTN_ELEM_F32)
-typedef float elem_native;  // the compiler's type for one element
-typedef float elem_t;       // storage type of an element in global memory and LDS
+// fp32 elements: how their products are formed.
+//   SPLIT3  every operand in three bfloat16 parts x = x0 + x1 + x2 (each the rest rounded to
+//           nearest: the sum is x exactly), six of the nine products of parts on the bf16 matrix
+//           instruction.  Left out are x1 y2, x2 y1 and x2 y2: at most 2^-25 of a product, 2^-28
+//           in the root mean square, where an fp32 addition rounds to 2^-25.  The bf16 rate is
+//           sixteen times the fp32 one, so this takes 6/16 of the time, and the operands that are
+//           contracted over the tokens can take the transposing LDS read.
+//   else    the fp32 matrix instruction (COTTN_F32_WHOLE: the *_f32w.hip files), where the parts do
+//           not fit the LDS (128 x 128) or fit it for one causal workgroup instead of two (128 x 32
+//           and 32 x 128: B4 H8 N2048 forward + backward 121 / 140 and 108 / 123 us, whole / parts).
+// Elsewhere the parts are the faster way: forward + backward, whole / parts, B4 H8 N2048 causal 32 x
+// 32 50 / 47 us, 64 x 64 106 / 88, 64 x 128 181 / 152, bidirectional 64 x 64 66 / 63, 128 x 64 122 /
+// 105; B32 H16 N512 causal 64 x 64 271 / 227.  Then the vector ALU is what they wait for (busy half of
+// the time, the matrix units a quarter): 5.5 instructions to part an element, 60 % of a step's.
+#if defined(COTTN_ELEM_F32) && defined(COTTN_F32_WHOLE)
+typedef float elem_native;  // the compiler's type for one element of an MFMA operand
+typedef float elem_t;       // storage type of an element in global memory
+typedef float lds_t;        // what the operand tiles and state copies in LDS are made of
+#define COTTN_SYM(name) name##_f32w
+#define COTTN_SYM_STR(name) #name "_f32w"
+#elif defined(COTTN_ELEM_F32)
+typedef __bf16 elem_native;
+typedef float elem_t;
+typedef uint16_t lds_t;
 #define COTTN_SYM(name) name##_f32
 #define COTTN_SYM_STR(name) #name "_f32"
 #elif defined(COTTN_ELEM_F16)
 typedef _Float16 elem_native;
 typedef uint16_t elem_t;
+typedef uint16_t lds_t;
 #define COTTN_SYM(name) name##_f16
 #define COTTN_SYM_STR(name) #name "_f16"
 #else
 typedef __bf16 elem_native;
 typedef uint16_t elem_t;
+typedef uint16_t lds_t;
 #define COTTN_SYM(name) name##_bf16
 #define COTTN_SYM_STR(name) #name "_bf16"
+#endif
+// launchers that both fp32 builds call and one defines
+#if defined(COTTN_ELEM_F32)
+#define COTTN_ELEM_SYM(name) name##_f32
+#else
+#define COTTN_ELEM_SYM(name) COTTN_SYM(name)
 #endif
 #ifdef COTTN_ELEM_F32
 constexpr bool ELEM_IS_F32 = true;
 #else
 constexpr bool ELEM_IS_F32 = false;
 #endif
+#if defined(COTTN_ELEM_F32) && !defined(COTTN_F32_WHOLE)
+#define COTTN_SPLIT3
+constexpr bool SPLIT3 = true;
+#else
+constexpr bool SPLIT3 = false;
+#endif
+constexpr bool F32_WHOLE = ELEM_IS_F32 && !SPLIT3;
 constexpr int ELEM = int(sizeof(elem_t));
+constexpr int LDS_ELEM = int(sizeof(lds_t));
 constexpr int EPP = 16 / ELEM;  // elements in a 16-byte piece of a row
-typedef __attribute__((ext_vector_type(8))) elem_native frag8;  // one MFMA operand fragment
+typedef __attribute__((ext_vector_type(8))) elem_native native8;
+#ifdef COTTN_SPLIT3
+struct frag8 { native8 part[3]; };   // one MFMA operand fragment
+#else
+typedef native8 frag8;
+#endif
 typedef __attribute__((ext_vector_type(2))) elem_native elem2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -45,7 +87,12 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 #define COTTN_LDS __attribute__((address_space(3)))
 
-// Row pitches (in elements) of 16-bit LDS arrays.  The LDS moves 64 lanes x 16 bytes in 4
+// Where column c of a row lies in an LDS tile or state copy.  SPLIT3: every 32 columns are 32
+// first, 32 second and 32 third parts, so that parts of an element are always 32 apart.
+constexpr int PART = 32;
+__host__ __device__ constexpr int lds_col(int c) { return SPLIT3 ? (c >> 5) * (3 * PART) + (c & (PART - 1)) : c; }
+
+// Row pitches (in lds_t) of 16-bit LDS arrays.  The LDS moves 64 lanes x 16 bytes in 4
 // cycles and 64 x 8 bytes in 2.4 at best (4 for a transposing read of rows that are 8 apart);
 // how the 64 addresses of an instruction fall into banks decides whether it gets there.
 // Measured on gfx950 with every access pattern of these kernels (cycles per wave instruction,
@@ -60,26 +107,39 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 // cols + 16 (unless four such tiles and a state copy would not fit the 160 KB of a compute
 // unit: 256-row chunks at d = 64), the state copies and the staging of finished rows
 // (8-byte writes) cols + 8.
-// fp32 rows take cols + 4 everywhere: the fp32 kernels time the same with 8, 12 and 16 (within
-// 3 %), and the smaller tiles leave room for a third workgroup on a compute unit (forward scan
-// at d = 64: 55 -> 52 KB).
-__host__ __device__ constexpr int lds_pitch(int cols) { return ELEM_IS_F32 ? cols + 4 : cols + 8; }
+// SPLIT3 rows are three times as long and read the same way: the same two paddings.
+// Whole fp32 rows take cols + 4 everywhere: 8, 12 and 16 time the same (within 3 %).
+__host__ __device__ constexpr int lds_pitch(int cols) {
+  return F32_WHOLE ? cols + 4 : (SPLIT3 ? 3 * cols : cols) + 8;
+}
 __host__ __device__ constexpr int tile_pitch(int cols, int rows) {
-  return !ELEM_IS_F32 && 2 * (4 * rows * (cols + 16) + cols * lds_pitch(cols)) + 1024 <= 160 * 1024
+  return SPLIT3 ? 3 * cols + 16
+         : !F32_WHOLE && 2 * (4 * rows * (cols + 16) + cols * lds_pitch(cols)) + 1024 <= 160 * 1024
              ? cols + 16
              : lds_pitch(cols);
+}
+// Pitch (in elem_t) of staged result rows, and between the row groups of a staging tile of its own.
+__host__ __device__ constexpr int stage_pitch(int cols) { return ELEM_IS_F32 ? cols + 4 : cols + 8; }
+__host__ __device__ constexpr int stage_tile_pitch(int cols, int rows) {
+  return SPLIT3 ? stage_pitch(cols) : tile_pitch(cols, rows);
 }
 
 // D(16x16) += A(16x32) * B(32x16), fp32 accumulate.
 // Lane l = 16*g + r holds  A[row r][k slots of g],  B[k slots of g][col r],
 // and D[row 4g+v][col r] in acc[v].  The order of the k slots is free as long as A and B
 // use the same one, which several kernels exploit to feed an accumulator tile straight
-// back in as an operand.  16-bit elements: one instruction.  fp32: eight of the 16x16x4 kind,
-// the j-th over the j-th element of every lane's fragment (256 flop per cycle and compute
-// unit, a sixteenth of the bf16 rate; the vector ALU without packed instructions reaches half
-// of that and would need its operands spread over the lanes by hand).
+// back in as an operand.  16-bit elements: one instruction.  SPLIT3: six, the smallest products
+// first.  Whole fp32: eight of the 16x16x4 kind, the j-th over the j-th element of every lane's
+// fragment (256 flop per cycle and compute unit, a sixteenth of the bf16 rate).
 __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
-#if defined(COTTN_ELEM_F32)
+#if defined(COTTN_SPLIT3)
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[0], b.part[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[2], b.part[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[1], b.part[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[0], b.part[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[1], b.part[0], acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part[0], b.part[0], acc, 0, 0, 0);
+#elif defined(COTTN_ELEM_F32)
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
   return acc;
@@ -92,10 +152,10 @@ __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
 
 // The k slots of lane row g = lane / 16 in a fragment whose k index runs over 32 consecutive
 // columns (or rows) of an LDS tile: elements 0..3 at slot_lo(g).., elements 4..7 at
-// slot_hi(g)...  16-bit: eight consecutive elements, one 16-byte read; fp32: two groups of four
-// 16 apart, so that the four lane rows of one 16-byte read cover 64 consecutive bytes.
-__device__ __forceinline__ int slot_lo(int g) { return ELEM_IS_F32 ? 4 * g : 8 * g; }
-__device__ __forceinline__ int slot_hi(int g) { return ELEM_IS_F32 ? 16 + 4 * g : 8 * g + 4; }
+// slot_hi(g)...  16-bit: eight consecutive elements, one 16-byte read; whole fp32: two groups of
+// four 16 apart, so that the four lane rows of one 16-byte read cover 64 consecutive bytes.
+__device__ __forceinline__ int slot_lo(int g) { return F32_WHOLE ? 4 * g : 8 * g; }
+__device__ __forceinline__ int slot_hi(int g) { return F32_WHOLE ? 16 + 4 * g : 8 * g + 4; }
 
 // The products over 32 tokens added to a sum that is longer.  fp32: formed on their own and added
 // as one addend, so that the sum is rounded once per 32 tokens and not once per four (causal, N =
@@ -107,11 +167,11 @@ __device__ __forceinline__ f32x4 mma16_add(frag8 a, frag8 b, f32x4 sum) {
   return f32x4{sum[0] + t[0], sum[1] + t[1], sum[2] + t[2], sum[3] + t[3]};
 }
 
-// fp32 only: the same over half of the k slots, the `half`-th four elements of every
+// Whole fp32 only: the same over half of the k slots, the `half`-th four elements of every
 // lane's fragments (what the other half would contract is known to be zero).
 __device__ __forceinline__ f32x4 mma16_half_add(frag8 a, frag8 b, f32x4 sum, int half) {
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#ifdef COTTN_ELEM_F32
+#ifdef COTTN_F32_WHOLE
   if (half == 0) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
@@ -123,13 +183,13 @@ __device__ __forceinline__ f32x4 mma16_half_add(frag8 a, frag8 b, f32x4 sum, int
   return f32x4{sum[0] + acc[0], sum[1] + acc[1], sum[2] + acc[2], sum[3] + acc[3]};
 }
 
-// fp32 only: the dot products of 16 rows at x (rows down the result tile) with 16 rows at y (rows
+// Whole fp32 only: the dot products of 16 rows at x (rows down the result tile) with 16 rows at y (rows
 // along it), over columns first_col .. first_col + 16 BLOCKS - 1 of both.  x, y: this lane's
 // row (lane % 16 of the 16), g: lane / 16.
 template <int BLOCKS>
-__device__ __forceinline__ f32x4 row_products(const elem_t* x, const elem_t* y, int first_col, int g) {
+__device__ __forceinline__ f32x4 row_products(const lds_t* x, const lds_t* y, int first_col, int g) {
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#ifdef COTTN_ELEM_F32
+#ifdef COTTN_F32_WHOLE
 #pragma unroll
   for (int i = 0; i < BLOCKS; ++i) {
     const f32x4 a = *reinterpret_cast<const f32x4*>(x + first_col + 16 * i + 4 * g);
@@ -143,8 +203,14 @@ __device__ __forceinline__ f32x4 row_products(const elem_t* x, const elem_t* y, 
 
 // Operand fragment whose k index runs along an LDS row; p: the row at the first of the 32
 // columns, g: lane / 16.
-__device__ __forceinline__ frag8 lds_row_frag(const elem_t* p, int g) {
-#ifdef COTTN_ELEM_F32
+__device__ __forceinline__ frag8 lds_row_frag(const lds_t* p, int g) {
+#if defined(COTTN_SPLIT3)
+  frag8 f;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    f.part[i] = __builtin_bit_cast(native8, *reinterpret_cast<const uint4*>(p + PART * i + slot_lo(g)));
+  return f;
+#elif defined(COTTN_ELEM_F32)
   const f32x4 lo = *reinterpret_cast<const f32x4*>(p + slot_lo(g));
   const f32x4 hi = *reinterpret_cast<const f32x4*>(p + slot_hi(g));
   return frag8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -156,19 +222,19 @@ __device__ __forceinline__ frag8 lds_row_frag(const elem_t* p, int g) {
 // Transposing 8-byte LDS read (gfx950): inside each group of 16 lanes, lane i passes the
 // address of 4 consecutive elements, taken as row i/4, columns 4*(i%4).. of a 4x16 block;
 // it receives column i of the block's 4 rows.
-#ifndef COTTN_ELEM_F32
-__device__ __forceinline__ s16x4 lds_read_tr(const elem_t* p) {
+#ifndef COTTN_F32_WHOLE
+__device__ __forceinline__ s16x4 lds_read_tr(const lds_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((COTTN_LDS s16x4*)(p));
 }
 #endif
 
 // Operand fragment whose k index runs DOWN the rows of a row-major LDS tile (pitch in
-// elements): the lane with r = lane%16 receives tile[k0 + 0..3][col0 + r] and
+// lds_t): the lane with r = lane%16 receives tile[k0 + 0..3][col0 + r] and
 // tile[k1 + 0..3][col0 + r].  k0/k1 are the first rows of the two 4-row groups that
-// fill this lane's 8 k slots.
-__device__ __forceinline__ frag8 lds_col_frag(const elem_t* tile, int pitch, int k0, int k1,
+// fill this lane's 8 k slots; col0 is a multiple of 16.
+__device__ __forceinline__ frag8 lds_col_frag(const lds_t* tile, int pitch, int k0, int k1,
                                                int col0, int r) {
-#ifdef COTTN_ELEM_F32
+#ifdef COTTN_F32_WHOLE
   // (no transposing read of 4-byte elements: a lane reads its column element by element)
   frag8 v;
 #pragma unroll
@@ -178,28 +244,35 @@ __device__ __forceinline__ frag8 lds_col_frag(const elem_t* tile, int pitch, int
   }
   return v;
 #else
-  const int sub_row = r >> 2, sub_col = (r & 3) * 4;
-  s16x4 lo = lds_read_tr(tile + (k0 + sub_row) * pitch + col0 + sub_col);
-  s16x4 hi = lds_read_tr(tile + (k1 + sub_row) * pitch + col0 + sub_col);
-  s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(frag8, v);
+  const int sub_row = r >> 2, sub_col = lds_col(col0) + (r & 3) * 4;
+  const auto part = [&](int off) {
+    s16x4 lo = lds_read_tr(tile + (k0 + sub_row) * pitch + sub_col + off);
+    s16x4 hi = lds_read_tr(tile + (k1 + sub_row) * pitch + sub_col + off);
+    s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(native8, v);
+  };
+#ifdef COTTN_SPLIT3
+  return frag8{{part(0), part(PART), part(2 * PART)}};
+#else
+  return part(0);
+#endif
 #endif
 }
 // The same over rows 32 ks .. 32 ks + 31, in the slot order of lds_row_frag.
-__device__ __forceinline__ frag8 lds_col_frag_ks(const elem_t* tile, int pitch, int ks, int g,
+__device__ __forceinline__ frag8 lds_col_frag_ks(const lds_t* tile, int pitch, int ks, int g,
                                                   int col0, int r) {
   return lds_col_frag(tile, pitch, 32 * ks + slot_lo(g), 32 * ks + slot_hi(g), col0, r);
 }
 
 // Elements <-> fp32; conversions to the element type round to nearest even.
-#ifndef COTTN_ELEM_F32
+#ifndef COTTN_F32_WHOLE
 // two values rounded and packed into one word (low half first): written as one vector
 // conversion so that it becomes the packed convert instruction, not two converts and a merge
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   typedef __attribute__((ext_vector_type(2))) float f32x2;
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, elem2));
 }
-// the two elements of a 32-bit word (low half first)
+// the two 16-bit values of a word (low half first)
 __device__ __forceinline__ void unpack2(uint32_t w, float& lo, float& hi) {
 #ifdef COTTN_ELEM_F16
   const elem2 p = __builtin_bit_cast(elem2, w);
@@ -210,6 +283,24 @@ __device__ __forceinline__ void unpack2(uint32_t w, float& lo, float& hi) {
   hi = __builtin_bit_cast(float, w & 0xFFFF0000u);
 #endif
 }
+#endif
+#ifdef COTTN_SPLIT3
+// x[0..3] as their three parts, two to a word: parts[i] holds the i-th ones
+__device__ __forceinline__ void split4(const float (&x)[4], uint2 (&parts)[3]) {
+  float rest[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    parts[i] = uint2{pack2(rest[0], rest[1]), pack2(rest[2], rest[3])};
+    if (i == 2) break;
+    float p[4];
+    unpack2(parts[i].x, p[0], p[1]);
+    unpack2(parts[i].y, p[2], p[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) rest[e] -= p[e];   // exact
+  }
+}
+#endif
+#ifndef COTTN_ELEM_F32
 // fp32 sum of squares of the two elements of a word, added to acc
 __device__ __forceinline__ float dot2_self(uint32_t w, float acc) {
   const elem2 p = __builtin_bit_cast(elem2, w);
@@ -240,6 +331,42 @@ __device__ __forceinline__ void load4(const elem_t* src, float* f) {
   const uint2 raw = *reinterpret_cast<const uint2*>(src);
   unpack2(raw.x, f[0], f[1]);
   unpack2(raw.y, f[2], f[3]);
+#endif
+}
+// The same four in an LDS tile or state copy.
+__device__ __forceinline__ void store4_lds(lds_t* dst, float a, float b, float c, float d) {
+#ifdef COTTN_SPLIT3
+  const float x[4] = {a, b, c, d};
+  uint2 parts[3];
+  split4(x, parts);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(dst + PART * i) = parts[i];
+#else
+  store4(dst, a, b, c, d);
+#endif
+}
+__device__ __forceinline__ void load4_lds(const lds_t* src, float* f) {
+#ifdef COTTN_SPLIT3
+  float p[3][4];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint2 raw = *reinterpret_cast<const uint2*>(src + PART * i);
+    unpack2(raw.x, p[i][0], p[i][1]);
+    unpack2(raw.y, p[i][2], p[i][3]);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) f[e] = (p[0][e] + p[1][e]) + p[2][e];   // exact
+#else
+  load4(src, f);
+#endif
+}
+// a 16-byte piece of a row to its place in an LDS tile
+__device__ __forceinline__ void store_piece_lds(lds_t* dst, uint4 raw) {
+#ifdef COTTN_SPLIT3
+  store4_lds(dst, __builtin_bit_cast(float, raw.x), __builtin_bit_cast(float, raw.y),
+             __builtin_bit_cast(float, raw.z), __builtin_bit_cast(float, raw.w));
+#else
+  *reinterpret_cast<uint4*>(dst) = raw;
 #endif
 }
 // a 16-byte piece of a row (EPP elements): its sum of squares, and the piece times a factor
@@ -276,7 +403,18 @@ __device__ __forceinline__ uint4 piece_times(uint4 raw, float f) {
 // lane row g is k slot 16 half + 4 g + v of the fragment.
 __device__ __forceinline__ void put_half(frag8& frag, int half, f32x4 acc, bool k0, bool k1,
                                          bool k2, bool k3) {
-#ifdef COTTN_ELEM_F32
+#if defined(COTTN_SPLIT3)
+  const float x[4] = {k0 ? acc[0] : 0.f, k1 ? acc[1] : 0.f, k2 ? acc[2] : 0.f, k3 ? acc[3] : 0.f};
+  uint2 parts[3];
+  split4(x, parts);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    u32x4 words = __builtin_bit_cast(u32x4, frag.part[i]);
+    words[2 * half + 0] = parts[i].x;
+    words[2 * half + 1] = parts[i].y;
+    frag.part[i] = __builtin_bit_cast(native8, words);
+  }
+#elif defined(COTTN_ELEM_F32)
   frag[4 * half + 0] = k0 ? acc[0] : 0.f;
   frag[4 * half + 1] = k1 ? acc[1] : 0.f;
   frag[4 * half + 2] = k2 ? acc[2] : 0.f;
@@ -438,10 +576,28 @@ __device__ __forceinline__ float inv_norm(float sum_sq, float eps) {
   return 1.0f / fmaxf(sqrtf(sum_sq), eps);
 }
 
-// The row factor of the tile kernels, min(1 / sqrt(sum_sq), inv_eps): the reciprocal square root
-// instruction (1 ulp of fp32) for 16-bit rows, correctly rounded steps for fp32 ones.
-__device__ __forceinline__ float row_inv_norm(float sum_sq, float inv_eps) {
-  return fminf(ELEM_IS_F32 ? 1.0f / sqrtf(sum_sq) : __builtin_amdgcn_rsqf(sum_sq), inv_eps);
+// The row factors of the tile kernels, out[p] = min(1 / sqrt(sum_sq[p]), inv_eps): the reciprocal
+// square root instruction (1 ulp of fp32), for fp32 rows with a Newton step, whose last addition is
+// the one rounding that shows.  A square root and a division, correctly rounded, are two, and three
+// times the instructions (a seventh of what the fp32 dQ scan issues in a step): left for 0,
+// infinity, NaN and what the instruction takes for 0.
+template <int PASSES>
+__device__ __forceinline__ void row_inv_norms(const float (&sum_sq)[PASSES], float inv_eps, float* out) {
+  bool exact_needed = false;
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    float y = __builtin_amdgcn_rsqf(sum_sq[p]);
+    if (ELEM_IS_F32) {
+      const float off = __builtin_fmaf(-sum_sq[p] * y, y, 1.0f);   // 1 - sum_sq y^2
+      exact_needed |= !(fabsf(off) < 0.5f);
+      y = __builtin_fmaf(0.5f * y, off, y);
+    }
+    out[p] = fminf(y, inv_eps);
+  }
+  if (ELEM_IS_F32 && __builtin_expect(__any(exact_needed), 0)) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) out[p] = fminf(1.0f / sqrtf(sum_sq[p]), inv_eps);
+  }
 }
 
 }  // namespace cottn

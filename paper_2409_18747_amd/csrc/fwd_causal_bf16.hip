@@ -59,8 +59,10 @@ struct FwdCfg {
   static constexpr int STATE = DK * SP;          // elements of the bf16 state copy
   // finished output rows (DV wide) are staged in the wave's own dead query rows when those are
   // wide enough, else in a tile of their own
-  static constexpr bool OWN_STAGE = lds_pitch(DV) > TPK;
-  static constexpr int LDS_BYTES = ELEM * (2 * TILEK + TILEV + STATE + (OWN_STAGE ? TILEV : 0)) + 4 * C;
+  static constexpr bool OWN_STAGE = ELEM * stage_pitch(DV) > LDS_ELEM * TPK;
+  static constexpr int OP = stage_tile_pitch(DV, C);   // of that tile, in elem_t
+  static constexpr int LDS_BYTES =
+      LDS_ELEM * (2 * TILEK + TILEV + STATE) + (OWN_STAGE ? ELEM * C * OP : 0) + 4 * C;
   static constexpr int WG_PER_CU = (160 * 1024) / LDS_BYTES;
   // waves per SIMD the register allocation is capped for (two workgroups per compute unit
   // when LDS allows, never more than the hardware needs for one workgroup)
@@ -74,7 +76,7 @@ struct FwdCfg {
   static constexpr int waves_per_eu() {
     if (CS == 1) return WAVES_PER_EU;
     const int own = NW * CS / 4;
-    const int wg = (160 * 1024) / (LDS_BYTES + ELEM * TILEV) >= 2 ? 2 : 1;
+    const int wg = (160 * 1024) / (LDS_BYTES + ELEM * C * OP) >= 2 ? 2 : 1;
     return own * wg > 4 ? (own > 4 ? own : 4) : own * wg;
   }
 };
@@ -85,10 +87,9 @@ struct FwdCfg {
 // two variants time the same and the smaller workgroup is kept.
 template <int DK, int DV, int C> struct FwdSplit { static constexpr int CS = ELEM_IS_F32 ? 2 : 1; };
 template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
-// (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four.  The
-// masked tile is formed by the two waves together, half of the features each, and not where
-// nothing of it is visible: an eighth of the products less.  B8 H12 N1024 d64 37 -> 34 us, of
-// which 15 us is MFMA time and 20 us the rows' way through HBM; d128 131 -> 122 us)
+// (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four.  B8 H12
+// N1024 d64 34.5 -> 30.5 us, operands in three parts against the fp32 matrix instruction, of which 20 us
+// is the rows' way through HBM; 64-row steps 40 us)
 
 // ---------------------------------------------------------------------------------------
 // Kernel 1: T[unit][g] = sum over the rows of segment g of kh^T v   (fp32, d_key x d_value;
@@ -109,8 +110,8 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];
 
   fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H);
   int unit, g;
@@ -185,15 +186,15 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   using StageV = TileStage<DV, C, Cfg::NT * CS>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
   constexpr bool OWN_STAGE = CS > 1 || Cfg::OWN_STAGE;
-  __shared__ __attribute__((aligned(16))) elem_t Qs[Cfg::TILEK];   // raw q rows
-  __shared__ __attribute__((aligned(16))) elem_t Ks[Cfg::TILEK];   // kh = r_j k_j
-  __shared__ __attribute__((aligned(16))) elem_t Vs[Cfg::TILEV];   // raw v rows
-  __shared__ __attribute__((aligned(16))) elem_t Sl[Cfg::STATE];   // state, [d_key][d_value]
+  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // raw q rows
+  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // kh = r_j k_j
+  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v rows
+  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // state, [d_key][d_value]
   // with two waves on a row group the q rows stay live in the other wave, and with outputs
   // wider than the queries they do not fit the q rows: own staging tile
-  __shared__ __attribute__((aligned(16))) elem_t Os[OWN_STAGE ? Cfg::TILEV : 8];
+  __shared__ __attribute__((aligned(16))) elem_t Os[OWN_STAGE ? C * Cfg::OP : 8];
   __shared__ float rq[C];
-  constexpr bool SHARE_MASKED = ELEM_IS_F32 && CS == 2 && C == 32;
+  constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, seq_len, s_per_unit, stream_q);
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   RowPieces<DV, NOT> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV, NOT>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
-  elem_t* stage = OWN_STAGE ? Os + 16 * rg * TPV : Qs + 16 * rg * TPK;
+  void* stage = OWN_STAGE ? static_cast<void*>(Os + 16 * rg * Cfg::OP) : static_cast<void*>(Qs + 16 * rg * TPK);
   const int col0 = 16 * NOT * cp;  // first output column of this wave
   for (int row0 = row_begin; row0 < row_end; row0 += C) {
     // ---- publish the state (bf16) and this chunk's tiles
@@ -268,8 +269,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y) {
-          store4(Sl + (16 * ST::col_tile(rg, cp, x) + r) * SP + 16 * ST::row_tile(rg, cp, y) + 4 * q4,
-                 sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
+          store4_lds(Sl + (16 * ST::col_tile(rg, cp, x) + r) * SP + lds_col(16 * ST::row_tile(rg, cp, y)) + 4 * q4,
+                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
         }
     }
     {
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     frag8 qf[Cfg::KSK];  // q rows of this wave: column-side operand of every product
 #pragma unroll
     for (int ks = 0; ks < Cfg::KSK; ++ks)
-      qf[ks] = lds_row_frag(Qs + (16 * rg + r) * TPK + 32 * ks, q4);
+      qf[ks] = lds_row_frag(Qs + (16 * rg + r) * TPK + lds_col(32 * ks), q4);
     // oacc[nt][v] = O[query 16 rg + r][value col0 + 16 nt + 4 q4 + v] before the row factor
     f32x4 oacc[NOT];
 #pragma unroll
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
         for (int half = 0; half < 2; ++half)
 #pragma unroll
           for (int ks = 0; ks < Cfg::KSK; ++ks)
-            kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + 32 * ks, q4);
+            kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + lds_col(32 * ks), q4);
       }
       if (SHARE_MASKED) __syncthreads();  // the partial tiles of the other waves are there
       __builtin_amdgcn_sched_barrier(0);
@@ -420,7 +421,7 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // few segments: no carry launch, each scan workgroup adds up the totals before its segment
   const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
   if (a.G > 1) {
-    err = COTTN_SYM(launch_fwd_segment_totals)(a, ws);
+    err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, ws);
     if (err != hipSuccess) return err;
     if (!sum_in_scan) {
       err = launch_fwd_state_carry(ws, units, a.G, DK * DV, a.stream);
@@ -440,6 +441,7 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
 
 }  // namespace
 
+#ifndef COTTN_F32_WHOLE   // (both fp32 builds take the totals of the split one)
 template <int DK, int DV, bool TILED>
 static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
   const elem_t* X = static_cast<const elem_t*>(t.X);
@@ -449,11 +451,12 @@ static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
   // workgroup has all of its loads in flight at once instead of paying one memory latency per
   // 64-row chunk, and several workgroups still fit a compute unit (two 256-row tiles of the
   // operand-tile pitch would leave room for one: measured 0.6 us slower on the GPT shape;
-  // fp32 tiles of wide heads fit twice only with 64 rows).
+  // fp32 rows in parts fit twice only with 64 rows, but 32 x 32 and 32 x 64).
   const dim3 grid(t.units * t.G);
-  constexpr bool TALL = ELEM * 128 * (lds_pitch(DK) + lds_pitch(DV)) <= 80 * 1024;
-  if (TALL && t.seg_rows >= 128)
-    return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 128, TILED>, grid, dim3(512),
+  constexpr bool TALL = LDS_ELEM * 128 * (lds_pitch(DK) + lds_pitch(DV)) <= 80 * 1024;
+  if constexpr (TALL)
+    if (t.seg_rows >= 128)
+      return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 128, TILED>, grid, dim3(512),
                          0, t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps,
                          t.seq_len, t.H);
   return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 64, TILED>, grid, dim3(256), 0,
@@ -484,6 +487,7 @@ hipError_t COTTN_SYM(launch_fwd_segment_totals)(const CausalArgs& a, float* dst)
   t.tiled = true;  // read by the scan kernels only
   return COTTN_SYM(launch_segment_totals)(t);
 }
+#endif
 
 #if !defined(COTTN_ELEM_F16) && !defined(COTTN_ELEM_F32)  // not specific to the element type
 hipError_t launch_fwd_state_carry(float* seg_state, int units, int G, int elems, hipStream_t st) {
@@ -494,17 +498,22 @@ hipError_t launch_fwd_state_carry(float* seg_state, int units, int G, int elems,
 #endif
 
 hipError_t COTTN_SYM(fwd_causal)(const CausalArgs& a) {
-#ifdef COTTN_ELEM_F32
+#if defined(COTTN_F32_WHOLE)
+  switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
+    case 32128032: return run_fwd_causal<32, 128, 32>(a);
+    case 128032032: return run_fwd_causal<128, 32, 32>(a);
+    case 128128032: return run_fwd_causal<128, 128, 32>(a);
+    default: return hipErrorInvalidValue;
+  }
+#elif defined(COTTN_ELEM_F32)
   switch ((a.dk * 1000 + a.dv) * 1000 + a.C) {
     case 32032032: return run_fwd_causal<32, 32, 32>(a);
     case 32064032: return run_fwd_causal<32, 64, 32>(a);
-    case 32128032: return run_fwd_causal<32, 128, 32>(a);
+    case 32128032: case 128032032: case 128128032: return fwd_causal_f32w(a);   // device_common.h: SPLIT3
     case 64032032: return run_fwd_causal<64, 32, 32>(a);
     case 64064032: return run_fwd_causal<64, 64, 32>(a);
     case 64128032: return run_fwd_causal<64, 128, 32>(a);
-    case 128032032: return run_fwd_causal<128, 32, 32>(a);
     case 128064032: return run_fwd_causal<128, 64, 32>(a);
-    case 128128032: return run_fwd_causal<128, 128, 32>(a);
     default: return hipErrorInvalidValue;
   }
 #else

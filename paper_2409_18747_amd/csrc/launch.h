@@ -119,6 +119,11 @@ hipError_t fwd_causal_f32(const CausalArgs& a);
 hipError_t bwd_causal_f32(const CausalArgs& a);
 hipError_t fwd_bidir_f32(const CausalArgs& a);
 hipError_t bwd_bidir_f32(const CausalArgs& a);
+// what the four above call where the fp32 matrix instruction is the better one (device_common.h: SPLIT3)
+hipError_t fwd_causal_f32w(const CausalArgs& a);
+hipError_t bwd_causal_f32w(const CausalArgs& a);
+hipError_t fwd_bidir_f32w(const CausalArgs& a);
+hipError_t bwd_bidir_f32w(const CausalArgs& a);
 hipError_t step_any(const StepArgs& a, int dtype);
 
 // small fp32 state kernels shared by all element types (defined next to their kernels)

@@ -64,10 +64,10 @@ struct TileStage {
   // rinv[p] = min(1/||row||, inv_eps) = 1 / max(||row||, eps) for the row this lane holds in
   // pass p (every lane of the row gets the same value).
   __device__ __forceinline__ void row_rinv(float inv_eps, float* rinv) const {
+    float sum_sq[PASSES];
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-      rinv[p] = row_inv_norm(group_sum<LPR>(piece_sum_sq(regs[p])), inv_eps);
-    }
+    for (int p = 0; p < PASSES; ++p) sum_sq[p] = group_sum<LPR>(piece_sum_sq(regs[p]));
+    row_inv_norms<PASSES>(sum_sq, inv_eps, rinv);
   }
 
   // out[local row] = rinv of that row (one lane per row writes)
@@ -80,25 +80,25 @@ struct TileStage {
     }
   }
 
-  __device__ __forceinline__ void commit_plain(elem_t* tile) const {
+  __device__ __forceinline__ void commit_plain(lds_t* tile) const {
     const int tid = threadIdx.x;
-    const int col = (tid % LPR) * EPP;
+    const int col = lds_col((tid % LPR) * EPP);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
-      if (C % RPP == 0 || lr < C) *reinterpret_cast<uint4*>(tile + lr * tile_pitch(D, C) + col) = regs[p];
+      if (C % RPP == 0 || lr < C) store_piece_lds(tile + lr * tile_pitch(D, C) + col, regs[p]);
     }
   }
 
   // tile[lr][:] = scale[p] * row, rounded to the element type
-  __device__ __forceinline__ void commit_scaled(elem_t* tile, const float* scale) const {
+  __device__ __forceinline__ void commit_scaled(lds_t* tile, const float* scale) const {
     const int tid = threadIdx.x;
-    const int col = (tid % LPR) * EPP;
+    const int col = lds_col((tid % LPR) * EPP);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
       if (C % RPP == 0 || lr < C)
-        *reinterpret_cast<uint4*>(tile + lr * tile_pitch(D, C) + col) = piece_times(regs[p], scale[p]);
+        store_piece_lds(tile + lr * tile_pitch(D, C) + col, piece_times(regs[p], scale[p]));
     }
   }
 };
@@ -151,7 +151,7 @@ struct SplitTiles {
   }
 };
 
-// fp32, two waves on each of the two row groups of a 32-row chunk: both need the group's masked
+// Whole fp32, two waves on each of the two row groups of a 32-row chunk: both need the group's masked
 // tiles, and an fp32 MFMA is slow enough that forming them twice shows (8 of the 24 products a
 // wave has in a chunk of the dK/dV scan at d = 64).  Each wave contracts half of the features and
 // passes its partial tile on through LDS: slot = one per tile of the group.
@@ -209,7 +209,7 @@ __device__ __forceinline__ void add_stored_states(f32x4 (&acc)[NCT][NRT], int fi
 // still being read: a barrier has to follow before they are written again.
 template <int DK, int DV, int C, int NT, class ST = AccTiles<DK, DV, NT / 64>>
 __device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT], TileStage<DK, C, NT>& kst,
-                                                  TileStage<DV, C, NT>& vst, elem_t* Ks, elem_t* Vs,
+                                                  TileStage<DV, C, NT>& vst, lds_t* Ks, lds_t* Vs,
                                                   const elem_t* __restrict__ Ku, const elem_t* __restrict__ Vu,
                                                   int row_begin, int row_end, float inv_eps, int w, int l) {
   constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);
@@ -259,15 +259,16 @@ struct RowPieces {
 // Turns a wave's result block whose accumulators are laid out TRANSPOSED (acc[nt][v] =
 // result[row r][column col0 + 16 nt + 4 q4 + v], i.e. each lane holds 4 consecutive columns
 // of one row) into row pieces: scales by the per-lane row factor, rounds to the element type, passes the
-// block through a staging area private to the wave (16 rows of lds_pitch(D) elements from
+// block through a staging area private to the wave (16 rows of stage_pitch(D) elements from
 // stage_rows on, columns col0..; it fits the wave's 16 rows of an operand tile, whose pitch is
-// larger) with 8-byte writes and reads it back as 16-byte pieces.
+// larger) with 8-byte writes (fp32: 16) and reads it back as 16-byte pieces.
 template <int D, int NTILES = D / 16>
 __device__ __forceinline__ void gather_rows_transposed(const f32x4* acc, float row_factor,
-                                                       elem_t* stage_rows, int l,
+                                                       void* stage, int l,
                                                        RowPieces<D, NTILES>& out, int col0 = 0) {
   using RP = RowPieces<D, NTILES>;
-  constexpr int PITCH = lds_pitch(D);
+  constexpr int PITCH = stage_pitch(D);
+  elem_t* stage_rows = static_cast<elem_t*>(stage);
   const int r = l % 16, q4 = l / 16;
 #pragma unroll
   for (int nt = 0; nt < NTILES; ++nt) {
@@ -318,12 +319,12 @@ __device__ __forceinline__ float sum_over_lane_rows(float x) {
 // an LDS tile, row pitch PITCH, holding either the raw row x or xh = r x) and returns their dot
 // product with dxh;
 template <int NTILES, int PITCH>
-__device__ __forceinline__ float dot_with_row(const f32x4* acc, const elem_t* x_rows, int col0,
+__device__ __forceinline__ float dot_with_row(const f32x4* acc, const lds_t* x_rows, int col0,
                                               float (&xv)[NTILES][4], int r, int q4) {
   float t = 0.f;
 #pragma unroll
   for (int nt = 0; nt < NTILES; ++nt) {
-    load4(x_rows + r * PITCH + col0 + 16 * nt + 4 * q4, xv[nt]);
+    load4_lds(x_rows + r * PITCH + lds_col(col0 + 16 * nt) + 4 * q4, xv[nt]);
 #pragma unroll
     for (int v = 0; v < 4; ++v) t += xv[nt][v] * acc[nt][v];
   }
