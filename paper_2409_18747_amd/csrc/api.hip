@@ -79,7 +79,8 @@ double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int 
 
 // Segments per (batch, head) for the causal calls: the least time by the model among the splits of up to
 // 640 workgroups (1024 for fp32, whose scans hold the longer steps, and for 32 x 32, of which a compute
-// unit runs four), or none.  Finer ones gain the backward little and cost the forward, which runs three
+// unit runs four; 768 where both hold, whose dK/dV scan it runs three of: 64 units of 2048 rows 8 segments 24 /
+// 70 us, 16 25 / 77), or none.  Finer ones gain the backward little and cost the forward, which runs three
 // workgroups or more at once, a round (768 units of 1024 rows at 64 x 64: 2 segments 87 / 291 us for the
 // forward / with its backward, 1 segment 64 / 270).  Others of the measured, forward / with backward: 16-bit
 // 128 x 128 8 units of 2048 rows 32 segments 30 / 55 us, 16 27 / 51, 8 29 / 71; 64 x 64 64 units of 2048
@@ -98,7 +99,7 @@ long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk
     return n_chunks >= 16 * want ? (512 + units - 1) / units : want;
   }
   const bool f32 = dtype == COTTN_F32, narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
-  const long most = f32 || narrowest ? 1024 : 640;
+  const long most = f32 && narrowest ? 768 : f32 || narrowest ? 1024 : 640;
   const bool cut = !f32 && !widest && ((n_chunks > 4 && units <= 160) || (narrowest && n_chunks > 8 && units < 384));
   double best = causal_call_us(units, N, n_chunks, 1, dtype, dk, dv);
   long best_g = 1;

@@ -800,17 +800,21 @@ hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, floa
 #endif
 
 #if defined(COTTN_F32_WHOLE)
-hipError_t fwd_bidir_f32w(const CausalArgs& a) { return run_fwd_bidir<128, 128>(a); }
-hipError_t bwd_bidir_f32w(const CausalArgs& a) { return run_bwd_bidir<128, 128>(a); }
+hipError_t fwd_bidir_f32w(const CausalArgs& a) {
+  return a.dk == 32 ? run_fwd_bidir<32, 32>(a) : run_fwd_bidir<128, 128>(a);
+}
+hipError_t bwd_bidir_f32w(const CausalArgs& a) {
+  return a.dk == 32 ? run_bwd_bidir<32, 32>(a) : run_bwd_bidir<128, 128>(a);
+}
 #else
-#ifdef COTTN_ELEM_F32   // the parts of its tiles and state do not fit the LDS
-#define COTTN_128_128(CALL, WHOLE) WHOLE(a)
+#ifdef COTTN_ELEM_F32   // device_common.h: SPLIT3
+#define COTTN_SQUARE(D, CALL, WHOLE) WHOLE(a)
 #else
-#define COTTN_128_128(CALL, WHOLE) CALL<128, 128>(a)
+#define COTTN_SQUARE(D, CALL, WHOLE) CALL<D, D>(a)
 #endif
 #define COTTN_FOR_EACH_DK_DV(CALL, WHOLE)                                                       \
   switch (a.dk * 1000 + a.dv) {                                                                 \
-    case 32032: return CALL<32, 32>(a);                                                         \
+    case 32032: return COTTN_SQUARE(32, CALL, WHOLE);                                           \
     case 32064: return CALL<32, 64>(a);                                                         \
     case 32128: return CALL<32, 128>(a);                                                        \
     case 64032: return CALL<64, 32>(a);                                                         \
@@ -818,7 +822,7 @@ hipError_t bwd_bidir_f32w(const CausalArgs& a) { return run_bwd_bidir<128, 128>(
     case 64128: return CALL<64, 128>(a);                                                        \
     case 128032: return CALL<128, 32>(a);                                                       \
     case 128064: return CALL<128, 64>(a);                                                       \
-    case 128128: return COTTN_128_128(CALL, WHOLE);                                             \
+    case 128128: return COTTN_SQUARE(128, CALL, WHOLE);                                         \
     default: return hipErrorInvalidValue;                                                       \
   }
 

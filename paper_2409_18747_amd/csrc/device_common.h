@@ -22,7 +22,9 @@ namespace cottn {
 //           contracted over the tokens can take the transposing LDS read.
 //   else    the fp32 matrix instruction (COTTN_F32_WHOLE: the *_f32w.hip files), where the parts do
 //           not fit the LDS (128 x 128) or fit it for one causal workgroup instead of two (128 x 32
-//           and 32 x 128: B4 H8 N2048 forward + backward 121 / 140 and 108 / 123 us, whole / parts).
+//           and 32 x 128: B4 H8 N2048 forward + backward 121 / 140 and 108 / 123 us, whole / parts), and
+//           where a row's few products are soon formed either way (32 x 32 without a mask, 32 / 33 us,
+//           and the segment totals of that shape, 4.8 / 5.6).
 // Elsewhere the parts are the faster way: forward + backward, whole / parts, B4 H8 N2048 causal 32 x
 // 32 50 / 47 us, 64 x 64 106 / 88, 64 x 128 181 / 152, bidirectional 64 x 64 66 / 63, 128 x 64 122 /
 // 105; B32 H16 N512 causal 64 x 64 271 / 227.  Then the vector ALU is what they wait for (busy half of

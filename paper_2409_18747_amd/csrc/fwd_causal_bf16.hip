@@ -441,7 +441,6 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
 
 }  // namespace
 
-#ifndef COTTN_F32_WHOLE   // (both fp32 builds take the totals of the split one)
 template <int DK, int DV, bool TILED>
 static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
   const elem_t* X = static_cast<const elem_t*>(t.X);
@@ -463,9 +462,18 @@ static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
                        t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps, t.seq_len, t.H);
 }
 
+#ifdef COTTN_F32_WHOLE
+hipError_t launch_segment_totals_32x32_f32w(const SegmentTotalsArgs& t) {
+  return t.tiled ? run_segment_totals<32, 32, true>(t) : run_segment_totals<32, 32, false>(t);
+}
+#else
 hipError_t COTTN_SYM(launch_segment_totals)(const SegmentTotalsArgs& t) {
   switch (t.dk * 1000 + t.dv) {
+#ifdef COTTN_ELEM_F32   // device_common.h: SPLIT3
+    case 32032: return launch_segment_totals_32x32_f32w(t);
+#else
     case 32032: return t.tiled ? run_segment_totals<32, 32, true>(t) : run_segment_totals<32, 32, false>(t);
+#endif
     case 32064: return t.tiled ? run_segment_totals<32, 64, true>(t) : run_segment_totals<32, 64, false>(t);
     case 32128: return t.tiled ? run_segment_totals<32, 128, true>(t) : run_segment_totals<32, 128, false>(t);
     case 64032: return t.tiled ? run_segment_totals<64, 32, true>(t) : run_segment_totals<64, 32, false>(t);

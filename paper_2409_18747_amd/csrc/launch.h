@@ -152,6 +152,7 @@ struct SegmentTotalsArgs {
 hipError_t launch_segment_totals_bf16(const SegmentTotalsArgs& t);
 hipError_t launch_segment_totals_f16(const SegmentTotalsArgs& t);
 hipError_t launch_segment_totals_f32(const SegmentTotalsArgs& t);
+hipError_t launch_segment_totals_32x32_f32w(const SegmentTotalsArgs& t);   // called by the line above
 hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, float* state,
                                 hipStream_t st);
 
