@@ -150,7 +150,9 @@ __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_t
 // consecutive values of one key row and publishes them with one 8-byte write to the row-major
 // LDS copy St[d_key][d_value]; the update's key-side operand is the K fragment already read
 // for the intra-chunk product.
-template <int DK, int DV, int C, int CS>
+//
+// REV: whether the launch has segments to leave reverse-time totals for.
+template <int DK, int DV, int C, int CS, bool REV>
 __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dq_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   // first; earlier segments need it), accumulated in that kernel's layout: element [v] of
   // lane (r, q4) of tile (y, x) is R[key 16 ct + r][value 16 rt + 4 q4 + v].
   f32x4 racc[RT::NCT][RT::NRT];
-  const bool with_rev = rev_totals != nullptr && g > 0;
+  const bool with_rev = REV && rev_totals != nullptr && g > 0;
 #pragma unroll
   for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
@@ -835,7 +837,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   char* ws = static_cast<char*>(a.workspace);
   const float* fwd_states = nullptr;
   float* rev_states = nullptr;
-  const dim3 grid(units * a.G), block(Cfg::NT);
+  const dim3 grid(units * a.G);
   const float inv_eps = 1.0f / a.eps;
   // few segments: no carry launches, the scan workgroups add up the totals they need
   const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
@@ -860,21 +862,33 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   }
   float* ds_partial = reinterpret_cast<float*>(ws);
   // the dQ scan leaves the reverse-time segment totals (of qh^T dO) behind for the dK/dV scan
-  err = launch_kernel(COTTN_SYM_STR(bwd_dq_scan), COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS>, grid, block, 0, a.stream, Q, K, V,
-                      dO, a.s, static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H,
-                      a.N, a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit,
-                      a.state_in);
+  const auto dq_scan = [&](auto kernel, int threads) {
+    return launch_kernel(COTTN_SYM_STR(bwd_dq_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
+                         static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H, a.N, a.G, a.seg_rows,
+                         inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in);
+  };
+  constexpr bool HALVED = !ELEM_IS_F32 && DK == 128 && DV == 128 && CR == 64 && CS == 2;
+  const long workgroups = long(units) * a.G;
+  if (HALVED && a.G == 1 && two_to_a_cu_dq(workgroups)) {
+    if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false>, 256);
+  } else {
+    err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true>, Cfg::NT);
+  }
   if (err != hipSuccess) return err;
   if (a.G > 1 && !sum_in_scan) {
     err = launch_bwd_state_carry(nullptr, rev_states, units, a.G, DK * DV, a.stream);
     if (err != hipSuccess) return err;
   }
   // the dK/dV kernel also reduces the ds partial sums written by the dQ kernel
-  return launch_kernel(COTTN_SYM_STR(bwd_dkdv_scan), COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS>, grid, block, 0, a.stream, Q,
-                       K, V, dO, a.s, static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV),
-                       rev_states, ds_partial, a.ds, a.B, a.H, a.N, a.G, a.seg_rows, inv_eps,
-                       sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, a.rev_state_in,
-                       a.rev_state_out);
+  const auto dkdv_scan = [&](auto kernel, int threads) {
+    return launch_kernel(COTTN_SYM_STR(bwd_dkdv_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
+                         static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), rev_states, ds_partial, a.ds, a.B,
+                         a.H, a.N, a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit,
+                         a.rev_state_in, a.rev_state_out);
+  };
+  if constexpr (HALVED)
+    if (two_to_a_cu_dkdv(workgroups)) return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, 32, CS>, 256);
+  return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS>, Cfg::NT);
 }
 
 }  // namespace

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
     const float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
     int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
-    int stream_q) {
+    int stream_q, int stream_kv) {
   using Cfg = FwdCfg<DK, DV, C>;
   constexpr int RG = C / 16;           // row groups of a chunk
   constexpr int NOT = Cfg::DTV / CS;   // output column tiles per wave
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
-                     sum_totals, seq_len, s_per_unit, stream_q);
+                     sum_totals, seq_len, s_per_unit, stream_q, stream_kv);
   int unit, g;
   unit_and_segment(blockIdx.x, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
@@ -225,8 +225,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   StageK qst, kst;
   StageV vst;
   qst.fetch(Qu, row_begin, row_end, stream_q != 0);
-  kst.fetch(Ku, row_begin, row_end);
-  vst.fetch(Vu, row_begin, row_end);
+  kst.fetch(Ku, row_begin, row_end, stream_kv != 0);
+  vst.fetch(Vu, row_begin, row_end, stream_kv != 0);
   // the state the sequence starts from (chunked prefill) belongs to every segment's start state
   f32x4 start[ST::NCT][ST::NRT];
   if (state_in != nullptr && ST::active(rg, cp)) {
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     }
     if (row0 + C < row_end) {
       qst.fetch(Qu, row0 + C, row_end, stream_q != 0);
-      kst.fetch(Ku, row0 + C, row_end);
-      vst.fetch(Vu, row0 + C, row_end);
+      kst.fetch(Ku, row0 + C, row_end, stream_kv != 0);
+      vst.fetch(Vu, row0 + C, row_end, stream_kv != 0);
     }
     if (row0 > row_begin)
       store_row_pieces<DV, NOT>(finished, Ou, row0 - C + 16 * rg, row_end, l, col0);
@@ -409,8 +409,6 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
 
 template <int DK, int DV, int C>
 hipError_t run_fwd_causal(const CausalArgs& a) {
-  constexpr int CS = FwdSplit<DK, DV, C>::CS;
-  using Cfg = FwdCfg<DK, DV, C>;
   const int units = a.B * a.H;
   const elem_t* Q = static_cast<const elem_t*>(a.Q);
   const elem_t* K = static_cast<const elem_t*>(a.K);
@@ -433,10 +431,20 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // keeps the K, V rows the totals kernel left in the L2 in place (long context: scan 98 ->
   // 87 us); below that size a backward that follows finds the rows cached, and plain loads win.
   const bool stream_q = 2.0 * units * double(a.N) * (DK + DV) * ELEM > 256.0 * 1024 * 1024;
-  return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), COTTN_SYM(fwd_causal_scan)<DK, DV, C, CS>, dim3(units * a.G),
-                       dim3(Cfg::NT * CS), 0, a.stream, Q, K, V, a.s, static_cast<elem_t*>(a.O), a.state,
-                       a.G > 1 ? ws : nullptr, a.state_in, a.H, a.N, a.G, a.seg_rows, inv_eps,
-                       sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0);
+  // Nobody reads K and V before them where there is one segment: non-temporally too once they outgrow
+  // that cache by themselves (256 sequences of 2048 rows, 16 heads of 128: 1660 -> 1610 us; 64 of 1000
+  // rows d64, whose K, V are found cached in part: 85 -> 105).
+  const bool stream_kv = a.G == 1 && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
+  const auto scan = [&](auto kernel, int threads) {
+    return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(units * a.G), dim3(threads), 0, a.stream, Q, K,
+                         V, a.s, static_cast<elem_t*>(a.O), a.state, a.G > 1 ? ws : nullptr, a.state_in, a.H, a.N,
+                         a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0,
+                         stream_kv ? 1 : 0);
+  };
+  constexpr int threads = 4 * C * FwdSplit<DK, DV, C>::CS;
+  if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
+    if (two_to_a_cu_forward(long(units) * a.G)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2>, 256);
+  return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS>, threads);
 }
 
 }  // namespace

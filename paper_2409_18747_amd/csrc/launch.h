@@ -58,6 +58,19 @@ constexpr bool causal_totals_in_place(long units, int G, int dk, int dv, bool f3
   const long kb = dk * dv <= 64 * 64 ? 264 + 10 * few : 200 + (f32 && dk * dv == 128 * 128 ? 24 : 13) * few;
   return long(G - 1) * dk * dv * 4 <= kb * 1024;
 }
+// 16-bit causal 128 x 128: the scans with 64-row steps fill a compute unit with one workgroup of eight
+// waves.  With 32-row steps two of four waves fit, whose steps hide each other's latencies, but every
+// row then pays twice for the state (its copy to LDS and the reads of it).  From 257 workgroups on, where
+// the former take another round, the latter are the faster ones (the forward moves 5.4 TB/s then):
+// 272 units of 300 rows forward / dQ / dK,dV 29.5 / 37.4 / 51.5 -> 27.0 / 32.6 / 41.6 us; 512 units of 1024
+// rows 106 / 140 / 203 -> 94 / 125 / 157; 1024 units of 500 rows 112 / 144 / 200 -> 96 / 134 / 166; up to
+// 256 workgroups they are not (256 of 512 rows 24.6 / 43.3 against 28.1 / 47.1 for forward / dK,dV).
+// Their own second round is the longer one: 704 units of 1328 rows 206 / 260 / 364 -> 232 / 300 / 330, 640
+// of 700 rows forward 102 -> 91, 560 of 777 rows dQ 150 -> 141..151.
+// The dQ scan has registers for them only where no reverse-time totals are due (G = 1).
+constexpr bool two_to_a_cu_forward(long workgroups) { return workgroups > 256 && (workgroups <= 640 || workgroups > 768); }
+constexpr bool two_to_a_cu_dq(long workgroups) { return workgroups > 256 && (workgroups <= 512 || workgroups > 768); }
+constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
 // Bidirectional: only the sums are needed, which a backward that is handed the forward's totals takes
 // over where they were left as they are; the line lies where the combine launch is the better one for
 // the forward alone (64 x 64 24 segments +1.3 us at 2 units, 64 x 128 12 +0.8, 128 x 128 8 +1.2).
