@@ -475,12 +475,13 @@ __device__ __forceinline__ float unit_scale(const float* __restrict__ s, int uni
                                             int per_unit) {
   return s[per_unit ? unit : unit % H];
 }
-// Zeros rows row_lo..row_hi-1 of a [.][D] tensor of elements (whole workgroup).
-template <int D>
+// Zeros rows row_lo..row_hi-1 of D columns of a [.][LD] tensor of elements (whole workgroup).
+template <int D, int LD = D>
 __device__ __forceinline__ void zero_rows(elem_t* __restrict__ dst, int row_lo, int row_hi) {
-  const long pieces = long(max(0, row_hi - row_lo)) * (D / EPP);
-  uint4* p = reinterpret_cast<uint4*>(dst + size_t(row_lo) * D);
-  for (long i = threadIdx.x; i < pieces; i += blockDim.x) p[i] = uint4{0u, 0u, 0u, 0u};
+  constexpr int PPR = D / EPP;
+  const long pieces = long(max(0, row_hi - row_lo)) * PPR;
+  for (long i = threadIdx.x; i < pieces; i += blockDim.x)
+    *reinterpret_cast<uint4*>(dst + size_t(row_lo + i / PPR) * LD + (i % PPR) * EPP) = uint4{0u, 0u, 0u, 0u};
 }
 
 // 16-byte store of a result that this library does not read again soon: marked non-temporal,

@@ -171,7 +171,10 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
 // group, each accumulates one half of the output columns and owns the state tiles whose
 // value side is that half.  Per-wave work and registers shrink; the workgroup has twice the
 // waves to cover latencies with.
-template <int DK, int DV, int C, int CS>
+//
+// LDV > DV (one segment): a workgroup takes DV of the LDV value columns, which the whole computation
+// leaves apart from one another but for the masked tiles; those are formed LDV / DV times.
+template <int DK, int DV, int C, int CS, int LDV = DV>
 __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())) void COTTN_SYM(fwd_causal_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
@@ -183,7 +186,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   constexpr int NOT = Cfg::DTV / CS;   // output column tiles per wave
   using ST = SplitTiles<DV, DK, RG, CS>;   // value rows, key columns (the state is held transposed)
   using StageK = TileStage<DK, C, Cfg::NT * CS>;
-  using StageV = TileStage<DV, C, Cfg::NT * CS>;
+  using StageV = TileStage<DV, C, Cfg::NT * CS, LDV>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
   constexpr bool OWN_STAGE = CS > 1 || Cfg::OWN_STAGE;
   __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // raw q rows
@@ -198,15 +201,20 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, seq_len, s_per_unit, stream_q, stream_kv);
-  int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+  int unit, g, part = 0;
+  if constexpr (LDV > DV) {
+    g = 0;
+    unit_and_segment(blockIdx.x, LDV / DV, unit, part);
+  } else {
+    unit_and_segment(blockIdx.x, G, unit, g);
+  }
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const int rg = row_group<RG, CS>(w), cp = w / RG;  // row group, column part
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Ku = K + size_t(unit) * N * DK;
-  const elem_t* Vu = V + size_t(unit) * N * DV;
-  elem_t* Ou = O + size_t(unit) * N * DV;
+  const elem_t* Vu = V + size_t(unit) * N * LDV + part * DV;
+  elem_t* Ou = O + size_t(unit) * N * LDV + part * DV;
   const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
@@ -230,15 +238,15 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   // the state the sequence starts from (chunked prefill) belongs to every segment's start state
   f32x4 start[ST::NCT][ST::NRT];
   if (state_in != nullptr && ST::active(rg, cp)) {
-    const float* src = state_in + size_t(unit) * DK * DV;
+    const float* src = state_in + size_t(unit) * DK * LDV + part * DV;
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
       for (int y = 0; y < ST::NRT; ++y)
-        start[x][y] = *reinterpret_cast<const f32x4*>(src + (16 * ST::col_tile(rg, cp, x) + r) * DV +
+        start[x][y] = *reinterpret_cast<const f32x4*>(src + (16 * ST::col_tile(rg, cp, x) + r) * LDV +
                                                       16 * ST::row_tile(rg, cp, y) + 4 * q4);
   }
-  if (seg_states != nullptr && g > 0 && ST::active(rg, cp)) {
+  if (LDV == DV && seg_states != nullptr && g > 0 && ST::active(rg, cp)) {
     const float* src = seg_states + size_t(unit) * G * DK * DV + 4 * l;
     add_stored_states<ST::STATE_BATCH>(
         sacc, sum_totals ? 0 : g, sum_totals ? g - 1 : g, [&](int gp, int x, int y) {
@@ -288,7 +296,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       vst.fetch(Vu, row0 + C, row_end, stream_kv != 0);
     }
     if (row0 > row_begin)
-      store_row_pieces<DV, NOT>(finished, Ou, row0 - C + 16 * rg, row_end, l, col0);
+      store_row_pieces<DV, NOT, LDV>(finished, Ou, row0 - C + 16 * rg, row_end, l, col0);
     __syncthreads();
 
     if constexpr (SHARE_MASKED) {
@@ -391,18 +399,18 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   }
   if (row_begin < row_end) {
     const int last = row_begin + (row_end - row_begin - 1) / C * C;
-    store_row_pieces<DV, NOT>(finished, Ou, last + 16 * rg, row_end, l, col0);
+    store_row_pieces<DV, NOT, LDV>(finished, Ou, last + 16 * rg, row_end, l, col0);
   }
 
-  if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, seg_end);  // rows that do not exist
 
   if (state_out != nullptr && g == G - 1 && ST::active(rg, cp)) {
-    float* out = state_out + size_t(unit) * DK * DV;
+    float* out = state_out + size_t(unit) * DK * LDV + part * DV;
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
       for (int y = 0; y < ST::NRT; ++y)
-        *reinterpret_cast<f32x4*>(out + (16 * ST::col_tile(rg, cp, x) + r) * DV +
+        *reinterpret_cast<f32x4*>(out + (16 * ST::col_tile(rg, cp, x) + r) * LDV +
                                   16 * ST::row_tile(rg, cp, y) + 4 * q4) = sacc[x][y];
   }
 }
@@ -435,13 +443,25 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // that cache by themselves (256 sequences of 2048 rows, 16 heads of 128: 1660 -> 1610 us; 64 of 1000
   // rows d64, whose K, V are found cached in part: 85 -> 105).
   const bool stream_kv = a.G == 1 && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
-  const auto scan = [&](auto kernel, int threads) {
-    return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(units * a.G), dim3(threads), 0, a.stream, Q, K,
+  const auto scan = [&](auto kernel, int threads, int parts = 1) {
+    return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(units * a.G * parts), dim3(threads), 0, a.stream, Q, K,
                          V, a.s, static_cast<elem_t*>(a.O), a.state, a.G > 1 ? ws : nullptr, a.state_in, a.H, a.N,
                          a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0,
                          stream_kv ? 1 : 0);
   };
   constexpr int threads = 4 * C * FwdSplit<DK, DV, C>::CS;
+  if constexpr (DV == 128 && !F32_WHOLE) {
+    const int parts = a.G == 1 ? value_parts(units, a.N, DK) : 1;
+    if constexpr (ELEM_IS_F32) {
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 32, 2, DV>, 256, 2);
+    } else {
+      if constexpr (DK == 128) {
+        if (parts == 4 && a.N <= 32) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 32, 2, DV>, 256, 4);
+        if (parts == 4) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 64, 1, DV>, 256, 4);
+      }
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 64, 1, DV>, 256, 2);
+    }
+  }
   if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
     if (two_to_a_cu_forward(long(units) * a.G)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2>, 256);
   return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS>, threads);

@@ -58,6 +58,19 @@ constexpr bool causal_totals_in_place(long units, int G, int dk, int dv, bool f3
   const long kb = dk * dv <= 64 * 64 ? 264 + 10 * few : 200 + (f32 && dk * dv == 128 * 128 ? 24 : 13) * few;
   return long(G - 1) * dk * dv * 4 <= kb * 1024;
 }
+// Workgroups that share the 128 value columns of a (batch, head) in a causal forward of one segment (and
+// so short or of many sequences).  Such a call lasts as long as one workgroup takes: launch, first rows
+// and state, a few steps, state out, and with up to 128 units half of the compute units have nothing to
+// do.  A part forms the masked tiles again and reads the same query and key rows, out of the L2 it shares
+// with the others (unit_and_segment).  128 x 128, whole / 2 / 4 parts: 128 units of 5 rows continued from a state
+// 9.5 / 7.3 / 6.3 us (with 32-row steps; 64-row ones 7.4), of 64 rows 8.5 / 7.7 / 6.8, of 128 rows 10.4 / 9.0 /
+// 9.7, 160 units of 128 rows 8.2 / 8.3 / 11.2, 512 units of 5 rows 14.9 / 17.1 / 16.7.  64 x 128, of which two
+// workgroups fit a compute unit either way, 256 units of 128 rows 8.0 / 7.5 us, of 400 rows 19.3 / 17.4; fp32
+// 256 units of 31 rows 7.5 / 7.0, of 100 rows 20.3 / 18.7.  At 64 columns parts of 32 gain nothing.
+constexpr int value_parts(long units, int N, int dk) {
+  if (units > (dk == 128 ? 128 : 256)) return 1;
+  return dk == 128 && N <= 64 ? 4 : 2;
+}
 // 16-bit causal 128 x 128: the scans with 64-row steps fill a compute unit with one workgroup of eight
 // waves.  With 32-row steps two of four waves fit, whose steps hide each other's latencies, but every
 // row then pays twice for the state (its copy to LDS and the reads of it).  From 257 workgroups on, where

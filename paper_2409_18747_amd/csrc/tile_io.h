@@ -26,7 +26,8 @@ __device__ __forceinline__ uint4 load_rows(const elem_t* p, bool stream) {
   return *reinterpret_cast<const uint4*>(p);
 }
 
-template <int D, int C, int NT>
+// (LD: elements from a row of the tensor to the next, more than D where D columns of it are taken.)
+template <int D, int C, int NT, int LD = D>
 struct TileStage {
   static constexpr int LPR = D / EPP;     // lanes per row
   static constexpr int RPP = NT / LPR;    // rows per pass
@@ -43,20 +44,20 @@ struct TileStage {
     const int tid = threadIdx.x;
     // a base that is the same for all lanes plus a 32-bit lane offset that is the same for all
     // tiles: the addresses then take scalar registers and one vector register
-    const elem_t* rows = base + size_t(row0) * D;
-    const unsigned lane = unsigned((tid / LPR) * D + (tid % LPR) * EPP);
+    const elem_t* rows = base + size_t(row0) * LD;
+    const unsigned lane = unsigned((tid / LPR) * LD + (tid % LPR) * EPP);
     if (C % RPP == 0 && row0 + C <= n_rows) {
       // whole tile in range (workgroup-uniform): plain loads at constant strides
 #pragma unroll
       for (int p = 0; p < PASSES; ++p)
-        regs[p] = load_rows(rows + p * RPP * D + lane, stream);
+        regs[p] = load_rows(rows + p * RPP * LD + lane, stream);
       return;
     }
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
       uint4 v = {0u, 0u, 0u, 0u};
-      if (lr < C && row0 + lr < n_rows) v = load_rows(rows + p * RPP * D + lane, stream);
+      if (lr < C && row0 + lr < n_rows) v = load_rows(rows + p * RPP * LD + lane, stream);
       regs[p] = v;
     }
   }
@@ -289,18 +290,18 @@ __device__ __forceinline__ void gather_rows_transposed(const f32x4* acc, float r
 // not written.  The scan kernels call this one chunk late (after the next chunk's loads have
 // been issued): the wait for those loads at the top of a chunk step is a wait for every
 // outstanding memory operation, and must not find stores that were issued a moment ago.
-template <int D, int NTILES = D / 16>
+template <int D, int NTILES = D / 16, int LD = D>
 __device__ __forceinline__ void store_row_pieces(const RowPieces<D, NTILES>& p,
                                                  elem_t* __restrict__ dst, int first_row,
                                                  int row_end, int l, int col0 = 0) {
   using RP = RowPieces<D, NTILES>;
-  elem_t* rows = dst + size_t(first_row) * D + col0;   // uniform over the wave
+  elem_t* rows = dst + size_t(first_row) * LD + col0;   // uniform over the wave
 #pragma unroll
   for (int j = 0; j < RP::PER_LANE; ++j) {
     const int i = l + 64 * j;
     const int lr = i / RP::PPR;
     if ((RP::PIECES % 64 == 0 || i < RP::PIECES) && first_row + lr < row_end)
-      store_streaming(rows + unsigned(lr * D + (i % RP::PPR) * EPP), p.v[j]);
+      store_streaming(rows + unsigned(lr * LD + (i % RP::PPR) * EPP), p.v[j]);
   }
 }
 
