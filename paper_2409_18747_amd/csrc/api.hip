@@ -85,10 +85,8 @@ double causal_call_us(long units, long N, long n_chunks, long g, int dtype, int 
 // forward / with its backward, 1 segment 64 / 270).  Others of the measured, forward / with backward: 16-bit
 // 128 x 128 8 units of 2048 rows 32 segments 30 / 55 us, 16 27 / 51, 8 29 / 71; 64 x 64 64 units of 2048
 // rows 6 segments 24 / 66, 8 22 / 59; 176 units of 600 rows 3 segments 19.8 / 61, 2 22.0 / 58, 1 17.8 / 62;
-// fp32 40 units of 1024 rows 8 segments 33 / 94, 11 29 / 80.  At 16-bit 128 x 128, whose scans run two
-// workgroups to a compute unit from 257 on (launch.h: two_to_a_cu_dkdv), the line is at 512: 272 units of
-// 1024 rows 2 segments 95 / 323 us, 1 84 / 310; 320 of 2048 180 / 652, 167 / 645 (3, which it
-// leaves out, 91 / 295 and 186 / 611).
+// fp32 40 units of 1024 rows 8 segments 33 / 94, 11 29 / 80.  Where the line costs most: 128 x 128 320 units
+// of 2048 rows 2 segments 180 / 652 us, 1 167 / 645, but 3, which it leaves out, 186 / 611.
 // No split at all leaves the backward waiting where units are few: up to 160 16-bit units of more than four
 // chunks (of 32 x 32 fewer than 384 of more than eight) take at least two segments, but at 128 x 128, where
 // one unit fills a compute unit (160 units of 300 rows at 64 x 32: 3 segments 10.0 / 26 us, 1 segment 9.1
@@ -101,7 +99,7 @@ long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk
     return n_chunks >= 16 * want ? (512 + units - 1) / units : want;
   }
   const bool f32 = dtype == COTTN_F32, narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
-  const long most = f32 && narrowest ? 768 : f32 || narrowest ? 1024 : widest ? 512 : 640;
+  const long most = f32 && narrowest ? 768 : f32 || narrowest ? 1024 : 640;
   const bool cut = !f32 && !widest && ((n_chunks > 4 && units <= 160) || (narrowest && n_chunks > 8 && units < 384));
   double best = causal_call_us(units, N, n_chunks, 1, dtype, dk, dv);
   long best_g = 1;
@@ -392,7 +390,7 @@ int cottn_fwd_causal_static(const void* Q, const void* K, const void* V, const f
   if (!make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, d, d, chunk, dtype, &plan)) return COTTN_E_SHAPE;
   size_t need = workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, d, d, plan);
   // a split of the library's own whose states do not fit the array gives way to the finest that does
-  // (d = 128: up to 512 workgroups, 1024 for fp32, have a state of 64 KB each)
+  // (d = 128: up to 640 workgroups, 1024 for fp32, have a state of 64 KB each)
   long most = 0;
   if (need > size_t(COTTN_STATIC_WORKSPACE_BYTES)) {
     const long most_that_fit = long(COTTN_STATIC_WORKSPACE_BYTES) / (long(B) * H * d * d * long(sizeof(float)));
