@@ -117,6 +117,41 @@ long causal_segments(long units, long N, long n_chunks, int C, int dtype, int dk
   return best_g;
 }
 
+// Chunks per workgroup where a causal call walks even shares (workspace.h) instead of G segments per unit,
+// or 0.  A split leaves compute units idle where units do not divide by them: 96 units at 128 x 128, of which a
+// compute unit runs one workgroup, are 192 workgroups of 8 steps, or 256 shares of 6.  A share that goes on into the
+// next unit costs little (its rows are prefetched across the boundary, its state starts from zero), but there are
+// totals to form, also where one segment had none, and more of them to add up: 3 and 4 steps' worth of
+// prologue in the comparison below, which was fitted to 360 shapes of 12 to 1100 units.
+//   Forward / with backward, segments -> shares: 16-bit 128 x 128 96 units of 1024 rows 36 / 117 -> 34 / 106 us, 68 of
+// 5010 117 / 379 -> 103 / 324, 272 of 1024 93 / 318 -> 80 / 261, 528 of 1464 219 / 818 -> 191 / 688; fp32 64 x 64 96
+// units of 1024 rows 43 / 130 -> 38 / 120, 129 of 816 53 / 147 -> 47 / 127, 282 of 571 69 / 198 -> 59 / 173; 128 x 128
+// 543 of 442 325 / 1219 -> 278 / 953; 64 x 128 308 of 582 168 / 502 -> 133 / 412.
+//   Not where it does not pay: 16-bit shapes of two workgroups to a compute unit, which wait for memory more than for
+// the fullest compute unit (64 x 64 96 units of 1024 rows 52.8 -> 51.9 us, 226 of 4238 at 128 x 64 167 / 599 -> 191 /
+// 624); one segment per unit that fits the chip at once, where a forward has no totals to form (fp32 64 x 128 220
+// units of 1719 rows 194 / 781 -> 277 / 849), or nearly (fp32 64 x 64 588 of 2516 439 / 1711 -> 472 / 1541).
+long causal_even_share(long units, long n_chunks, long G, int dtype, int dk, int dv) {
+  const bool f32 = dtype == COTTN_F32;
+  if (!even_shares_built(dk, dv, f32)) return 0;
+  const long at_once = f32 && dk == 64 && dv == 64 ? 2 : 1, places = at_once * kComputeUnits;
+  const long share = (units * n_chunks + places - 1) / places;
+  if (share < 3 || !causal_totals_in_place(units, int((n_chunks + share - 1) / share) + 1, dk, dv, f32)) return 0;
+  const long workgroups = units * G, steps = (n_chunks + G - 1) / G;
+  double rounds = 1.0;   // of the segments, as long as `steps` each
+  if (workgroups <= places) {
+    if (G == 1 || workgroups <= kComputeUnits * (at_once - 1)) return 0;
+  } else if (f32) {
+    if (at_once == 2 && G == 1) return 0;
+    rounds = double((workgroups + places - 1) / places);
+  } else {   // two to a compute unit then (launch.h: two_to_a_cu_forward)
+    if (workgroups > 640 || (workgroups <= 512 && G == 1)) return 0;
+    rounds = workgroups <= 512 ? 1.5 : 2.5;
+  }
+  const double gain = (rounds * double(steps) + 3.0) / (double(share) + (at_once == 2 ? 3.0 : 4.0));
+  return gain >= (at_once == 2 ? 1.08 : 1.05) ? share : 0;
+}
+
 // Segments per (batch, head) for the bidirectional calls.  Their kernels have no chain to
 // shorten and little to set up: about three workgroups per compute unit measured best (B24 H8 N3000
 // d64, forward + backward: 155 us with 4 segments, 169 with 2), in at most four segments, whose
@@ -189,8 +224,36 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   plan->C = C;
   plan->G = plan->by_unit ? 1 : int(G);
   plan->seg_rows = int((plan->by_unit ? n_chunks : chunks_per_seg) * C);
+  plan->even_rows = 0;
+  plan->slots = G > 1 ? units * G : 0;
+  plan->pieces = units * G;
+  if (!bidir && g_tuned_segments <= 0 && most_segments <= 0 && C <= 64 && n_chunks > 0) {
+    const long share = causal_even_share(units, n_chunks, G, dtype, dk, dv);
+    if (share > 0 && (units * n_chunks + share) * C < (1L << 31)) {
+      const long workgroups = (units * n_chunks + share - 1) / share;
+      plan->even_rows = int(share * C);
+      if (plan->slots < workgroups) plan->slots = workgroups;
+      if (plan->pieces < workgroups + units) plan->pieces = workgroups + units;
+    }
+  }
   return true;
 }
+
+namespace {
+
+// The walk of a causal call: even shares where the plan has them, but for a padded batch.
+void set_walk(CausalArgs* a, const SeqPlan& plan) {
+  const long units = long(a->B) * a->H;
+  const bool even = plan.even_rows > 0 && a->seq_len == nullptr;
+  a->C = plan.C;
+  a->G = plan.G;
+  a->slots = plan.slots;
+  a->unit_rows = even ? (a->N + plan.C - 1) / plan.C * plan.C : 0;
+  a->seg_rows = even ? plan.even_rows : plan.seg_rows;
+  a->workgroups = int(even ? (units * a->unit_rows + a->seg_rows - 1) / a->seg_rows : units * plan.G);
+}
+
+}  // namespace
 
 bool profile_on() { return g_profile_on; }
 
@@ -337,7 +400,8 @@ int fwd_causal_any(const void* Q, const void* K, const void* V, const float* s, 
   CausalArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.s = s; a.O = O; a.state = state; a.state_in = state_in;
   a.workspace = workspace; a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
-  a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
+  a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv;
+  set_walk(&a, plan);
   a.eps = eps; a.stream = stream;
   return map_hip(dtype == COTTN_BF16 ? fwd_causal_bf16(a) : dtype == COTTN_F16 ? fwd_causal_f16(a) : fwd_causal_f32(a));
 }
@@ -450,14 +514,16 @@ int bwd_causal_any(const void* Q, const void* K, const void* V, const float* s, 
   a.Q = Q; a.K = K; a.V = V; a.s = s; a.dO = dO; a.dQ = dQ; a.dK = dK; a.dV = dV; a.ds = ds;
   a.state_in = state_in; a.rev_state_in = rev_state_in; a.rev_state_out = rev_state_out;
   a.workspace = workspace; a.seq_len = seq_len; a.s_per_unit = seq_len != nullptr;
-  a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv; a.C = plan.C; a.G = plan.G; a.seg_rows = plan.seg_rows;
+  a.B = B; a.H = H; a.N = N; a.dk = dk; a.dv = dv;
+  set_walk(&a, plan);
   a.eps = eps; a.stream = stream;
   // the forward's segment states are taken over only if the forward split the sequence as
   // the backward does
-  if (fwd_workspace != nullptr && plan.G > 1) {
+  if (fwd_workspace != nullptr && (plan.G > 1 || a.unit_rows > 0)) {
     SeqPlan fwd_plan;
     if (make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dtype, &fwd_plan) &&
-        fwd_plan.C == plan.C && fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows) {
+        fwd_plan.C == plan.C && fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows &&
+        fwd_plan.even_rows == plan.even_rows) {
       st = check_workspace(fwd_workspace, fwd_workspace_bytes,
                            workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, dk, dv, fwd_plan));
       if (st != COTTN_OK) return st;

@@ -152,14 +152,14 @@ __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_t
 // for the intra-chunk product.
 //
 // REV: whether the launch has segments to leave reverse-time totals for.
-template <int DK, int DV, int C, int CS, bool REV>
+template <int DK, int DV, int C, int CS, bool REV, bool EVEN>
 __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dq_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
     const float* __restrict__ fwd_states, float* __restrict__ rev_totals,
     float* __restrict__ ds_partial, int H, int N, int G, int seg_rows, float inv_eps,
     int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
-    const float* __restrict__ state_in) {
+    const float* __restrict__ state_in, int units, int unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
   using AT = SplitTiles<DK, DV, Cfg::RG, CS>;   // forward-time state: key rows, value columns
   using RT = SplitTiles<DV, DK, Cfg::RG, CS>;   // reverse-time total: value rows, key columns
@@ -187,30 +187,29 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   Masked& masked = *reinterpret_cast<Masked*>(IN_STAGE ? reinterpret_cast<char*>(Os) : masked_lds);
 
   fetch_argument_now(Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G, seg_rows,
-                     inv_eps, sum_totals, seq_len, s_per_unit, state_in);
-  int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+                     inv_eps, sum_totals, seq_len, s_per_unit, state_in, units, unit_rows);
+  const Span span = span_of_workgroup<false, EVEN>(units, N, G, seg_rows, unit_rows);
+  int unit = span.unit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const int rg = row_group<Cfg::RG, CS>(w), cp = w / Cfg::RG;   // row group, column part
-  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;   // (of the rows fetched next, from there on)
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dQu = dQ + size_t(unit) * N * DK;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
-  const int row_begin = g * seg_rows;
-  const int seg_end = min(N, row_begin + seg_rows);
-  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
+  float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_begin = span.begin;
+  int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
 
   // fwd_states holds the carried prefixes (slot g = state at the start of segment g) or, with
   // sum_totals set, the raw segment totals, which this workgroup then adds up itself
   f32x4 sacc[AT::NCT][AT::NRT];
-  // By-product for the dK/dV kernel: this segment's total of qh^T dO (segments after the
-  // first; earlier segments need it), accumulated in that kernel's layout: element [v] of
+  // By-product for the dK/dV kernel: the first piece's total of qh^T dO (unless it begins its
+  // unit; the workgroups before this one need it), accumulated in that kernel's layout: element [v] of
   // lane (r, q4) of tile (y, x) is R[key 16 ct + r][value 16 rt + 4 q4 + v].
   f32x4 racc[RT::NCT][RT::NRT];
-  const bool with_rev = REV && rev_totals != nullptr && g > 0;
+  bool with_rev = REV && rev_totals != nullptr && span.mid_unit;
 #pragma unroll
   for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
@@ -227,17 +226,17 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
-  if (fwd_states != nullptr && g > 0 && AT::active(rg, cp)) {
-    const float* src = fwd_states + size_t(unit) * G * DK * DV;
+  if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(
-        sacc, sum_totals ? 0 : g, sum_totals ? g - 1 : g, [&](int gp, int x, int y) {
+        sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
+        [&](int slot, int x, int y) {
           return *reinterpret_cast<const f32x4*>(
-              src + size_t(gp) * DK * DV +
+              fwd_states + size_t(slot) * DK * DV +
               tiled_state_offset(AT::row_tile(rg, cp, y), AT::col_tile(rg, cp, x), DV / 16, l));
         });
   }
   // the state of the rows before this piece of the sequence belongs to every segment's start
-  if (state_in != nullptr && AT::active(rg, cp)) {
+  const auto add_state_in = [&] {
     const float* src = state_in + size_t(unit) * DK * DV;
 #pragma unroll
     for (int x = 0; x < AT::NCT; ++x)
@@ -245,14 +244,40 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       for (int y = 0; y < AT::NRT; ++y)
         sacc[x][y] += *reinterpret_cast<const f32x4*>(src + (16 * AT::row_tile(rg, cp, y) + r) * DV +
                                                       16 * AT::col_tile(rg, cp, x) + 4 * q4);
-  }
+  };
+  if (state_in != nullptr && AT::active(rg, cp)) add_state_in();
+  const auto store_rev_total = [&] {
+    float* out = rev_totals + size_t(span.slot) * DK * DV;
+#pragma unroll
+    for (int x = 0; x < RT::NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < RT::NRT; ++y)
+        store_state_words(out + tiled_state_offset(RT::col_tile(rg, cp, x), RT::row_tile(rg, cp, y), DV / 16, l),
+                          racc[x][y]);
+  };
+  // the piece's share of ds: lanes of the first lane row hold the row sums.  Pieces are numbered in the
+  // order of their rows: slot + unit with even shares (one more piece for every unit begun)
+  const auto store_ds = [&] {
+    ds_lane = group_sum<64>(ds_lane);
+    if (l == 0) ds_wave[w] = ds_lane;
+    __syncthreads();
+    if (tid == 0) {
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < Cfg::NW; ++i) t += ds_wave[i];
+      ds_partial[span.slot + (EVEN ? unit : 0)] = t;
+    }
+    ds_lane = 0.f;
+  };
 
   constexpr int NKT = Cfg::NKT;
   const int colk = 16 * NKT * cp;  // first result column of this wave
   RowPieces<DK, NKT> finished;  // dQ rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DK, NKT>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
-  for (int row0 = row_begin; row0 < row_end; row0 += C) {
+  elem_t* done_dQ = dQu;
+  int done_row = 0, done_end = 0, row0 = row_begin, left = span.left;   // done_end = 0: nothing finished yet
+  for (bool more = row0 < row_end; more;) {
     if (AT::active(rg, cp)) {
 #pragma unroll
       for (int x = 0; x < AT::NCT; ++x)
@@ -272,14 +297,23 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       vst.commit_plain(Vs);
       gst.commit_plain(Gs);
     }
-    if (row0 + C < row_end) {
-      qst.fetch(Qu, row0 + C, row_end);
-      kst.fetch(Ku, row0 + C, row_end);
-      vst.fetch(Vu, row0 + C, row_end);
-      gst.fetch(Gu, row0 + C, row_end);
+    // the next step's rows: of this unit, or the first ones of the next
+    const bool cross = EVEN && left > 0 && row0 + C >= row_end;
+    const int next_row = cross ? 0 : row0 + C, next_end = cross ? min(N, left) : row_end;
+    more = next_row < next_end;
+    if (cross) {
+      Qu += size_t(N) * DK;
+      Ku += size_t(N) * DK;
+      Vu += size_t(N) * DV;
+      Gu += size_t(N) * DV;
     }
-    if (row0 > row_begin)
-      store_row_pieces<DK, NKT>(finished, dQu, row0 - C + 16 * rg, row_end, l, colk);
+    if (more) {
+      qst.fetch(Qu, next_row, next_end);
+      kst.fetch(Ku, next_row, next_end);
+      vst.fetch(Vu, next_row, next_end);
+      gst.fetch(Gu, next_row, next_end);
+    }
+    if (done_end > 0) store_row_pieces<DK, NKT>(finished, done_dQ, done_row + 16 * rg, done_end, l, colk);
     __syncthreads();
 
     if constexpr (Cfg::SHARE_MASKED) {
@@ -430,34 +464,32 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
                                                     : static_cast<void*>(Gs + 16 * rg * TPV),
                                     l, finished, colk);
     __syncthreads();
-  }
-  if (row_begin < row_end) {
-    const int last = row_begin + (row_end - row_begin - 1) / C * C;
-    store_row_pieces<DK, NKT>(finished, dQu, last + 16 * rg, row_end, l, colk);
-  }
-
-  if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, seg_end);  // rows that do not exist
-
-  if (with_rev && RT::active(rg, cp)) {
-    float* out = rev_totals + (size_t(unit) * G + g) * DK * DV;
+    done_dQ = dQu;
+    done_row = row0;
+    done_end = row_end;
+    if (cross) {   // the unit ends here
+      if (with_rev && RT::active(rg, cp)) store_rev_total();
+      with_rev = false;
+      store_ds();
+      ++unit;
+      left -= unit_rows;
+      dQu += size_t(N) * DK;
+      scale = unit_scale(s, unit, H, s_per_unit);
 #pragma unroll
-    for (int x = 0; x < RT::NCT; ++x)
+      for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
-      for (int y = 0; y < RT::NRT; ++y)
-        store_state_words(out + tiled_state_offset(RT::col_tile(rg, cp, x), RT::row_tile(rg, cp, y), DV / 16, l),
-                          racc[x][y]);
+        for (int y = 0; y < AT::NRT; ++y) sacc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (state_in != nullptr && AT::active(rg, cp)) add_state_in();
+    }
+    row0 = next_row;
+    row_end = next_end;
   }
+  if (done_end > 0) store_row_pieces<DK, NKT>(finished, done_dQ, done_row + 16 * rg, done_end, l, colk);
 
-  // per-workgroup partial of ds: lanes of the first lane row hold the row sums
-  ds_lane = group_sum<64>(ds_lane);
-  if (l == 0) ds_wave[w] = ds_lane;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < Cfg::NW; ++i) t += ds_wave[i];
-    ds_partial[size_t(unit) * G + g] = t;
-  }
+  if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, span.end);  // rows that do not exist
+
+  if (with_rev && RT::active(rg, cp)) store_rev_total();
+  store_ds();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -467,14 +499,14 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 // is R[16 ct + r][16 rt + 4 q4 + v], published with one 8-byte write to the row-major LDS
 // copy Rl[d_key][d_value]; the update's row-side operand is the dO fragment already read
 // for the intra-chunk dV product.
-template <int DK, int DV, int C, int CS>
+template <int DK, int DV, int C, int CS, bool EVEN>
 __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dkdv_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dK,
     elem_t* __restrict__ dV, const float* __restrict__ rev_states,
     const float* __restrict__ ds_partial, float* __restrict__ ds, int B, int H, int N, int G,
     int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
-    const float* __restrict__ rev_in, float* __restrict__ rev_out) {
+    const float* __restrict__ rev_in, float* __restrict__ rev_out, int unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
   using AT = SplitTiles<DV, DK, Cfg::RG, CS>;   // value rows, key columns (the state is held transposed)
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -491,28 +523,37 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   __shared__ MaskedExchange<Cfg::SHARE_MASKED ? 4 : 0> masked;
 
   fetch_argument_now(Q, K, V, dO, s, dK, dV, rev_states, ds_partial, ds, B, H, N, G, seg_rows,
-                     inv_eps, sum_totals, seq_len, s_per_unit, rev_in, rev_out);
-  int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+                     inv_eps, sum_totals, seq_len, s_per_unit, rev_in, rev_out, unit_rows);
+  const Span span = span_of_workgroup<true, EVEN>(B * H, N, G, seg_rows, unit_rows);
+  int unit = span.unit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const int rg = row_group<Cfg::RG, CS>(w), cp = w / Cfg::RG;   // row group, column part
-  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;   // (of the rows fetched next, from there on)
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dKu = dK + size_t(unit) * N * DK;
   elem_t* dVu = dV + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
-  const int row_begin = g * seg_rows;
-  const int seg_end = min(N, row_begin + seg_rows);
-  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
-  const int n_chunks = (row_end - row_begin + C - 1) / C;
+  float scale = unit_scale(s, unit, H, s_per_unit);
+  int row_begin = span.begin;   // of the piece walked, and its end
+  int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));
 
   // the first H workgroups also finish ds: ds[h] = sum over batches and segments of the
   // partial sums the dQ kernel left behind (with a scale per (batch, head): the first B*H
-  // workgroups, ds[b][h] = sum over the segments)
-  if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
+  // workgroups, ds[b][h] = sum over the segments; with even shares there can be fewer workgroups)
+  if constexpr (EVEN) {
+    if (w == 0)
+      for (int h = blockIdx.x; h < H; h += gridDim.x) {
+        float t = 0.f;
+        for (int b = l; b < B; b += 64) {
+          const int u = b * H + h, last = ((u + 1) * unit_rows - 1) / seg_rows;
+          for (int slot = u * unit_rows / seg_rows; slot <= last; ++slot) t += ds_partial[slot + u];
+        }
+        t = group_sum<64>(t);
+        if (l == 0) ds[h] = t;
+      }
+  } else if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
     float t = 0.f;
     const int n = s_per_unit ? G : B * G;
     for (int i = l; i < n; i += 64)
@@ -532,24 +573,25 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   // the last chunk's rows and the stored states are all requested before anything waits
   StageK qst, kst;
   StageV vst, gst;
-  if (n_chunks > 0) {  // (a segment of a padded batch can be empty)
-    const int first = row_begin + (n_chunks - 1) * C;
-    qst.fetch(Qu, first, row_end);
-    kst.fetch(Ku, first, row_end);
-    vst.fetch(Vu, first, row_end);
-    gst.fetch(Gu, first, row_end);
+  bool more = row_begin < row_end;   // (a segment of a padded batch can be empty)
+  int row0 = row_begin + (row_end - row_begin - 1) / C * C;
+  if (more) {
+    qst.fetch(Qu, row0, row_end);
+    kst.fetch(Ku, row0, row_end);
+    vst.fetch(Vu, row0, row_end);
+    gst.fetch(Gu, row0, row_end);
   }
-  if (rev_states != nullptr && g < G - 1 && AT::active(rg, cp)) {
-    const float* src = rev_states + size_t(unit) * G * DK * DV;
+  if (rev_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(
-        racc, sum_totals ? g + 1 : g, sum_totals ? G - 1 : g, [&](int gp, int x, int y) {
+        racc, sum_totals ? span.slot + 1 : span.slot, sum_totals ? span.outermost : span.slot,
+        [&](int slot, int x, int y) {
           return *reinterpret_cast<const f32x4*>(
-              src + size_t(gp) * DK * DV +
+              rev_states + size_t(slot) * DK * DV +
               tiled_state_offset(AT::col_tile(rg, cp, x), AT::row_tile(rg, cp, y), DV / 16, l));
         });
   }
   // the reverse state of the rows after this piece of the sequence belongs to every segment
-  if (rev_in != nullptr && AT::active(rg, cp)) {
+  const auto add_rev_in = [&] {
     const float* src = rev_in + size_t(unit) * DK * DV;
 #pragma unroll
     for (int x = 0; x < AT::NCT; ++x)
@@ -557,7 +599,18 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       for (int y = 0; y < AT::NRT; ++y)
         racc[x][y] += *reinterpret_cast<const f32x4*>(src + (16 * AT::col_tile(rg, cp, x) + r) * DV +
                                                       16 * AT::row_tile(rg, cp, y) + 4 * q4);
-  }
+  };
+  if (rev_in != nullptr && AT::active(rg, cp)) add_rev_in();
+  // at the first row of a unit: the reverse state of the whole piece and what followed it
+  const auto store_rev_out = [&] {
+    float* out = rev_out + size_t(unit) * DK * DV;
+#pragma unroll
+    for (int x = 0; x < AT::NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < AT::NRT; ++y)
+        *reinterpret_cast<f32x4*>(out + (16 * AT::col_tile(rg, cp, x) + r) * DV +
+                                  16 * AT::row_tile(rg, cp, y) + 4 * q4) = racc[x][y];
+  };
 
   constexpr int NKT = Cfg::NKT, NVT = Cfg::NVT;
   const int colk = 16 * NKT * cp, colv = 16 * NVT * cp;  // first result columns of this wave
@@ -567,8 +620,9 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   for (int j = 0; j < RowPieces<DK, NKT>::PER_LANE; ++j) done_k.v[j] = uint4{0u, 0u, 0u, 0u};
 #pragma unroll
   for (int j = 0; j < RowPieces<DV, NVT>::PER_LANE; ++j) done_v.v[j] = uint4{0u, 0u, 0u, 0u};
-  for (int c = n_chunks - 1; c >= 0; --c) {
-    const int row0 = row_begin + c * C;
+  elem_t *done_dK = dKu, *done_dV = dVu;
+  int done_row = 0, done_end = 0, left = span.left;   // done_end = 0: nothing finished yet
+  while (more) {
     if (AT::active(rg, cp)) {
 #pragma unroll
       for (int x = 0; x < AT::NCT; ++x)
@@ -588,15 +642,26 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       vst.commit_plain(Vs);
       gst.commit_plain(Gs);
     }
-    if (c > 0) {
-      qst.fetch(Qu, row0 - C, row_end);
-      kst.fetch(Ku, row0 - C, row_end);
-      vst.fetch(Vu, row0 - C, row_end);
-      gst.fetch(Gu, row0 - C, row_end);
+    // the next step's rows: of this unit, or the last ones of the unit before
+    const bool cross = EVEN && left > 0 && row0 == row_begin;
+    const int next_begin = cross ? max(0, unit_rows - left) : row_begin, next_end = cross ? N : row_end;
+    const int next_row = cross ? next_begin + (N - next_begin - 1) / C * C : row0 - C;
+    more = cross || row0 > row_begin;
+    if (cross) {
+      Qu -= size_t(N) * DK;
+      Ku -= size_t(N) * DK;
+      Vu -= size_t(N) * DV;
+      Gu -= size_t(N) * DV;
     }
-    if (c < n_chunks - 1) {
-      store_row_pieces<DK, NKT>(done_k, dKu, row0 + C + 16 * rg, row_end, l, colk);
-      store_row_pieces<DV, NVT>(done_v, dVu, row0 + C + 16 * rg, row_end, l, colv);
+    if (more) {
+      qst.fetch(Qu, next_row, next_end);
+      kst.fetch(Ku, next_row, next_end);
+      vst.fetch(Vu, next_row, next_end);
+      gst.fetch(Gu, next_row, next_end);
+    }
+    if (done_end > 0) {
+      store_row_pieces<DK, NKT>(done_k, done_dK, done_row + 16 * rg, done_end, l, colk);
+      store_row_pieces<DV, NVT>(done_v, done_dV, done_row + 16 * rg, done_end, l, colv);
     }
     __syncthreads();
 
@@ -805,25 +870,36 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     gather_rows_transposed<DK, NKT>(dk, scale * rj, Ks + 16 * rg * TPK, l, done_k, colk);
     gather_rows_transposed<DV, NVT>(dv, scale * rj, Vs + 16 * rg * TPV, l, done_v, colv);
     __syncthreads();
+    done_dK = dKu;
+    done_dV = dVu;
+    done_row = row0;
+    done_end = row_end;
+    if (cross) {   // the unit begins here
+      if (rev_out != nullptr && AT::active(rg, cp)) store_rev_out();
+      --unit;
+      left -= unit_rows;
+      dKu -= size_t(N) * DK;
+      dVu -= size_t(N) * DV;
+      scale = unit_scale(s, unit, H, s_per_unit);
+#pragma unroll
+      for (int x = 0; x < AT::NCT; ++x)
+#pragma unroll
+        for (int y = 0; y < AT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (rev_in != nullptr && AT::active(rg, cp)) add_rev_in();
+    }
+    row_begin = next_begin;
+    row0 = next_row;
+    row_end = next_end;
   }
-  if (n_chunks > 0) {
-    store_row_pieces<DK, NKT>(done_k, dKu, row_begin + 16 * rg, row_end, l, colk);
-    store_row_pieces<DV, NVT>(done_v, dVu, row_begin + 16 * rg, row_end, l, colv);
+  if (done_end > 0) {
+    store_row_pieces<DK, NKT>(done_k, done_dK, done_row + 16 * rg, done_end, l, colk);
+    store_row_pieces<DV, NVT>(done_v, done_dV, done_row + 16 * rg, done_end, l, colv);
   }
   if (seq_len != nullptr) {  // rows that do not exist
-    zero_rows<DK>(dKu, row_end, seg_end);
-    zero_rows<DV>(dVu, row_end, seg_end);
+    zero_rows<DK>(dKu, row_end, span.end);
+    zero_rows<DV>(dVu, row_end, span.end);
   }
-  // the first segment ends with the reverse state of the whole piece and what followed it
-  if (rev_out != nullptr && g == 0 && AT::active(rg, cp)) {
-    float* out = rev_out + size_t(unit) * DK * DV;
-#pragma unroll
-    for (int x = 0; x < AT::NCT; ++x)
-#pragma unroll
-      for (int y = 0; y < AT::NRT; ++y)
-        *reinterpret_cast<f32x4*>(out + (16 * AT::col_tile(rg, cp, x) + r) * DV +
-                                  16 * AT::row_tile(rg, cp, y) + 4 * q4) = racc[x][y];
-  }
+  if (rev_out != nullptr && row_begin == 0 && AT::active(rg, cp)) store_rev_out();
 }
 
 template <int DK, int DV, int C, int CR = BwdSplit<DK, DV, C>::CR, int CS = BwdSplit<DK, DV, C>::CS>
@@ -837,17 +913,18 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   char* ws = static_cast<char*>(a.workspace);
   const float* fwd_states = nullptr;
   float* rev_states = nullptr;
-  const dim3 grid(units * a.G);
+  const dim3 grid(a.workgroups);
+  const bool even = a.unit_rows > 0;
   const float inv_eps = 1.0f / a.eps;
   // few segments: no carry launches, the scan workgroups add up the totals they need
-  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
+  const bool sum_in_scan = even || causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
   hipError_t err;
-  if (a.G > 1) {
+  if (a.G > 1 || even) {
     // Forward-time states: taken over from the forward call when it left them behind (raw
     // totals or carried prefixes, by the same rule as here), else recomputed from K and V.
     float* own_fwd = reinterpret_cast<float*>(ws);
-    rev_states = reinterpret_cast<float*>(ws + state_array_bytes(a.B, a.H, DK, DV, a.G));
-    ws += 2 * state_array_bytes(a.B, a.H, DK, DV, a.G);
+    rev_states = reinterpret_cast<float*>(ws + state_slots_bytes(a.slots, DK, DV));
+    ws += 2 * state_slots_bytes(a.slots, DK, DV);
     if (a.saved_fwd_states != nullptr) {
       fwd_states = a.saved_fwd_states;
     } else {
@@ -865,17 +942,20 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const auto dq_scan = [&](auto kernel, int threads) {
     return launch_kernel(COTTN_SYM_STR(bwd_dq_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
                          static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H, a.N, a.G, a.seg_rows,
-                         inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in);
+                         inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in, units,
+                         a.unit_rows);
   };
+  constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32);
   constexpr bool HALVED = !ELEM_IS_F32 && DK == 128 && DV == 128 && CR == 64 && CS == 2;
-  const long workgroups = long(units) * a.G;
-  if (HALVED && a.G == 1 && two_to_a_cu_dq(workgroups)) {
-    if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false>, 256);
+  if (HALVED && a.G == 1 && !even && two_to_a_cu_dq(a.workgroups)) {
+    if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, false>, 256);
+  } else if (even) {
+    if constexpr (EVEN_BUILT) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, true>, Cfg::NT);
   } else {
-    err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true>, Cfg::NT);
+    err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, false>, Cfg::NT);
   }
   if (err != hipSuccess) return err;
-  if (a.G > 1 && !sum_in_scan) {
+  if (!sum_in_scan) {
     err = launch_bwd_state_carry(nullptr, rev_states, units, a.G, DK * DV, a.stream);
     if (err != hipSuccess) return err;
   }
@@ -884,11 +964,14 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
     return launch_kernel(COTTN_SYM_STR(bwd_dkdv_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
                          static_cast<elem_t*>(a.dK), static_cast<elem_t*>(a.dV), rev_states, ds_partial, a.ds, a.B,
                          a.H, a.N, a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit,
-                         a.rev_state_in, a.rev_state_out);
+                         a.rev_state_in, a.rev_state_out, a.unit_rows);
   };
   if constexpr (HALVED)
-    if (two_to_a_cu_dkdv(workgroups)) return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, 32, CS>, 256);
-  return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS>, Cfg::NT);
+    if (!even && two_to_a_cu_dkdv(a.workgroups))
+      return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, 32, CS, false>, 256);
+  if constexpr (EVEN_BUILT)
+    if (even) return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, true>, Cfg::NT);
+  return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, false>, Cfg::NT);
 }
 
 }  // namespace

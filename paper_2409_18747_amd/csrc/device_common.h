@@ -546,6 +546,49 @@ __device__ __forceinline__ void unit_and_segment(int index, int G, int& unit, in
   }
 }
 
+// The rows a workgroup of the causal kernels walks, first to last or last to first.
+//   One segment of one unit: segment g of seg_rows rows, numbered as above.
+//   An even share (EVEN): the units laid end to end, unit_rows (a whole number of chunks) for
+//   each, cut every seg_rows rows.  A share may begin in the middle of a unit and go on into the next
+//   ones, so that every workgroup has the same number of steps whatever the number of units is.
+// The states that workgroups leave for each other (Kh^T V of the last piece of a share, Qh^T dO of the
+// first) have one slot per workgroup either way.  Neighbouring shares go to one XCD, as segments do.
+struct Span {
+  int unit, begin, end;   // the first piece walked: rows begin .. end - 1 of a unit
+  int left;               // rows of the share beyond that unit, in the direction walked
+  int slot, outermost;    // the workgroup's slot; that of the unit's first (reverse: last) workgroup
+  bool mid_unit;          // rows of the unit come before (reverse: after) the piece
+};
+__device__ __forceinline__ int even_workgroup() {
+  const int per_xcd = gridDim.x / 8, index = blockIdx.x;
+  return index < 8 * per_xcd ? index % 8 * per_xcd + index / 8 : index;
+}
+template <bool REVERSE, bool EVEN>
+__device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int seg_rows, int unit_rows) {
+  Span s;
+  if constexpr (!EVEN) {
+    int g;
+    unit_and_segment(blockIdx.x, G, s.unit, g);
+    s.begin = g * seg_rows;
+    s.end = min(N, s.begin + seg_rows);
+    s.left = 0;
+    s.slot = s.unit * G + g;
+    s.outermost = REVERSE ? s.unit * G + G - 1 : s.unit * G;
+    s.mid_unit = REVERSE ? g < G - 1 : g > 0;
+    return s;
+  }
+  s.slot = even_workgroup();
+  const int lo = s.slot * seg_rows, hi = min(lo + seg_rows, units * unit_rows);
+  s.unit = REVERSE ? (hi - 1) / unit_rows : lo / unit_rows;
+  const int start = s.unit * unit_rows, stop = start + unit_rows;
+  s.begin = max(lo - start, 0);
+  s.end = min(N, min(hi, stop) - start);
+  s.left = REVERSE ? max(start - lo, 0) : max(hi - stop, 0);
+  s.outermost = REVERSE ? (stop - 1) / seg_rows : start / seg_rows;
+  s.mid_unit = REVERSE ? hi < stop : lo > start;
+  return s;
+}
+
 // In place, for 4 neighbouring elements of a stack of n matrices `stride` floats apart:
 // matrix k (in walking order: first to last, or last to first with `reverse`) <- sum of the
 // matrices walked before it.  The last matrix walked never held a value and is not read.  The

@@ -98,14 +98,15 @@ template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
 // dealt to the XCDs by their index, and what this kernel reads stays in that XCD's L2 for the
 // scan workgroup of the same (unit, g) in the next launch.  Segment g of a unit writes slot g
 // of the unit's n_slots slots; segments at or beyond n_compute have no total to form and
-// leave at once (the causal forward needs all segments but the last).  The bidirectional
+// leave at once (the causal forward needs all segments but the last).  With even shares (unit_rows > 0;
+// n_slots is not used) a workgroup forms the total of its last piece, unless that ends its unit.  The bidirectional
 // path uses it for Kh^T V (row-major slots, TILED = false; the causal scans read theirs tile
 // by tile, TILED = true).
 template <int DK, int DV, int C, bool TILED>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
     const elem_t* __restrict__ K, const elem_t* __restrict__ V, float* __restrict__ seg_state,
     int N, int n_slots, int n_compute, int seg_rows, float inv_eps,
-    const int* __restrict__ seq_len, int H) {
+    const int* __restrict__ seq_len, int H, int units, int unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -113,16 +114,17 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];
   __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];
 
-  fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H);
-  int unit, g;
-  unit_and_segment(blockIdx.x, n_slots, unit, g);
-  if (g >= n_compute) return;
+  fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H, units, unit_rows);
+  const Span span = unit_rows == 0 ? span_of_workgroup<false, false>(units, N, n_slots, seg_rows, 0)
+                                   : span_of_workgroup<true, true>(units, N, n_slots, seg_rows, unit_rows);
+  const int unit = span.unit;
+  if (unit_rows == 0 ? span.slot - span.outermost >= n_compute : !span.mid_unit) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
-  const int row_begin = g * seg_rows;
-  const int row_end = min(valid_rows(seq_len, unit, H, N), row_begin + seg_rows);
+  const int row_begin = span.begin;
+  const int row_end = min(valid_rows(seq_len, unit, H, N), span.end);
 
   f32x4 acc[ST::NCT][ST::NRT];   // layout: add_rows_to_state
 #pragma unroll
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   vst.fetch(Vu, row_begin, row_end);
   add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, row_begin, row_end, inv_eps, w, l);
   if (ST::active(w)) {
-    float* out = seg_state + (size_t(unit) * n_slots + g) * DK * DV;
+    float* out = seg_state + size_t(span.slot) * DK * DV;
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
@@ -174,13 +176,13 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
 //
 // LDV > DV (one segment): a workgroup takes DV of the LDV value columns, which the whole computation
 // leaves apart from one another but for the masked tiles; those are formed LDV / DV times.
-template <int DK, int DV, int C, int CS, int LDV = DV>
+template <int DK, int DV, int C, int CS, bool EVEN, int LDV = DV>
 __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())) void COTTN_SYM(fwd_causal_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
     const float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
     int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
-    int stream_q, int stream_kv) {
+    int stream_q, int stream_kv, int units, int unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
   constexpr int RG = C / 16;           // row groups of a chunk
   constexpr int NOT = Cfg::DTV / CS;   // output column tiles per wave
@@ -200,25 +202,26 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
-                     sum_totals, seq_len, s_per_unit, stream_q, stream_kv);
-  int unit, g, part = 0;
+                     sum_totals, seq_len, s_per_unit, stream_q, stream_kv, units, unit_rows);
+  Span span;
+  int part = 0;
   if constexpr (LDV > DV) {
-    g = 0;
-    unit_and_segment(blockIdx.x, LDV / DV, unit, part);
+    span = Span{0, 0, N, 0, 0, 0, false};
+    unit_and_segment(blockIdx.x, LDV / DV, span.unit, part);
   } else {
-    unit_and_segment(blockIdx.x, G, unit, g);
+    span = span_of_workgroup<false, EVEN>(units, N, G, seg_rows, unit_rows);
   }
+  int unit = span.unit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const int rg = row_group<RG, CS>(w), cp = w / RG;  // row group, column part
-  const elem_t* Qu = Q + size_t(unit) * N * DK;
+  const elem_t* Qu = Q + size_t(unit) * N * DK;   // (of the rows fetched next, from there on)
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * LDV + part * DV;
   elem_t* Ou = O + size_t(unit) * N * LDV + part * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
-  const int row_begin = g * seg_rows;
-  const int seg_end = min(N, row_begin + seg_rows);
-  const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
+  float scale = unit_scale(s, unit, H, s_per_unit);
+  const int row_begin = span.begin;
+  int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
 
   // running state in fp32 accumulators, seeded with the segment's prefix ([d_key][d_value])
   // seg_states holds either the carried prefixes (slot g = state at the start of segment g)
@@ -237,7 +240,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   vst.fetch(Vu, row_begin, row_end, stream_kv != 0);
   // the state the sequence starts from (chunked prefill) belongs to every segment's start state
   f32x4 start[ST::NCT][ST::NRT];
-  if (state_in != nullptr && ST::active(rg, cp)) {
+  const auto load_start = [&] {
     const float* src = state_in + size_t(unit) * DK * LDV + part * DV;
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
@@ -245,32 +248,46 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       for (int y = 0; y < ST::NRT; ++y)
         start[x][y] = *reinterpret_cast<const f32x4*>(src + (16 * ST::col_tile(rg, cp, x) + r) * LDV +
                                                       16 * ST::row_tile(rg, cp, y) + 4 * q4);
-  }
-  if (LDV == DV && seg_states != nullptr && g > 0 && ST::active(rg, cp)) {
-    const float* src = seg_states + size_t(unit) * G * DK * DV + 4 * l;
-    add_stored_states<ST::STATE_BATCH>(
-        sacc, sum_totals ? 0 : g, sum_totals ? g - 1 : g, [&](int gp, int x, int y) {
-          return *reinterpret_cast<const f32x4*>(
-              src + size_t(gp) * DK * DV +
-              tiled_state_offset(ST::col_tile(rg, cp, x), ST::row_tile(rg, cp, y), DV / 16, 0));
-        });
-  }
-
-  if (state_in != nullptr && ST::active(rg, cp)) {
+  };
+  const auto add_start = [&] {
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
       for (int y = 0; y < ST::NRT; ++y)
 #pragma unroll
         for (int v = 0; v < 4; ++v) sacc[x][y][v] += start[x][y][v];
+  };
+  // the state after the last row of a unit
+  const auto store_final = [&] {
+    float* out = state_out + size_t(unit) * DK * LDV + part * DV;
+#pragma unroll
+    for (int x = 0; x < ST::NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < ST::NRT; ++y)
+        *reinterpret_cast<f32x4*>(out + (16 * ST::col_tile(rg, cp, x) + r) * LDV +
+                                  16 * ST::row_tile(rg, cp, y) + 4 * q4) = sacc[x][y];
+  };
+  if (state_in != nullptr && ST::active(rg, cp)) load_start();
+  if (LDV == DV && seg_states != nullptr && span.mid_unit && ST::active(rg, cp)) {
+    const float* src = seg_states + 4 * l;
+    add_stored_states<ST::STATE_BATCH>(
+        sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
+        [&](int slot, int x, int y) {
+          return *reinterpret_cast<const f32x4*>(
+              src + size_t(slot) * DK * DV +
+              tiled_state_offset(ST::col_tile(rg, cp, x), ST::row_tile(rg, cp, y), DV / 16, 0));
+        });
   }
+  if (state_in != nullptr && ST::active(rg, cp)) add_start();
 
   RowPieces<DV, NOT> finished;  // output rows of the previous chunk, stored one chunk late
 #pragma unroll
   for (int j = 0; j < RowPieces<DV, NOT>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
   void* stage = OWN_STAGE ? static_cast<void*>(Os + 16 * rg * Cfg::OP) : static_cast<void*>(Qs + 16 * rg * TPK);
   const int col0 = 16 * NOT * cp;  // first output column of this wave
-  for (int row0 = row_begin; row0 < row_end; row0 += C) {
+  elem_t* done_O = Ou;
+  int done_row = 0, done_end = 0, row0 = row_begin, left = span.left;   // done_end = 0: nothing finished yet
+  for (bool more = row0 < row_end; more;) {
     // ---- publish the state (bf16) and this chunk's tiles
     if (ST::active(rg, cp)) {
 #pragma unroll
@@ -290,13 +307,22 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       kst.commit_scaled(Ks, rk);
       vst.commit_plain(Vs);
     }
-    if (row0 + C < row_end) {
-      qst.fetch(Qu, row0 + C, row_end, stream_q != 0);
-      kst.fetch(Ku, row0 + C, row_end, stream_kv != 0);
-      vst.fetch(Vu, row0 + C, row_end, stream_kv != 0);
+    // the next step's rows: of this unit, or the first ones of the next
+    const bool cross = EVEN && left > 0 && row0 + C >= row_end;
+    const int next_row = cross ? 0 : row0 + C, next_end = cross ? min(N, left) : row_end;
+    more = next_row < next_end;
+    if (cross) {
+      Qu += size_t(N) * DK;
+      Ku += size_t(N) * DK;
+      Vu += size_t(N) * LDV;
     }
-    if (row0 > row_begin)
-      store_row_pieces<DV, NOT, LDV>(finished, Ou, row0 - C + 16 * rg, row_end, l, col0);
+    if (more) {
+      qst.fetch(Qu, next_row, next_end, stream_q != 0);
+      kst.fetch(Ku, next_row, next_end, stream_kv != 0);
+      vst.fetch(Vu, next_row, next_end, stream_kv != 0);
+    }
+    if (done_end > 0)
+      store_row_pieces<DV, NOT, LDV>(finished, done_O, done_row + 16 * rg, done_end, l, col0);
     __syncthreads();
 
     if constexpr (SHARE_MASKED) {
@@ -396,23 +422,32 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     wave_lds_sync();
     gather_rows_transposed<DV, NOT>(oacc, row_factor, stage, l, finished, col0);
     __syncthreads();  // all reads of Ks, Vs, Sl done before the next chunk overwrites them
-  }
-  if (row_begin < row_end) {
-    const int last = row_begin + (row_end - row_begin - 1) / C * C;
-    store_row_pieces<DV, NOT, LDV>(finished, Ou, last + 16 * rg, row_end, l, col0);
-  }
-
-  if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, seg_end);  // rows that do not exist
-
-  if (state_out != nullptr && g == G - 1 && ST::active(rg, cp)) {
-    float* out = state_out + size_t(unit) * DK * LDV + part * DV;
+    done_O = Ou;
+    done_row = row0;
+    done_end = row_end;
+    if (cross) {   // the unit ends here
+      if (state_out != nullptr && ST::active(rg, cp)) store_final();
+      ++unit;
+      left -= unit_rows;
+      Ou += size_t(N) * LDV;
+      scale = unit_scale(s, unit, H, s_per_unit);
 #pragma unroll
-    for (int x = 0; x < ST::NCT; ++x)
+      for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
-      for (int y = 0; y < ST::NRT; ++y)
-        *reinterpret_cast<f32x4*>(out + (16 * ST::col_tile(rg, cp, x) + r) * LDV +
-                                  16 * ST::row_tile(rg, cp, y) + 4 * q4) = sacc[x][y];
+        for (int y = 0; y < ST::NRT; ++y) sacc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (state_in != nullptr && ST::active(rg, cp)) {
+        load_start();
+        add_start();
+      }
+    }
+    row0 = next_row;
+    row_end = next_end;
   }
+  if (done_end > 0) store_row_pieces<DV, NOT, LDV>(finished, done_O, done_row + 16 * rg, done_end, l, col0);
+
+  if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, span.end);  // rows that do not exist
+
+  if (state_out != nullptr && (EVEN ? row_end : span.end) == N && ST::active(rg, cp)) store_final();
 }
 
 template <int DK, int DV, int C>
@@ -425,8 +460,9 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   const float inv_eps = 1.0f / a.eps;
   hipError_t err = hipSuccess;
   // few segments: no carry launch, each scan workgroup adds up the totals before its segment
-  const bool sum_in_scan = causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
-  if (a.G > 1) {
+  const bool even = a.unit_rows > 0;
+  const bool sum_in_scan = even || causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
+  if (a.G > 1 || even) {
     err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, ws);
     if (err != hipSuccess) return err;
     if (!sum_in_scan) {
@@ -442,29 +478,31 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // Nobody reads K and V before them where there is one segment: non-temporally too once they outgrow
   // that cache by themselves (256 sequences of 2048 rows, 16 heads of 128: 1660 -> 1610 us; 64 of 1000
   // rows d64, whose K, V are found cached in part: 85 -> 105).
-  const bool stream_kv = a.G == 1 && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
+  const bool stream_kv = a.G == 1 && !even && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
   const auto scan = [&](auto kernel, int threads, int parts = 1) {
-    return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(units * a.G * parts), dim3(threads), 0, a.stream, Q, K,
-                         V, a.s, static_cast<elem_t*>(a.O), a.state, a.G > 1 ? ws : nullptr, a.state_in, a.H, a.N,
+    return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(a.workgroups * parts), dim3(threads), 0, a.stream, Q, K,
+                         V, a.s, static_cast<elem_t*>(a.O), a.state, a.G > 1 || even ? ws : nullptr, a.state_in, a.H, a.N,
                          a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0,
-                         stream_kv ? 1 : 0);
+                         stream_kv ? 1 : 0, units, a.unit_rows);
   };
   constexpr int threads = 4 * C * FwdSplit<DK, DV, C>::CS;
   if constexpr (DV == 128 && !F32_WHOLE) {
-    const int parts = a.G == 1 ? value_parts(units, a.N, DK) : 1;
+    const int parts = a.G == 1 && !even ? value_parts(units, a.N, DK) : 1;
     if constexpr (ELEM_IS_F32) {
-      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 32, 2, DV>, 256, 2);
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 32, 2, false, DV>, 256, 2);
     } else {
       if constexpr (DK == 128) {
-        if (parts == 4 && a.N <= 32) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 32, 2, DV>, 256, 4);
-        if (parts == 4) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 64, 1, DV>, 256, 4);
+        if (parts == 4 && a.N <= 32) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 32, 2, false, DV>, 256, 4);
+        if (parts == 4) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 64, 1, false, DV>, 256, 4);
       }
-      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 64, 1, DV>, 256, 2);
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 64, 1, false, DV>, 256, 2);
     }
   }
   if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
-    if (two_to_a_cu_forward(long(units) * a.G)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2>, 256);
-  return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS>, threads);
+    if (!even && two_to_a_cu_forward(a.workgroups)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2, false>, 256);
+  if constexpr (even_shares_built(DK, DV, ELEM_IS_F32))
+    if (even) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, true>, threads);
+  return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, false>, threads);
 }
 
 }  // namespace
@@ -479,15 +517,16 @@ static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
   // 64-row chunk, and several workgroups still fit a compute unit (two 256-row tiles of the
   // operand-tile pitch would leave room for one: measured 0.6 us slower on the GPT shape;
   // fp32 rows in parts fit twice only with 64 rows, but 32 x 32 and 32 x 64).
-  const dim3 grid(t.units * t.G);
+  const dim3 grid(t.unit_rows > 0 ? t.workgroups : t.units * t.G);
   constexpr bool TALL = LDS_ELEM * 128 * (lds_pitch(DK) + lds_pitch(DV)) <= 80 * 1024;
   if constexpr (TALL)
     if (t.seg_rows >= 128)
       return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 128, TILED>, grid, dim3(512),
                          0, t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps,
-                         t.seq_len, t.H);
+                         t.seq_len, t.H, t.units, t.unit_rows);
   return launch_kernel(COTTN_SYM_STR(fwd_segment_state), COTTN_SYM(fwd_segment_state)<DK, DV, 64, TILED>, grid, dim3(256), 0,
-                       t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps, t.seq_len, t.H);
+                       t.stream, X, Y, t.dst, t.N, t.G, t.n_compute, t.seg_rows, inv_eps, t.seq_len, t.H,
+                       t.units, t.unit_rows);
 }
 
 #ifdef COTTN_F32_WHOLE
@@ -519,7 +558,7 @@ hipError_t COTTN_SYM(launch_fwd_segment_totals)(const CausalArgs& a, float* dst)
   t.X = a.K; t.Y = a.V; t.dst = dst;
   t.units = a.B * a.H; t.N = a.N; t.dk = a.dk; t.dv = a.dv; t.G = a.G; t.n_compute = a.G - 1;
   t.seg_rows = a.seg_rows; t.eps = a.eps; t.stream = a.stream;
-  t.seq_len = a.seq_len; t.H = a.H;
+  t.seq_len = a.seq_len; t.H = a.H; t.unit_rows = a.unit_rows; t.workgroups = a.workgroups;
   t.tiled = true;  // read by the scan kernels only
   return COTTN_SYM(launch_segment_totals)(t);
 }

@@ -31,6 +31,10 @@ struct CausalArgs {
   // dk, dv: head dimensions of queries / keys and of values / outputs (Sec. 2.1: d_H_key,
   // d_H_value); Q, K, dQ, dK are [B][H][N][dk], V, O, dO, dV [B][H][N][dv], states [dk][dv]
   int B, H, N, dk, dv, C, G, seg_rows;
+  // even shares (causal; workspace.h): rows of a unit in the units laid end to end, else 0 and G segments
+  // of seg_rows rows per unit; workgroups of a scan either way, and state slots of a workspace array
+  int unit_rows, workgroups;
+  long slots;
   bool by_unit;                   // bidirectional only: a (batch, head) per workgroup, G = 1
   float eps;
   hipStream_t stream;
@@ -84,6 +88,10 @@ constexpr int value_parts(long units, int N, int dk) {
 constexpr bool two_to_a_cu_forward(long workgroups) { return workgroups > 256 && (workgroups <= 640 || workgroups > 768); }
 constexpr bool two_to_a_cu_dq(long workgroups) { return workgroups > 256 && (workgroups <= 512 || workgroups > 768); }
 constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
+// Shapes built for even shares (api.hip: causal_even_share, which asks for no others).
+constexpr bool even_shares_built(int dk, int dv, bool f32) {
+  return (dk == 128 && dv == 128) || (f32 && dk >= 64 && dv >= 64);
+}
 // Bidirectional: only the sums are needed, which a backward that is handed the forward's totals takes
 // over where they were left as they are; the line lies where the combine launch is the better one for
 // the forward alone (64 x 64 24 segments +1.3 us at 2 units, 64 x 128 12 +0.8, 128 x 128 8 +1.2).
@@ -173,6 +181,7 @@ struct SegmentTotalsArgs {
   // dst row-major [dk][dv] per slot (false), or in the tile order the causal scan kernels read
   // their stored states in (device_common.h: tiled_state_offset, tile (key tile, value tile))
   bool tiled;
+  int unit_rows, workgroups;  // even shares, as in CausalArgs (0: segments)
   hipStream_t stream;
 };
 hipError_t launch_segment_totals_bf16(const SegmentTotalsArgs& t);

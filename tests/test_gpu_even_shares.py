@@ -1,0 +1,102 @@
+"""Causal calls whose workgroups walk even shares of the units laid end to end: shares that begin, end and
+cross inside units, more shares than units and fewer, lengths that are no whole number of steps; forward,
+backward with and without the forward's states, pieces handed on by their states, and a repeat of the same
+bits, against the oracle's linear forms.  A shape that stops taking even shares fails here."""
+import numpy as np
+import pytest
+
+from helpers import TOL, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+SHAPES = [("bf16", 8, 11, 700, 128, 128), ("f16", 8, 12, 820, 128, 128), ("bf16", 44, 12, 333, 128, 128),
+          ("f32", 43, 3, 300, 64, 64), ("f32", 257, 1, 130, 64, 128), ("f32", 8, 11, 333, 128, 64),
+          ("f32", 20, 13, 130, 128, 128)]
+
+
+@pytest.fixture(scope="module")
+def cottn():
+    import paper_2409_18747_amd.binding as b
+    b.cottn_tune_segments(0)
+    yield b
+    b.cottn_tune_segments(0)
+
+
+def code(cottn, dtype):
+    return {"f32": cottn.COTTN_F32, "bf16": cottn.COTTN_BF16, "f16": cottn.COTTN_F16}[dtype]
+
+
+def draw(B, H, N, dk, dv, dtype, seed):
+    from paper_2409_18747_amd import workloads
+    x = workloads.draw(B, H, N, max(dk, dv), dtype, seed)
+    return {"Q": x["Q"][..., :dk].copy(), "K": x["K"][..., :dk].copy(), "V": x["V"][..., :dv].copy(),
+            "dO": x["dO"][..., :dv].copy(), "s": x["s"]}
+
+
+@pytest.mark.parametrize("dtype,B,H,N,dk,dv", SHAPES)
+def test_against_oracle(cottn, oracle, dtype, B, H, N, dk, dv):
+    import torch
+    c = code(cottn, dtype)
+    g = cottn.cottn_segments_dkdv(cottn.OP_BWD_CAUSAL, B, H, N, dk, dv, 0, c)
+    own = cottn.cottn_workspace_bytes_dkdv(cottn.OP_BWD_CAUSAL, B, H, N, dk, dv, 0, c)
+    cottn.cottn_tune_segments(g)
+    assert cottn.cottn_workspace_bytes_dkdv(cottn.OP_BWD_CAUSAL, B, H, N, dk, dv, 0, c) != own   # even shares have pieces to count
+    cottn.cottn_tune_segments(0)
+    x = draw(B, H, N, dk, dv, dtype, 950 + N)
+    Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
+    s = to_device(x["s"], "f32")
+    ws = torch.full((cottn.cottn_workspace_bytes_dkdv(cottn.OP_FWD_CAUSAL, B, H, N, dk, dv, 0, c),), 255, dtype=torch.uint8, device="cuda")
+    bws = torch.full((own,), 255, dtype=torch.uint8, device="cuda")   # (NaN wherever nothing is written)
+    state = torch.full((B, H, dk, dv), float("nan"), dtype=torch.float32, device="cuda")
+    O = cottn.cottn_fwd_causal_dkdv(Q, K, V, s, state=state, workspace=ws)
+    grads = cottn.cottn_bwd_causal_dkdv(Q, K, V, s, dO, workspace=bws, fwd_workspace=ws)
+    rebuilt = cottn.cottn_bwd_causal_dkdv(Q, K, V, s, dO)
+    again = cottn.cottn_bwd_causal_dkdv(Q, K, V, s, dO)
+    ref, S = oracle.fwd_recurrent(x["Q"], x["K"], x["V"], x["s"])
+    g_ref = oracle.bwd_recurrent(x["Q"], x["K"], x["V"], x["s"], x["dO"])
+    errs = {"O": rel_err(to_host(O), ref), "state": rel_err(to_host(state), S)}
+    errs.update({n: rel_err(to_host(a), r) for n, a, r in zip(("dQ", "dK", "dV"), grads, g_ref)})
+    errs["ds"] = rel_err(to_host(grads[3]), g_ref[3]) if dk != dv else rel_err_ds(to_host(grads[3]), g_ref[3], ds_terms_rss(oracle, x))
+    print(dtype, B, H, N, dk, dv, {k: "%.2e" % v for k, v in errs.items()}, flush=True)
+    assert max(errs.values()) <= TOL[dtype], errs
+    for a, b, d in zip(grads, rebuilt, again):
+        assert torch.equal(b, d)
+        assert rel_err(to_host(b), to_host(a)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,B,H,N", [("bf16", 8, 11, 700), ("f16", 44, 12, 333)])
+def test_pieces(cottn, dtype, B, H, N):
+    """Two pieces of N rows, each walked in even shares, the states handed on both ways, equal one call."""
+    import torch
+    x = draw(B, H, 2 * N, 128, 128, dtype, 970)
+    Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
+    s = to_device(x["s"], "f32")
+    O, g = cottn.cottn_fwd_causal(Q, K, V, s), cottn.cottn_bwd_causal(Q, K, V, s, dO)
+    parts = [tuple(t[:, :, a:a + N].contiguous() for t in (Q, K, V, dO)) for a in (0, N)]
+    zero, mid, end, rev = (torch.zeros(B, H, 128, 128, device="cuda") for _ in range(4))
+    O0 = cottn.cottn_fwd_causal_from_state(*parts[0][:3], s, zero, state=mid)
+    O1 = cottn.cottn_fwd_causal_from_state(*parts[1][:3], s, mid, state=end)
+    g1 = cottn.cottn_bwd_causal_from_state(*parts[1][:3], s, parts[1][3], state_in=mid, rev_state_out=rev)
+    g0 = cottn.cottn_bwd_causal_from_state(*parts[0][:3], s, parts[0][3], state_in=zero, rev_state_in=rev)
+    errs = {"O": rel_err(to_host(torch.cat((O0, O1), 2)), to_host(O)), "ds": rel_err(to_host(g0[3] + g1[3]), to_host(g[3]))}
+    errs.update({n: rel_err(to_host(torch.cat((a, b), 2)), to_host(c)) for n, a, b, c in zip(("dQ", "dK", "dV"), g0, g1, g)})
+    print(dtype, errs, flush=True)
+    assert max(errs.values()) <= TOL[dtype], errs
+
+
+def test_padded_batch_of_such_a_shape(cottn, oracle):
+    """Calls with lengths keep to segments, in the workspace the query answers for both."""
+    import torch
+    B, H, N, dtype = 8, 11, 700, "bf16"
+    x = draw(B, H, N, 128, 128, dtype, 990)
+    lens = [700, 0, 1, 64, 350, 351, 640, 699]
+    sc = np.linspace(0.5, 1.5, B * H, dtype=np.float32).reshape(B, H)
+    Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
+    s, n = to_device(sc, "f32"), torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, H, N, 128, 0, cottn.COTTN_BF16), dtype=torch.uint8, device="cuda")
+    O = to_host(cottn.cottn_fwd_causal_varlen(Q, K, V, s, n, workspace=ws))
+    g = [to_host(t) for t in cottn.cottn_bwd_causal_varlen(Q, K, V, s, n, dO, fwd_workspace=ws)]
+    ref = [oracle.fwd_varlen(x["Q"], x["K"], x["V"], sc, lens)[0], *oracle.bwd_varlen(x["Q"], x["K"], x["V"], sc, x["dO"], lens)[:3]]
+    for name, a, r in zip(("O", "dQ", "dK", "dV"), [O] + g[:3], ref):
+        e = rel_err(a, r)
+        print(name, "%.2e" % e, flush=True)
+        assert e <= TOL[dtype], (name, e)
