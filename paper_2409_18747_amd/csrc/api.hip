@@ -225,6 +225,7 @@ bool make_plan(int op, int B, int H, int N, int dk, int dv, int chunk, int dtype
   plan->G = plan->by_unit ? 1 : int(G);
   plan->seg_rows = int((plan->by_unit ? n_chunks : chunks_per_seg) * C);
   plan->even_rows = 0;
+  plan->own_prefix = !bidir && C <= 64 && own_prefix(units, int(G), plan->seg_rows, dk, dv, dtype == COTTN_F32);
   plan->slots = G > 1 ? units * G : 0;
   plan->pieces = units * G;
   if (!bidir && g_tuned_segments <= 0 && most_segments <= 0 && C <= 64 && n_chunks > 0) {
@@ -248,6 +249,7 @@ void set_walk(CausalArgs* a, const SeqPlan& plan) {
   a->C = plan.C;
   a->G = plan.G;
   a->slots = plan.slots;
+  a->own_prefix = !even && plan.own_prefix;
   a->unit_rows = even ? (a->N + plan.C - 1) / plan.C * plan.C : 0;
   a->seg_rows = even ? plan.even_rows : plan.seg_rows;
   a->workgroups = int(even ? (units * a->unit_rows + a->seg_rows - 1) / a->seg_rows : units * plan.G);
@@ -523,7 +525,7 @@ int bwd_causal_any(const void* Q, const void* K, const void* V, const float* s, 
     SeqPlan fwd_plan;
     if (make_plan(COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dtype, &fwd_plan) &&
         fwd_plan.C == plan.C && fwd_plan.G == plan.G && fwd_plan.seg_rows == plan.seg_rows &&
-        fwd_plan.even_rows == plan.even_rows) {
+        fwd_plan.even_rows == plan.even_rows && fwd_plan.own_prefix == plan.own_prefix) {
       st = check_workspace(fwd_workspace, fwd_workspace_bytes,
                            workspace_bytes_for(COTTN_OP_FWD_CAUSAL, B, H, dk, dv, fwd_plan));
       if (st != COTTN_OK) return st;

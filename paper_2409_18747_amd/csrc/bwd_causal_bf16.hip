@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_t
 // for the intra-chunk product.
 //
 // REV: whether the launch has segments to leave reverse-time totals for.
-template <int DK, int DV, int C, int CS, bool REV, bool EVEN>
+template <int DK, int DV, int C, int CS, bool REV, int WALK>
 __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dq_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
@@ -161,6 +161,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
     const float* __restrict__ state_in, int units, int unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
+  constexpr bool EVEN = WALK == EVEN_SHARES;
   using AT = SplitTiles<DK, DV, Cfg::RG, CS>;   // forward-time state: key rows, value columns
   using RT = SplitTiles<DV, DK, Cfg::RG, CS>;   // reverse-time total: value rows, key columns
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -226,7 +227,13 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
-  if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
+  if constexpr (WALK == OWN_PREFIX) {
+    if (span.mid_unit)
+      add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV>(
+          Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
+          [&](int y) { return AT::row_tile(rg, cp, y); }, [&](int x) { return AT::col_tile(rg, cp, x); },
+          [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+  } else if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(
         sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
         [&](int slot, int x, int y) {
@@ -927,7 +934,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
     ws += 2 * state_slots_bytes(a.slots, DK, DV);
     if (a.saved_fwd_states != nullptr) {
       fwd_states = a.saved_fwd_states;
-    } else {
+    } else if (!a.own_prefix) {
       err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, own_fwd);
       if (err != hipSuccess) return err;
       if (!sum_in_scan) {
@@ -942,17 +949,19 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const auto dq_scan = [&](auto kernel, int threads) {
     return launch_kernel(COTTN_SYM_STR(bwd_dq_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
                          static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H, a.N, a.G, a.seg_rows,
-                         inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in, units,
-                         a.unit_rows);
+                         inv_eps, sum_in_scan && !a.own_prefix ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in,
+                         units, a.unit_rows);
   };
   constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32);
   constexpr bool HALVED = !ELEM_IS_F32 && DK == 128 && DV == 128 && CR == 64 && CS == 2;
   if (HALVED && a.G == 1 && !even && two_to_a_cu_dq(a.workgroups)) {
-    if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, false>, 256);
+    if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, SEGMENTS>, 256);
   } else if (even) {
-    if constexpr (EVEN_BUILT) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, true>, Cfg::NT);
+    if constexpr (EVEN_BUILT) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT);
+  } else if (a.own_prefix && fwd_states == nullptr) {
+    if constexpr (C <= 64) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
   } else {
-    err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, false>, Cfg::NT);
+    err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, SEGMENTS>, Cfg::NT);
   }
   if (err != hipSuccess) return err;
   if (!sum_in_scan) {

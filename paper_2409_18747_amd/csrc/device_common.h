@@ -589,6 +589,11 @@ __device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int s
   return s;
 }
 
+// How the causal scans walk (a template parameter, so that no walk pays for the others): segments, with
+// the states of earlier ones from the workspace; even shares; segments of short sequences, whose
+// workgroups form the state of the rows before them by themselves (launch.h: own_prefix).
+enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, OWN_PREFIX = 2 };
+
 // In place, for 4 neighbouring elements of a stack of n matrices `stride` floats apart:
 // matrix k (in walking order: first to last, or last to first with `reverse`) <- sum of the
 // matrices walked before it.  The last matrix walked never held a value and is not read.  The

@@ -176,14 +176,15 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
 //
 // LDV > DV (one segment): a workgroup takes DV of the LDV value columns, which the whole computation
 // leaves apart from one another but for the masked tiles; those are formed LDV / DV times.
-template <int DK, int DV, int C, int CS, bool EVEN, int LDV = DV>
+template <int DK, int DV, int C, int CS, int WALK, int LDV = DV>
 __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())) void COTTN_SYM(fwd_causal_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
-    const float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
+    float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
     int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
     int stream_q, int stream_kv, int units, int unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
+  constexpr bool EVEN = WALK == EVEN_SHARES;
   constexpr int RG = C / 16;           // row groups of a chunk
   constexpr int NOT = Cfg::DTV / CS;   // output column tiles per wave
   using ST = SplitTiles<DV, DK, RG, CS>;   // value rows, key columns (the state is held transposed)
@@ -268,7 +269,24 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
                                   16 * ST::row_tile(rg, cp, y) + 4 * q4) = sacc[x][y];
   };
   if (state_in != nullptr && ST::active(rg, cp)) load_start();
-  if (LDV == DV && seg_states != nullptr && span.mid_unit && ST::active(rg, cp)) {
+  if constexpr (WALK == OWN_PREFIX) {
+    if (span.mid_unit) {
+      add_rows_before<DK, DV, C, Cfg::NT * CS, ST::NCT, ST::NRT, LDV>(
+          Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, ST::active(rg, cp),
+          [&](int x) { return ST::col_tile(rg, cp, x); }, [&](int y) { return ST::row_tile(rg, cp, y); },
+          [&](int x, int y, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+      // for the backward, where a carry launch would have left it
+      if (ST::active(rg, cp)) {
+#pragma unroll
+        for (int x = 0; x < ST::NCT; ++x)
+#pragma unroll
+          for (int y = 0; y < ST::NRT; ++y)
+            store_state_words(seg_states + size_t(span.slot) * DK * DV +
+                                  tiled_state_offset(ST::col_tile(rg, cp, x), ST::row_tile(rg, cp, y), DV / 16, l),
+                              sacc[x][y]);
+      }
+    }
+  } else if (LDV == DV && seg_states != nullptr && span.mid_unit && ST::active(rg, cp)) {
     const float* src = seg_states + 4 * l;
     add_stored_states<ST::STATE_BATCH>(
         sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
@@ -462,7 +480,7 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // few segments: no carry launch, each scan workgroup adds up the totals before its segment
   const bool even = a.unit_rows > 0;
   const bool sum_in_scan = even || causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
-  if (a.G > 1 || even) {
+  if ((a.G > 1 || even) && !a.own_prefix) {
     err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, ws);
     if (err != hipSuccess) return err;
     if (!sum_in_scan) {
@@ -489,20 +507,22 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   if constexpr (DV == 128 && !F32_WHOLE) {
     const int parts = a.G == 1 && !even ? value_parts(units, a.N, DK) : 1;
     if constexpr (ELEM_IS_F32) {
-      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 32, 2, false, DV>, 256, 2);
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 32, 2, SEGMENTS, DV>, 256, 2);
     } else {
       if constexpr (DK == 128) {
-        if (parts == 4 && a.N <= 32) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 32, 2, false, DV>, 256, 4);
-        if (parts == 4) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 64, 1, false, DV>, 256, 4);
+        if (parts == 4 && a.N <= 32) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 32, 2, SEGMENTS, DV>, 256, 4);
+        if (parts == 4) return scan(COTTN_SYM(fwd_causal_scan)<DK, 32, 64, 1, SEGMENTS, DV>, 256, 4);
       }
-      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 64, 1, false, DV>, 256, 2);
+      if (parts > 1) return scan(COTTN_SYM(fwd_causal_scan)<DK, 64, 64, 1, SEGMENTS, DV>, 256, 2);
     }
   }
   if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
-    if (!even && two_to_a_cu_forward(a.workgroups)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2, false>, 256);
+    if (!even && !a.own_prefix && two_to_a_cu_forward(a.workgroups)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2, SEGMENTS>, 256);
   if constexpr (even_shares_built(DK, DV, ELEM_IS_F32))
-    if (even) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, true>, threads);
-  return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, false>, threads);
+    if (even) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_SHARES>, threads);
+  if constexpr (C <= 64)
+    if (a.own_prefix) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX>, threads);
+  return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, SEGMENTS>, threads);
 }
 
 }  // namespace

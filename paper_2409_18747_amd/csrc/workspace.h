@@ -14,6 +14,7 @@ struct SeqPlan {
   // causal: rows of an even share of the units laid end to end (a whole number of chunks; device_common.h:
   // Span), or 0.  Calls without lengths walk even shares where the plan has them, others the G segments.
   int even_rows;
+  bool own_prefix;   // causal: launch.h
   long slots;     // causal: state slots of a workspace array, enough for either
   long pieces;    // causal: partial sums of ds, likewise
 };
