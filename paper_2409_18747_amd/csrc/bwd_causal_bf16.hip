@@ -925,6 +925,9 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const float inv_eps = 1.0f / a.eps;
   // few segments: no carry launches, the scan workgroups add up the totals they need
   const bool sum_in_scan = even || causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
+  // an own-prefix forward leaves carried prefixes
+  const bool carried = a.own_prefix && a.saved_fwd_states != nullptr;
+  const bool rebuild = a.own_prefix && !carried;
   hipError_t err;
   if (a.G > 1 || even) {
     // Forward-time states: taken over from the forward call when it left them behind (raw
@@ -934,7 +937,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
     ws += 2 * state_slots_bytes(a.slots, DK, DV);
     if (a.saved_fwd_states != nullptr) {
       fwd_states = a.saved_fwd_states;
-    } else if (!a.own_prefix) {
+    } else if (!rebuild) {
       err = COTTN_ELEM_SYM(launch_fwd_segment_totals)(a, own_fwd);
       if (err != hipSuccess) return err;
       if (!sum_in_scan) {
@@ -949,7 +952,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const auto dq_scan = [&](auto kernel, int threads) {
     return launch_kernel(COTTN_SYM_STR(bwd_dq_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
                          static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H, a.N, a.G, a.seg_rows,
-                         inv_eps, sum_in_scan && !a.own_prefix ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in,
+                         inv_eps, sum_in_scan && !carried ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in,
                          units, a.unit_rows);
   };
   constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32);
@@ -958,7 +961,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
     if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, SEGMENTS>, 256);
   } else if (even) {
     if constexpr (EVEN_BUILT) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT);
-  } else if (a.own_prefix && fwd_states == nullptr) {
+  } else if (rebuild) {
     if constexpr (C <= 64) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
   } else {
     err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, SEGMENTS>, Cfg::NT);

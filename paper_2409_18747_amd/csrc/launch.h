@@ -89,34 +89,39 @@ constexpr int value_parts(long units, int N, int dk) {
 constexpr bool two_to_a_cu_forward(long workgroups) { return workgroups > 256 && (workgroups <= 640 || workgroups > 768); }
 constexpr bool two_to_a_cu_dq(long workgroups) { return workgroups > 256 && (workgroups <= 512 || workgroups > 768); }
 constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
-// Whether the workgroups of a causal call in segments form the state of the rows before them by themselves
-// instead of adding up what a totals launch left: in the forward, which leaves it in the workspace as a carry
-// launch would, and in the dQ scan of a backward that was not handed that workspace.  A launch takes 4 us and more
-// of a small call, its kernel and the totals' way through the workspace about as long again; a step of
-// the reduction 0.3 to 1.2 us, one after the other over the rows before the last segment.  The line is the
-// number of those rows up to which the forward alone is the faster one too.  Forward / with backward / with
-// backward that rebuilds the state, totals launch -> own prefix: 64 x 64 2 units of 256 rows 10.4 / 22.9 / 35.4 ->
-// 7.9 / 20.4 / 30.0 us, of 640 10.4 / 22.6 / 35.0 -> 8.7 / 20.6 / 30.5, 100 of 320 10.4 / 25.7 / 34.9 -> 8.5 / 24.5 /
-// 30.1, of 512 11.5 / 32.2 / 36.2 -> 11.4 / 31.6 / 35.4, of 1024 17.3 / 50.3 / 55.6 -> 19.2 / 50.9 / 58.3; 32 x 32 10
-// units of 1024 10.5 / 22.8 / 35.2 -> 9.6 / 20.3 / 30.4; 128 x 32 100 of 400 13.2 / 37.7 / 42.7 -> 11.7 / 36.0 / 39.8, of
-// 512 13.6 / 39.0 / 43.6 -> 14.2 / 39.6 / 46.8; 128 x 128 40 of 256 12.9 / 32.4 / 39.1 -> 9.9 / 28.8 / 31.9,
-// 100 of 640 in two segments 27.6 / 79.1 / 88.3 -> 22.4 / 73.4 / 77.6; fp32 32 x 32 2 of 256 10.0 / 22.3 / 35.3 ->
-// 7.9 / 20.0 / 30.3, of 512 10.8 / 23.4 / 36.4 -> 12.1 / 22.5 / 31.3; 64 x 64 100 of 130 14.2 / 34.6 / 41.7 -> 12.2 /
-// 32.3 / 36.4, 40 of 256 12.4 / 34.0 / 38.7 -> 13.6 / 35.6 / 41.6; 64 x 128 100 of 200 in two segments 26.3 / 74.9 /
-// 82.9 -> 21.3 / 68.9 / 74.0; 128 x 128 100 of 130 38.6 / 106 / 121 -> 29.1 / 94 /
-// 102.
+// Whether the workgroups of a causal call in segments form the state of the rows before them by themselves instead
+// of adding up what a totals launch left: in the forward, which leaves it in the workspace as a carry launch would,
+// and in the dQ scan of a backward that was not handed that workspace.  A launch takes 4 us and more of a small
+// call, its kernel and the totals' way through the workspace about as long again; a step of the reduction 0.3 to
+// 1.2 us, one after the other over the rows before the last segment.  The line is the number of those rows up to
+// which the forward alone is the faster one too.  Forward / with backward / with backward that rebuilds the state,
+// totals launch -> own prefix: 64 x 64 2 units of 256 rows 10.4 / 22.9 / 35.4 -> 7.9 / 20.4 / 30.0 us, of 640 10.4
+// / 22.6 / 35.0 -> 8.7 / 20.6 / 30.5, 100 of 320 10.4 / 25.7 / 34.9 -> 8.5 / 24.5 / 30.1, 15 of 777 10.9 / 25.5 /
+// 35.8 -> 11.4 / 25.1 / 32.3, 100 of 512 11.5 / 32.2 / 36.2 -> 11.4 / 31.6 / 35.4, of 1024 17.3 / 50.3 / 55.6 ->
+// 19.2 / 50.9 / 58.3; 32 x 32 10 units of 1024 10.5 / 22.8 / 35.2 -> 9.6 / 20.3 / 30.4; 64 x 32 15 of 777 12.9 /
+// 27.2 / 40.0 -> 10.0 / 23.9 / 34.7; 64 x 128 4 of 777 14.1 / 31.0 / 44.4 -> 13.5 / 31.1 / 39.1, 15 of 777 15.7 /
+// 37.2 / 41.8 -> 14.1 / 34.7 / 43.0; 128 x 64 15.5 / 37.7 / 42.7 -> 15.0 / 36.3 / 46.0; 128 x 32 100 of 400 13.2 /
+// 37.7 / 42.7 -> 11.7 / 36.0 / 39.8, of 512 13.6 / 39.0 / 43.6 -> 14.2 / 39.6 / 46.8; 128 x 128 40 of 256 12.9 /
+// 32.4 / 39.1 -> 9.9 / 28.8 / 31.9, 100 of 640 in two segments 27.6 / 79.1 / 88.3 -> 22.4 / 73.4 / 77.6; fp32 32 x
+// 32 2 of 256 10.0 / 22.3 / 35.3 -> 7.9 / 20.0 / 30.3, of 512 10.8 / 23.4 / 36.4 -> 12.1 / 22.5 / 31.3; 64 x 64 100
+// of 130 14.2 / 34.6 / 41.7 -> 12.2 / 32.3 / 36.4, 40 of 256 12.4 / 34.0 / 38.7 -> 13.6 / 35.6 / 41.6; 64 x 128 100
+// of 200 in two segments 26.3 / 74.9 / 82.9 -> 21.3 / 68.9 / 74.0; 128 x 128 100 of 130 38.6 / 106 / 121 -> 29.1 /
+// 94 / 102.
 constexpr bool own_prefix(long units, int G, long seg_rows, int dk, int dv, bool f32) {
   if (G < 2) return false;
   const long workgroups = units * G, rows = (G - 1) * seg_rows;
-  const bool narrowest = dk == 32 && dv == 32, widest = dk == 128 && dv == 128;
+  const bool narrow = dk * dv <= 2048, widest = dk == 128 && dv == 128;
   if (f32 && G == 2) return rows <= 224;
   if (f32 && widest) return false;
-  if (f32 && narrowest) return rows <= (workgroups <= 128 ? 288 : workgroups <= 384 ? 224 : 128);
+  if (f32 && dk * dv == 1024) return rows <= (workgroups <= 128 ? 288 : workgroups <= 384 ? 224 : 128);
   if (f32) return rows <= (workgroups <= 80 ? 192 : 128);
   if (widest && G == 2 && workgroups <= 256) return rows <= 1024;
-  if (narrowest && workgroups <= 256) return rows <= 960;
-  return rows <= (workgroups <= 128 ? 576 : workgroups <= 256 || narrowest ? 448 : 320);
+  if (narrow && workgroups <= 256) return rows <= 960;
+  // segments of one step: as many totals to add as steps to take
+  if (seg_rows == 64 && workgroups <= 256) return rows <= (dk <= 64 && dv == 128 && workgroups <= 128 ? 768 : 576);
+  return rows <= (workgroups <= 256 || narrow ? 448 : 320);
 }
+
 // Shapes built for even shares (api.hip: causal_even_share, which asks for no others).
 constexpr bool even_shares_built(int dk, int dv, bool f32) {
   return (dk == 128 && dv == 128) || (f32 && dk >= 64 && dv >= 64);
