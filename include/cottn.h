@@ -84,9 +84,9 @@ typedef enum {
 
 /* Bytes of workspace the given operation needs for these arguments (0 for COTTN_OP_STEP).
  * Returns (size_t)-1 if the arguments are not supported.  Host only; touches no GPU.
- * A causal call keeps one fp32 state per segment (the backward two) where the library cuts a sequence
- * into more than one, which it does only up to 640 segments in all (1024 for fp32 and for 32 x 32): 64
- * MB of states at most. */
+ * A causal call keeps one fp32 state per workgroup (the backward two) where the library cuts sequences
+ * into segments, or all of them laid end to end into even shares; it takes up to 640 workgroups then (1024
+ * for fp32 and for 32 x 32): 64 MB of states at most. */
 size_t cottn_workspace_bytes(int op, int B, int H, int N, int d, int chunk, int dtype);
 
 /* Number of sequence segments per (batch, head) the library will scan in parallel for
@@ -152,7 +152,9 @@ int cottn_fwd_causal_from_state(const void* Q, const void* K, const void* V, con
  *   Kh^T V, which the backward needs again: given them it does not rebuild them from K and V.
  *   They are taken over only when forward and backward split the sequence the same way
  *   (cottn_segments agrees for both ops); otherwise the argument is ignored.
- *   Contents that do not come from such a call give wrong gradients, not an error. */
+ *   Contents that do not come from such a call give wrong gradients, not an error: a padded
+ *   batch's backward takes a *_varlen forward's workspace and no other, and the reverse (calls with
+ *   lengths cut sequences into segments, calls without may take even shares). */
 int cottn_bwd_causal(const void* Q, const void* K, const void* V, const float* s, const void* dO,
                      void* dQ, void* dK, void* dV, float* ds, const void* fwd_workspace,
                      size_t fwd_workspace_bytes, void* workspace, size_t workspace_bytes, int B,
