@@ -927,7 +927,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const bool sum_in_scan = even || causal_totals_in_place(units, a.G, DK, DV, ELEM_IS_F32);
   // an own-prefix forward leaves carried prefixes
   const bool carried = a.own_prefix && a.saved_fwd_states != nullptr;
-  const bool rebuild = a.own_prefix && !carried;
+  const bool rebuild = a.own_prefix && !carried && own_prefix_dq(units, a.G, a.seg_rows, DK, DV, ELEM_IS_F32);
   hipError_t err;
   if (a.G > 1 || even) {
     // Forward-time states: taken over from the forward call when it left them behind (raw

@@ -91,7 +91,7 @@ constexpr bool two_to_a_cu_dq(long workgroups) { return workgroups > 256 && (wor
 constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
 // Whether the workgroups of a causal call in segments form the state of the rows before them by themselves instead
 // of adding up what a totals launch left: in the forward, which leaves it in the workspace as a carry launch would,
-// and in the dQ scan of a backward that was not handed that workspace.  A launch takes 4 us and more of a small
+// and in the dQ scan of a backward that was not handed that workspace (own_prefix_dq).  A launch takes 4 us and more of a small
 // call, its kernel and the totals' way through the workspace about as long again; a step of the reduction 0.3 to
 // 1.2 us, one after the other over the rows before the last segment.  The line is the number of those rows up to
 // which the forward alone is the faster one too.  Forward / with backward / with backward that rebuilds the state,
@@ -107,7 +107,7 @@ constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
 // of 130 14.2 / 34.6 / 41.7 -> 12.2 / 32.3 / 36.4, 40 of 256 12.4 / 34.0 / 38.7 -> 13.6 / 35.6 / 41.6; 64 x 128 100
 // of 200 in two segments 26.3 / 74.9 / 82.9 -> 21.3 / 68.9 / 74.0; 128 x 128 100 of 130 38.6 / 106 / 121 -> 29.1 /
 // 94 / 102.
-constexpr bool own_prefix(long units, int G, long seg_rows, int dk, int dv, bool f32) {
+constexpr bool own_prefix_dq(long units, int G, long seg_rows, int dk, int dv, bool f32) {
   if (G < 2) return false;
   const long workgroups = units * G, rows = (G - 1) * seg_rows;
   const bool narrow = dk * dv <= 2048, widest = dk == 128 && dv == 128;
@@ -120,6 +120,21 @@ constexpr bool own_prefix(long units, int G, long seg_rows, int dk, int dv, bool
   // segments of one step: as many totals to add as steps to take
   if (seg_rows == 64 && workgroups <= 256) return rows <= (dk <= 64 && dv == 128 && workgroups <= 128 ? 768 : 576);
   return rows <= (workgroups <= 256 || narrow ? 448 : 320);
+}
+// The forward does so a little further than the dQ scan: with up to four segments, of several steps each, the totals
+// launch lasts nearly as long as reducing the rows before the last segment in its own workgroup.  A backward that
+// rebuilds the state takes the totals launch there.  Forward / with backward / with backward that rebuilds the state, totals launch -> own
+// prefix, device time: 100 units of 400 rows 64 x 64 11.7 / 30.9 / 35.2 -> 10.5 / 29.4 / 34.1 us, 64 x 128 15.9 /
+// 45.4 / 51.5 -> 14.5 / 43.9 / 49.7, 32 x 128 13.0 / 37.8 / 42.3 -> 11.6 / 36.2 / 40.8; 150 of 400 128 x 64 22.3 / 61.5 /
+// 70.0 -> 17.2 / 56.6 / 64.6; 120 of 640 64 x 64 15.5 / 41.9 / 47.5 -> 13.8 / 39.1 / 45.2; 128 x 128 80 of 640 24.0 /
+// 70.1 / 77.3 -> 19.6 / 64.5 / 72.4, of 777 29.6 / 82.8 / 94.7 -> 23.7 / 76.8 / 87.7.  Not beyond: 64 x 64 100 of 1024
+// 18.4 / 50.1 -> 19.9 / 50.7, five segments 70 of 640 64 x 128 17.5 / 48.4 -> 19.1 / 48.9, and not at 128 x 32, 100 of
+// 450 13.2 / 38.5 -> 14.1 / 38.9.
+constexpr bool own_prefix(long units, int G, long seg_rows, int dk, int dv, bool f32) {
+  if (own_prefix_dq(units, G, seg_rows, dk, dv, f32)) return true;
+  if (f32 || G < 2 || G > 4 || dk * dv <= 2048 || (dk == 128 && dv == 32)) return false;
+  const bool widest = dk == 128 && dv == 128;
+  return units * G <= (widest ? 256 : 512) && (G - 1) * seg_rows <= (widest ? 768 : 576);
 }
 
 // Shapes built for even shares (api.hip: causal_even_share, which asks for no others).

@@ -8,14 +8,17 @@ import pytest
 from helpers import TOL, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
 
 pytestmark = pytest.mark.gpu
-# rows before the last segment: at the line and beyond it, or the shortest that take segments
+# rows before the last segment: at the line and beyond it, or the shortest that take segments; last, those
+# where only the forward does so, and the first ones beyond
 SHAPES = [("bf16", 1, 1, 130, 64, 64), ("f16", 2, 5, 640, 64, 64), ("bf16", 2, 5, 705, 64, 64), ("f16", 8, 5, 511, 64, 64),
           ("bf16", 2, 5, 1023, 32, 32), ("f16", 10, 10, 513, 32, 32), ("bf16", 2, 1, 577, 128, 128),
           ("bf16", 10, 10, 641, 128, 128), ("f16", 10, 10, 333, 128, 128), ("bf16", 10, 10, 321, 128, 32),
           ("f16", 5, 8, 400, 32, 128), ("bf16", 3, 3, 257, 128, 64), ("f16", 2, 2, 777, 64, 128), ("bf16", 2, 5, 1023, 64, 32),
           ("f32", 1, 1, 65, 32, 32), ("f32", 1, 2, 319, 32, 32),
           ("f32", 1, 2, 321, 32, 32), ("f32", 10, 10, 129, 32, 32), ("f32", 1, 1, 33, 64, 64), ("f32", 10, 10, 130, 64, 64),
-          ("f32", 1, 2, 199, 64, 64), ("f32", 10, 10, 101, 128, 128), ("f32", 10, 10, 255, 64, 128), ("f32", 4, 1, 66, 128, 32)]
+          ("f32", 1, 2, 199, 64, 64), ("f32", 10, 10, 101, 128, 128), ("f32", 10, 10, 255, 64, 128), ("f32", 4, 1, 66, 128, 32),
+          ("bf16", 10, 10, 385, 64, 64), ("f16", 10, 15, 399, 128, 64), ("bf16", 12, 10, 640, 32, 128), ("f16", 12, 10, 577, 64, 128),
+          ("bf16", 12, 10, 705, 64, 64), ("bf16", 16, 5, 777, 128, 128), ("f16", 6, 10, 769, 128, 128), ("bf16", 6, 10, 1025, 128, 128)]
 
 
 @pytest.fixture(scope="module")
