@@ -20,6 +20,8 @@ namespace cottn {
 //           in the root mean square, where an fp32 addition rounds to 2^-25.  The bf16 rate is
 //           sixteen times the fp32 one, so this takes 6/16 of the time, and the operands that are
 //           contracted over the tokens can take the transposing LDS read.
+//           Range: an element above 3.38e38 rounds to infinity, and an infinite one makes what it
+//           enters NaN (infinity less itself is its second part).
 //   else    the fp32 matrix instruction (COTTN_F32_WHOLE: the *_f32w.hip files), where the parts do
 //           not fit the LDS (128 x 128) or fit it for one causal workgroup instead of two (128 x 32
 //           and 32 x 128: B4 H8 N2048 forward + backward 121 / 140 and 108 / 123 us, whole / parts), and
