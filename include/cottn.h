@@ -152,9 +152,7 @@ int cottn_fwd_causal_from_state(const void* Q, const void* K, const void* V, con
  *   Kh^T V, which the backward needs again: given them it does not rebuild them from K and V.
  *   They are taken over only when forward and backward split the sequence the same way
  *   (cottn_segments agrees for both ops); otherwise the argument is ignored.
- *   Contents that do not come from such a call give wrong gradients, not an error: a padded
- *   batch's backward takes a *_varlen forward's workspace and no other, and the reverse (calls with
- *   lengths cut sequences into segments, calls without may take even shares). */
+ *   Contents that do not come from such a call give wrong gradients, not an error. */
 int cottn_bwd_causal(const void* Q, const void* K, const void* V, const float* s, const void* dO,
                      void* dQ, void* dK, void* dV, float* ds, const void* fwd_workspace,
                      size_t fwd_workspace_bytes, void* workspace, size_t workspace_bytes, int B,

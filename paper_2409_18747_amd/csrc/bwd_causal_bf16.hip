@@ -158,10 +158,10 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
     const float* __restrict__ fwd_states, float* __restrict__ rev_totals,
     float* __restrict__ ds_partial, int H, int N, int G, int seg_rows, float inv_eps,
-    int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
+    int sum_totals, const int* __restrict__ lengths, int s_per_unit,
     const float* __restrict__ state_in, int units, int unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
-  constexpr bool EVEN = WALK == EVEN_SHARES;
+  constexpr bool EVEN = walks_even(WALK);
   using AT = SplitTiles<DK, DV, Cfg::RG, CS>;   // forward-time state: key rows, value columns
   using RT = SplitTiles<DV, DK, Cfg::RG, CS>;   // reverse-time total: value rows, key columns
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -188,7 +188,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   Masked& masked = *reinterpret_cast<Masked*>(IN_STAGE ? reinterpret_cast<char*>(Os) : masked_lds);
 
   fetch_argument_now(Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G, seg_rows,
-                     inv_eps, sum_totals, seq_len, s_per_unit, state_in, units, unit_rows);
+                     inv_eps, sum_totals, lengths, s_per_unit, state_in, units, unit_rows);
+  const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
   const Span span = span_of_workgroup<false, EVEN>(units, N, G, seg_rows, unit_rows);
   int unit = span.unit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
@@ -202,6 +203,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = span.begin;
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
+  int piece_end = span.end;   // of the same, with the rows that do not exist
 
   // fwd_states holds the carried prefixes (slot g = state at the start of segment g) or, with
   // sum_totals set, the raw segment totals, which this workgroup then adds up itself
@@ -227,12 +229,17 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
-  if constexpr (WALK == OWN_PREFIX) {
-    if (span.mid_unit)
-      add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV>(
-          Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
-          [&](int y) { return AT::row_tile(rg, cp, y); }, [&](int x) { return AT::col_tile(rg, cp, x); },
-          [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+  const auto form_prefix = [&] {
+    add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV>(
+        Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
+        [&](int y) { return AT::row_tile(rg, cp, y); }, [&](int x) { return AT::col_tile(rg, cp, x); },
+        [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+  };
+  bool no_states = WALK == OWN_PREFIX;
+  if constexpr (WALK == EVEN_SHARES)   // (sum_totals 2: the states are a forward's that may have left none)
+    no_states = sum_totals == 2 && fwd_states[size_t(gridDim.x - 1) * DK * DV] != EVEN_MARK;
+  if ((WALK == OWN_PREFIX || WALK == EVEN_SHARES) && no_states) {
+    if (span.mid_unit) form_prefix();
   } else if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(
         sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
@@ -284,7 +291,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   for (int j = 0; j < RowPieces<DK, NKT>::PER_LANE; ++j) finished.v[j] = uint4{0u, 0u, 0u, 0u};
   elem_t* done_dQ = dQu;
   int done_row = 0, done_end = 0, row0 = row_begin, left = span.left;   // done_end = 0: nothing finished yet
-  for (bool more = row0 < row_end; more;) {
+  for (bool more = WALK == EVEN_PADDED || row0 < row_end; more;) {
     if (AT::active(rg, cp)) {
 #pragma unroll
       for (int x = 0; x < AT::NCT; ++x)
@@ -306,8 +313,9 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     }
     // the next step's rows: of this unit, or the first ones of the next
     const bool cross = EVEN && left > 0 && row0 + C >= row_end;
-    const int next_row = cross ? 0 : row0 + C, next_end = cross ? min(N, left) : row_end;
-    more = next_row < next_end;
+    const int next_row = cross ? 0 : row0 + C;
+    const int next_end = cross ? min(valid_rows(seq_len, unit + 1, H, N), left) : row_end;
+    more = (WALK == EVEN_PADDED && cross) || next_row < next_end;
     if (cross) {
       Qu += size_t(N) * DK;
       Ku += size_t(N) * DK;
@@ -478,6 +486,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       if (with_rev && RT::active(rg, cp)) store_rev_total();
       with_rev = false;
       store_ds();
+      if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, N);
+      piece_end = min(N, left);
       ++unit;
       left -= unit_rows;
       dQu += size_t(N) * DK;
@@ -493,7 +503,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   }
   if (done_end > 0) store_row_pieces<DK, NKT>(finished, done_dQ, done_row + 16 * rg, done_end, l, colk);
 
-  if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, span.end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, piece_end);  // rows that do not exist
 
   if (with_rev && RT::active(rg, cp)) store_rev_total();
   store_ds();
@@ -506,15 +516,16 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 // is R[16 ct + r][16 rt + 4 q4 + v], published with one 8-byte write to the row-major LDS
 // copy Rl[d_key][d_value]; the update's row-side operand is the dO fragment already read
 // for the intra-chunk dV product.
-template <int DK, int DV, int C, int CS, bool EVEN>
+template <int DK, int DV, int C, int CS, int WALK>
 __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dkdv_scan)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dK,
     elem_t* __restrict__ dV, const float* __restrict__ rev_states,
     const float* __restrict__ ds_partial, float* __restrict__ ds, int B, int H, int N, int G,
-    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
+    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
     const float* __restrict__ rev_in, float* __restrict__ rev_out, int unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
+  constexpr bool EVEN = walks_even(WALK);
   using AT = SplitTiles<DV, DK, Cfg::RG, CS>;   // value rows, key columns (the state is held transposed)
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
@@ -530,7 +541,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   __shared__ MaskedExchange<Cfg::SHARE_MASKED ? 4 : 0> masked;
 
   fetch_argument_now(Q, K, V, dO, s, dK, dV, rev_states, ds_partial, ds, B, H, N, G, seg_rows,
-                     inv_eps, sum_totals, seq_len, s_per_unit, rev_in, rev_out, unit_rows);
+                     inv_eps, sum_totals, lengths, s_per_unit, rev_in, rev_out, unit_rows);
+  const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
   const Span span = span_of_workgroup<true, EVEN>(B * H, N, G, seg_rows, unit_rows);
   int unit = span.unit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
@@ -545,15 +557,16 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   float scale = unit_scale(s, unit, H, s_per_unit);
   int row_begin = span.begin;   // of the piece walked, and its end
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));
+  int piece_end = span.end;   // with the rows that do not exist
 
   // the first H workgroups also finish ds: ds[h] = sum over batches and segments of the
   // partial sums the dQ kernel left behind (with a scale per (batch, head): the first B*H
   // workgroups, ds[b][h] = sum over the segments; with even shares there can be fewer workgroups)
   if constexpr (EVEN) {
     if (w == 0)
-      for (int h = blockIdx.x; h < H; h += gridDim.x) {
+      for (int h = blockIdx.x; h < (seq_len != nullptr ? B * H : H); h += gridDim.x) {
         float t = 0.f;
-        for (int b = l; b < B; b += 64) {
+        for (int b = l; b < (seq_len != nullptr ? 1 : B); b += 64) {
           const int u = b * H + h, last = ((u + 1) * unit_rows - 1) / seg_rows;
           for (int slot = u * unit_rows / seg_rows; slot <= last; ++slot) t += ds_partial[slot + u];
         }
@@ -580,7 +593,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   // the last chunk's rows and the stored states are all requested before anything waits
   StageK qst, kst;
   StageV vst, gst;
-  bool more = row_begin < row_end;   // (a segment of a padded batch can be empty)
+  bool more = WALK == EVEN_PADDED || row_begin < row_end;   // (a segment of a padded batch can be empty)
   int row0 = row_begin + (row_end - row_begin - 1) / C * C;
   if (more) {
     qst.fetch(Qu, row0, row_end);
@@ -651,8 +664,9 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     }
     // the next step's rows: of this unit, or the last ones of the unit before
     const bool cross = EVEN && left > 0 && row0 == row_begin;
-    const int next_begin = cross ? max(0, unit_rows - left) : row_begin, next_end = cross ? N : row_end;
-    const int next_row = cross ? next_begin + (N - next_begin - 1) / C * C : row0 - C;
+    const int next_begin = cross ? max(0, unit_rows - left) : row_begin;
+    const int next_end = cross ? max(next_begin, valid_rows(seq_len, unit - 1, H, N)) : row_end;
+    const int next_row = cross ? next_begin + (next_end - next_begin - 1) / C * C : row0 - C;
     more = cross || row0 > row_begin;
     if (cross) {
       Qu -= size_t(N) * DK;
@@ -883,6 +897,11 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     done_end = row_end;
     if (cross) {   // the unit begins here
       if (rev_out != nullptr && AT::active(rg, cp)) store_rev_out();
+      if (seq_len != nullptr) {
+        zero_rows<DK>(dKu, row_end, piece_end);
+        zero_rows<DV>(dVu, row_end, piece_end);
+      }
+      piece_end = N;
       --unit;
       left -= unit_rows;
       dKu -= size_t(N) * DK;
@@ -903,8 +922,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     store_row_pieces<DV, NVT>(done_v, done_dV, done_row + 16 * rg, done_end, l, colv);
   }
   if (seq_len != nullptr) {  // rows that do not exist
-    zero_rows<DK>(dKu, row_end, span.end);
-    zero_rows<DV>(dVu, row_end, span.end);
+    zero_rows<DK>(dKu, row_end, piece_end);
+    zero_rows<DV>(dVu, row_end, piece_end);
   }
   if (rev_out != nullptr && row_begin == 0 && AT::active(rg, cp)) store_rev_out();
 }
@@ -952,7 +971,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   const auto dq_scan = [&](auto kernel, int threads) {
     return launch_kernel(COTTN_SYM_STR(bwd_dq_scan), kernel, grid, dim3(threads), 0, a.stream, Q, K, V, dO, a.s,
                          static_cast<elem_t*>(a.dQ), fwd_states, rev_states, ds_partial, a.H, a.N, a.G, a.seg_rows,
-                         inv_eps, sum_in_scan && !carried ? 1 : 0, a.seq_len, a.s_per_unit, a.state_in,
+                         inv_eps, sum_in_scan && !carried ? (a.marked && a.saved_fwd_states != nullptr ? 2 : 1) : 0, a.seq_len, a.s_per_unit, a.state_in,
                          units, a.unit_rows);
   };
   constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32);
@@ -960,7 +979,9 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   if (HALVED && a.G == 1 && !even && two_to_a_cu_dq(a.workgroups)) {
     if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, SEGMENTS>, 256);
   } else if (even) {
-    if constexpr (EVEN_BUILT) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT);
+    if constexpr (EVEN_BUILT)
+      err = a.seq_len == nullptr ? dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT)
+                                 : dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_PADDED>, Cfg::NT);
   } else if (rebuild) {
     if constexpr (C <= 64) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
   } else {
@@ -980,10 +1001,12 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
   };
   if constexpr (HALVED)
     if (!even && two_to_a_cu_dkdv(a.workgroups))
-      return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, 32, CS, false>, 256);
+      return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, 32, CS, SEGMENTS>, 256);
   if constexpr (EVEN_BUILT)
-    if (even) return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, true>, Cfg::NT);
-  return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, false>, Cfg::NT);
+    if (even)
+      return a.seq_len == nullptr ? dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, EVEN_SHARES>, Cfg::NT)
+                                  : dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, EVEN_PADDED>, Cfg::NT);
+  return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, SEGMENTS>, Cfg::NT);
 }
 
 }  // namespace

@@ -592,9 +592,14 @@ __device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int s
 }
 
 // How the causal scans walk (a template parameter, so that no walk pays for the others): segments, with
-// the states of earlier ones from the workspace; even shares; segments of short sequences, whose
+// the states of earlier ones from the workspace; even shares, of sequences of one length or of a padded
+// batch (a piece without rows that exist takes a step of zeros); segments of short sequences, whose
 // workgroups form the state of the rows before them by themselves (launch.h: own_prefix).
-enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, OWN_PREFIX = 2 };
+enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, EVEN_PADDED = 2, OWN_PREFIX = 3 };
+// What the last share's slot, which holds no state, begins with in a forward's workspace: whether the states
+// there are those of even shares (launch.h: CausalArgs::marked).
+constexpr float EVEN_MARK = 1.0f, NO_EVEN_MARK = 0.0f;
+constexpr bool walks_even(int walk) { return walk == EVEN_SHARES || walk == EVEN_PADDED; }
 
 // In place, for 4 neighbouring elements of a stack of n matrices `stride` floats apart:
 // matrix k (in walking order: first to last, or last to first with `reverse`) <- sum of the

@@ -118,7 +118,11 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   const Span span = unit_rows == 0 ? span_of_workgroup<false, false>(units, N, n_slots, seg_rows, 0)
                                    : span_of_workgroup<true, true>(units, N, n_slots, seg_rows, unit_rows);
   const int unit = span.unit;
-  if (unit_rows == 0 ? span.slot - span.outermost >= n_compute : !span.mid_unit) return;
+  if (unit_rows == 0 ? span.slot - span.outermost >= n_compute : !span.mid_unit) {
+    if (unit_rows > 0 && span.slot == int(gridDim.x) - 1 && threadIdx.x == 0)
+      seg_state[size_t(span.slot) * DK * DV] = EVEN_MARK;
+    return;
+  }
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const elem_t* Ku = K + size_t(unit) * N * DK;
@@ -181,10 +185,10 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
     float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
-    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ seq_len, int s_per_unit,
+    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
     int stream_q, int stream_kv, int units, int unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
-  constexpr bool EVEN = WALK == EVEN_SHARES;
+  constexpr bool EVEN = walks_even(WALK);
   constexpr int RG = C / 16;           // row groups of a chunk
   constexpr int NOT = Cfg::DTV / CS;   // output column tiles per wave
   using ST = SplitTiles<DV, DK, RG, CS>;   // value rows, key columns (the state is held transposed)
@@ -203,7 +207,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
-                     sum_totals, seq_len, s_per_unit, stream_q, stream_kv, units, unit_rows);
+                     sum_totals, lengths, s_per_unit, stream_q, stream_kv, units, unit_rows);
+  const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
   Span span;
   int part = 0;
   if constexpr (LDV > DV) {
@@ -223,6 +228,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = span.begin;
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
+  int piece_end = span.end;   // of the same, with the rows that do not exist
 
   // running state in fp32 accumulators, seeded with the segment's prefix ([d_key][d_value])
   // seg_states holds either the carried prefixes (slot g = state at the start of segment g)
@@ -269,6 +275,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
                                   16 * ST::row_tile(rg, cp, y) + 4 * q4) = sacc[x][y];
   };
   if (state_in != nullptr && ST::active(rg, cp)) load_start();
+  if constexpr (even_shares_built(DK, DV, ELEM_IS_F32) && WALK == SEGMENTS && LDV == DV)
+    if (G == 1 && seg_states != nullptr && blockIdx.x == 0 && tid == 0) *seg_states = NO_EVEN_MARK;
   if constexpr (WALK == OWN_PREFIX) {
     if (span.mid_unit) {
       add_rows_before<DK, DV, C, Cfg::NT * CS, ST::NCT, ST::NRT, LDV>(
@@ -305,7 +313,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   const int col0 = 16 * NOT * cp;  // first output column of this wave
   elem_t* done_O = Ou;
   int done_row = 0, done_end = 0, row0 = row_begin, left = span.left;   // done_end = 0: nothing finished yet
-  for (bool more = row0 < row_end; more;) {
+  for (bool more = WALK == EVEN_PADDED || row0 < row_end; more;) {
     // ---- publish the state (bf16) and this chunk's tiles
     if (ST::active(rg, cp)) {
 #pragma unroll
@@ -327,8 +335,9 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     }
     // the next step's rows: of this unit, or the first ones of the next
     const bool cross = EVEN && left > 0 && row0 + C >= row_end;
-    const int next_row = cross ? 0 : row0 + C, next_end = cross ? min(N, left) : row_end;
-    more = next_row < next_end;
+    const int next_row = cross ? 0 : row0 + C;
+    const int next_end = cross ? min(valid_rows(seq_len, unit + 1, H, N), left) : row_end;
+    more = (WALK == EVEN_PADDED && cross) || next_row < next_end;
     if (cross) {
       Qu += size_t(N) * DK;
       Ku += size_t(N) * DK;
@@ -445,6 +454,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     done_end = row_end;
     if (cross) {   // the unit ends here
       if (state_out != nullptr && ST::active(rg, cp)) store_final();
+      if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, N);
+      piece_end = min(N, left);
       ++unit;
       left -= unit_rows;
       Ou += size_t(N) * LDV;
@@ -463,9 +474,9 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   }
   if (done_end > 0) store_row_pieces<DV, NOT, LDV>(finished, done_O, done_row + 16 * rg, done_end, l, col0);
 
-  if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, span.end);  // rows that do not exist
+  if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, piece_end);  // rows that do not exist
 
-  if (state_out != nullptr && (EVEN ? row_end : span.end) == N && ST::active(rg, cp)) store_final();
+  if (state_out != nullptr && piece_end == N && ST::active(rg, cp)) store_final();
 }
 
 template <int DK, int DV, int C>
@@ -497,9 +508,11 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   // that cache by themselves (256 sequences of 2048 rows, 16 heads of 128: 1660 -> 1610 us; 64 of 1000
   // rows d64, whose K, V are found cached in part: 85 -> 105).
   const bool stream_kv = a.G == 1 && !even && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
+  float* states = a.G > 1 || even ? ws : nullptr;
+  if (a.marked && !even) states = ws + (a.slots - 1) * DK * DV;   // (only the mark)
   const auto scan = [&](auto kernel, int threads, int parts = 1) {
     return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(a.workgroups * parts), dim3(threads), 0, a.stream, Q, K,
-                         V, a.s, static_cast<elem_t*>(a.O), a.state, a.G > 1 || even ? ws : nullptr, a.state_in, a.H, a.N,
+                         V, a.s, static_cast<elem_t*>(a.O), a.state, states, a.state_in, a.H, a.N,
                          a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0,
                          stream_kv ? 1 : 0, units, a.unit_rows);
   };
@@ -519,7 +532,10 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
     if (!even && !a.own_prefix && two_to_a_cu_forward(a.workgroups)) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, 32, 2, SEGMENTS>, 256);
   if constexpr (even_shares_built(DK, DV, ELEM_IS_F32))
-    if (even) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_SHARES>, threads);
+    if (even)
+      return a.seq_len == nullptr
+                 ? scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_SHARES>, threads)
+                 : scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_PADDED>, threads);
   if constexpr (C <= 64)
     if (a.own_prefix) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX>, threads);
   return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, SEGMENTS>, threads);

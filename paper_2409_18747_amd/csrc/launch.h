@@ -35,6 +35,10 @@ struct CausalArgs {
   // of seg_rows rows per unit; workgroups of a scan either way, and state slots of a workspace array
   int unit_rows, workgroups;
   long slots;
+  // Even shares of units that would otherwise be one segment each: calls with lengths keep to those segments
+  // and leave no states.  A forward notes in the last slot which it did, and a backward without lengths that
+  // is handed states of none forms them itself, so that either forward suits either backward.
+  bool marked;
   bool own_prefix;   // segments whose workgroups form the state before them themselves (own_prefix below)
   bool by_unit;                   // bidirectional only: a (batch, head) per workgroup, G = 1
   float eps;

@@ -12,7 +12,7 @@ struct SeqPlan {
   int seg_rows;
   bool by_unit;   // a bidirectional call that takes a whole (batch, head) per workgroup (bidir_by_unit), G = 1
   // causal: rows of an even share of the units laid end to end (a whole number of chunks; device_common.h:
-  // Span), or 0.  Calls without lengths walk even shares where the plan has them, others the G segments.
+  // Span), or 0: G segments.
   int even_rows;
   bool own_prefix;   // causal: launch.h
   long slots;     // causal: state slots of a workspace array, enough for either

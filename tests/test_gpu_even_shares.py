@@ -83,20 +83,54 @@ def test_pieces(cottn, dtype, B, H, N):
     assert max(errs.values()) <= TOL[dtype], errs
 
 
-def test_padded_batch_of_such_a_shape(cottn, oracle):
-    """Calls with lengths keep to segments, in the workspace the query answers for both."""
+PADDED = [("bf16", 8, 11, 700, 128, [700, 0, 1, 64, 350, 351, 640, 699]), ("f16", 44, 12, 333, 128, [0, 333, 64, 65] * 11),
+          ("f32", 8, 12, 400, 64, [0, 400, 0, 0, 33, 399, 1, 0]), ("f32", 20, 13, 130, 128, [130, 0, 32, 129, 97] * 4)]
+
+
+@pytest.mark.parametrize("dtype,B,H,N,d,lens", PADDED)
+def test_padded_batches_of_such_shapes(cottn, oracle, dtype, B, H, N, d, lens):
+    """Lengths that end before, inside and at the end of a share's pieces, and sequences without a row."""
     import torch
-    B, H, N, dtype = 8, 11, 700, "bf16"
-    x = draw(B, H, N, 128, 128, dtype, 990)
-    lens = [700, 0, 1, 64, 350, 351, 640, 699]
+    c = code(cottn, dtype)
+    x = draw(B, H, N, d, d, dtype, 990)
     sc = np.linspace(0.5, 1.5, B * H, dtype=np.float32).reshape(B, H)
     Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
     s, n = to_device(sc, "f32"), torch.tensor(lens, dtype=torch.int32, device="cuda")
-    ws = torch.empty(cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, H, N, 128, 0, cottn.COTTN_BF16), dtype=torch.uint8, device="cuda")
-    O = to_host(cottn.cottn_fwd_causal_varlen(Q, K, V, s, n, workspace=ws))
-    g = [to_host(t) for t in cottn.cottn_bwd_causal_varlen(Q, K, V, s, n, dO, fwd_workspace=ws)]
-    ref = [oracle.fwd_varlen(x["Q"], x["K"], x["V"], sc, lens)[0], *oracle.bwd_varlen(x["Q"], x["K"], x["V"], sc, x["dO"], lens)[:3]]
-    for name, a, r in zip(("O", "dQ", "dK", "dV"), [O] + g[:3], ref):
-        e = rel_err(a, r)
-        print(name, "%.2e" % e, flush=True)
-        assert e <= TOL[dtype], (name, e)
+    ws, bws = (torch.full((cottn.cottn_workspace_bytes(op, B, H, N, d, 0, c),), 255, dtype=torch.uint8, device="cuda")
+               for op in (cottn.OP_FWD_CAUSAL, cottn.OP_BWD_CAUSAL))   # (NaN wherever nothing is written)
+    state = torch.full((B, H, d, d), float("nan"), device="cuda")
+    O = to_host(cottn.cottn_fwd_causal_varlen(Q, K, V, s, n, state=state, workspace=ws))
+    O_ref, S_ref = oracle.fwd_varlen(x["Q"], x["K"], x["V"], sc, lens)
+    g_ref = oracle.bwd_varlen(x["Q"], x["K"], x["V"], sc, x["dO"], lens)
+    assert rel_err(to_host(state), S_ref) <= TOL[dtype]
+    for kept in (ws, None):
+        g = [to_host(t) for t in cottn.cottn_bwd_causal_varlen(Q, K, V, s, n, dO, workspace=bws.fill_(255), fwd_workspace=kept)]
+        errs = {k: rel_err(a, r) for k, a, r in zip(("O", "dQ", "dK", "dV"), [O] + g[:3], [O_ref, *g_ref[:3]])}
+        errs["ds"] = rel_err_ds(g[3], g_ref[3], ds_terms_rss(oracle, x, lens=lens, per_unit=True))
+        print(dtype, B, H, N, d, kept is not None, {k: "%.2e" % v for k, v in errs.items()}, flush=True)
+        assert max(errs.values()) <= TOL[dtype], errs
+        assert all((a[b, :, m:] == 0).all() for a in [O] + g[:3] for b, m in enumerate(lens))
+
+
+@pytest.mark.parametrize("dtype,B,H,N,d", [("bf16", 8, 11, 700, 128), ("f32", 8, 12, 400, 64), ("f16", 44, 12, 333, 128),
+                                           ("f32", 20, 13, 130, 128), ("f32", 31, 11, 150, 128)])
+def test_workspaces_change_hands(cottn, dtype, B, H, N, d):
+    """A forward without lengths leaves what a backward with lengths takes where all of them are N, and the
+    reverse; and a forward overwrites what an earlier one of the other kind left."""
+    import torch
+    x = draw(B, H, N, d, d, dtype, 995)
+    Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
+    s, n = to_device(x["s"], "f32"), torch.full((B,), N, dtype=torch.int32, device="cuda")
+    per_unit = s.expand(B, H).contiguous()
+    first, second = (torch.full((cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, H, N, d, 0, code(cottn, dtype)),), 255,
+                                dtype=torch.uint8, device="cuda") for _ in range(2))
+    fixed = lambda ws: cottn.cottn_fwd_causal(Q, K, V, s, workspace=ws)
+    padded = lambda ws: cottn.cottn_fwd_causal_varlen(Q, K, V, per_unit, n, workspace=ws)
+    want = cottn.cottn_bwd_causal(Q, K, V, s, dO)
+    for a, b in ((fixed, padded), (padded, fixed)):
+        a(first), b(second)
+        for ws in (first, second):
+            for got in (cottn.cottn_bwd_causal(Q, K, V, s, dO, fwd_workspace=ws),
+                        cottn.cottn_bwd_causal_varlen(Q, K, V, per_unit, n, dO, fwd_workspace=ws)):
+                for g, w in zip(got[:3], want):
+                    assert rel_err(to_host(g), to_host(w)) <= TOL[dtype]
