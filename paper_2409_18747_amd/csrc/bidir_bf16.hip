@@ -33,6 +33,7 @@
 #include "workspace.h"
 
 namespace cottn {
+namespace COTTN_NS {
 namespace {
 
 // DK, DV: head dimensions of queries / keys and of values / outputs (Sec. 2.1); the matrices
@@ -57,13 +58,16 @@ struct BiCfg {
   // not cost a workgroup, otherwise in the dead Q tile, whose rows are always wide enough
   static constexpr int DQ_BYTES = LDS_ELEM * (TILEK + TILEV + STATE) + 8 * C;
   static constexpr int DQ_STAGE_BYTES = ELEM * C * stage_tile_pitch(DK, C);
+  static constexpr bool DQ_STAGE_IN_Q = SPLIT3 || REDO;
   static constexpr bool DQ_OWN_STAGE =
+      REDO ? false :
       SPLIT3 ? 160 * 1024 / (DQ_BYTES + DQ_STAGE_BYTES) == 160 * 1024 / DQ_BYTES
              : ELEM * stage_pitch(DK) > LDS_ELEM * TPV || DQ_BYTES + DQ_STAGE_BYTES <= 160 * 1024;
 };
 
 // Slot 0 <- sum over g of the slots, one matrix element per thread (grid: elems/256 workgroups
 // per (batch, head)); `state` (may be null) receives it too.
+#ifndef COTTN_REDO
 __global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals, int G, int elems,
                                                      float* __restrict__ state) {
   // one grid dimension: (unit, 256-element block of the matrix), so that B*H is not limited to
@@ -84,12 +88,13 @@ __global__ __launch_bounds__(256) void bidir_combine(float* __restrict__ totals,
   p[e] = a;
   if (state != nullptr) state[size_t(unit) * elems + e] = a;
 }
+#endif
 
 // dst (LDS, elements, row-major [DK][DV] with row pitch SP) <- sum of the first n_sum of the
 // [DK][DV] fp32 matrices at src; the fp32 sum also goes to `copy` when that is not null.
 template <int DK, int DV, int NT, int SP>
 __device__ __forceinline__ void stage_summed_matrix(lds_t* dst, const float* __restrict__ src,
-                                                    int n_sum, float* __restrict__ copy) {
+                                                    int n_sum, float* __restrict__ copy, Unparted& un) {
   // up to 16 of a thread's loads are in flight before the first is waited for: PIECES pieces of
   // BATCH matrices (a batch that reaches beyond the last matrix re-reads it and drops it)
   constexpr int PASSES = DK * DV / (4 * NT), PIECES = PASSES < 1 ? 1 : PASSES < 4 ? PASSES : 4;
@@ -120,7 +125,7 @@ __device__ __forceinline__ void stage_summed_matrix(lds_t* dst, const float* __r
     for (int i = 0; i < PIECES; ++i) {
       const int e = e0 + 4 * NT * i;
       if (copy != nullptr) *reinterpret_cast<f32x4*>(copy + e) = sum[i];
-      store4_lds(dst + (e / DV) * SP + lds_col(e % DV), sum[i][0], sum[i][1], sum[i][2], sum[i][3]);
+      store4_lds(dst + (e / DV) * SP + lds_col(e % DV), sum[i][0], sum[i][1], sum[i][2], sum[i][3], un);
     }
   }
 }
@@ -131,7 +136,7 @@ template <int DK, int DV, int C>
 __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& qst, lds_t* Qs, const lds_t* Sl,
                                            elem_t* Os, float* rq, const elem_t* __restrict__ Qu,
                                            elem_t* __restrict__ Ou, float scale, int row_begin, int row_end,
-                                           float inv_eps, int w, int l) {
+                                           float inv_eps, int w, int l, Unparted& un) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
   constexpr int TP = Cfg::TPK, SP = Cfg::SP;
@@ -145,7 +150,7 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
     {
       float rqv[Stage::PASSES];
       qst.row_rinv(inv_eps, rqv);
-      qst.commit_plain(Qs);
+      qst.commit_plain(Qs, un);
       qst.store_rinv(rq, rqv);
     }
     if (row0 + C < row_end) qst.fetch(Qu, row0 + C, row_end);
@@ -171,7 +176,7 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
     __builtin_amdgcn_sched_barrier(0);
     const float row_factor = scale * rq[16 * w + r];
     wave_lds_sync();  // this wave's reads of its Qs rows precede the staging writes
-    gather_rows_transposed<DV>(oacc, row_factor, stage, l, finished);
+    gather_rows_transposed<DV>(oacc, row_factor, stage, l, finished, un);
     __syncthreads();
   }
   if (row_begin < row_end) {
@@ -184,17 +189,18 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
 // n_sum stored matrices per unit at a stride of `slots` matrices; the workgroup of segment 0
 // writes their sum to `state` when that is asked for.
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
+COTTN_KERNEL((C * 4), fwd_bidir_apply)
     const elem_t* __restrict__ Q, const float* __restrict__ s, elem_t* __restrict__ O,
     const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, int H, int N,
     int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];  // raw q
-  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];  // [d_key][d_value]
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::FWD_OWN_STAGE ? C * stage_tile_pitch(DV, C) : 8];
-  __shared__ float rq[C];
+  COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)  // raw q
+  COTTN_LDS_ARRAY(lds_t, Sl, Cfg::STATE, 1)  // [d_key][d_value]
+  COTTN_LDS_ARRAY(elem_t, Os, Cfg::FWD_OWN_STAGE ? C * stage_tile_pitch(DV, C) : 8, 2)
+  COTTN_LDS_ARRAY(float, rq, C, 3)
 
+  Unparted un;
   fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
                      s_per_unit);
   int unit, g;
@@ -211,11 +217,20 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_apply)(
   qst.fetch(Qu, row_begin, row_end);
   stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, totals + size_t(unit) * slots * DK * DV, n_sum,
                                   (state != nullptr && g == 0) ? state + size_t(unit) * DK * DV
-                                                               : nullptr);
+                                                               : nullptr, un);
 
   apply_rows<DK, DV, C>(qst, Qs, Sl, Cfg::FWD_OWN_STAGE ? Os : nullptr, rq, Qu, Ou, scale, row_begin, row_end,
-                        inv_eps, w, l);
+                        inv_eps, w, l, un);
   if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, seg_end);  // rows that do not exist
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<Cfg::NW>(rq)) {
+    using Whole = f32w::BiCfg<DK, DV, C>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::STATE <= Cfg::STATE &&
+                  Whole::FWD_OWN_STAGE == Cfg::FWD_OWN_STAGE, "whole rows fit, and finished ones are staged alike");
+    void* const room[] = {Qs, Sl, Os, rq};
+    f32w::fwd_bidir_apply<DK, DV, C>(room, Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len, s_per_unit);
+  }
+#endif
 }
 
 // dQ rows row_begin .. row_end - 1 of one unit, with S in Sl (not yet behind a barrier); the first C
@@ -227,7 +242,7 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
                                         f32x4 (&racc)[RT::NCT][RT::NRT], float& ds_lane, lds_t* Qs, lds_t* Gs,
                                         elem_t* Os, const lds_t* Sl, float* rq, const elem_t* __restrict__ Qu,
                                         const elem_t* __restrict__ Gu, elem_t* __restrict__ dQu, float scale,
-                                        int row_begin, int row_end, float inv_eps, int w, int l) {
+                                        int row_begin, int row_end, float inv_eps, int w, int l, Unparted& un) {
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
@@ -239,9 +254,9 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
     {
       float rqv[StageK::PASSES];
       qst.row_rinv(inv_eps, rqv);
-      qst.commit_scaled(Qs, rqv);
+      qst.commit_scaled(Qs, rqv, un);
       qst.store_rinv(rq, rqv);
-      gst.commit_plain(Gs);
+      gst.commit_plain(Gs, un);
     }
     if (row0 + C < row_end) {
       qst.fetch(Qu, row0 + C, row_end);
@@ -294,9 +309,9 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
     if (!Cfg::DQ_OWN_STAGE) __syncthreads();  // every wave is done with the dO tile
     gather_rows_transposed<DK>(dq, scale * ri,
                                Cfg::DQ_OWN_STAGE ? static_cast<void*>(Os + 16 * w * stage_tile_pitch(DK, C))
-                               : SPLIT3          ? static_cast<void*>(Qs + 16 * w * TPK)
+                               : Cfg::DQ_STAGE_IN_Q ? static_cast<void*>(Qs + 16 * w * TPK)
                                                  : static_cast<void*>(Gs + 16 * w * TPV),
-                               l, finished);
+                               l, finished, un);
     __syncthreads();
   }
   if (row_begin < row_end) {
@@ -315,7 +330,7 @@ __device__ __forceinline__ void dq_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>& 
 // contracts them over the tokens), so finished dQ rows are staged in a tile of their own where
 // that fits.
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
+COTTN_KERNEL((C * 4), bwd_bidir_dq)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ dO, const float* __restrict__ s,
     elem_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
     float* __restrict__ g_totals, float* __restrict__ ds_partial, int H, int N, int G,
@@ -324,13 +339,14 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? C * stage_tile_pitch(DK, C) : 8];   // finished dQ rows
-  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // Kh^T V, [d_key][d_value]
-  __shared__ float rq[C];
-  __shared__ float ds_wave[Cfg::NW];
+  COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)   // qh = r_i q_i
+  COTTN_LDS_ARRAY(lds_t, Gs, Cfg::TILEV, 1)   // dO
+  COTTN_LDS_ARRAY(elem_t, Os, Cfg::DQ_OWN_STAGE ? C * stage_tile_pitch(DK, C) : 8, 2)   // finished dQ rows
+  COTTN_LDS_ARRAY(lds_t, Sl, Cfg::STATE, 3)   // Kh^T V, [d_key][d_value]
+  COTTN_LDS_ARRAY(float, rq, C, 4)
+  COTTN_LDS_ARRAY(float, ds_wave, Cfg::NW, 5)
 
+  Unparted un;
   fetch_argument_now(Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows,
                      inv_eps, seq_len, s_per_unit);
   int unit, g;
@@ -349,7 +365,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
   StageV gst;
   qst.fetch(Qu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
-  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
+  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr, un);
 
   // racc[x][y]: element [v] of lane (r, q4) is G[key 16 ct + r][value 16 rt + 4 q4 + v]
   f32x4 racc[RT::NCT][RT::NRT];
@@ -359,11 +375,13 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
     for (int y = 0; y < RT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
   float ds_lane = 0.f;
   dq_rows<DK, DV, C>(qst, gst, racc, ds_lane, Qs, Gs, Cfg::DQ_OWN_STAGE ? Os : nullptr, Sl, rq, Qu, Gu, dQu, scale,
-                     row_begin, row_end, inv_eps, w, l);
+                     row_begin, row_end, inv_eps, w, l, un);
   if (seq_len != nullptr) zero_rows<DK>(dQu, row_end, seg_end);  // rows that do not exist
 
   if (RT::active(w)) {
     float* out = g_totals + (size_t(unit) * slots + g) * DK * DV;
+#pragma unroll
+    for (int x = 0; x < RT::NCT; ++x) un.results<RT::NRT>(racc[x]);
 #pragma unroll
     for (int x = 0; x < RT::NCT; ++x)
 #pragma unroll
@@ -381,6 +399,15 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dq)(
     for (int i = 0; i < Cfg::NW; ++i) t += ds_wave[i];
     ds_partial[size_t(unit) * G + g] = t;
   }
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<Cfg::NW>(rq)) {
+    using Whole = f32w::BiCfg<DK, DV, C>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
+    void* const room[] = {Qs, Gs, Os, Sl, rq, ds_wave};
+    f32w::bwd_bidir_dq<DK, DV, C>(room, Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows, inv_eps,
+                                  seq_len, s_per_unit);
+  }
+#endif
 }
 
 // dK and dV rows row_begin .. row_end - 1 of one unit, with G in Gl (not yet behind a barrier);
@@ -391,7 +418,7 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
                                           const lds_t* Gl, float* rk, const elem_t* __restrict__ Ku,
                                           const elem_t* __restrict__ Vu, elem_t* __restrict__ dKu,
                                           elem_t* __restrict__ dVu, float scale, int row_begin, int row_end,
-                                          float inv_eps, int w, int l) {
+                                          float inv_eps, int w, int l, Unparted& un) {
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
@@ -406,9 +433,9 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
     {
       float rkv[StageK::PASSES];
       kst.row_rinv(inv_eps, rkv);
-      kst.commit_plain(Ks);
+      kst.commit_plain(Ks, un);
       kst.store_rinv(rk, rkv);
-      vst.commit_plain(Vs);
+      vst.commit_plain(Vs, un);
     }
     if (row0 + C < row_end) {
       kst.fetch(Ku, row0 + C, row_end);
@@ -459,8 +486,8 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
     const float t = dot_with_row<Cfg::DTK, TPK>(dk, Ks + 16 * w * TPK, 0, xv, r, q4);
     project_out_row<Cfg::DTK, false>(dk, xv, t, rj, inv_eps);
     wave_lds_sync();  // own rows of Ks, Vs were read before the staging writes
-    gather_rows_transposed<DK>(dk, scale * rj, Ks + 16 * w * TPK, l, done_k);
-    gather_rows_transposed<DV>(dv, scale * rj, Vs + 16 * w * TPV, l, done_v);
+    gather_rows_transposed<DK>(dk, scale * rj, Ks + 16 * w * TPK, l, done_k, un);
+    gather_rows_transposed<DV>(dv, scale * rj, Vs + 16 * w * TPV, l, done_v, un);
     __syncthreads();
   }
   if (row_begin < row_end) {
@@ -476,7 +503,7 @@ __device__ __forceinline__ void dkdv_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT>
 //   dkh^T = G V^T (over d_value),  (k G)^T = G^T k^T (over d_key),
 //   dk_j = s r_j (dkh_j - kh_j (kh_j . dkh_j)),  dv_j = s r_j (k_j G).
 template <int DK, int DV, int C>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
+COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
     const elem_t* __restrict__ K, const elem_t* __restrict__ V, const float* __restrict__ s,
     elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
     int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, int H,
@@ -484,11 +511,12 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];
-  __shared__ __attribute__((aligned(16))) lds_t Gl[Cfg::STATE];  // Qh^T dO, [d_key][d_value]
-  __shared__ float rk[C];
+  COTTN_LDS_ARRAY(lds_t, Ks, Cfg::TILEK, 0)   // raw k
+  COTTN_LDS_ARRAY(lds_t, Vs, Cfg::TILEV, 1)
+  COTTN_LDS_ARRAY(lds_t, Gl, Cfg::STATE, 2)   // Qh^T dO, [d_key][d_value]
+  COTTN_LDS_ARRAY(float, rk, C, 3)
 
+  Unparted un;
   fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
                      seg_rows, inv_eps, seq_len, s_per_unit);
   int unit, g;
@@ -518,13 +546,22 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_dkdv)(
     t = group_sum<64>(t);
     if (l == 0) ds[blockIdx.x] = t;
   }
-  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Gl, g_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr);
+  stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Gl, g_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr, un);
 
-  dkdv_rows<DK, DV, C>(kst, vst, Ks, Vs, Gl, rk, Ku, Vu, dKu, dVu, scale, row_begin, row_end, inv_eps, w, l);
+  dkdv_rows<DK, DV, C>(kst, vst, Ks, Vs, Gl, rk, Ku, Vu, dKu, dVu, scale, row_begin, row_end, inv_eps, w, l, un);
   if (seq_len != nullptr) {  // rows that do not exist
     zero_rows<DK>(dKu, row_end, seg_end);
     zero_rows<DV>(dVu, row_end, seg_end);
   }
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<Cfg::NW>(rk)) {
+    using Whole = f32w::BiCfg<DK, DV, C>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
+    void* const room[] = {Ks, Vs, Gl, rk};
+    f32w::bwd_bidir_dkdv<DK, DV, C>(room, K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G, seg_rows,
+                                    inv_eps, seq_len, s_per_unit);
+  }
+#endif
 }
 
 // ---------------------------------------------------------------------------------------
@@ -551,6 +588,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // [d_key][d_value]
   __shared__ float rq[C];
 
+  Unparted un;
   fetch_argument_now(Q, K, V, s, O, totals, state, H, N, inv_eps, seq_len, s_per_unit);
   const int unit = blockIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, r = l % 16, q4 = l / 16;
@@ -571,7 +609,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   kst.fetch(Ku, 0, row_end);
   vst.fetch(Vu, 0, row_end);
   qst.fetch(Qu, 0, row_end);
-  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, 0, row_end, inv_eps, w, l);
+  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, 0, row_end, inv_eps, w, l, un);
   if (ST::active(w)) {
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
@@ -585,7 +623,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
       }
   }
   __syncthreads();  // every wave is done with the K and V tiles
-  apply_rows<DK, DV, C>(qst, Ks, Sl, Cfg::FWD_OWN_STAGE ? Vs : nullptr, rq, Qu, Ou, scale, 0, row_end, inv_eps, w, l);
+  apply_rows<DK, DV, C>(qst, Ks, Sl, Cfg::FWD_OWN_STAGE ? Vs : nullptr, rq, Qu, Ou, scale, 0, row_end, inv_eps, w, l, un);
   if (seq_len != nullptr) zero_rows<DV>(Ou, row_end, N);  // rows that do not exist
 }
 
@@ -609,6 +647,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
   __shared__ float rq[C];
   __shared__ float ds_wave[Cfg::NW];
 
+  Unparted un;
   fetch_argument_now(Q, K, V, dO, s, dQ, dK, dV, s_totals, ds_out, H, N, inv_eps, seq_len, s_per_unit);
   const int unit = blockIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, r = l % 16, q4 = l / 16;
@@ -620,7 +659,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
   TileStage<DV, C, Cfg::NT> gst, vst;
   qst.fetch(Q + k_rows, 0, row_end);
   gst.fetch(dO + v_rows, 0, row_end);
-  stage_summed_matrix<DK, DV, Cfg::NT, SP>(Sl, s_totals + size_t(unit) * DK * DV, 1, nullptr);
+  stage_summed_matrix<DK, DV, Cfg::NT, SP>(Sl, s_totals + size_t(unit) * DK * DV, 1, nullptr, un);
   f32x4 racc[RT::NCT][RT::NRT];
 #pragma unroll
   for (int x = 0; x < RT::NCT; ++x)
@@ -628,7 +667,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
     for (int y = 0; y < RT::NRT; ++y) racc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
   float ds_lane = 0.f;
   dq_rows<DK, DV, C>(qst, gst, racc, ds_lane, Qs, Gs, Cfg::DQ_OWN_STAGE ? Os : nullptr, Sl, rq, Q + k_rows,
-                     dO + v_rows, dQ + k_rows, scale, 0, row_end, inv_eps, w, l);
+                     dO + v_rows, dQ + k_rows, scale, 0, row_end, inv_eps, w, l, un);
   kst.fetch(K + k_rows, 0, row_end);
   vst.fetch(V + v_rows, 0, row_end);
   if (seq_len != nullptr) zero_rows<DK>(dQ + k_rows, row_end, N);  // rows that do not exist
@@ -651,7 +690,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
                racc[x][y][1], racc[x][y][2], racc[x][y][3]);
   }
   dkdv_rows<DK, DV, C>(kst, vst, Qs, Gs, Sl, rq, K + k_rows, V + v_rows, dK + k_rows, dV + v_rows, scale, 0, row_end,
-                       inv_eps, w, l);
+                       inv_eps, w, l, un);
   if (seq_len != nullptr) {  // rows that do not exist
     zero_rows<DK>(dK + k_rows, row_end, N);
     zero_rows<DV>(dV + v_rows, row_end, N);
@@ -668,6 +707,7 @@ __global__ __launch_bounds__(64) void bidir_sum_ds(const float* __restrict__ ds_
 }
 #endif  // COTTN_ELEM_F32
 
+#ifndef COTTN_REDO
 SegmentTotalsArgs totals_args(const CausalArgs& a, const void* X, const void* Y, float* dst) {
   SegmentTotalsArgs t{};
   t.X = X; t.Y = Y; t.dst = dst;
@@ -788,8 +828,13 @@ hipError_t run_bwd_bidir(const CausalArgs& a) {
     if (a.C == 64) return run_bwd_bidir_rows<DK, DV, 64>(a);
   return hipErrorInvalidValue;
 }
+#endif  // COTTN_REDO
 
 }  // namespace
+}  // namespace COTTN_NS
+
+#ifndef COTTN_REDO
+using namespace COTTN_NS;
 
 #if !defined(COTTN_ELEM_F16) && !defined(COTTN_ELEM_F32)  // not specific to the element type
 hipError_t launch_bidir_combine(float* totals, int units, int G, int elems, float* state,
@@ -830,5 +875,7 @@ hipError_t COTTN_SYM(fwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_
 
 hipError_t COTTN_SYM(bwd_bidir)(const CausalArgs& a) { COTTN_FOR_EACH_DK_DV(run_bwd_bidir, bwd_bidir_f32w) }
 #endif
+
+#endif  // COTTN_REDO
 
 }  // namespace cottn

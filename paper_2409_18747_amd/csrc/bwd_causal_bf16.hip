@@ -48,6 +48,7 @@
 #include "workspace.h"
 
 namespace cottn {
+namespace COTTN_NS {
 namespace {
 
 // DK, DV: the head dimensions of the keys / queries and of the values / outputs (Sec. 2.1:
@@ -75,8 +76,9 @@ struct BwdCfg {
   // unit, and must when the finished rows (DK wide) do not fit the rows of the dO tile (the parts of
   // SPLIT3 rows leave room for them in the Q tile)
   static constexpr int OP = stage_tile_pitch(DK, C);   // of that tile, in elem_t
+  static constexpr bool DQ_STAGE_IN_Q = SPLIT3 || REDO;
   static constexpr bool DQ_OWN_STAGE =
-      (!SPLIT3 && ELEM * stage_pitch(DK) > LDS_ELEM * TPV) ||
+      (!DQ_STAGE_IN_Q && ELEM * stage_pitch(DK) > LDS_ELEM * TPV) ||
       (CS == 1 && LDS_BYTES + ELEM * C * OP <= 160 * 1024 &&
        (160 * 1024) / (LDS_BYTES + ELEM * C * OP) == WG_PER_CU);
   // The operands of a 32-token step are read in several groups (masked tiles first), each used
@@ -85,7 +87,7 @@ struct BwdCfg {
   // that one group's reads hide behind the other wave's.
   static constexpr bool PHASED = CS == 2 && (ELEM_IS_F32 || (DK == 128 && DV == 128));
   // masked tiles formed by the two waves of a row group together (MaskedExchange); 32-row chunks
-  static constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
+  static constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -130,6 +132,7 @@ template <int DK, int DV, int C> struct BwdSplit {
 //           blockIdx.y == 1: slot g <- sum of rev totals of segments > g.
 // Totals that were never computed (fwd slot G-1, rev slot 0) are not read; a null array is
 // skipped.
+#ifndef COTTN_REDO
 __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_tot,
                                                        float* __restrict__ rev_tot, int G,
                                                        int elems_per_state, long total) {
@@ -140,6 +143,7 @@ __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_t
   exclusive_running_sum(tot + unit * G * elems_per_state + e, G, size_t(elems_per_state),
                         blockIdx.y == 1);
 }
+#endif
 
 // ---------------------------------------------------------------------------------------
 // Kernel 3: dQ of one segment, chunks in forward order.  Wave w owns query rows 16w..16w+15.
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(256) void bwd_state_carry(float* __restrict__ fwd_t
 //
 // REV: whether the launch has segments to leave reverse-time totals for.
 template <int DK, int DV, int C, int CS, bool REV, int WALK>
-__global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dq_scan)(
+COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
     const float* __restrict__ fwd_states, float* __restrict__ rev_totals,
@@ -167,26 +171,27 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SPV;
-  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // qh = r_i q_i
-  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // kh = r_j k_j
-  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v
-  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) lds_t St[DK * Cfg::SPV];  // state, [d_key][d_value]
+  COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)   // qh = r_i q_i
+  COTTN_LDS_ARRAY(lds_t, Ks, Cfg::TILEK, 1)   // kh = r_j k_j
+  COTTN_LDS_ARRAY(lds_t, Vs, Cfg::TILEV, 2)   // raw v
+  COTTN_LDS_ARRAY(lds_t, Gs, Cfg::TILEV, 3)   // dO
+  COTTN_LDS_ARRAY(lds_t, St, Cfg::STATE, 4)   // state, [d_key][d_value]
   // Every wave reads all rows of all four tiles until the end of a chunk (the reverse total
   // contracts Qs and Gs over the tokens), so finished dQ rows are staged in a tile of their
   // own when LDS has room for one; otherwise behind a barrier in the dead dO (SPLIT3: Q) tile.
-  __shared__ __attribute__((aligned(16))) elem_t Os[Cfg::DQ_OWN_STAGE ? C * Cfg::OP : 8];
-  __shared__ float rq[C];
-  __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
-  __shared__ float ds_wave[Cfg::NW];
+  COTTN_LDS_ARRAY(elem_t, Os, Cfg::DQ_OWN_STAGE ? C * Cfg::OP : 8, 5)
+  COTTN_LDS_ARRAY(float, rq, C, 6)
+  COTTN_LDS_ARRAY(float, xdot, CS > 1 ? CS * C : 1, 7)   // row dot products of the column parts
+  COTTN_LDS_ARRAY(float, ds_wave, Cfg::NW, 8)
   // A tiles of the two key halves: in the staging tile where there is one (it is written a
   // barrier after the last of them is read), so that 128 x 32 keeps two workgroups
   constexpr bool IN_STAGE = Cfg::SHARE_MASKED && Cfg::DQ_OWN_STAGE;
   using Masked = MaskedExchange<Cfg::SHARE_MASKED ? 2 : 0>;
-  static_assert(!IN_STAGE || sizeof(Masked) <= sizeof(Os), "the tiles fit the staging tile");
+  static_assert(!IN_STAGE || int(sizeof(Masked)) <= ELEM * C * Cfg::OP, "the tiles fit the staging tile");
   __shared__ __attribute__((aligned(16))) char masked_lds[Cfg::SHARE_MASKED && !IN_STAGE ? sizeof(Masked) : 16];
   Masked& masked = *reinterpret_cast<Masked*>(IN_STAGE ? reinterpret_cast<char*>(Os) : masked_lds);
 
+  Unparted un;
   fetch_argument_now(Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G, seg_rows,
                      inv_eps, sum_totals, lengths, s_per_unit, state_in, units, unit_rows);
   const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
@@ -233,7 +238,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV>(
         Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
         [&](int y) { return AT::row_tile(rg, cp, y); }, [&](int x) { return AT::col_tile(rg, cp, x); },
-        [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+        [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); },
+        un);
   };
   bool no_states = WALK == OWN_PREFIX;
   if constexpr (WALK == EVEN_SHARES)   // (sum_totals 2: the states are a forward's that may have left none)
@@ -262,6 +268,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   if (state_in != nullptr && AT::active(rg, cp)) add_state_in();
   const auto store_rev_total = [&] {
     float* out = rev_totals + size_t(span.slot) * DK * DV;
+#pragma unroll
+    for (int x = 0; x < RT::NCT; ++x) un.results<RT::NRT>(racc[x]);
 #pragma unroll
     for (int x = 0; x < RT::NCT; ++x)
 #pragma unroll
@@ -298,18 +306,18 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 #pragma unroll
         for (int y = 0; y < AT::NRT; ++y) {
           store4_lds(St + (16 * AT::row_tile(rg, cp, y) + r) * SP + lds_col(16 * AT::col_tile(rg, cp, x)) + 4 * q4,
-                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
+                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3], un);
         }
     }
     {
       float rqv[StageK::PASSES], rkv[StageK::PASSES];
       qst.row_rinv(inv_eps, rqv);
       kst.row_rinv(inv_eps, rkv);
-      qst.commit_scaled(Qs, rqv);
+      qst.commit_scaled(Qs, rqv, un);
       qst.store_rinv(rq, rqv);
-      kst.commit_scaled(Ks, rkv);
-      vst.commit_plain(Vs);
-      gst.commit_plain(Gs);
+      kst.commit_scaled(Ks, rkv, un);
+      vst.commit_plain(Vs, un);
+      gst.commit_plain(Gs, un);
     }
     // the next step's rows: of this unit, or the first ones of the next
     const bool cross = EVEN && left > 0 && row0 + C >= row_end;
@@ -390,7 +398,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
           // t[v] = dO_(16 rg + r) . v_(16jt + 4 q4 + v); keep key <= query
           const bool full = jt < rg, diag = jt == rg;
           put_half(af, half, t, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
-                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
+                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r), un);
         }
       };
       frag8 qcol[RT::NCT], grow[RT::NRT];
@@ -428,7 +436,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       __builtin_amdgcn_sched_barrier(0);
       if (diag_or_below) {
         if (!Cfg::PHASED) form_masked();
-        if (Cfg::SHARE_MASKED && rg == 0) {
+        if (Cfg::HALF_VISIBLE && rg == 0) {
 #pragma unroll
           for (int nt = 0; nt < NKT; ++nt) dq[nt] = mma16_half_add(kc[nt], af, dq[nt], 0);
         } else {
@@ -475,9 +483,9 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     if (CS == 1 && !Cfg::DQ_OWN_STAGE) __syncthreads();  // every wave is done with the dO tile
     gather_rows_transposed<DK, NKT>(dq, scale * ri,
                                     Cfg::DQ_OWN_STAGE ? static_cast<void*>(Os + 16 * rg * Cfg::OP)
-                                    : SPLIT3        ? static_cast<void*>(Qs + 16 * rg * TPK)
+                                    : Cfg::DQ_STAGE_IN_Q ? static_cast<void*>(Qs + 16 * rg * TPK)
                                                     : static_cast<void*>(Gs + 16 * rg * TPV),
-                                    l, finished, colk);
+                                    l, finished, un, colk);
     __syncthreads();
     done_dQ = dQu;
     done_row = row0;
@@ -507,6 +515,16 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 
   if (with_rev && RT::active(rg, cp)) store_rev_total();
   store_ds();
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<Cfg::NW>(rq)) {
+    using Whole = f32w::BwdCfg<DK, DV, C, CS>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
+    void* const room[] = {Qs, Ks, Vs, Gs, St, Os, rq, xdot, ds_wave};
+    f32w::bwd_dq_scan<DK, DV, C, CS, REV, WALK>(room, Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G,
+                                                seg_rows, inv_eps, sum_totals, lengths, s_per_unit, state_in, units,
+                                                unit_rows);
+  }
+#endif
 }
 
 // ---------------------------------------------------------------------------------------
@@ -517,7 +535,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 // copy Rl[d_key][d_value]; the update's row-side operand is the dO fragment already read
 // for the intra-chunk dV product.
 template <int DK, int DV, int C, int CS, int WALK>
-__global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) void COTTN_SYM(bwd_dkdv_scan)(
+COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dK,
     elem_t* __restrict__ dV, const float* __restrict__ rev_states,
@@ -530,16 +548,17 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SPV;
-  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // r_i q_i
-  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // raw k
-  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v
-  __shared__ __attribute__((aligned(16))) lds_t Gs[Cfg::TILEV];   // dO
-  __shared__ __attribute__((aligned(16))) lds_t Rl[DK * Cfg::SPV];  // reverse state, [d_key][d_value]
-  __shared__ float rk[C];
-  __shared__ float xdot[CS > 1 ? CS * C : 1];   // row dot products of the column parts
+  COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)   // r_i q_i
+  COTTN_LDS_ARRAY(lds_t, Ks, Cfg::TILEK, 1)   // raw k
+  COTTN_LDS_ARRAY(lds_t, Vs, Cfg::TILEV, 2)   // raw v
+  COTTN_LDS_ARRAY(lds_t, Gs, Cfg::TILEV, 3)   // dO
+  COTTN_LDS_ARRAY(lds_t, Rl, Cfg::STATE, 4)   // reverse state, [d_key][d_value]
+  COTTN_LDS_ARRAY(float, rk, C, 5)
+  COTTN_LDS_ARRAY(float, xdot, CS > 1 ? CS * C : 1, 6)   // row dot products of the column parts
   // P tiles of the two query halves, then the A tiles
   __shared__ MaskedExchange<Cfg::SHARE_MASKED ? 4 : 0> masked;
 
+  Unparted un;
   fetch_argument_now(Q, K, V, dO, s, dK, dV, rev_states, ds_partial, ds, B, H, N, G, seg_rows,
                      inv_eps, sum_totals, lengths, s_per_unit, rev_in, rev_out, unit_rows);
   const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
@@ -625,6 +644,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
   const auto store_rev_out = [&] {
     float* out = rev_out + size_t(unit) * DK * DV;
 #pragma unroll
+    for (int x = 0; x < AT::NCT; ++x) un.results<AT::NRT>(racc[x]);
+#pragma unroll
     for (int x = 0; x < AT::NCT; ++x)
 #pragma unroll
       for (int y = 0; y < AT::NRT; ++y)
@@ -649,18 +670,18 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 #pragma unroll
         for (int y = 0; y < AT::NRT; ++y) {
           store4_lds(Rl + (16 * AT::col_tile(rg, cp, x) + r) * SP + lds_col(16 * AT::row_tile(rg, cp, y)) + 4 * q4,
-                     racc[x][y][0], racc[x][y][1], racc[x][y][2], racc[x][y][3]);
+                     racc[x][y][0], racc[x][y][1], racc[x][y][2], racc[x][y][3], un);
         }
     }
     {
       float rqv[StageK::PASSES], rkv[StageK::PASSES];
       qst.row_rinv(inv_eps, rqv);
       kst.row_rinv(inv_eps, rkv);
-      qst.commit_scaled(Qs, rqv);
-      kst.commit_plain(Ks);
+      qst.commit_scaled(Qs, rqv, un);
+      kst.commit_plain(Ks, un);
       kst.store_rinv(rk, rkv);
-      vst.commit_plain(Vs);
-      gst.commit_plain(Gs);
+      vst.commit_plain(Vs, un);
+      gst.commit_plain(Gs, un);
     }
     // the next step's rows: of this unit, or the last ones of the unit before
     const bool cross = EVEN && left > 0 && row0 == row_begin;
@@ -774,7 +795,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
         const int it = 2 * p + half;
         const bool full = it > rg, diag = it == rg;
         put_half(f, half, t, full || (diag && r <= 4 * q4 + 0), full || (diag && r <= 4 * q4 + 1),
-                 full || (diag && r <= 4 * q4 + 2), full || (diag && r <= 4 * q4 + 3));
+                 full || (diag && r <= 4 * q4 + 2), full || (diag && r <= 4 * q4 + 3), un);
       };
       const auto form_p = [&](int half) {
         f32x4 t = {0.f, 0.f, 0.f, 0.f};
@@ -836,7 +857,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
       }
       if (diag_or_above) {
         if (Cfg::PHASED) {
-          if (Cfg::SHARE_MASKED && rg == 1) {
+          if (Cfg::HALF_VISIBLE && rg == 1) {
 #pragma unroll
             for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_half_add(gc[nt], pf, dv[nt], 1);
           } else {
@@ -863,7 +884,7 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
 #pragma unroll
           for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_add(gc[nt], pf, dv[nt]);
         }
-        if (Cfg::SHARE_MASKED && rg == 1) {
+        if (Cfg::HALF_VISIBLE && rg == 1) {
 #pragma unroll
           for (int nt = 0; nt < NKT; ++nt) dk[nt] = mma16_half_add(qc[nt], af, dk[nt], 1);
         } else {
@@ -888,8 +909,8 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     }
     project_out_row<NKT, false>(dk, xv, t, rj, inv_eps);
     if (CS == 1) wave_lds_sync();  // own Ks / Vs rows (kf, vf, raw k) were read before the staging writes
-    gather_rows_transposed<DK, NKT>(dk, scale * rj, Ks + 16 * rg * TPK, l, done_k, colk);
-    gather_rows_transposed<DV, NVT>(dv, scale * rj, Vs + 16 * rg * TPV, l, done_v, colv);
+    gather_rows_transposed<DK, NKT>(dk, scale * rj, Ks + 16 * rg * TPK, l, done_k, un, colk);
+    gather_rows_transposed<DV, NVT>(dv, scale * rj, Vs + 16 * rg * TPV, l, done_v, un, colv);
     __syncthreads();
     done_dK = dKu;
     done_dV = dVu;
@@ -926,8 +947,18 @@ __global__ __launch_bounds__(C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)) 
     zero_rows<DV>(dVu, row_end, piece_end);
   }
   if (rev_out != nullptr && row_begin == 0 && AT::active(rg, cp)) store_rev_out();
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<Cfg::NW>(rk)) {
+    using Whole = f32w::BwdCfg<DK, DV, C, CS>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
+    void* const room[] = {Qs, Ks, Vs, Gs, Rl, rk, xdot};
+    f32w::bwd_dkdv_scan<DK, DV, C, CS, WALK>(room, Q, K, V, dO, s, dK, dV, rev_states, ds_partial, ds, B, H, N, G, seg_rows,
+                                             inv_eps, sum_totals, lengths, s_per_unit, rev_in, rev_out, unit_rows);
+  }
+#endif
 }
 
+#ifndef COTTN_REDO
 template <int DK, int DV, int C, int CR = BwdSplit<DK, DV, C>::CR, int CS = BwdSplit<DK, DV, C>::CS>
 hipError_t run_bwd_causal(const CausalArgs& a) {
   using Cfg = BwdCfg<DK, DV, CR, CS>;
@@ -1008,8 +1039,13 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
                                   : dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, EVEN_PADDED>, Cfg::NT);
   return dkdv_scan(COTTN_SYM(bwd_dkdv_scan)<DK, DV, CR, CS, SEGMENTS>, Cfg::NT);
 }
+#endif  // COTTN_REDO
 
 }  // namespace
+}  // namespace COTTN_NS
+
+#ifndef COTTN_REDO
+using namespace COTTN_NS;
 
 #if !defined(COTTN_ELEM_F16) && !defined(COTTN_ELEM_F32)  // not specific to the element type
 hipError_t launch_bwd_state_carry(float* fwd_tot, float* rev_tot, int units, int G, int elems,
@@ -1061,5 +1097,7 @@ hipError_t COTTN_SYM(bwd_causal)(const CausalArgs& a) {
   }
 #endif
 }
+
+#endif  // COTTN_REDO
 
 }  // namespace cottn

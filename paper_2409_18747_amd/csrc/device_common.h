@@ -7,21 +7,40 @@
 // including anything, fp32 with COTTN_ELEM_F32 (the *_f16.hip and *_f32.hip files do exactly
 // that and then include the kernel source).  fp32 comes in two ways, see SPLIT3 below.
 // COTTN_SYM(name) appends the element's suffix to kernel and launcher names.
-#pragma once
+//
+// No include guard: a translation unit includes this once for each way it computes in, each time in a
+// namespace of its own (COTTN_NS).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#undef COTTN_NS
+#undef COTTN_SYM
+#undef COTTN_SYM_STR
+#undef COTTN_ELEM_SYM
+#undef COTTN_SPLIT3
+#if defined(COTTN_ELEM_F32) && defined(COTTN_F32_WHOLE)
+#define COTTN_NS f32w
+#elif defined(COTTN_ELEM_F32)
+#define COTTN_NS f32
+#elif defined(COTTN_ELEM_F16)
+#define COTTN_NS f16
+#else
+#define COTTN_NS bf16
+#endif
+
 namespace cottn {
+namespace COTTN_NS {
 
 // fp32 elements: how their products are formed.
 //   SPLIT3  every operand in three bfloat16 parts x = x0 + x1 + x2 (each the rest rounded to
-//           nearest: the sum is x exactly), six of the nine products of parts on the bf16 matrix
-//           instruction.  Left out are x1 y2, x2 y1 and x2 y2: at most 2^-25 of a product, 2^-28
-//           in the root mean square, where an fp32 addition rounds to 2^-25.  The bf16 rate is
-//           sixteen times the fp32 one, so this takes 6/16 of the time, and the operands that are
-//           contracted over the tokens can take the transposing LDS read.
-//           Range: an element above 3.38e38 rounds to infinity, and an infinite one makes what it
-//           enters NaN (infinity less itself is its second part).
+//           nearest: from 2^-110 up to 3.38e38 the sum is x exactly), six of the nine products of
+//           parts on the bf16 matrix instruction.  Left out are x1 y2, x2 y1 and x2 y2: together just
+//           under 2^-24 of a product at most, 2^-27.4 in the root mean square of normal values, where
+//           an fp32 addition rounds to 2^-24 at most.  The bf16 rate is sixteen times the fp32 one, so
+//           this takes 6/16 of the time, and the operands that are contracted over the tokens can take
+//           the transposing LDS read.
+//           Beyond that range, and where something is infinite or not a number, the workgroup that
+//           meets it does its work again with whole products (Unparted).
 //   else    the fp32 matrix instruction (COTTN_F32_WHOLE: the *_f32w.hip files), where the parts do
 //           not fit the LDS (128 x 128) or fit it for one causal workgroup instead of two (128 x 32
 //           and 32 x 128: B4 H8 N2048 forward + backward 121 / 140 and 108 / 123 us, whole / parts), and
@@ -89,6 +108,7 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
+#undef COTTN_LDS
 #define COTTN_LDS __attribute__((address_space(3)))
 
 // Where column c of a row lies in an LDS tile or state copy.  SPLIT3: every 32 columns are 32
@@ -153,6 +173,21 @@ __device__ __forceinline__ f32x4 mma16(frag8 a, frag8 b, f32x4 acc) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 #endif
 }
+
+// The kernels of the tile files are written once and are two things.  Kernels; and, with COTTN_REDO defined, functions
+// that a workgroup of the same kernel on parts calls to do its work again (Unparted), with their LDS arrays
+// where that kernel's are: room[at] for the array numbered `at`.
+#undef COTTN_KERNEL
+#undef COTTN_LDS_ARRAY
+#ifdef COTTN_REDO
+constexpr bool REDO = true;
+#define COTTN_KERNEL(bounds, name) __device__ __forceinline__ void name(void* const* room,
+#define COTTN_LDS_ARRAY(type, name, count, at) type* const name = static_cast<type*>(room[at]);
+#else
+constexpr bool REDO = false;
+#define COTTN_KERNEL(bounds, name) __global__ __launch_bounds__ bounds void COTTN_SYM(name)(
+#define COTTN_LDS_ARRAY(type, name, count, at) __shared__ __attribute__((aligned(16))) type name[count];
+#endif
 
 // The k slots of lane row g = lane / 16 in a fragment whose k index runs over 32 consecutive
 // columns (or rows) of an LDS tile: elements 0..3 at slot_lo(g).., elements 4..7 at
@@ -288,10 +323,67 @@ __device__ __forceinline__ void unpack2(uint32_t w, float& lo, float& hi) {
 #endif
 }
 #endif
+// SPLIT3: whether this wave parted a value that its parts fall short of, or left a result that is not finite.
+// The kernels ask at their end whether a wave of the workgroup did, which then does its work again with
+// whole products.  (Nothing to note elsewhere.)
+//   The lowest bit of a value lies 23 places below its first, and that of a bfloat16 number nowhere below 2^-133
+// (the matrix instruction takes subnormal ones as they are): parts are exact from 2^-110 on.  An infinite value,
+// and one that rounds to infinity, makes the results that it enters NaN.
+//   Four packed 16-bit instructions to four values, written out: the compiler makes the comparisons long before
+// it adds them up, in registers that the scans do not have.  With them and what follows from them, against no regard
+// to the range, forward + backward: B8 H12 N1024 d64 117 -> 119 us (with a comparison of the rest and a scalar
+// instruction to each value 123), 64 units of 2048 rows 145 -> 153, 300 of 1000 at 64 x 128 660 -> 703, whose dQ
+// scan in even shares pays most, 200 -> 227.
+struct Unparted {
 #ifdef COTTN_SPLIT3
-// x[0..3] as their three parts, two to a word: parts[i] holds the i-th ones
-__device__ __forceinline__ void split4(const float (&x)[4], uint2 (&parts)[3]) {
-  float rest[4] = {x[0], x[1], x[2], x[3]};
+  uint32_t least = 0xFFFFFFFFu;   // of each half, 2 |first part| - 1 as bits: 0 is the largest
+  bool not_finite = false;
+  __device__ __forceinline__ void first_parts(uint2 pairs) {
+    uint32_t a, b;
+    asm("v_pk_mad_u16 %1, %3, 2, -1 op_sel_hi:[1,0,0]\n\tv_pk_mad_u16 %2, %4, 2, -1 op_sel_hi:[1,0,0]\n\t"
+        "v_pk_min_u16 %0, %0, %1\n\tv_pk_min_u16 %0, %0, %2"
+        : "+v"(least), "=&v"(a), "=&v"(b) : "v"(pairs.x), "v"(pairs.y));
+  }
+  template <int TILES>
+  __device__ __forceinline__ void results(const f32x4* t, float factor = 1.f) {   // factor times the tiles
+    float largest = 0.f;   // NaN if one is
+#pragma unroll
+    for (int i = 0; i < TILES; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) largest = __builtin_elementwise_maximum(largest, fabsf(t[i][v]));
+    not_finite |= __any(!(largest * fabsf(factor) < __builtin_inff()));
+  }
+  // scratch: LDS that no wave reads or writes any more
+  template <int NW>
+  __device__ __forceinline__ bool in_workgroup(void* scratch) const {
+    int* met = static_cast<int*>(scratch);
+    constexpr uint32_t LIMIT = 2 * ((127 - 110) << 7) - 1;
+    const bool here = __any(not_finite || (least & 0xFFFFu) < LIMIT || (least >> 16) < LIMIT);
+    if (threadIdx.x % 64 == 0) met[threadIdx.x / 64] = here;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");   // (no wait for the stores of results)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) any |= met[i];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any) == 0, 1)) return false;
+    __threadfence();   // what this workgroup stored is in place before it stores again
+    __syncthreads();
+    return true;
+  }
+#else
+  template <int TILES>
+  __device__ __forceinline__ void results(const f32x4*, float = 1.f) {}
+#endif
+};
+#ifdef COTTN_SPLIT3
+// x[0..3] as their three parts, two to a word: parts[i] holds the i-th ones.  SCALED: the parts of f x[0..3], of
+// the products as they are before rounding (the last part is rounded).
+template <bool SCALED = false>
+__device__ __forceinline__ void split4(const float (&x)[4], uint2 (&parts)[3], Unparted& un, float f = 1.f) {
+  float rest[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) rest[e] = SCALED ? f * x[e] : x[e];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     parts[i] = uint2{pack2(rest[0], rest[1]), pack2(rest[2], rest[3])};
@@ -300,8 +392,9 @@ __device__ __forceinline__ void split4(const float (&x)[4], uint2 (&parts)[3]) {
     unpack2(parts[i].x, p[0], p[1]);
     unpack2(parts[i].y, p[2], p[3]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) rest[e] -= p[e];   // exact
+    for (int e = 0; e < 4; ++e) rest[e] = SCALED && i == 0 ? __builtin_fmaf(f, x[e], -p[e]) : rest[e] - p[e];
   }
+  un.first_parts(parts[0]);
 }
 #endif
 #ifndef COTTN_ELEM_F32
@@ -338,11 +431,11 @@ __device__ __forceinline__ void load4(const elem_t* src, float* f) {
 #endif
 }
 // The same four in an LDS tile or state copy.
-__device__ __forceinline__ void store4_lds(lds_t* dst, float a, float b, float c, float d) {
+__device__ __forceinline__ void store4_lds(lds_t* dst, float a, float b, float c, float d, Unparted& un) {
 #ifdef COTTN_SPLIT3
   const float x[4] = {a, b, c, d};
   uint2 parts[3];
-  split4(x, parts);
+  split4(x, parts, un);
 #pragma unroll
   for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(dst + PART * i) = parts[i];
 #else
@@ -364,15 +457,6 @@ __device__ __forceinline__ void load4_lds(const lds_t* src, float* f) {
   load4(src, f);
 #endif
 }
-// a 16-byte piece of a row to its place in an LDS tile
-__device__ __forceinline__ void store_piece_lds(lds_t* dst, uint4 raw) {
-#ifdef COTTN_SPLIT3
-  store4_lds(dst, __builtin_bit_cast(float, raw.x), __builtin_bit_cast(float, raw.y),
-             __builtin_bit_cast(float, raw.z), __builtin_bit_cast(float, raw.w));
-#else
-  *reinterpret_cast<uint4*>(dst) = raw;
-#endif
-}
 // a 16-byte piece of a row (EPP elements): its sum of squares, and the piece times a factor
 __device__ __forceinline__ float piece_sum_sq(uint4 raw) {
   const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
@@ -381,7 +465,7 @@ __device__ __forceinline__ float piece_sum_sq(uint4 raw) {
   for (int e = 0; e < 4; ++e) {
 #ifdef COTTN_ELEM_F32
     const float x = __builtin_bit_cast(float, w[e]);
-    ss += x * x;
+    ss = __builtin_fmaf(x, x, ss);
 #else
     ss = dot2_self(w[e], ss);
 #endif
@@ -402,15 +486,29 @@ __device__ __forceinline__ uint4 piece_times(uint4 raw, float f) {
   }
   return uint4{w[0], w[1], w[2], w[3]};
 }
+// such a piece, or the piece times a factor, to its place in an LDS tile
+template <bool SCALED>
+__device__ __forceinline__ void store_piece_lds(lds_t* dst, uint4 raw, float f, Unparted& un) {
+#ifdef COTTN_SPLIT3
+  const float x[4] = {__builtin_bit_cast(float, raw.x), __builtin_bit_cast(float, raw.y), __builtin_bit_cast(float, raw.z),
+                      __builtin_bit_cast(float, raw.w)};
+  uint2 parts[3];
+  split4<SCALED>(x, parts, un, f);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(dst + PART * i) = parts[i];
+#else
+  *reinterpret_cast<uint4*>(dst) = SCALED ? piece_times(raw, f) : raw;
+#endif
+}
 
 // Fills half of an operand fragment with a masked accumulator tile: the tile's element [v] of
 // lane row g is k slot 16 half + 4 g + v of the fragment.
 __device__ __forceinline__ void put_half(frag8& frag, int half, f32x4 acc, bool k0, bool k1,
-                                         bool k2, bool k3) {
+                                         bool k2, bool k3, Unparted& un) {
 #if defined(COTTN_SPLIT3)
   const float x[4] = {k0 ? acc[0] : 0.f, k1 ? acc[1] : 0.f, k2 ? acc[2] : 0.f, k3 ? acc[3] : 0.f};
   uint2 parts[3];
-  split4(x, parts);
+  split4(x, parts, un);
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     u32x4 words = __builtin_bit_cast(u32x4, frag.part[i]);
@@ -658,4 +756,5 @@ __device__ __forceinline__ void row_inv_norms(const float (&sum_sq)[PASSES], flo
   }
 }
 
+}  // namespace COTTN_NS
 }  // namespace cottn

@@ -42,6 +42,7 @@
 #include "tile_io.h"
 
 namespace cottn {
+namespace COTTN_NS {
 namespace {
 
 // DK, DV: the head dimensions of the keys / queries and of the values / outputs (Sec. 2.1:
@@ -103,7 +104,7 @@ template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
 // path uses it for Kh^T V (row-major slots, TILED = false; the causal scans read theirs tile
 // by tile, TILED = true).
 template <int DK, int DV, int C, bool TILED>
-__global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
+COTTN_KERNEL((C * 4), fwd_segment_state)
     const elem_t* __restrict__ K, const elem_t* __restrict__ V, float* __restrict__ seg_state,
     int N, int n_slots, int n_compute, int seg_rows, float inv_eps,
     const int* __restrict__ seq_len, int H, int units, int unit_rows) {
@@ -111,9 +112,10 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
-  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];
-  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];
+  COTTN_LDS_ARRAY(lds_t, Ks, Cfg::TILEK, 0)
+  COTTN_LDS_ARRAY(lds_t, Vs, Cfg::TILEV, 1)
 
+  Unparted un;
   fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H, units, unit_rows);
   const Span span = unit_rows == 0 ? span_of_workgroup<false, false>(units, N, n_slots, seg_rows, 0)
                                    : span_of_workgroup<true, true>(units, N, n_slots, seg_rows, unit_rows);
@@ -140,9 +142,11 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
   StageV vst;
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
-  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, row_begin, row_end, inv_eps, w, l);
+  add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, row_begin, row_end, inv_eps, w, l, un);
   if (ST::active(w)) {
     float* out = seg_state + size_t(span.slot) * DK * DV;
+#pragma unroll
+    for (int x = 0; x < ST::NCT; ++x) un.results<ST::NRT>(acc[x]);
 #pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
@@ -151,11 +155,22 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_segment_state)(
                                        : (16 * ST::row_tile(w, y) + r) * DV + 16 * ST::col_tile(w, x) + 4 * q4),
                           acc[x][y]);
   }
+#ifdef COTTN_SPLIT3
+  __syncthreads();
+  if (un.in_workgroup<Cfg::NW>(Ks)) {
+    using Whole = f32w::FwdCfg<DK, DV, C>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV, "whole rows fit");
+    void* const room[] = {Ks, Vs};
+    f32w::fwd_segment_state<DK, DV, C, TILED>(room, K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len,
+                                              H, units, unit_rows);
+  }
+#endif
 }
 
 // ---------------------------------------------------------------------------------------
 // Kernel 2: in place, per (unit, element): slot g <- sum of slots < g (exclusive prefix
 // along the segment axis); slot n_slots-1 never held a total and only receives its prefix.
+#ifndef COTTN_REDO
 __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_state, int n_slots,
                                                        int elems_per_state, long total) {
   const long idx = (long(blockIdx.x) * 256 + threadIdx.x) * 4;  // 4 elements per thread
@@ -164,6 +179,7 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
   exclusive_running_sum(seg_state + unit * n_slots * elems_per_state + e, n_slots,
                         size_t(elems_per_state), false);
 }
+#endif
 
 // ---------------------------------------------------------------------------------------
 // Kernel 3: the chunk scan of one segment.
@@ -181,7 +197,7 @@ __global__ __launch_bounds__(256) void fwd_state_carry(float* __restrict__ seg_s
 // LDV > DV (one segment): a workgroup takes DV of the LDV value columns, which the whole computation
 // leaves apart from one another but for the masked tiles; those are formed LDV / DV times.
 template <int DK, int DV, int C, int CS, int WALK, int LDV = DV>
-__global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())) void COTTN_SYM(fwd_causal_scan)(
+COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd_causal_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
     float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
@@ -196,16 +212,17 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   using StageV = TileStage<DV, C, Cfg::NT * CS, LDV>;
   constexpr int TPK = Cfg::TPK, TPV = Cfg::TPV, SP = Cfg::SP;
   constexpr bool OWN_STAGE = CS > 1 || Cfg::OWN_STAGE;
-  __shared__ __attribute__((aligned(16))) lds_t Qs[Cfg::TILEK];   // raw q rows
-  __shared__ __attribute__((aligned(16))) lds_t Ks[Cfg::TILEK];   // kh = r_j k_j
-  __shared__ __attribute__((aligned(16))) lds_t Vs[Cfg::TILEV];   // raw v rows
-  __shared__ __attribute__((aligned(16))) lds_t Sl[Cfg::STATE];   // state, [d_key][d_value]
+  COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)   // raw q rows
+  COTTN_LDS_ARRAY(lds_t, Ks, Cfg::TILEK, 1)   // kh = r_j k_j
+  COTTN_LDS_ARRAY(lds_t, Vs, Cfg::TILEV, 2)   // raw v rows
+  COTTN_LDS_ARRAY(lds_t, Sl, Cfg::STATE, 3)   // state, [d_key][d_value]
   // with two waves on a row group the q rows stay live in the other wave, and with outputs
   // wider than the queries they do not fit the q rows: own staging tile
-  __shared__ __attribute__((aligned(16))) elem_t Os[OWN_STAGE ? C * Cfg::OP : 8];
-  __shared__ float rq[C];
-  constexpr bool SHARE_MASKED = F32_WHOLE && CS == 2 && C == 32;
+  COTTN_LDS_ARRAY(elem_t, Os, OWN_STAGE ? C * Cfg::OP : 8, 4)
+  COTTN_LDS_ARRAY(float, rq, C, 5)
+  constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
+  Unparted un;
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, lengths, s_per_unit, stream_q, stream_kv, units, unit_rows);
   const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
@@ -268,6 +285,8 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   const auto store_final = [&] {
     float* out = state_out + size_t(unit) * DK * LDV + part * DV;
 #pragma unroll
+    for (int x = 0; x < ST::NCT; ++x) un.results<ST::NRT>(sacc[x]);
+#pragma unroll
     for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
       for (int y = 0; y < ST::NRT; ++y)
@@ -282,9 +301,12 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
       add_rows_before<DK, DV, C, Cfg::NT * CS, ST::NCT, ST::NRT, LDV>(
           Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, ST::active(rg, cp),
           [&](int x) { return ST::col_tile(rg, cp, x); }, [&](int y) { return ST::row_tile(rg, cp, y); },
-          [&](int x, int y, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); });
+          [&](int x, int y, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); },
+          un);
       // for the backward, where a carry launch would have left it
       if (ST::active(rg, cp)) {
+#pragma unroll
+        for (int x = 0; x < ST::NCT; ++x) un.results<ST::NRT>(sacc[x]);
 #pragma unroll
         for (int x = 0; x < ST::NCT; ++x)
 #pragma unroll
@@ -321,17 +343,17 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
 #pragma unroll
         for (int y = 0; y < ST::NRT; ++y) {
           store4_lds(Sl + (16 * ST::col_tile(rg, cp, x) + r) * SP + lds_col(16 * ST::row_tile(rg, cp, y)) + 4 * q4,
-                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3]);
+                     sacc[x][y][0], sacc[x][y][1], sacc[x][y][2], sacc[x][y][3], un);
         }
     }
     {
       float rk[StageK::PASSES], rqv[StageK::PASSES];
       qst.row_rinv(inv_eps, rqv);
       kst.row_rinv(inv_eps, rk);
-      qst.commit_plain(Qs);
+      qst.commit_plain(Qs, un);
       qst.store_rinv(rq, rqv);
-      kst.commit_scaled(Ks, rk);
-      vst.commit_plain(Vs);
+      kst.commit_scaled(Ks, rk, un);
+      vst.commit_plain(Vs, un);
     }
     // the next step's rows: of this unit, or the first ones of the next
     const bool cross = EVEN && left > 0 && row0 + C >= row_end;
@@ -423,9 +445,9 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
           // pacc[v] = q_(16 rg + r) . k_(16jt + 4*q4 + v); keep key <= query
           const bool full = jt < rg, diag = jt == rg;
           put_half(pf, half, pacc, full || (diag && 4 * q4 + 0 <= r), full || (diag && 4 * q4 + 1 <= r),
-                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r));
+                   full || (diag && 4 * q4 + 2 <= r), full || (diag && 4 * q4 + 3 <= r), un);
         }
-        if (SHARE_MASKED && rg == 0) {
+        if (HALF_VISIBLE && rg == 0) {
 #pragma unroll
           for (int nt = 0; nt < NOT; ++nt) oacc[nt] = mma16_half_add(vc[nt], pf, oacc[nt], 0);
         } else {
@@ -447,7 +469,7 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
     // through its part of the staging tile
     const float row_factor = scale * rq[16 * rg + r];
     wave_lds_sync();
-    gather_rows_transposed<DV, NOT>(oacc, row_factor, stage, l, finished, col0);
+    gather_rows_transposed<DV, NOT>(oacc, row_factor, stage, l, finished, un, col0);
     __syncthreads();  // all reads of Ks, Vs, Sl done before the next chunk overwrites them
     done_O = Ou;
     done_row = row0;
@@ -477,8 +499,21 @@ __global__ __launch_bounds__(C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_
   if (seq_len != nullptr) zero_rows<DV, LDV>(Ou, row_end, piece_end);  // rows that do not exist
 
   if (state_out != nullptr && piece_end == N && ST::active(rg, cp)) store_final();
+#ifdef COTTN_SPLIT3
+  if (un.in_workgroup<RG * CS>(rq)) {
+    using Whole = f32w::FwdCfg<DK, DV, C>;
+    static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE &&
+                      CS == 2 && Whole::OP == Cfg::OP,
+                  "whole rows fit, and finished ones are staged alike");
+    void* const room[] = {Qs, Ks, Vs, Sl, Os, rq};
+    f32w::fwd_causal_scan<DK, DV, C, CS, WALK, LDV>(room, Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows,
+                                                    inv_eps, sum_totals, lengths, s_per_unit, stream_q, stream_kv, units,
+                                                    unit_rows);
+  }
+#endif
 }
 
+#ifndef COTTN_REDO
 template <int DK, int DV, int C>
 hipError_t run_fwd_causal(const CausalArgs& a) {
   const int units = a.B * a.H;
@@ -540,8 +575,13 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
     if (a.own_prefix) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX>, threads);
   return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, SEGMENTS>, threads);
 }
+#endif  // COTTN_REDO
 
 }  // namespace
+}  // namespace COTTN_NS
+
+#ifndef COTTN_REDO
+using namespace COTTN_NS;
 
 template <int DK, int DV, bool TILED>
 static hipError_t run_segment_totals(const SegmentTotalsArgs& t) {
@@ -647,5 +687,7 @@ hipError_t COTTN_SYM(fwd_causal)(const CausalArgs& a) {
   }
 #endif
 }
+
+#endif  // COTTN_REDO
 
 }  // namespace cottn

@@ -9,6 +9,7 @@
 #include "launch.h"
 
 namespace cottn {
+using namespace COTTN_NS;
 namespace {
 
 __device__ __forceinline__ float sigmoid(float x) { return 1.0f / (1.0f + __expf(-x)); }

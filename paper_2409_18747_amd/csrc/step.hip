@@ -12,6 +12,7 @@
 #include "launch.h"
 
 namespace cottn {
+using namespace COTTN_NS;
 namespace {
 
 // q, k, v, o elements: float, or one of the two 16-bit types (converted with the compiler's

@@ -10,10 +10,10 @@
 // rescaled on its way into LDS (K in the forward and dQ passes, Q in the dK/dV pass).  A
 // rescaled row has norm at most 1, so this is safe in IEEE half precision too: no row is
 // ever multiplied by the factor of another row, which is 1/eps when that row is zero.
-#pragma once
-#include "device_common.h"
+// Included behind device_common.h, and as often.
 
 namespace cottn {
+namespace COTTN_NS {
 
 // A workgroup of NT threads moves a tile of C rows x D columns.  Each lane owns 16
 // consecutive bytes (EPP columns) of a row; D/EPP neighbouring lanes share a row, so a
@@ -81,25 +81,25 @@ struct TileStage {
     }
   }
 
-  __device__ __forceinline__ void commit_plain(lds_t* tile) const {
+  __device__ __forceinline__ void commit_plain(lds_t* tile, Unparted& un) const {
     const int tid = threadIdx.x;
     const int col = lds_col((tid % LPR) * EPP);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
-      if (C % RPP == 0 || lr < C) store_piece_lds(tile + lr * tile_pitch(D, C) + col, regs[p]);
+      if (C % RPP == 0 || lr < C) store_piece_lds<false>(tile + lr * tile_pitch(D, C) + col, regs[p], 1.f, un);
     }
   }
 
   // tile[lr][:] = scale[p] * row, rounded to the element type
-  __device__ __forceinline__ void commit_scaled(lds_t* tile, const float* scale) const {
+  __device__ __forceinline__ void commit_scaled(lds_t* tile, const float* scale, Unparted& un) const {
     const int tid = threadIdx.x;
     const int col = lds_col((tid % LPR) * EPP);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int lr = p * RPP + tid / LPR;
       if (C % RPP == 0 || lr < C)
-        store_piece_lds(tile + lr * tile_pitch(D, C) + col, piece_times(regs[p], scale[p]));
+        store_piece_lds<true>(tile + lr * tile_pitch(D, C) + col, regs[p], scale[p], un);
     }
   }
 };
@@ -212,15 +212,15 @@ template <int DK, int DV, int C, int NT, class ST = AccTiles<DK, DV, NT / 64>>
 __device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT], TileStage<DK, C, NT>& kst,
                                                   TileStage<DV, C, NT>& vst, lds_t* Ks, lds_t* Vs,
                                                   const elem_t* __restrict__ Ku, const elem_t* __restrict__ Vu,
-                                                  int row_begin, int row_end, float inv_eps, int w, int l) {
+                                                  int row_begin, int row_end, float inv_eps, int w, int l, Unparted& un) {
   constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);
   const int r = l % 16, q4 = l / 16;
   for (int row0 = row_begin; row0 < row_end; row0 += C) {
     float rk[TileStage<DK, C, NT>::PASSES];
     kst.row_rinv(inv_eps, rk);
     __syncthreads();  // previous chunk's reads of Ks/Vs are done
-    kst.commit_scaled(Ks, rk);
-    vst.commit_plain(Vs);
+    kst.commit_scaled(Ks, rk, un);
+    vst.commit_plain(Vs, un);
     if (row0 + C < row_end) {
       kst.fetch(Ku, row0 + C, row_end);
       vst.fetch(Vu, row0 + C, row_end);
@@ -253,7 +253,8 @@ __device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT]
 template <int DK, int DV, int C, int NT, int NK, int NV, int LDV, class KeyTile, class ValueTile, class Add>
 __device__ __forceinline__ void add_rows_before(lds_t* Ks, lds_t* Vs, const elem_t* __restrict__ Ku,
                                                 const elem_t* __restrict__ Vu, int n_rows, float inv_eps, int l,
-                                                bool active, KeyTile key_tile, ValueTile value_tile, Add add) {
+                                                bool active, KeyTile key_tile, ValueTile value_tile, Add add,
+                                                Unparted& un) {
   constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);
   const int r = l % 16, q4 = l / 16;
   TileStage<DK, C, NT> kst;
@@ -263,8 +264,8 @@ __device__ __forceinline__ void add_rows_before(lds_t* Ks, lds_t* Vs, const elem
   for (int row0 = 0; row0 < n_rows; row0 += C) {
     float rk[TileStage<DK, C, NT>::PASSES];
     kst.row_rinv(inv_eps, rk);
-    kst.commit_scaled(Ks, rk);
-    vst.commit_plain(Vs);
+    kst.commit_scaled(Ks, rk, un);
+    vst.commit_plain(Vs, un);
     if (row0 + C < n_rows) {
       kst.fetch(Ku, row0 + C, n_rows);
       vst.fetch(Vu, row0 + C, n_rows);
@@ -309,11 +310,12 @@ struct RowPieces {
 template <int D, int NTILES = D / 16>
 __device__ __forceinline__ void gather_rows_transposed(const f32x4* acc, float row_factor,
                                                        void* stage, int l,
-                                                       RowPieces<D, NTILES>& out, int col0 = 0) {
+                                                       RowPieces<D, NTILES>& out, Unparted& un, int col0 = 0) {
   using RP = RowPieces<D, NTILES>;
   constexpr int PITCH = stage_pitch(D);
   elem_t* stage_rows = static_cast<elem_t*>(stage);
   const int r = l % 16, q4 = l / 16;
+  un.results<NTILES>(acc, row_factor);
 #pragma unroll
   for (int nt = 0; nt < NTILES; ++nt) {
     store4(stage_rows + r * PITCH + col0 + 16 * nt + 4 * q4, row_factor * acc[nt][0],
@@ -387,4 +389,5 @@ __device__ __forceinline__ float project_out_row(f32x4* acc, const float (&xv)[N
   return NORMALISED ? t : rinv * t;
 }
 
+}  // namespace COTTN_NS
 }  // namespace cottn
