@@ -86,6 +86,9 @@ struct BwdCfg {
   // 128 x 128, where everything at once does not fit, and for fp32, whose products take so long
   // that one group's reads hide behind the other wave's.
   static constexpr bool PHASED = CS == 2 && (ELEM_IS_F32 || (DK == 128 && DV == 128));
+  // So does the 16-bit dK/dV scan at 32 x 128, whose eight tiles of dV leave 17 to 20 registers spilled
+  // otherwise: 512 units of 512 rows 53.3 -> 39.4 us, 96 of 1024 26.0 -> 18.5.
+  static constexpr bool DKDV_PHASED = PHASED || (!ELEM_IS_F32 && CS == 1 && DK == 32 && DV == 128);
   // masked tiles formed by the two waves of a row group together (MaskedExchange); 32-row chunks
   static constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
@@ -701,9 +704,11 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
       vst.fetch(Vu, next_row, next_end);
       gst.fetch(Gu, next_row, next_end);
     }
-    if (done_end > 0) {
-      store_row_pieces<DK, NKT>(done_k, done_dK, done_row + 16 * rg, done_end, l, colk);
-      store_row_pieces<DV, NVT>(done_v, done_dV, done_row + 16 * rg, done_end, l, colv);
+    if (EVEN ? done_end > 0 : row0 + C < row_end) {
+      store_row_pieces<DK, NKT>(done_k, EVEN ? done_dK : dKu, (EVEN ? done_row : row0 + C) + 16 * rg,
+                                EVEN ? done_end : row_end, l, colk);
+      store_row_pieces<DV, NVT>(done_v, EVEN ? done_dV : dVu, (EVEN ? done_row : row0 + C) + 16 * rg,
+                                EVEN ? done_end : row_end, l, colv);
     }
     __syncthreads();
 
@@ -822,7 +827,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
           put_masked(af, half, ta);
         }
         __builtin_amdgcn_sched_barrier(0);
-      } else if (Cfg::PHASED && diag_or_above) {
+      } else if (Cfg::DKDV_PHASED && diag_or_above) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           read_queries(half);
@@ -856,7 +861,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
             racc[x][y] = mma16_add(AT::ROW_OPERAND_IS_RESULT_COLUMN ? gc[y] : grow[y], qcol[x], racc[x][y]);
       }
       if (diag_or_above) {
-        if (Cfg::PHASED) {
+        if (Cfg::DKDV_PHASED) {
           if (Cfg::HALF_VISIBLE && rg == 1) {
 #pragma unroll
             for (int nt = 0; nt < NVT; ++nt) dv[nt] = mma16_half_add(gc[nt], pf, dv[nt], 1);
@@ -938,9 +943,11 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
     row0 = next_row;
     row_end = next_end;
   }
-  if (done_end > 0) {
-    store_row_pieces<DK, NKT>(done_k, done_dK, done_row + 16 * rg, done_end, l, colk);
-    store_row_pieces<DV, NVT>(done_v, done_dV, done_row + 16 * rg, done_end, l, colv);
+  if (EVEN ? done_end > 0 : row_begin < row_end) {
+    store_row_pieces<DK, NKT>(done_k, EVEN ? done_dK : dKu, (EVEN ? done_row : row_begin) + 16 * rg,
+                              EVEN ? done_end : row_end, l, colk);
+    store_row_pieces<DV, NVT>(done_v, EVEN ? done_dV : dVu, (EVEN ? done_row : row_begin) + 16 * rg,
+                              EVEN ? done_end : row_end, l, colv);
   }
   if (seq_len != nullptr) {  // rows that do not exist
     zero_rows<DK>(dKu, row_end, piece_end);
