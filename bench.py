@@ -227,7 +227,9 @@ def run_d128(torch, cottn, workloads, cpu):
     return {"ms_per_step": ms, "tokens_per_s": B * N / (ms * 1e-3), "algorithmic_GBs": byt / ms / 1e6,
             "frac_of_hbm_peak": byt / ms / 1e6 / HBM_PEAK_GBS,
             "flops": flop_rates(B * H * N, d, chunk, ms * 1e-3),
+            # (where the call walks even shares instead of segments, the workspace has a state for each share)
             "segments": cottn.cottn_segments(cottn.OP_FWD_CAUSAL, B, H, N, d),
+            "state_slots": cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, H, N, d) // (4 * d * d),
             "kernels": kernel_times(cottn, d128, 50)}
 
 

@@ -92,6 +92,11 @@ size_t cottn_workspace_bytes(int op, int B, int H, int N, int d, int chunk, int 
 /* Number of sequence segments per (batch, head) the library will scan in parallel for
  * these arguments (1 = one serial chunk scan per (b, h)); 0 if unsupported.  Informational:
  * the chunked regrouping of the cumulative sum of eq. attn_2 is exact for any value.
+ * Where a causal call walks even shares of all sequences laid end to end instead (16-bit 128 x 128
+ * and fp32 64 and 128 wide, for numbers of sequences that segments would not spread evenly), a
+ * (batch, head) has no one number of pieces: the answer is that of the segments the shares were
+ * chosen over, which is what cottn_tune_segments(answer) makes run.  (The workspace has one state
+ * per share or per segment, whichever are more.)
  * cottn_tune_segments(g) forces the value for later calls made by the CALLING THREAD (g <= 0
  * restores the built-in heuristic); it is a knob for tests and tuning runs and the only state
  * the library keeps between calls besides the profiling totals below.  A backward call that is

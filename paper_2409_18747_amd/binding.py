@@ -207,6 +207,7 @@ def cottn_workspace_bytes(op, B, H, N, d, chunk=0, dtype=COTTN_BF16) -> int:
 
 
 def cottn_segments(op, B, H, N, d, chunk=0, dtype=COTTN_BF16) -> int:
+    """Segments per (batch, head); those that even shares were chosen over where a causal call walks shares."""
     return lib.cottn_segments(op, B, H, N, d, chunk, dtype)
 
 

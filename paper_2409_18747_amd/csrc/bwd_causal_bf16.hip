@@ -1012,7 +1012,9 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
                          inv_eps, sum_in_scan && !carried ? (a.marked && a.saved_fwd_states != nullptr ? 2 : 1) : 0, a.seq_len, a.s_per_unit, a.state_in,
                          units, a.unit_rows);
   };
-  constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32);
+  // (one wave per row group at 128 x 128 is for more workgroups than a split or shares ever make: threads_fit)
+  constexpr bool VERY_MANY = !ELEM_IS_F32 && DK == 128 && DV == 128 && CS == 1;
+  constexpr bool EVEN_BUILT = even_shares_built(DK, DV, ELEM_IS_F32) && !VERY_MANY;
   constexpr bool HALVED = !ELEM_IS_F32 && DK == 128 && DV == 128 && CR == 64 && CS == 2;
   if (HALVED && a.G == 1 && !even && two_to_a_cu_dq(a.workgroups)) {
     if constexpr (HALVED) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, 32, CS, false, SEGMENTS>, 256);
@@ -1021,7 +1023,7 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
       err = a.seq_len == nullptr ? dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT)
                                  : dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_PADDED>, Cfg::NT);
   } else if (rebuild) {
-    if constexpr (C <= 64) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
+    if constexpr (C <= 64 && !VERY_MANY) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
   } else {
     err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, SEGMENTS>, Cfg::NT);
   }
