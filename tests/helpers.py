@@ -7,6 +7,18 @@ import numpy as np
 TOL = {"f32": 1e-4, "bf16": 2e-2, "f16": 2.5e-3}
 
 
+def code(cottn, dtype):
+    return {"f32": cottn.COTTN_F32, "bf16": cottn.COTTN_BF16, "f16": cottn.COTTN_F16}[dtype]
+
+
+def draw_dkdv(B, H, N, dk, dv, dtype, seed):
+    """A workload with keys and values of different widths, out of one of the wider."""
+    from paper_2409_18747_amd import workloads
+    x = workloads.draw(B, H, N, max(dk, dv), dtype, seed)
+    return {"Q": x["Q"][..., :dk].copy(), "K": x["K"][..., :dk].copy(), "V": x["V"][..., :dv].copy(),
+            "dO": x["dO"][..., :dv].copy(), "s": x["s"]}
+
+
 def rel_err(got, ref):
     got = np.asarray(got, dtype=np.float64)
     ref = np.asarray(ref, dtype=np.float64)

@@ -5,7 +5,7 @@ bits, against the oracle's linear forms.  A shape that stops taking even shares 
 import numpy as np
 import pytest
 
-from helpers import TOL, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
+from helpers import TOL, code, draw_dkdv as draw, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 SHAPES = [("bf16", 8, 11, 700, 128, 128), ("f16", 8, 12, 820, 128, 128), ("bf16", 44, 12, 333, 128, 128),
@@ -19,17 +19,6 @@ def cottn():
     b.cottn_tune_segments(0)
     yield b
     b.cottn_tune_segments(0)
-
-
-def code(cottn, dtype):
-    return {"f32": cottn.COTTN_F32, "bf16": cottn.COTTN_BF16, "f16": cottn.COTTN_F16}[dtype]
-
-
-def draw(B, H, N, dk, dv, dtype, seed):
-    from paper_2409_18747_amd import workloads
-    x = workloads.draw(B, H, N, max(dk, dv), dtype, seed)
-    return {"Q": x["Q"][..., :dk].copy(), "K": x["K"][..., :dk].copy(), "V": x["V"][..., :dv].copy(),
-            "dO": x["dO"][..., :dv].copy(), "s": x["s"]}
 
 
 @pytest.mark.parametrize("dtype,B,H,N,dk,dv", SHAPES)

@@ -1,24 +1,32 @@
 """Short causal calls in segments whose workgroups form the state of the rows before them by themselves: both
-sides of the rule's line, the first and last segment of one step and a ragged one, a given start state, padded
+sides of the rule's line, by the launches that each call makes, the first and last segment of one step and a ragged one, a given start state, padded
 batches with lengths that end before, inside and behind a segment; forward, the states that it leaves to the
 backward, and the backward that rebuilds them, against the oracle's linear forms."""
 import numpy as np
 import pytest
 
-from helpers import TOL, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
+from helpers import TOL, code, draw_dkdv as draw, ds_terms_rss, rel_err, rel_err_ds, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 # rows before the last segment: at the line and beyond it, or the shortest that take segments; last, those
-# where only the forward does so, and the first ones beyond
-SHAPES = [("bf16", 1, 1, 130, 64, 64), ("f16", 2, 5, 640, 64, 64), ("bf16", 2, 5, 705, 64, 64), ("f16", 8, 5, 511, 64, 64),
-          ("bf16", 2, 5, 1023, 32, 32), ("f16", 10, 10, 513, 32, 32), ("bf16", 2, 1, 577, 128, 128),
-          ("bf16", 10, 10, 641, 128, 128), ("f16", 10, 10, 333, 128, 128), ("bf16", 10, 10, 321, 128, 32),
-          ("f16", 5, 8, 400, 32, 128), ("bf16", 3, 3, 257, 128, 64), ("f16", 2, 2, 777, 64, 128), ("bf16", 2, 5, 1023, 64, 32),
-          ("f32", 1, 1, 65, 32, 32), ("f32", 1, 2, 319, 32, 32),
-          ("f32", 1, 2, 321, 32, 32), ("f32", 10, 10, 129, 32, 32), ("f32", 1, 1, 33, 64, 64), ("f32", 10, 10, 130, 64, 64),
-          ("f32", 1, 2, 199, 64, 64), ("f32", 10, 10, 101, 128, 128), ("f32", 10, 10, 255, 64, 128), ("f32", 4, 1, 66, 128, 32),
-          ("bf16", 10, 10, 385, 64, 64), ("f16", 10, 15, 399, 128, 64), ("bf16", 12, 10, 640, 32, 128), ("f16", 12, 10, 577, 64, 128),
-          ("bf16", 12, 10, 705, 64, 64), ("bf16", 16, 5, 777, 128, 128), ("f16", 6, 10, 769, 128, 128), ("bf16", 6, 10, 1025, 128, 128)]
+# where only the forward does so, and the first ones beyond.  With each, which calls form their states
+# themselves: the forward and a backward that rebuilds them, the forward alone, or neither.
+SHAPES = [("bf16", 1, 1, 130, 64, 64, "both"), ("f16", 2, 5, 640, 64, 64, "both"),
+          ("bf16", 2, 5, 705, 64, 64, "neither"), ("f16", 8, 5, 511, 64, 64, "both"),
+          ("bf16", 2, 5, 1023, 32, 32, "both"), ("f16", 10, 10, 513, 32, 32, "neither"),
+          ("bf16", 2, 1, 577, 128, 128, "both"), ("bf16", 10, 10, 641, 128, 128, "both"),
+          ("f16", 10, 10, 333, 128, 128, "both"), ("bf16", 10, 10, 321, 128, 32, "both"),
+          ("f16", 5, 8, 400, 32, 128, "both"), ("bf16", 3, 3, 257, 128, 64, "both"),
+          ("f16", 2, 2, 777, 64, 128, "both"), ("bf16", 2, 5, 1023, 64, 32, "both"), ("f32", 1, 1, 65, 32, 32, "both"),
+          ("f32", 1, 2, 319, 32, 32, "both"), ("f32", 1, 2, 321, 32, 32, "neither"),
+          ("f32", 10, 10, 129, 32, 32, "both"), ("f32", 1, 1, 33, 64, 64, "both"),
+          ("f32", 10, 10, 130, 64, 64, "both"), ("f32", 1, 2, 199, 64, 64, "both"),
+          ("f32", 10, 10, 101, 128, 128, "both"), ("f32", 10, 10, 255, 64, 128, "both"),
+          ("f32", 4, 1, 66, 128, 32, "both"), ("bf16", 10, 10, 385, 64, 64, "forward"),
+          ("f16", 10, 15, 399, 128, 64, "forward"), ("bf16", 12, 10, 640, 32, 128, "forward"),
+          ("f16", 12, 10, 577, 64, 128, "forward"), ("bf16", 12, 10, 705, 64, 64, "forward"),
+          ("bf16", 16, 5, 777, 128, 128, "forward"), ("f16", 6, 10, 769, 128, 128, "forward"),
+          ("bf16", 6, 10, 1025, 128, 128, "neither")]
 
 
 @pytest.fixture(scope="module")
@@ -29,19 +37,8 @@ def cottn():
     b.cottn_tune_segments(0)
 
 
-def code(cottn, dtype):
-    return {"f32": cottn.COTTN_F32, "bf16": cottn.COTTN_BF16, "f16": cottn.COTTN_F16}[dtype]
-
-
-def draw(B, H, N, dk, dv, dtype, seed):
-    from paper_2409_18747_amd import workloads
-    x = workloads.draw(B, H, N, max(dk, dv), dtype, seed)
-    return {"Q": x["Q"][..., :dk].copy(), "K": x["K"][..., :dk].copy(), "V": x["V"][..., :dv].copy(),
-            "dO": x["dO"][..., :dv].copy(), "s": x["s"]}
-
-
-@pytest.mark.parametrize("dtype,B,H,N,dk,dv", SHAPES)
-def test_against_oracle(cottn, oracle, dtype, B, H, N, dk, dv):
+@pytest.mark.parametrize("dtype,B,H,N,dk,dv,own", SHAPES)
+def test_against_oracle(cottn, oracle, dtype, B, H, N, dk, dv, own):
     import torch
     c = code(cottn, dtype)
     assert cottn.cottn_segments_dkdv(cottn.OP_BWD_CAUSAL, B, H, N, dk, dv, 0, c) > 1
@@ -51,9 +48,15 @@ def test_against_oracle(cottn, oracle, dtype, B, H, N, dk, dv):
     ws, bws = (torch.full((cottn.cottn_workspace_bytes_dkdv(op, B, H, N, dk, dv, 0, c),), 255, dtype=torch.uint8, device="cuda")
                for op in (cottn.OP_FWD_CAUSAL, cottn.OP_BWD_CAUSAL))   # (NaN wherever nothing is written)
     state = torch.full((B, H, dk, dv), float("nan"), dtype=torch.float32, device="cuda")
+    cottn.profile_start()
     O = cottn.cottn_fwd_causal_dkdv(Q, K, V, s, state=state, workspace=ws)
+    forward = cottn.profile_stop()
     grads = cottn.cottn_bwd_causal_dkdv(Q, K, V, s, dO, workspace=bws, fwd_workspace=ws)
+    cottn.profile_start()
     rebuilt = cottn.cottn_bwd_causal_dkdv(Q, K, V, s, dO, workspace=bws.fill_(255))
+    for names, itself in ((forward, own != "neither"), (cottn.profile_stop(), own == "both")):
+        assert any(n.startswith("fwd_segment_state") for n in names) != itself, sorted(names)
+    assert own == "neither" or len(forward) == 1
     ref, S = oracle.fwd_recurrent(x["Q"], x["K"], x["V"], x["s"])
     g_ref = oracle.bwd_recurrent(x["Q"], x["K"], x["V"], x["s"], x["dO"])
     errs = {"O": rel_err(to_host(O), ref), "state": rel_err(to_host(state), S)}

@@ -98,6 +98,34 @@ def test_causal_totals_of_sixteen_units(cottn, oracle, dtype, segments, launch):
     assert _sums_launched(cottn) == launch
 
 
+# (width, units, segments, steps of a segment, whether carry launches add up): both sides of the same lines with so
+# many rows before the last segment that no call forms its state from them
+@pytest.mark.parametrize("d,units,segments,steps,carry", [(64, 2, 5, 2, False), (64, 2, 18, 2, False), (64, 2, 19, 2, True),
+                                                          (128, 2, 4, 5, False), (128, 2, 5, 2, True), (128, 16, 7, 2, False),
+                                                          (128, 16, 8, 2, True), (32, 2, 17, 2, False)])
+def test_causal_totals_of_long_segments(cottn, oracle, d, units, segments, steps, carry):
+    for dtype, saved in (("bf16", True), ("f16", False)):
+        N = 64 * steps * segments - 5
+        cottn.profile_start()
+        run_shape(cottn, oracle, True, 2, units // 2, N, d, d, dtype, seed=1460 + d + segments, segments=segments, saved=saved)
+        names = set(cottn.profile_stop())
+        assert "fwd_segment_state_" + dtype in names
+        assert ("fwd_state_carry" in names) == carry and ("bwd_state_carry" in names) == carry
+
+
+# fp32 steps are 32 rows; at 128 x 128 and 16 units the line lies further, and two segments of any length start from
+# their own prefix up to 224 rows
+@pytest.mark.parametrize("d,units,segments,steps,carry", [(64, 2, 5, 3, False), (64, 2, 18, 2, False), (64, 2, 19, 2, True),
+                                                          (128, 2, 4, 1, False), (128, 16, 10, 1, False), (128, 16, 11, 1, True)])
+def test_causal_totals_of_long_segments_f32(cottn, oracle, d, units, segments, steps, carry):
+    N = 32 * steps * segments - 5
+    cottn.profile_start()
+    run_shape(cottn, oracle, True, 2, units // 2, N, d, d, "f32", seed=1480 + d + segments, segments=segments, saved=False)
+    names = set(cottn.profile_stop())
+    assert "fwd_segment_state_f32" in names
+    assert ("fwd_state_carry" in names) == carry and ("bwd_state_carry" in names) == carry
+
+
 @pytest.mark.parametrize("d,segments,launch", [(64, 5, False), (64, 24, False), (64, 25, True), (128, 10, False),
                                                (128, 11, True), (32, 17, False)])
 def test_bidirectional_totals_added_in_place_or_combined(cottn, oracle, d, segments, launch):

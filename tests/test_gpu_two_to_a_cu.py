@@ -1,6 +1,7 @@
 """16-bit causal 128 x 128 calls of more than 256 workgroups, whose scans take 32-row steps: one segment
-(no reverse-time totals) and several, lengths around the ends of the steps, padded batches and a sequence
-continued from a state, against the oracle at the usual tolerance."""
+(no reverse-time totals) and several that start from totals, lengths around the ends of the steps, padded
+batches and a sequence continued from a state, against the oracle at the usual tolerance.  (Of two and three
+segments, calls with few rows before the last one form its state themselves, in 64-row steps.)"""
 import numpy as np
 import pytest
 
@@ -84,3 +85,44 @@ def test_padded(cottn, oracle):
             for r, t in zip(ref[1:], oracle.bwd_quadratic(*a[:3], sc[b], a[3])[:3]):
                 r[b, :, :m] = t
     check({k: rel_err(t, r) for k, t, r in zip(("O", "dQ", "dK", "dV"), [O] + g[:3], ref)}, dtype, "padded")
+
+
+# (sequences, rows, segments): more than 256 workgroups and more than 320 rows before the last segment
+FROM_TOTALS = [(130, 700, 2), (129, 769, 2), (100, 500, 3)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,N,segments", FROM_TOTALS)
+def test_segments_from_totals(cottn, oracle, B, N, segments, dtype):
+    import torch
+    from paper_2409_18747_amd import workloads
+    c = cottn.COTTN_BF16 if dtype == "bf16" else cottn.COTTN_F16
+    x = workloads.draw(B, 1, N, D, dtype, seed=920 + N)
+    Q, K, V, dO = (to_device(x[k], dtype) for k in ("Q", "K", "V", "dO"))
+    s = to_device(x["s"], "f32")
+    cottn.cottn_tune_segments(segments)
+    assert cottn.cottn_segments(cottn.OP_FWD_CAUSAL, B, 1, N, D, 0, c) == segments and B * segments > 256
+    state = torch.full((B, 1, D, D), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.full((cottn.cottn_workspace_bytes(cottn.OP_FWD_CAUSAL, B, 1, N, D, 0, c),), 255, dtype=torch.uint8, device="cuda")
+    cottn.profile_start()
+    O = cottn.cottn_fwd_causal(Q, K, V, s, state=state, workspace=ws)
+    assert set(cottn.profile_stop()) == {"fwd_segment_state_" + dtype, "fwd_causal_scan_" + dtype}
+    ref, S = oracle.fwd_recurrent(x["Q"], x["K"], x["V"], x["s"])
+    g_ref = oracle.bwd_recurrent(x["Q"], x["K"], x["V"], x["s"], x["dO"])
+    errs = {"O": rel_err(to_host(O), ref), "state": rel_err(to_host(state), S)}
+    for kept in (ws, None):
+        g = cottn.cottn_bwd_causal(Q, K, V, s, dO, fwd_workspace=kept)
+        errs.update({n: rel_err(to_host(a), r) for n, a, r in zip(("dQ", "dK", "dV"), g, g_ref)})
+        check(errs, dtype, "totals B%d N%d seg%d %s" % (B, N, segments, dtype))
+    # from a state, and padded
+    cut = N - 200
+    zero, mid, end = (torch.zeros(B, 1, D, D, device="cuda") for _ in range(3))
+    cottn.cottn_fwd_causal_from_state(*(t[:, :, :200].contiguous() for t in (Q, K, V)), s, zero, state=mid)
+    O1 = cottn.cottn_fwd_causal_from_state(*(t[:, :, 200:].contiguous() for t in (Q, K, V)), s, mid, state=end)
+    check({"O from state": rel_err(to_host(O1), ref[:, :, 200:]), "state": rel_err(to_host(end), S)}, dtype, "cut %d" % cut)
+    lens = np.array([(37 * b) % (N + 1) for b in range(B)])
+    P = to_host(cottn.cottn_fwd_causal_varlen(Q, K, V, s.expand(B, 1).contiguous(),
+                                              torch.tensor(lens, dtype=torch.int32, device="cuda")))
+    rows = np.arange(N)[None, None, :, None] < lens[:, None, None, None]   # (a row sees the rows before it alone)
+    assert (P[np.broadcast_to(~rows, P.shape)] == 0).all()
+    check({"O padded": rel_err(P, ref * rows)}, dtype, "lengths")
