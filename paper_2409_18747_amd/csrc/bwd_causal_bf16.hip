@@ -116,9 +116,10 @@ struct BwdCfg {
 //
 // fp32: 32-row chunks are two row groups, and two waves on each make a workgroup of four, of which the
 // tiles and the state in parts (device_common.h: SPLIT3) leave room for two at 64 x 64.  B8 H12 N1024 d64:
-// dQ 46 -> 38 us, dK/dV 52 -> 44 us against the fp32 matrix instruction; the scans' rows take 25 and 30 us
-// through HBM.  The vector ALU bounds them: 5.5 instructions part an element, of the rows once and of the
-// state once a step.  64-row steps with eight waves, one workgroup to a compute unit, take 51 and 63
+// dQ 46 -> 38 us, dK/dV 52 -> 44 against the fp32 matrix instruction, both in segments and before a value's
+// range was noted (in even shares 36.8 / 41.1 without that note, 38.2 / 43.5 with it); the scans' rows take 25 and 30 us
+// through HBM.  The vector ALU bounds them: 6.5 instructions part an element and note its range, of the rows
+// once and of the state once a step.  64-row steps with eight waves, one workgroup to a compute unit, take 51 and 63
 // us; products of results straight into their sums (no instruction for the addition) 38 and 45, at
 // 1.2 times the error.
 // Where the whole fp32 kernels stand, an MFMA has a sixteenth of the bf16 rate: 32 rows instead of 64

@@ -48,8 +48,9 @@ namespace COTTN_NS {
 //           and the segment totals of that shape, 4.8 / 5.6).
 // Elsewhere the parts are the faster way: forward + backward, whole / parts, B4 H8 N2048 causal 32 x
 // 32 50 / 47 us, 64 x 64 106 / 88, 64 x 128 181 / 152, bidirectional 64 x 64 66 / 63, 128 x 64 122 /
-// 105; B32 H16 N512 causal 64 x 64 271 / 227.  Then the vector ALU is what they wait for (busy half of
-// the time, the matrix units a quarter): 5.5 instructions to part an element, 60 % of a step's.
+// 105; B32 H16 N512 causal 64 x 64 271 / 227.  Then the vector ALU is what they wait for (it issues in
+// 46 to 50 % of the cycles of the 64 x 64 scans, the matrix units are busy in 26 to 30 %): 6.5 instructions to part
+// an element and note its range, about half of a step's.
 #if defined(COTTN_ELEM_F32) && defined(COTTN_F32_WHOLE)
 typedef float elem_native;  // the compiler's type for one element of an MFMA operand
 typedef float elem_t;       // storage type of an element in global memory
@@ -689,10 +690,11 @@ __device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int s
   return s;
 }
 
-// How the causal scans walk (a template parameter, so that no walk pays for the others): segments, with
-// the states of earlier ones from the workspace; even shares, of sequences of one length or of a padded
-// batch (a piece without rows that exist takes a step of zeros); segments of short sequences, whose
-// workgroups form the state of the rows before them by themselves (launch.h: own_prefix).
+// How the causal scans walk (a template parameter: chosen at run time, one walk's registers spill in
+// another): segments, with the states of earlier ones from the workspace; even shares, of sequences of
+// one length or of a padded batch (a piece without rows that exist takes a step of zeros); segments of
+// short sequences, whose workgroups form the state of the rows before them by themselves (launch.h:
+// own_prefix).
 enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, EVEN_PADDED = 2, OWN_PREFIX = 3 };
 // What the last share's slot, which holds no state, begins with in a forward's workspace: whether the states
 // there are those of even shares (launch.h: CausalArgs::marked).

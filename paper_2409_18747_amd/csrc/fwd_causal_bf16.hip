@@ -89,8 +89,8 @@ struct FwdCfg {
 template <int DK, int DV, int C> struct FwdSplit { static constexpr int CS = ELEM_IS_F32 ? 2 : 1; };
 template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
 // (fp32: chunks of 32 rows are two row groups, so two waves each make a workgroup of four.  B8 H12
-// N1024 d64 34.5 -> 30.5 us, operands in three parts against the fp32 matrix instruction, of which 20 us
-// is the rows' way through HBM; 64-row steps 40 us)
+// N1024 d64 34.5 -> 30.5 us, operands in three parts against the fp32 matrix instruction (in even shares 28.1,
+// with the range of the values noted 29.5), of which 20 us is the rows' way through HBM; 64-row steps 40 us)
 
 // ---------------------------------------------------------------------------------------
 // Kernel 1: T[unit][g] = sum over the rows of segment g of kh^T v   (fp32, d_key x d_value;

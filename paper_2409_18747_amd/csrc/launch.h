@@ -103,7 +103,10 @@ constexpr bool two_to_a_cu_dkdv(long workgroups) { return workgroups > 256; }
 // / 22.6 / 35.0 -> 8.7 / 20.6 / 30.5, 100 of 320 10.4 / 25.7 / 34.9 -> 8.5 / 24.5 / 30.1, 15 of 777 10.9 / 25.5 /
 // 35.8 -> 11.4 / 25.1 / 32.3, 100 of 512 11.5 / 32.2 / 36.2 -> 11.4 / 31.6 / 35.4, of 1024 17.3 / 50.3 / 55.6 ->
 // 19.2 / 50.9 / 58.3; 32 x 32 10 units of 1024 10.5 / 22.8 / 35.2 -> 9.6 / 20.3 / 30.4; 64 x 32 15 of 777 12.9 /
-// 27.2 / 40.0 -> 10.0 / 23.9 / 34.7; 64 x 128 4 of 777 14.1 / 31.0 / 44.4 -> 13.5 / 31.1 / 39.1, 15 of 777 15.7 /
+// 27.2 / 40.0 -> 10.0 / 23.9 / 34.7; 64 x 128 4 of 777 14.1 / 31.0 / 44.4 -> 13.5 / 31.1 / 39.1 (between 640 and 832
+// rows, forward / with backward: 2 units of 650 15.7 / 33.2 -> 12.0 / 29.4, of 700 16.1 / 33.9 -> 12.5 / 29.8, of 830
+// 16.0 / 34.0 -> 13.9 / 31.3, 4 of 650 16.0 / 34.2 -> 12.2 / 29.6, of 830 16.2 / 34.3 -> 14.1 / 31.7; 32 x 128 2, 4 and
+// 8 units 13.0 / 28.0 -> 9.9..11.4 / 24.3..24.8), 15 of 777 15.7 /
 // 37.2 / 41.8 -> 14.1 / 34.7 / 43.0; 128 x 64 15.5 / 37.7 / 42.7 -> 15.0 / 36.3 / 46.0; 128 x 32 100 of 400 13.2 /
 // 37.7 / 42.7 -> 11.7 / 36.0 / 39.8, of 512 13.6 / 39.0 / 43.6 -> 14.2 / 39.6 / 46.8; 128 x 128 40 of 256 12.9 /
 // 32.4 / 39.1 -> 9.9 / 28.8 / 31.9, 100 of 640 in two segments 27.6 / 79.1 / 88.3 -> 22.4 / 73.4 / 77.6; fp32 32 x
