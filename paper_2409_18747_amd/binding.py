@@ -1,6 +1,11 @@
-"""ctypes binding of libcottn.so: the same names as the C ABI (include/cottn.h), taking torch
+"""Binding of libcottn.so: the same names as the C ABI (include/cottn.h), taking torch
 tensors.  Argument marshalling only — every step of the computation runs in the HIP kernels.
 PyTorch supplies device memory and the stream handle, nothing else.
+
+The marshalling is here, over ctypes, for every call, and once more in C++ (csrc/marshal.cpp, module _marshal) for
+plain tensors on the current stream, which the attention and step calls try first: it does the whole call, or nothing and
+answers None.  Decode step of 16 states 7.4 -> 3.5 us a call, of which the launch is 3.1; five drafted tokens of 128
+states 7.9 -> 6.6, a forward of 2 x 256 rows of 32 fp32 with its two allocations 9.9 -> 7.5 (the kernels from there on).
 
 The library must have been built (``python -m paper_2409_18747_amd.build``); there is no
 fallback: a missing library raises at first use.
@@ -9,6 +14,11 @@ import ctypes
 import os
 
 import torch
+
+try:
+    from . import _marshal
+except ImportError as e:
+    raise ImportError("_marshal.so is not built: run `python -m paper_2409_18747_amd.build`") from e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 library_path = os.path.join(_HERE, "libcottn.so")
@@ -102,6 +112,7 @@ def _load():
     lib.cottn_profile_launches.argtypes = [i]
     lib.cottn_profile_ms.restype = ctypes.c_double
     lib.cottn_profile_ms.argtypes = [i]
+    _marshal.bind(library_path, CottnError)
     return lib
 
 
@@ -119,10 +130,9 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError("tensors must be float32, bfloat16 or float16, got %s" % t.dtype)
 
 
-# The checks and conversions below run on every call, and the smallest calls (a decode step, a few
-# drafted tokens) last no longer on the GPU than a handful of them on the host: attributes are
+# The checks and conversions below run on every call that _marshal leaves to them: attributes are
 # read once, ctypes converts plain ints by itself, and the current stream comes as its handle
-# (building the Stream object takes 2.9 us of a decode step that took 10.9 us and takes 7.4 now).
+# (building the Stream object takes 2.9 us).
 
 # torch has no public call for the handle alone; where a build lacks these two, the Stream object has it
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -242,10 +252,18 @@ def _grads(Q, dQ, dK, dV, ds, ds_shape):
     return dQ, dK, dV, ds
 
 
+# the variants of a forward or backward as _marshal numbers them
+_CAUSAL, _CAUSAL_FROM_STATE, _CAUSAL_VARLEN, _CAUSAL_DKDV, _BIDIR, _BIDIR_VARLEN, _BIDIR_DKDV = range(7)
+
+
 def cottn_fwd_causal(Q, K, V, s, O=None, state=None, workspace=None, chunk=0, eps=1e-6,
                      stream=None):
     """O = s_h (Qhat Khat^T (.) M) V; returns O (allocated if not given).  `state`, if given,
     receives sum_j khat_j^T v_j as float32 [B, H, d, d]."""
+    if stream is None:
+        done = _marshal.fwd(_CAUSAL, Q, K, V, s, None, None, O, state, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     if O is None:
         O = torch.empty_like(Q)
@@ -282,6 +300,10 @@ def cottn_fwd_causal_from_state(Q, K, V, s, state_in, O=None, state=None, worksp
                                 eps=1e-6, stream=None):
     """cottn_fwd_causal for a piece of a longer sequence: starts from `state_in` (float32
     [B, H, d, d]) and leaves the state after the piece in `state` (a different tensor)."""
+    if stream is None:
+        done = _marshal.fwd(_CAUSAL_FROM_STATE, Q, K, V, s, None, state_in, O, state, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     if O is None:
         O = torch.empty_like(Q)
@@ -304,6 +326,11 @@ def cottn_bwd_causal(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspa
 
     fwd_workspace: the workspace tensor the matching cottn_fwd_causal call used (untouched
     since), or None; see include/cottn.h."""
+    if stream is None:
+        done = _marshal.bwd(_CAUSAL, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     dQ, dK, dV, ds = _grads(Q, dQ, dK, dV, ds, (H,))
     _rows_like(Q, K=K, V=V, dO=dO, dQ=dQ, dK=dK, dV=dV)
@@ -324,6 +351,11 @@ def cottn_bwd_causal_from_state(Q, K, V, s, dO, state_in=None, rev_state_in=None
     """cottn_bwd_causal for one piece of a sequence processed in pieces: state_in is the
     forward-time state before the piece, rev_state_in the reverse-time state after it;
     returns (dQ, dK, dV, ds) and fills rev_state_out (float32 [B, H, d, d]) when given."""
+    if stream is None:
+        done = _marshal.bwd(_CAUSAL_FROM_STATE, Q, K, V, s, None, dO, state_in, rev_state_in, dQ, dK, dV, ds, rev_state_out,
+                         fwd_workspace, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     dQ, dK, dV, ds = _grads(Q, dQ, dK, dV, ds, (H,))
     _rows_like(Q, K=K, V=V, dO=dO, dQ=dQ, dK=dK, dV=dV)
@@ -345,6 +377,10 @@ def cottn_bwd_causal_from_state(Q, K, V, s, dO, state_in=None, rev_state_in=None
 
 def cottn_fwd_bidir(Q, K, V, s, O=None, state=None, workspace=None, eps=1e-6, stream=None):
     """O = s_h Qhat (Khat^T V); returns O."""
+    if stream is None:
+        done = _marshal.fwd(_BIDIR, Q, K, V, s, None, None, O, state, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     if O is None:
         O = torch.empty_like(Q)
@@ -363,6 +399,11 @@ def cottn_bwd_bidir(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspac
                     stream=None, fwd_workspace=None):
     """Gradients of cottn_fwd_bidir; returns (dQ, dK, dV, ds).  fwd_workspace: the workspace
     tensor of the matching cottn_fwd_bidir call (untouched since), or None."""
+    if stream is None:
+        done = _marshal.bwd(_BIDIR, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     dQ, dK, dV, ds = _grads(Q, dQ, dK, dV, ds, (H,))
     _rows_like(Q, K=K, V=V, dO=dO, dQ=dQ, dK=dK, dV=dV)
@@ -380,6 +421,10 @@ def cottn_bwd_bidir(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspac
 def cottn_fwd_causal_varlen(Q, K, V, s, seq_len, O=None, state=None, workspace=None, chunk=0,
                             eps=1e-6, stream=None):
     """cottn_fwd_causal for a padded batch: seq_len int32 [B], s float32 [B, H]."""
+    if stream is None:
+        done = _marshal.fwd(_CAUSAL_VARLEN, Q, K, V, s, seq_len, None, O, state, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     if O is None:
         O = torch.empty_like(Q)
@@ -399,6 +444,11 @@ def cottn_fwd_causal_varlen(Q, K, V, s, seq_len, O=None, state=None, workspace=N
 def cottn_bwd_causal_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, ds=None,
                             workspace=None, chunk=0, eps=1e-6, stream=None, fwd_workspace=None):
     """cottn_bwd_causal for a padded batch; returns (dQ, dK, dV, ds) with ds float32 [B, H]."""
+    if stream is None:
+        done = _marshal.bwd(_CAUSAL_VARLEN, Q, K, V, s, seq_len, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     dQ, dK, dV, ds = _grads(Q, dQ, dK, dV, ds, (B, H))
     _rows_like(Q, K=K, V=V, dO=dO, dQ=dQ, dK=dK, dV=dV)
@@ -418,6 +468,10 @@ def cottn_bwd_causal_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, 
 def cottn_fwd_bidir_varlen(Q, K, V, s, seq_len, O=None, state=None, workspace=None, eps=1e-6,
                            stream=None):
     """cottn_fwd_bidir for a padded batch: seq_len int32 [B], s float32 [B, H]."""
+    if stream is None:
+        done = _marshal.fwd(_BIDIR_VARLEN, Q, K, V, s, seq_len, None, O, state, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     if O is None:
         O = torch.empty_like(Q)
@@ -437,6 +491,11 @@ def cottn_fwd_bidir_varlen(Q, K, V, s, seq_len, O=None, state=None, workspace=No
 def cottn_bwd_bidir_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, ds=None,
                            workspace=None, eps=1e-6, stream=None, fwd_workspace=None):
     """cottn_bwd_bidir for a padded batch; returns (dQ, dK, dV, ds) with ds float32 [B, H]."""
+    if stream is None:
+        done = _marshal.bwd(_BIDIR_VARLEN, Q, K, V, s, seq_len, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, d, dt = _dims(Q)
     dQ, dK, dV, ds = _grads(Q, dQ, dK, dV, ds, (B, H))
     _rows_like(Q, K=K, V=V, dO=dO, dQ=dQ, dK=dK, dV=dV)
@@ -455,6 +514,10 @@ def cottn_bwd_bidir_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, d
 
 def cottn_scale_from_m_varlen(m, seq_len, s=None, stream=None):
     """s[b, h] = seq_len[b]^(-sigmoid(m[h]))."""
+    if stream is None:
+        done = _marshal.scale_varlen(m, seq_len, None, s)
+        if done is not None:
+            return done
     B, H = seq_len.numel(), m.numel()
     _f32("m", m, H, m.device)
     _check_lengths(seq_len, B, m.device)
@@ -468,6 +531,10 @@ def cottn_scale_from_m_varlen(m, seq_len, s=None, stream=None):
 
 def cottn_scale_backward_varlen(m, seq_len, ds, dm=None, stream=None):
     """dm[h] = sum_b ds[b, h] * d s[b, h] / d m[h]."""
+    if stream is None and ds is not None:
+        done = _marshal.scale_varlen(m, seq_len, ds, dm)
+        if done is not None:
+            return done
     B, H = seq_len.numel(), m.numel()
     _f32("m", m, H, m.device)
     _check_lengths(seq_len, B, m.device)
@@ -482,6 +549,10 @@ def cottn_scale_backward_varlen(m, seq_len, ds, dm=None, stream=None):
 
 def cottn_step(q, k, v, s, state, o=None, eps=1e-6, stream=None):
     """state += khat^T v (in place); returns o = s_h qhat state.  q, k, v are [B, H, d]."""
+    if stream is None:
+        done = _marshal.step(0, q, k, v, s, state, o, eps)
+        if done is not None:
+            return done
     if q.dim() != 3:
         raise ValueError("q must be [B, H, d], got shape %s" % (tuple(q.shape),))
     B, H, d = q.shape
@@ -565,6 +636,10 @@ def cottn_fwd_causal_dkdv(Q, K, V, s, O=None, state=None, workspace=None, chunk=
                           stream=None):
     """cottn_fwd_causal with d_key = Q.shape[-1] and d_value = V.shape[-1]; returns O (like V).
     `state`, if given, receives float32 [B, H, d_key, d_value]."""
+    if stream is None:
+        done = _marshal.fwd(_CAUSAL_DKDV, Q, K, V, s, None, None, O, state, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
     if O is None:
         O = torch.empty_like(V)
@@ -593,6 +668,11 @@ def cottn_bwd_causal_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, wo
                           chunk=0, eps=1e-6, stream=None, fwd_workspace=None):
     """cottn_bwd_causal with d_key = Q.shape[-1] and d_value = V.shape[-1] (dO like V);
     returns (dQ, dK, dV, ds)."""
+    if stream is None:
+        done = _marshal.bwd(_CAUSAL_DKDV, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, chunk, eps)
+        if done is not None:
+            return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
     dQ, dK, dV, ds = _grads_dkdv(Q, V, dQ, dK, dV, ds, H)
     _rows_like(Q, K=K, dQ=dQ, dK=dK)
@@ -611,6 +691,10 @@ def cottn_bwd_causal_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, wo
 
 def cottn_fwd_bidir_dkdv(Q, K, V, s, O=None, state=None, workspace=None, eps=1e-6, stream=None):
     """cottn_fwd_bidir with d_key = Q.shape[-1] and d_value = V.shape[-1]; returns O (like V)."""
+    if stream is None:
+        done = _marshal.fwd(_BIDIR_DKDV, Q, K, V, s, None, None, O, state, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
     if O is None:
         O = torch.empty_like(V)
@@ -629,6 +713,11 @@ def cottn_fwd_bidir_dkdv(Q, K, V, s, O=None, state=None, workspace=None, eps=1e-
 def cottn_bwd_bidir_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspace=None,
                          eps=1e-6, stream=None, fwd_workspace=None):
     """cottn_bwd_bidir with d_key = Q.shape[-1] and d_value = V.shape[-1]; returns (dQ, dK, dV, ds)."""
+    if stream is None:
+        done = _marshal.bwd(_BIDIR_DKDV, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
+                         fwd_workspace, workspace, 0, eps)
+        if done is not None:
+            return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
     dQ, dK, dV, ds = _grads_dkdv(Q, V, dQ, dK, dV, ds, H)
     _rows_like(Q, K=K, dQ=dQ, dK=dK)
@@ -648,6 +737,10 @@ def cottn_bwd_bidir_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, wor
 def cottn_step_dkdv(q, k, v, s, state, o=None, eps=1e-6, stream=None):
     """cottn_step with q, k [B, H, d_key] and v [B, H, d_value]; state float32 [B, H, d_key, d_value]
     updated in place; returns o (like v)."""
+    if stream is None:
+        done = _marshal.step(1, q, k, v, s, state, o, eps)
+        if done is not None:
+            return done
     if q.dim() != 3 or v.dim() != 3:
         raise ValueError("q and v must be [B, H, d], got shapes %s and %s" % (tuple(q.shape), tuple(v.shape)))
     B, H, dk = q.shape
