@@ -91,6 +91,8 @@ struct BwdCfg {
   static constexpr bool DKDV_PHASED = PHASED || (!ELEM_IS_F32 && CS == 1 && DK == 32 && DV == 128);
   // masked tiles formed by the two waves of a row group together (MaskedExchange); 32-row chunks
   static constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
+  // steps that OWN_PREFIX_SETS takes at a time: the second through the tiles of Q and dO, two more through their own
+  static constexpr int PREFIX_SETS = prefix_sets_built(DK, DV, ELEM_IS_F32, false);
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -187,6 +189,8 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   COTTN_LDS_ARRAY(float, rq, C, 6)
   COTTN_LDS_ARRAY(float, xdot, CS > 1 ? CS * C : 1, 7)   // row dot products of the column parts
   COTTN_LDS_ARRAY(float, ds_wave, Cfg::NW, 8)
+  constexpr int SETS = WALK == OWN_PREFIX_SETS ? Cfg::PREFIX_SETS : 1;
+  COTTN_LDS_ARRAY(lds_t, Ps, SETS > 2 ? (SETS - 2) * (Cfg::TILEK + Cfg::TILEV) : 8, 9)   // kh and v of further steps
   // A tiles of the two key halves: in the staging tile where there is one (it is written a
   // barrier after the last of them is read), so that 128 x 32 keeps two workgroups
   constexpr bool IN_STAGE = Cfg::SHARE_MASKED && Cfg::DQ_OWN_STAGE;
@@ -239,16 +243,22 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   vst.fetch(Vu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
   const auto form_prefix = [&] {
-    add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV>(
-        Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
+    lds_t *k_tiles[SETS], *v_tiles[SETS];
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) {
+      k_tiles[i] = i == 0 ? Ks : i == 1 ? Qs : Ps + (i - 2) * Cfg::TILEK;
+      v_tiles[i] = i == 0 ? Vs : i == 1 ? Gs : Ps + (SETS - 2) * Cfg::TILEK + (i - 2) * Cfg::TILEV;
+    }
+    add_rows_before<DK, DV, C, Cfg::NT, AT::NRT, AT::NCT, DV, SETS>(
+        k_tiles, v_tiles, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, AT::active(rg, cp),
         [&](int y) { return AT::row_tile(rg, cp, y); }, [&](int x) { return AT::col_tile(rg, cp, x); },
         [&](int y, int x, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); },
         un);
   };
-  bool no_states = WALK == OWN_PREFIX;
+  bool no_states = walks_own_prefix(WALK);
   if constexpr (WALK == EVEN_SHARES)   // (sum_totals 2: the states are a forward's that may have left none)
     no_states = sum_totals == 2 && fwd_states[size_t(gridDim.x - 1) * DK * DV] != EVEN_MARK;
-  if ((WALK == OWN_PREFIX || WALK == EVEN_SHARES) && no_states) {
+  if ((walks_own_prefix(WALK) || WALK == EVEN_SHARES) && no_states) {
     if (span.mid_unit) form_prefix();
   } else if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(
@@ -523,7 +533,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   if (un.in_workgroup<Cfg::NW>(rq)) {
     using Whole = f32w::BwdCfg<DK, DV, C, CS>;
     static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
-    void* const room[] = {Qs, Ks, Vs, Gs, St, Os, rq, xdot, ds_wave};
+    void* const room[] = {Qs, Ks, Vs, Gs, St, Os, rq, xdot, ds_wave, Ps};
     f32w::bwd_dq_scan<DK, DV, C, CS, REV, WALK>(room, Q, K, V, dO, s, dQ, fwd_states, rev_totals, ds_partial, H, N, G,
                                                 seg_rows, inv_eps, sum_totals, lengths, s_per_unit, state_in, units,
                                                 unit_rows);
@@ -1024,7 +1034,11 @@ hipError_t run_bwd_causal(const CausalArgs& a) {
       err = a.seq_len == nullptr ? dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_SHARES>, Cfg::NT)
                                  : dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, EVEN_PADDED>, Cfg::NT);
   } else if (rebuild) {
-    if constexpr (C <= 64 && !VERY_MANY) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
+    const bool by_sets = Cfg::PREFIX_SETS > 1 && prefix_by_sets(a.workgroups);
+    if constexpr (Cfg::PREFIX_SETS > 1 && C <= 64)
+      if (by_sets) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX_SETS>, Cfg::NT);
+    if constexpr (C <= 64 && !VERY_MANY)
+      if (!by_sets) err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, OWN_PREFIX>, Cfg::NT);
   } else {
     err = dq_scan(COTTN_SYM(bwd_dq_scan)<DK, DV, CR, CS, true, SEGMENTS>, Cfg::NT);
   }

@@ -694,8 +694,9 @@ __device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int s
 // another): segments, with the states of earlier ones from the workspace; even shares, of sequences of
 // one length or of a padded batch (a piece without rows that exist takes a step of zeros); segments of
 // short sequences, whose workgroups form the state of the rows before them by themselves (launch.h:
-// own_prefix).
-enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, EVEN_PADDED = 2, OWN_PREFIX = 3 };
+// own_prefix), the same several steps at a time.
+enum Walk { SEGMENTS = 0, EVEN_SHARES = 1, EVEN_PADDED = 2, OWN_PREFIX = 3, OWN_PREFIX_SETS = 4 };
+constexpr bool walks_own_prefix(int walk) { return walk == OWN_PREFIX || walk == OWN_PREFIX_SETS; }
 // What the last share's slot, which holds no state, begins with in a forward's workspace: whether the states
 // there are those of even shares (launch.h: CausalArgs::marked).
 constexpr float EVEN_MARK = 1.0f, NO_EVEN_MARK = 0.0f;

@@ -65,6 +65,10 @@ struct FwdCfg {
   static constexpr int LDS_BYTES =
       LDS_ELEM * (2 * TILEK + TILEV + STATE) + (OWN_STAGE ? ELEM * C * OP : 0) + 4 * C;
   static constexpr int WG_PER_CU = (160 * 1024) / LDS_BYTES;
+  // steps that OWN_PREFIX_SETS takes at a time, and the elements of the tiles that the second and further ones need
+  // (the first of them the q tile too)
+  static constexpr int PREFIX_SETS = prefix_sets_built(DK, DV, ELEM_IS_F32, true);
+  static constexpr int PREFIX_TILES = PREFIX_SETS < 2 ? 0 : (PREFIX_SETS - 1) * TILEV + (PREFIX_SETS - 2) * TILEK;
   // waves per SIMD the register allocation is capped for (two workgroups per compute unit
   // when LDS allows, never more than the hardware needs for one workgroup)
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
@@ -220,6 +224,8 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   // wider than the queries they do not fit the q rows: own staging tile
   COTTN_LDS_ARRAY(elem_t, Os, OWN_STAGE ? C * Cfg::OP : 8, 4)
   COTTN_LDS_ARRAY(float, rq, C, 5)
+  constexpr int SETS = WALK == OWN_PREFIX_SETS ? Cfg::PREFIX_SETS : 1;
+  COTTN_LDS_ARRAY(lds_t, Ps, SETS > 1 ? Cfg::PREFIX_TILES : 8, 6)   // v and kh of further steps of an own prefix
   constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   Unparted un;
@@ -296,10 +302,16 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   if (state_in != nullptr && ST::active(rg, cp)) load_start();
   if constexpr (even_shares_built(DK, DV, ELEM_IS_F32) && WALK == SEGMENTS && LDV == DV)
     if (G == 1 && seg_states != nullptr && blockIdx.x == 0 && tid == 0) *seg_states = NO_EVEN_MARK;
-  if constexpr (WALK == OWN_PREFIX) {
+  if constexpr (walks_own_prefix(WALK)) {
     if (span.mid_unit) {
-      add_rows_before<DK, DV, C, Cfg::NT * CS, ST::NCT, ST::NRT, LDV>(
-          Ks, Vs, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, ST::active(rg, cp),
+      lds_t *k_tiles[SETS], *v_tiles[SETS];
+#pragma unroll
+      for (int i = 0; i < SETS; ++i) {
+        k_tiles[i] = i == 0 ? Ks : i == 1 ? Qs : Ps + (SETS - 1) * Cfg::TILEV + (i - 2) * Cfg::TILEK;
+        v_tiles[i] = i == 0 ? Vs : Ps + (i - 1) * Cfg::TILEV;
+      }
+      add_rows_before<DK, DV, C, Cfg::NT * CS, ST::NCT, ST::NRT, LDV, SETS>(
+          k_tiles, v_tiles, Ku, Vu, min(row_begin, valid_rows(seq_len, unit, H, N)), inv_eps, l, ST::active(rg, cp),
           [&](int x) { return ST::col_tile(rg, cp, x); }, [&](int y) { return ST::row_tile(rg, cp, y); },
           [&](int x, int y, const frag8& kf, const frag8& vf) { sacc[x][y] = mma16_add(vf, kf, sacc[x][y]); },
           un);
@@ -505,7 +517,7 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
     static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE &&
                       CS == 2 && Whole::OP == Cfg::OP,
                   "whole rows fit, and finished ones are staged alike");
-    void* const room[] = {Qs, Ks, Vs, Sl, Os, rq};
+    void* const room[] = {Qs, Ks, Vs, Sl, Os, rq, Ps};
     f32w::fwd_causal_scan<DK, DV, C, CS, WALK, LDV>(room, Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows,
                                                     inv_eps, sum_totals, lengths, s_per_unit, stream_q, stream_kv, units,
                                                     unit_rows);
@@ -572,7 +584,12 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
                  ? scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_SHARES>, threads)
                  : scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, EVEN_PADDED>, threads);
   if constexpr (C <= 64)
-    if (a.own_prefix) return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX>, threads);
+    if (a.own_prefix) {
+      if constexpr (FwdCfg<DK, DV, C>::PREFIX_SETS > 1)
+        if (prefix_by_sets(a.workgroups))
+          return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX_SETS>, threads);
+      return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, OWN_PREFIX>, threads);
+    }
   return scan(COTTN_SYM(fwd_causal_scan)<DK, DV, C, FwdSplit<DK, DV, C>::CS, SEGMENTS>, threads);
 }
 #endif  // COTTN_REDO

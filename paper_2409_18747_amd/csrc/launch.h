@@ -144,6 +144,18 @@ constexpr bool own_prefix(long units, int G, long seg_rows, int dk, int dv, bool
   return units * G <= (widest ? 256 : 512) && (G - 1) * seg_rows <= (widest ? 768 : 576);
 }
 
+// Steps that they take of it at a time.  A step of narrow rows is two barriers and the waits around them more than
+// work, so that four at once gain where a compute unit has room for their tiles, one workgroup each: forward / backward
+// that rebuilds the state, one -> four: 32 x 32 10 units of 1024 rows 8.4 -> 7.4 / dQ 8.9 -> 8.2 us, 30 of 512 with
+// backward 18.3 -> 17.3, fp32 2 of 256 7.2 -> 6.5 / 7.6 -> 7.1, 10 of 250 7.7 -> 7.0 / 8.1 -> 7.6; 64 x 32 15 of 777 forward 9.3 ->
+// 8.4, dQ 9.6 -> 9.7.  Wider rows do not: 64 x 64 2 of 256 5.1 -> 4.9, 40 of 512 8.7 -> 8.6, 64 x 128 4 of 777 12.9 -> 13.9,
+// 128 x 64 15 of 640 12.0 -> 12.4, 32 x 64 10 of 960 8.4 -> 8.4, fp32 10 of 192 7.2 -> 7.5; nor do more workgroups: 32 x 32
+// 100 of 512 8.3 -> 9.0.
+constexpr int prefix_sets_built(int dk, int dv, bool f32, bool forward) {
+  return (dk == 32 && dv == 32) || (forward && !f32 && dk == 64 && dv == 32) ? 4 : 1;
+}
+constexpr bool prefix_by_sets(long workgroups) { return workgroups <= 256; }
+
 // Shapes built for even shares (api.hip: causal_even_share, which asks for no others).
 constexpr bool even_shares_built(int dk, int dv, bool f32) {
   return (dk == 128 && dv == 128) || (f32 && dk >= 64 && dv >= 64);

@@ -247,44 +247,56 @@ __device__ __forceinline__ void add_rows_to_state(f32x4 (&acc)[ST::NCT][ST::NRT]
   }
 }
 
-// acc += kh^T v over rows 0 .. n_rows - 1 of one unit, C rows at a time, the tiles of the state dealt to
-// the waves as in the scan that goes on from them: key tiles key_tile(i), value tiles value_tile(j), and
-// add(i, j, k fragment, v fragment).  Ends behind a barrier.
-template <int DK, int DV, int C, int NT, int NK, int NV, int LDV, class KeyTile, class ValueTile, class Add>
-__device__ __forceinline__ void add_rows_before(lds_t* Ks, lds_t* Vs, const elem_t* __restrict__ Ku,
-                                                const elem_t* __restrict__ Vu, int n_rows, float inv_eps, int l,
-                                                bool active, KeyTile key_tile, ValueTile value_tile, Add add,
-                                                Unparted& un) {
+// acc += kh^T v over rows 0 .. n_rows - 1 of one unit, SETS x C rows at a time (each C rows through tiles of their
+// own, Ks[i] and Vs[i]), the tiles of the state dealt to the waves as in the scan that goes on from them: key
+// tiles key_tile(i), value tiles value_tile(j), and add(i, j, k fragment, v fragment).  Ends behind a barrier.
+template <int DK, int DV, int C, int NT, int NK, int NV, int LDV, int SETS, class KeyTile, class ValueTile, class Add>
+__device__ __forceinline__ void add_rows_before(lds_t* (&Ks)[SETS], lds_t* (&Vs)[SETS],
+                                                const elem_t* __restrict__ Ku, const elem_t* __restrict__ Vu, int n_rows,
+                                                float inv_eps, int l, bool active, KeyTile key_tile, ValueTile value_tile,
+                                                Add add, Unparted& un) {
   constexpr int TPK = tile_pitch(DK, C), TPV = tile_pitch(DV, C);
   const int r = l % 16, q4 = l / 16;
-  TileStage<DK, C, NT> kst;
-  TileStage<DV, C, NT, LDV> vst;
-  kst.fetch(Ku, 0, n_rows);
-  vst.fetch(Vu, 0, n_rows);
-  for (int row0 = 0; row0 < n_rows; row0 += C) {
-    float rk[TileStage<DK, C, NT>::PASSES];
-    kst.row_rinv(inv_eps, rk);
-    kst.commit_scaled(Ks, rk, un);
-    vst.commit_plain(Vs, un);
-    if (row0 + C < n_rows) {
-      kst.fetch(Ku, row0 + C, n_rows);
-      vst.fetch(Vu, row0 + C, n_rows);
+  TileStage<DK, C, NT> kst[SETS];
+  TileStage<DV, C, NT, LDV> vst[SETS];
+  const auto fetch = [&](int row0) {
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) {
+      if (i > 0 && row0 + i * C >= n_rows) break;
+      kst[i].fetch(Ku, row0 + i * C, n_rows);
+      vst[i].fetch(Vu, row0 + i * C, n_rows);
     }
+  };
+  fetch(0);
+  for (int row0 = 0; row0 < n_rows; row0 += SETS * C) {
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) {
+      if (i > 0 && row0 + i * C >= n_rows) break;
+      float rk[TileStage<DK, C, NT>::PASSES];
+      kst[i].row_rinv(inv_eps, rk);
+      kst[i].commit_scaled(Ks[i], rk, un);
+      vst[i].commit_plain(Vs[i], un);
+    }
+    if (row0 + SETS * C < n_rows) fetch(row0 + SETS * C);
     __syncthreads();
     if (active) {
 #pragma unroll
-      for (int p = 0; p < C / 32; ++p) {
-        frag8 kf[NK], vf[NV];
+      for (int i = 0; i < SETS; ++i) {
+        if (i > 0 && row0 + i * C >= n_rows) break;
 #pragma unroll
-        for (int i = 0; i < NK; ++i) kf[i] = lds_col_frag_ks(Ks, TPK, p, q4, 16 * key_tile(i), r);
+        for (int p = 0; p < C / 32; ++p) {
+          frag8 kf[NK], vf[NV];
 #pragma unroll
-        for (int j = 0; j < NV; ++j) vf[j] = lds_col_frag_ks(Vs, TPV, p, q4, 16 * value_tile(j), r);
-        __builtin_amdgcn_sched_barrier(0);
+          for (int x = 0; x < NK; ++x) kf[x] = lds_col_frag_ks(Ks[i], TPK, p, q4, 16 * key_tile(x), r);
 #pragma unroll
-        for (int i = 0; i < NK; ++i)
+          for (int y = 0; y < NV; ++y) vf[y] = lds_col_frag_ks(Vs[i], TPV, p, q4, 16 * value_tile(y), r);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int j = 0; j < NV; ++j) add(i, j, kf[i], vf[j]);
-        __builtin_amdgcn_sched_barrier(0);
+          for (int x = 0; x < NK; ++x)
+#pragma unroll
+            for (int y = 0; y < NV; ++y) add(x, y, kf[x], vf[y]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
     __syncthreads();

@@ -56,3 +56,15 @@ def test_own_prefix(tmp_path):
         args = "%d, %d, %d, %d, %d, %s" % (units, G, rows, dk, dv, "true" if f32 else "false")
         rules += ["own_prefix(%s) == %s" % (args, "true" if forward else "false"), "own_prefix_dq(%s) == %s" % (args, "true" if dq else "false")]
     holds(tmp_path, rules)
+
+
+def test_own_prefix_by_sets(tmp_path):
+    """Four steps at a time at 32 x 32, and in the 16-bit forward at 64 x 32, up to 256 workgroups."""
+    rules = ["prefix_by_sets(256)", "!prefix_by_sets(257)"]
+    for dk in (32, 64, 128):
+        for dv in (32, 64, 128):
+            for f32 in (False, True):
+                for forward in (False, True):
+                    four = (dk, dv) == (32, 32) or ((dk, dv) == (64, 32) and forward and not f32)
+                    rules.append("prefix_sets_built(%d, %d, %s, %s) == %d" % (dk, dv, str(f32).lower(), str(forward).lower(), 4 if four else 1))
+    holds(tmp_path, rules)
