@@ -93,6 +93,7 @@ struct BwdCfg {
   static constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   // steps that OWN_PREFIX_SETS takes at a time: the second through the tiles of Q and dO, two more through their own
   static constexpr int PREFIX_SETS = prefix_sets_built(DK, DV, ELEM_IS_F32, false);
+  static constexpr bool SKIP_UNSEEN = skips_unseen(CS, C), DQ_SKIP_UNSEEN = SKIP_UNSEEN && DV == 128;
   static constexpr int WAVES_RAW = (WG_PER_CU >= 2 ? 2 : 1) * NW / 4;
   // never budget registers for more than two waves per SIMD unless one workgroup alone needs
   // it: spilling costs more than the second workgroup of a large chunk gains
@@ -395,13 +396,19 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSV; ++ks)
+          for (int ks = 0; ks < Cfg::KSV; ++ks) {
+            if (Cfg::DQ_SKIP_UNSEEN && half > rg) break;
             vr[half][ks] = lds_row_frag(Vs + (16 * (2 * p + half) + r) * TPV + lds_col(32 * ks), q4);
+          }
       };
       const auto form_masked = [&] {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           const int jt = 2 * p + half;
+          if (Cfg::DQ_SKIP_UNSEEN && half > rg) {
+            put_no_half(af, half);
+            break;
+          }
           f32x4 t = {0.f, 0.f, 0.f, 0.f};
           if constexpr (Cfg::SHARE_MASKED) {
             if (half <= rg) t = masked.get(half, w, l);
@@ -841,6 +848,11 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
       } else if (Cfg::DKDV_PHASED && diag_or_above) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
+          if (Cfg::SKIP_UNSEEN && half < rg) {
+            put_no_half(pf, half);
+            put_no_half(af, half);
+            continue;
+          }
           read_queries(half);
           __builtin_amdgcn_sched_barrier(0);
           put_masked(pf, half, form_p(half));

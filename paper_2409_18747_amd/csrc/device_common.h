@@ -530,6 +530,18 @@ __device__ __forceinline__ void put_half(frag8& frag, int half, f32x4 acc, bool 
 #endif
 }
 
+// The same with zeros, of a tile that the mask leaves nothing of.
+__device__ __forceinline__ void put_no_half(frag8& frag, int half) {
+#if defined(COTTN_SPLIT3)
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    u32x4 words = __builtin_bit_cast(u32x4, frag.part[i]);
+    words[2 * half + 0] = words[2 * half + 1] = 0u;
+    frag.part[i] = __builtin_bit_cast(native8, words);
+  }
+#endif
+}
+
 // x of another lane of the same row of 16 lanes, chosen by a DPP control word: no LDS
 // traffic and no extra latency, unlike a general cross-lane permute.
 template <int DPP_CTRL>

@@ -228,6 +228,7 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   COTTN_LDS_ARRAY(lds_t, Ps, SETS > 1 ? Cfg::PREFIX_TILES : 8, 6)   // v and kh of further steps of an own prefix
   constexpr bool HALF_VISIBLE = F32_WHOLE && CS == 2 && C == 32, SHARE_MASKED = HALF_VISIBLE && !REDO;
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
+  constexpr bool SKIP_UNSEEN = skips_unseen(CS, C);
   Unparted un;
   fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
                      sum_totals, lengths, s_per_unit, stream_q, stream_kv, units, unit_rows);
@@ -437,8 +438,10 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
-          for (int ks = 0; ks < Cfg::KSK; ++ks)
+          for (int ks = 0; ks < Cfg::KSK; ++ks) {
+            if (SKIP_UNSEEN && half > rg) break;
             kr[half][ks] = lds_row_frag(Ks + (16 * (2 * p + half) + r) * TPK + lds_col(32 * ks), q4);
+          }
       }
       if (SHARE_MASKED) __syncthreads();  // the partial tiles of the other waves are there
       __builtin_amdgcn_sched_barrier(0);
@@ -447,6 +450,10 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           const int jt = 2 * p + half;
+          if (SKIP_UNSEEN && half > rg) {
+            put_no_half(pf, half);
+            break;
+          }
           f32x4 pacc = {0.f, 0.f, 0.f, 0.f};
           if constexpr (SHARE_MASKED) {
             if (half <= rg) pacc = masked.get(half, w, l);
