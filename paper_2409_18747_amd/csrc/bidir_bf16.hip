@@ -191,8 +191,8 @@ __device__ __forceinline__ void apply_rows(TileStage<DK, C, BiCfg<DK, DV, C>::NT
 template <int DK, int DV, int C>
 COTTN_KERNEL((C * 4), fwd_bidir_apply)
     const elem_t* __restrict__ Q, const float* __restrict__ s, elem_t* __restrict__ O,
-    const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, int H, int N,
-    int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+    const float* __restrict__ totals, int slots, int n_sum, float* __restrict__ state, Divisor H, int N,
+    Divisor G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit, int units) {
   using Cfg = BiCfg<DK, DV, C>;
   using Stage = TileStage<DK, C, Cfg::NT>;
   COTTN_LDS_ARRAY(lds_t, Qs, Cfg::TILEK, 0)  // raw q
@@ -202,19 +202,19 @@ COTTN_KERNEL((C * 4), fwd_bidir_apply)
 
   Unparted un;
   fetch_argument_now(Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len,
-                     s_per_unit);
+                     s_per_unit, units);
   int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+  unit_and_segment(blockIdx.x, units, G, unit, g);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   elem_t* Ou = O + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
 
   Stage qst;
   qst.fetch(Qu, row_begin, row_end);
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, totals + size_t(unit) * slots * DK * DV, n_sum,
                                   (state != nullptr && g == 0) ? state + size_t(unit) * DK * DV
                                                                : nullptr, un);
@@ -228,7 +228,7 @@ COTTN_KERNEL((C * 4), fwd_bidir_apply)
     static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::STATE <= Cfg::STATE &&
                   Whole::FWD_OWN_STAGE == Cfg::FWD_OWN_STAGE, "whole rows fit, and finished ones are staged alike");
     void* const room[] = {Qs, Sl, Os, rq};
-    f32w::fwd_bidir_apply<DK, DV, C>(room, Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len, s_per_unit);
+    f32w::fwd_bidir_apply<DK, DV, C>(room, Q, s, O, totals, slots, n_sum, state, H, N, G, seg_rows, inv_eps, seq_len, s_per_unit, units);
   }
 #endif
 }
@@ -333,8 +333,8 @@ template <int DK, int DV, int C>
 COTTN_KERNEL((C * 4), bwd_bidir_dq)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ dO, const float* __restrict__ s,
     elem_t* __restrict__ dQ, const float* __restrict__ s_totals, int slots, int n_sum,
-    float* __restrict__ g_totals, float* __restrict__ ds_partial, int H, int N, int G,
-    int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+    float* __restrict__ g_totals, float* __restrict__ ds_partial, Divisor H, int N, Divisor G,
+    int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit, int units) {
   using Cfg = BiCfg<DK, DV, C>;
   using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -348,15 +348,14 @@ COTTN_KERNEL((C * 4), bwd_bidir_dq)
 
   Unparted un;
   fetch_argument_now(Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows,
-                     inv_eps, seq_len, s_per_unit);
+                     inv_eps, seq_len, s_per_unit, units);
   int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+  unit_and_segment(blockIdx.x, units, G, unit, g);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64,
             r = l % 16, q4 = l / 16;
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dQu = dQ + size_t(unit) * N * DK;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
@@ -365,6 +364,7 @@ COTTN_KERNEL((C * 4), bwd_bidir_dq)
   StageV gst;
   qst.fetch(Qu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr, un);
 
   // racc[x][y]: element [v] of lane (r, q4) is G[key 16 ct + r][value 16 rt + 4 q4 + v]
@@ -405,7 +405,7 @@ COTTN_KERNEL((C * 4), bwd_bidir_dq)
     static_assert(2 * Whole::TILEK <= Cfg::TILEK && 2 * Whole::TILEV <= Cfg::TILEV && 2 * Whole::STATE <= Cfg::STATE, "whole rows fit");
     void* const room[] = {Qs, Gs, Os, Sl, rq, ds_wave};
     f32w::bwd_bidir_dq<DK, DV, C>(room, Q, dO, s, dQ, s_totals, slots, n_sum, g_totals, ds_partial, H, N, G, seg_rows, inv_eps,
-                                  seq_len, s_per_unit);
+                                  seq_len, s_per_unit, units);
   }
 #endif
 }
@@ -506,8 +506,8 @@ template <int DK, int DV, int C>
 COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
     const elem_t* __restrict__ K, const elem_t* __restrict__ V, const float* __restrict__ s,
     elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ g_totals, int slots,
-    int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, int H,
-    int N, int G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
+    int n_sum, const float* __restrict__ ds_partial, int n_ds, float* __restrict__ ds, int B, Divisor H,
+    int N, Divisor G, int seg_rows, float inv_eps, const int* __restrict__ seq_len, int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using StageK = TileStage<DK, C, Cfg::NT>;
   using StageV = TileStage<DV, C, Cfg::NT>;
@@ -520,13 +520,12 @@ COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
   fetch_argument_now(K, V, s, dK, dV, g_totals, slots, n_sum, ds_partial, n_ds, ds, B, H, N, G,
                      seg_rows, inv_eps, seq_len, s_per_unit);
   int unit, g;
-  unit_and_segment(blockIdx.x, G, unit, g);
+  unit_and_segment(blockIdx.x, B * H, G, unit, g);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
   elem_t* dKu = dK + size_t(unit) * N * DK;
   elem_t* dVu = dV + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
@@ -535,9 +534,10 @@ COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
   StageV vst;
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
+  const float scale = unit_scale(s, unit, H, s_per_unit);
 
   // ds[h] = sum of the shares of all batches (ds[b][h], one batch, with a scale per unit)
-  if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
+  if (int(blockIdx.x) < (s_per_unit ? B * H.n : H.n) && w == 0) {
     float t = 0.f;
     const int n = s_per_unit ? n_ds : B * n_ds;
     for (int i = l; i < n; i += 64)
@@ -578,7 +578,7 @@ template <int DK, int DV, int C>
 __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ totals,
-    float* __restrict__ state, int H, int N, float inv_eps, const int* __restrict__ seq_len,
+    float* __restrict__ state, Divisor H, int N, float inv_eps, const int* __restrict__ seq_len,
     int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
@@ -596,7 +596,6 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
   elem_t* Ou = O + size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_end = valid_rows(seq_len, unit, H, N);
 
   f32x4 acc[ST::NCT][ST::NRT];   // layout: add_rows_to_state
@@ -609,6 +608,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   kst.fetch(Ku, 0, row_end);
   vst.fetch(Vu, 0, row_end);
   qst.fetch(Qu, 0, row_end);
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, 0, row_end, inv_eps, w, l, un);
   if (ST::active(w)) {
 #pragma unroll
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
     elem_t* __restrict__ dK, elem_t* __restrict__ dV, const float* __restrict__ s_totals,
-    float* __restrict__ ds_out, int H, int N, float inv_eps, const int* __restrict__ seq_len,
+    float* __restrict__ ds_out, Divisor H, int N, float inv_eps, const int* __restrict__ seq_len,
     int s_per_unit) {
   using Cfg = BiCfg<DK, DV, C>;
   using RT = AccTiles<DV, DK, Cfg::NW>;   // total of Qh^T dO: value rows, key columns
@@ -652,13 +652,13 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(bwd_bidir_unit)(
   const int unit = blockIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, r = l % 16, q4 = l / 16;
   const size_t k_rows = size_t(unit) * N * DK, v_rows = size_t(unit) * N * DV;
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_end = valid_rows(seq_len, unit, H, N);
 
   TileStage<DK, C, Cfg::NT> qst, kst;
   TileStage<DV, C, Cfg::NT> gst, vst;
   qst.fetch(Q + k_rows, 0, row_end);
   gst.fetch(dO + v_rows, 0, row_end);
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   stage_summed_matrix<DK, DV, Cfg::NT, SP>(Sl, s_totals + size_t(unit) * DK * DV, 1, nullptr, un);
   f32x4 racc[RT::NCT][RT::NRT];
 #pragma unroll
@@ -746,7 +746,7 @@ hipError_t run_fwd_bidir_rows(const CausalArgs& a) {
     return launch_kernel(COTTN_SYM_STR(fwd_bidir_apply), kernel, dim3(units * a.G), dim3(rows * 4), 0, a.stream,
                          static_cast<const elem_t*>(a.Q), a.s, static_cast<elem_t*>(a.O), totals, a.G,
                          sum_in_apply ? a.G : 1, sum_in_apply ? a.state : nullptr, a.H, a.N, a.G, a.seg_rows,
-                         1.0f / a.eps, a.seq_len, a.s_per_unit);
+                         1.0f / a.eps, a.seq_len, a.s_per_unit, units);
   };
   if constexpr (!ELEM_IS_F32 && DK == 128 && DV == 128)
     if (in_rounds) return apply(COTTN_SYM(fwd_bidir_apply)<DK, DV, 64>, 64);
@@ -797,7 +797,7 @@ hipError_t run_bwd_bidir_rows(const CausalArgs& a) {
                       dim3(Cfg::NT), 0, a.stream, static_cast<const elem_t*>(a.Q),
                       static_cast<const elem_t*>(a.dO), a.s, static_cast<elem_t*>(a.dQ), s_src, a.G,
                       few ? a.G : 1, g_totals, ds_partial, a.H, a.N, a.G, a.seg_rows, 1.0f / a.eps,
-                      a.seq_len, a.s_per_unit);
+                      a.seq_len, a.s_per_unit, units);
   if (err != hipSuccess) return err;
   if (!few) {
     err = launch_bidir_combine(g_totals, units, a.G, DK * DV, nullptr, a.stream);

@@ -168,9 +168,9 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dQ,
     const float* __restrict__ fwd_states, float* __restrict__ rev_totals,
-    float* __restrict__ ds_partial, int H, int N, int G, int seg_rows, float inv_eps,
+    float* __restrict__ ds_partial, Divisor H, int N, Divisor G, Divisor seg_rows, float inv_eps,
     int sum_totals, const int* __restrict__ lengths, int s_per_unit,
-    const float* __restrict__ state_in, int units, int unit_rows) {
+    const float* __restrict__ state_in, int units, Divisor unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
   constexpr bool EVEN = walks_even(WALK);
   using AT = SplitTiles<DK, DV, Cfg::RG, CS>;   // forward-time state: key rows, value columns
@@ -214,7 +214,6 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   const elem_t* Vu = V + size_t(unit) * N * DV;
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dQu = dQ + size_t(unit) * N * DK;
-  float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = span.begin;
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
   int piece_end = span.end;   // of the same, with the rows that do not exist
@@ -243,6 +242,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
+  float scale = unit_scale(s, unit, H, s_per_unit);
   const auto form_prefix = [&] {
     lds_t *k_tiles[SETS], *v_tiles[SETS];
 #pragma unroll
@@ -560,9 +560,9 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const elem_t* __restrict__ dO, const float* __restrict__ s, elem_t* __restrict__ dK,
     elem_t* __restrict__ dV, const float* __restrict__ rev_states,
-    const float* __restrict__ ds_partial, float* __restrict__ ds, int B, int H, int N, int G,
-    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
-    const float* __restrict__ rev_in, float* __restrict__ rev_out, int unit_rows) {
+    const float* __restrict__ ds_partial, float* __restrict__ ds, int B, Divisor H, int N, Divisor G,
+    Divisor seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
+    const float* __restrict__ rev_in, float* __restrict__ rev_out, Divisor unit_rows) {
   using Cfg = BwdCfg<DK, DV, C, CS>;
   constexpr bool EVEN = walks_even(WALK);
   using AT = SplitTiles<DV, DK, Cfg::RG, CS>;   // value rows, key columns (the state is held transposed)
@@ -594,34 +594,9 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dKu = dK + size_t(unit) * N * DK;
   elem_t* dVu = dV + size_t(unit) * N * DV;
-  float scale = unit_scale(s, unit, H, s_per_unit);
   int row_begin = span.begin;   // of the piece walked, and its end
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));
   int piece_end = span.end;   // with the rows that do not exist
-
-  // the first H workgroups also finish ds: ds[h] = sum over batches and segments of the
-  // partial sums the dQ kernel left behind (with a scale per (batch, head): the first B*H
-  // workgroups, ds[b][h] = sum over the segments; with even shares there can be fewer workgroups)
-  if constexpr (EVEN) {
-    if (w == 0)
-      for (int h = blockIdx.x; h < (seq_len != nullptr ? B * H : H); h += gridDim.x) {
-        float t = 0.f;
-        for (int b = l; b < (seq_len != nullptr ? 1 : B); b += 64) {
-          const int u = b * H + h, last = ((u + 1) * unit_rows - 1) / seg_rows;
-          for (int slot = u * unit_rows / seg_rows; slot <= last; ++slot) t += ds_partial[slot + u];
-        }
-        t = group_sum<64>(t);
-        if (l == 0) ds[h] = t;
-      }
-  } else if (int(blockIdx.x) < (s_per_unit ? B * H : H) && w == 0) {
-    float t = 0.f;
-    const int n = s_per_unit ? G : B * G;
-    for (int i = l; i < n; i += 64)
-      t += s_per_unit ? ds_partial[size_t(blockIdx.x) * G + i]
-                      : ds_partial[(size_t(i / G) * H + blockIdx.x) * G + (i % G)];
-    t = group_sum<64>(t);
-    if (l == 0) ds[blockIdx.x] = t;
-  }
 
   // rev_states holds the carried suffixes (slot g = reverse state at the end of segment g)
   // or, with sum_totals set, the raw segment totals of the later segments to be added up here
@@ -640,6 +615,30 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
     kst.fetch(Ku, row0, row_end);
     vst.fetch(Vu, row0, row_end);
     gst.fetch(Gu, row0, row_end);
+  }
+  float scale = unit_scale(s, unit, H, s_per_unit);
+  // the first H workgroups also finish ds: ds[h] = sum over batches and segments of the
+  // partial sums the dQ kernel left behind (with a scale per (batch, head): the first B*H
+  // workgroups, ds[b][h] = sum over the segments; with even shares there can be fewer workgroups)
+  if constexpr (EVEN) {
+    if (w == 0)
+      for (int h = blockIdx.x; h < (seq_len != nullptr ? B * H.n : H.n); h += gridDim.x) {
+        float t = 0.f;
+        for (int b = l; b < (seq_len != nullptr ? 1 : B); b += 64) {
+          const int u = b * H + h, last = quotient((u + 1) * unit_rows - 1, seg_rows);
+          for (int slot = quotient(u * unit_rows, seg_rows); slot <= last; ++slot) t += ds_partial[slot + u];
+        }
+        t = group_sum<64>(t);
+        if (l == 0) ds[h] = t;
+      }
+  } else if (int(blockIdx.x) < (s_per_unit ? B * H.n : H.n) && w == 0) {
+    float t = 0.f;
+    const int n = s_per_unit ? G.n : B * G.n;
+    for (int i = l; i < n; i += 64)
+      t += s_per_unit ? ds_partial[size_t(blockIdx.x) * G + i]
+                      : ds_partial[(size_t(quotient(i, G)) * H + blockIdx.x) * G + (i - quotient(i, G) * G)];
+    t = group_sum<64>(t);
+    if (l == 0) ds[blockIdx.x] = t;
   }
   if (rev_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
     add_stored_states<AT::STATE_BATCH>(

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch.h"
+
 #undef COTTN_NS
 #undef COTTN_SYM
 #undef COTTN_SYM_STR
@@ -579,14 +581,14 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Padded batches (sequences of different lengths in one [B][H][N][d] tensor): rows at or
 // beyond seq_len[batch] do not exist.  They are never read, contribute to no sum, and the
 // rows of every output tensor there are written as zeros.  Without lengths all N rows exist.
-__device__ __forceinline__ int valid_rows(const int* __restrict__ seq_len, int unit, int H, int N) {
-  return seq_len != nullptr ? min(N, max(0, seq_len[unit / H])) : N;
+__device__ __forceinline__ int valid_rows(const int* __restrict__ seq_len, int unit, const Divisor& H, int N) {
+  return seq_len != nullptr ? min(N, max(0, seq_len[quotient(unit, H)])) : N;
 }
 // The scale is one value per head, or, for padded batches whose stabiliser depends on each
 // sequence's own length (Sec. 3.3), one per (batch, head).
-__device__ __forceinline__ float unit_scale(const float* __restrict__ s, int unit, int H,
+__device__ __forceinline__ float unit_scale(const float* __restrict__ s, int unit, const Divisor& H,
                                             int per_unit) {
-  return s[per_unit ? unit : unit % H];
+  return s[per_unit ? unit : unit - quotient(unit, H) * H.n];
 }
 // Zeros rows row_lo..row_hi-1 of D columns of a [.][LD] tensor of elements (whole workgroup).
 template <int D, int LD = D>
@@ -632,6 +634,7 @@ template <class T>
 __device__ __forceinline__ void fetch_argument_now(const T& x) {
   asm volatile("" ::"s"(x));
 }
+__device__ __forceinline__ void fetch_argument_now(const Divisor& x) { asm volatile("" ::"s"(x.n), "s"(x.scaled)); }
 template <class T, class... Rest>
 __device__ __forceinline__ void fetch_argument_now(const T& x, const Rest&... rest) {
   fetch_argument_now(x);
@@ -646,16 +649,16 @@ __device__ __forceinline__ void fetch_argument_now(const T& x, const Rest&... re
 // states that the workgroups of a unit write for each other never cross to another L2.
 // (Measured on B8 H12 N1024 d64: 1.6 us of a 56 us step against unit = index / G.)
 // Units beyond the last whole group of 8 are numbered plainly.
-__device__ __forceinline__ void unit_and_segment(int index, int G, int& unit, int& g) {
-  const int n_units = gridDim.x / G;
-  const int grouped = (n_units / 8) * 8 * G;
+__device__ __forceinline__ void unit_and_segment(int index, int units, const Divisor& G, int& unit, int& g) {
+  const int whole = units & ~7, grouped = whole * G.n;
   if (index < grouped) {
-    const int in_group = index % (8 * G);
-    unit = (index / (8 * G)) * 8 + in_group % 8;
-    g = in_group / 8;
+    const int q = quotient(index >> 3, G);   // index / (8 G)
+    unit = 8 * q + (index & 7);
+    g = (index >> 3) - q * G.n;
   } else {
-    unit = (n_units / 8) * 8 + (index - grouped) / G;
-    g = (index - grouped) % G;
+    const int q = quotient(index - grouped, G);
+    unit = whole + q;
+    g = index - grouped - q * G.n;
   }
 }
 
@@ -672,16 +675,18 @@ struct Span {
   int slot, outermost;    // the workgroup's slot; that of the unit's first (reverse: last) workgroup
   bool mid_unit;          // rows of the unit come before (reverse: after) the piece
 };
-__device__ __forceinline__ int even_workgroup() {
-  const int per_xcd = gridDim.x / 8, index = blockIdx.x;
+__device__ __forceinline__ int even_workgroup(int units, const Divisor& seg_rows, int unit_rows) {
+  const int workgroups = quotient(units * unit_rows + seg_rows.n - 1, seg_rows);
+  const int per_xcd = workgroups / 8, index = blockIdx.x;
   return index < 8 * per_xcd ? index % 8 * per_xcd + index / 8 : index;
 }
 template <bool REVERSE, bool EVEN>
-__device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int seg_rows, int unit_rows) {
+__device__ __forceinline__ Span span_of_workgroup(int units, int N, const Divisor& G, const Divisor& seg_rows,
+                                                  const Divisor& unit_rows) {
   Span s;
   if constexpr (!EVEN) {
     int g;
-    unit_and_segment(blockIdx.x, G, s.unit, g);
+    unit_and_segment(blockIdx.x, units, G, s.unit, g);
     s.begin = g * seg_rows;
     s.end = min(N, s.begin + seg_rows);
     s.left = 0;
@@ -690,14 +695,14 @@ __device__ __forceinline__ Span span_of_workgroup(int units, int N, int G, int s
     s.mid_unit = REVERSE ? g < G - 1 : g > 0;
     return s;
   }
-  s.slot = even_workgroup();
+  s.slot = even_workgroup(units, seg_rows, unit_rows);
   const int lo = s.slot * seg_rows, hi = min(lo + seg_rows, units * unit_rows);
-  s.unit = REVERSE ? (hi - 1) / unit_rows : lo / unit_rows;
+  s.unit = quotient(REVERSE ? hi - 1 : lo, unit_rows);
   const int start = s.unit * unit_rows, stop = start + unit_rows;
   s.begin = max(lo - start, 0);
   s.end = min(N, min(hi, stop) - start);
   s.left = REVERSE ? max(start - lo, 0) : max(hi - stop, 0);
-  s.outermost = REVERSE ? (stop - 1) / seg_rows : start / seg_rows;
+  s.outermost = quotient(REVERSE ? stop - 1 : start, seg_rows);
   s.mid_unit = REVERSE ? hi < stop : lo > start;
   return s;
 }

@@ -110,8 +110,8 @@ template <> struct FwdSplit<128, 128, 64> { static constexpr int CS = 2; };
 template <int DK, int DV, int C, bool TILED>
 COTTN_KERNEL((C * 4), fwd_segment_state)
     const elem_t* __restrict__ K, const elem_t* __restrict__ V, float* __restrict__ seg_state,
-    int N, int n_slots, int n_compute, int seg_rows, float inv_eps,
-    const int* __restrict__ seq_len, int H, int units, int unit_rows) {
+    int N, Divisor n_slots, int n_compute, Divisor seg_rows, float inv_eps,
+    const int* __restrict__ seq_len, Divisor H, int units, Divisor unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
   using ST = AccTiles<DK, DV, Cfg::NW>;   // key rows, value columns
   using StageK = TileStage<DK, C, Cfg::NT>;
@@ -121,7 +121,7 @@ COTTN_KERNEL((C * 4), fwd_segment_state)
 
   Unparted un;
   fetch_argument_now(K, V, seg_state, N, n_slots, n_compute, seg_rows, inv_eps, seq_len, H, units, unit_rows);
-  const Span span = unit_rows == 0 ? span_of_workgroup<false, false>(units, N, n_slots, seg_rows, 0)
+  const Span span = unit_rows == 0 ? span_of_workgroup<false, false>(units, N, n_slots, seg_rows, unit_rows)
                                    : span_of_workgroup<true, true>(units, N, n_slots, seg_rows, unit_rows);
   const int unit = span.unit;
   if (unit_rows == 0 ? span.slot - span.outermost >= n_compute : !span.mid_unit) {
@@ -204,9 +204,9 @@ template <int DK, int DV, int C, int CS, int WALK, int LDV = DV>
 COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd_causal_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
-    float* __restrict__ seg_states, const float* __restrict__ state_in, int H, int N, int G,
-    int seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
-    int stream_q, int stream_kv, int units, int unit_rows) {
+    float* __restrict__ seg_states, const float* __restrict__ state_in, Divisor H, int N, Divisor G,
+    Divisor seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
+    int stream_q, int stream_kv, int units, Divisor unit_rows) {
   using Cfg = FwdCfg<DK, DV, C>;
   constexpr bool EVEN = walks_even(WALK);
   constexpr int RG = C / 16;           // row groups of a chunk
@@ -237,7 +237,10 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   int part = 0;
   if constexpr (LDV > DV) {
     span = Span{0, 0, N, 0, 0, 0, false};
-    unit_and_segment(blockIdx.x, LDV / DV, span.unit, part);
+    constexpr int PARTS = LDV / DV;   // numbered as segments are: those of a unit on one XCD
+    const int index = blockIdx.x, whole = units & ~7, in_group = index % (8 * PARTS), rest = index - whole * PARTS;
+    span.unit = rest < 0 ? index / (8 * PARTS) * 8 + in_group % 8 : whole + rest / PARTS;
+    part = rest < 0 ? in_group / 8 : rest % PARTS;
   } else {
     span = span_of_workgroup<false, EVEN>(units, N, G, seg_rows, unit_rows);
   }
@@ -249,7 +252,6 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * LDV + part * DV;
   elem_t* Ou = O + size_t(unit) * N * LDV + part * DV;
-  float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = span.begin;
   int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), span.end));   // of the piece walked
   int piece_end = span.end;   // of the same, with the rows that do not exist
@@ -269,6 +271,7 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   qst.fetch(Qu, row_begin, row_end, stream_q != 0);
   kst.fetch(Ku, row_begin, row_end, stream_kv != 0);
   vst.fetch(Vu, row_begin, row_end, stream_kv != 0);
+  float scale = unit_scale(s, unit, H, s_per_unit);
   // the state the sequence starts from (chunked prefill) belongs to every segment's start state
   f32x4 start[ST::NCT][ST::NRT];
   const auto load_start = [&] {

@@ -68,3 +68,13 @@ def test_own_prefix_by_sets(tmp_path):
                     four = (dk, dv) == (32, 32) or ((dk, dv) == (64, 32) and forward and not f32)
                     rules.append("prefix_sets_built(%d, %d, %s, %s) == %d" % (dk, dv, str(f32).lower(), str(forward).lower(), 4 if four else 1))
     holds(tmp_path, rules)
+
+
+def test_quotients_of_kernel_arguments(tmp_path):
+    """Divisor and quotient: around multiples of small and large divisors, up to the largest row numbers and indexes."""
+    rules = []
+    for n in (1, 2, 3, 7, 8, 12, 13, 96, 641, 777, 1000, 4096, 65535, 65537, 16777216, 1073741823, 2147483647):
+        xs = {0, 1, n - 1, n, 2147483647, 2147483646, 2147483647 // n * n, 2147483647 // n * n - 1, 536870912, 1234567890}
+        xs |= {k * n + e for k in (1, 2, 3, 1000003) for e in (-1, 0, 1)}
+        rules += ["quotient(%d, Divisor(%d)) == %d" % (x, n, x // n) for x in sorted(xs) if 0 <= x <= 2147483647]
+    holds(tmp_path, rules + ["Divisor(0) == 0"])
