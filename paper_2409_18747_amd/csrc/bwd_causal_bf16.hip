@@ -262,7 +262,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dq_scan)
   if ((walks_own_prefix(WALK) || WALK == EVEN_SHARES) && no_states) {
     if (span.mid_unit) form_prefix();
   } else if (fwd_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
-    add_stored_states<AT::STATE_BATCH>(
+    add_stored_states<AT::STATE_BATCH, AT::STATE_MANY>(
         sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
         [&](int slot, int x, int y) {
           return *reinterpret_cast<const f32x4*>(
@@ -641,7 +641,7 @@ COTTN_KERNEL((C * 4 * CS, (BwdCfg<DK, DV, C, CS>::WAVES_PER_EU)), bwd_dkdv_scan)
     if (l == 0) ds[blockIdx.x] = t;
   }
   if (rev_states != nullptr && span.mid_unit && AT::active(rg, cp)) {
-    add_stored_states<AT::STATE_BATCH>(
+    add_stored_states<AT::STATE_BATCH, AT::STATE_MANY>(
         racc, sum_totals ? span.slot + 1 : span.slot, sum_totals ? span.outermost : span.slot,
         [&](int slot, int x, int y) {
           return *reinterpret_cast<const f32x4*>(

@@ -334,7 +334,7 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
     }
   } else if (LDV == DV && seg_states != nullptr && span.mid_unit && ST::active(rg, cp)) {
     const float* src = seg_states + 4 * l;
-    add_stored_states<ST::STATE_BATCH>(
+    add_stored_states<ST::STATE_BATCH, ST::STATE_MANY>(
         sacc, sum_totals ? span.outermost : span.slot, sum_totals ? span.slot - 1 : span.slot,
         [&](int slot, int x, int y) {
           return *reinterpret_cast<const f32x4*>(

@@ -116,8 +116,6 @@ struct AccTiles {
   static constexpr int NCT = (NW >= CT) ? 1 : CT / NW;      // column tiles per wave
   static constexpr int WPC = (NW >= CT) ? NW / CT : 1;      // waves per tile column
   static constexpr int NRT = (WPC >= RT) ? 1 : RT / WPC;    // row tiles per wave
-  // stored states a wave loads at once when it seeds its accumulators (register budget)
-  static constexpr int STATE_BATCH = NCT * NRT <= 4 ? 3 : NCT * NRT <= 8 ? 2 : 1;
   __device__ static __forceinline__ bool active(int w) { return (w / CT) * NRT < RT; }
   __device__ static __forceinline__ int col_tile(int w, int x) { return (w % CT) + x * NW; }
   __device__ static __forceinline__ int row_tile(int w, int y) {
@@ -139,7 +137,14 @@ struct SplitTiles {
   // whether the row-side operand of the state update is among the fragments of the wave's
   // result columns (else it is read separately)
   static constexpr bool ROW_OPERAND_IS_RESULT_COLUMN = CS == 1 ? One::WPC == 1 : true;
-  static constexpr int STATE_BATCH = NCT * NRT <= 4 ? 3 : NCT * NRT <= 8 ? 2 : 1;
+  // Stored states a wave loads at once when it seeds its accumulators, up to BATCH of them and beyond (register budget).
+  // More at once save latencies until the 64 bytes a cycle of the vector L1 are the bound, and the registers cost the
+  // wider scans their schedule.  Kernels with BATCH at once / these: 15 units of 777 rows at 64 x 128 dK/dV 11.3 / 10.1 us,
+  // 4 of 2000 at 32 x 32 forward 5.4 / 5.2 and dK/dV 5.9 / 5.6, fp32 10 of 800 at 32 x 32 forward 6.5 / 5.4.  Not taken:
+  // 5 at four tiles, 15 of 777 at 64 x 64 forward 5.8 / 6.5, and 4 at 128 x 128, 96 of 1024 forward 24.9 / 25.2.
+  static constexpr int TILES = NCT * NRT, STATE_BATCH = TILES <= 4 ? 3 : TILES <= 8 ? 2 : 1;
+  static constexpr int STATE_MANY =
+      TILES <= 2 ? 6 : TILES > 4 && TILES <= 8 && DR * DC < 128 * 128 ? 4 : STATE_BATCH;
   static_assert(CS == 1 || RT % CS == 0, "column parts must be whole tiles");
   __device__ static __forceinline__ bool active(int rg, int cp) {
     return CS == 1 ? One::active(rg) : rg < CT;
@@ -184,31 +189,37 @@ constexpr bool skips_unseen(int waves_per_group, int rows) { return SPLIT3 && wa
 
 // acc += the wave's tiles of the stored states first..last, `load(state, x, y)` returning
 // tile (x, y) of one of them.  States are taken BATCH at a time with every load of a batch
-// issued before the first addition, so a batch costs one memory latency, not one per state.
+// issued before the first addition, so a batch costs one memory latency, not one per state; MANY at a time
+// while there are more than BATCH of them.
 // Slots of the last batch beyond `last` re-read `last` (an address already in flight) and
 // are discarded.
 template <int BATCH, int NCT, int NRT, class LoadTile>
+__device__ __forceinline__ void add_stored_batch(f32x4 (&acc)[NCT][NRT], int base, int last, LoadTile load) {
+  f32x4 t[BATCH][NCT][NRT];
+#pragma unroll
+  for (int i = 0; i < BATCH; ++i)
+#pragma unroll
+    for (int x = 0; x < NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < NRT; ++y) t[i][x][y] = load(min(base + i, last), x, y);
+#pragma unroll
+  for (int i = 0; i < BATCH; ++i) {
+    const bool keep = base + i <= last;
+#pragma unroll
+    for (int x = 0; x < NCT; ++x)
+#pragma unroll
+      for (int y = 0; y < NRT; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[x][y][v] += keep ? t[i][x][y][v] : 0.f;
+  }
+}
+template <int BATCH, int MANY, int NCT, int NRT, class LoadTile>
 __device__ __forceinline__ void add_stored_states(f32x4 (&acc)[NCT][NRT], int first, int last,
                                                   LoadTile load) {
-  for (int base = first; base <= last; base += BATCH) {
-    f32x4 t[BATCH][NCT][NRT];
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i)
-#pragma unroll
-      for (int x = 0; x < NCT; ++x)
-#pragma unroll
-        for (int y = 0; y < NRT; ++y) t[i][x][y] = load(min(base + i, last), x, y);
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const bool keep = base + i <= last;
-#pragma unroll
-      for (int x = 0; x < NCT; ++x)
-#pragma unroll
-        for (int y = 0; y < NRT; ++y)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[x][y][v] += keep ? t[i][x][y][v] : 0.f;
-    }
-  }
+  int base = first;
+  if constexpr (MANY > BATCH)
+    for (; base + BATCH <= last; base += MANY) add_stored_batch<MANY>(acc, base, last, load);
+  for (; base <= last; base += BATCH) add_stored_batch<BATCH>(acc, base, last, load);
 }
 
 // acc += kh^T v over rows row_begin .. row_end - 1 of one unit, C rows at a time; the first C rows
