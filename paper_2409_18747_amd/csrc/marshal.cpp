@@ -165,6 +165,14 @@ struct Call {
   }
 };
 
+// Other threads run Python meanwhile, as under ctypes: an allocation or a launch may wait for the GPU.
+struct Unlocked {
+  PyThreadState* const thread = PyEval_SaveThread();
+  Unlocked() = default;
+  Unlocked(const Unlocked&) = delete;
+  ~Unlocked() { PyEval_RestoreThread(thread); }
+};
+
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // the given object, or a new tensor (of `made`), as a result
@@ -218,47 +226,50 @@ PyObject* fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     have = lib.workspace_bytes_dkdv(is_bidir(variant) ? COTTN_OP_FWD_BIDIR : COTTN_OP_FWD_CAUSAL, B, H, N, dk, dv, chunk, dt);
     if (have == size_t(-1)) Py_RETURN_NONE;
   }
-  if (O == nullptr) {
-    made = at::empty(V->sizes(), V->options());
-    O = &made;
-  }
-  if (!given_workspace && have > 0) {
-    scratch = at::empty({int64_t(have)}, Q->options().dtype(at::kByte));
-    workspace = scratch.data_ptr();
-  }
-  const void *q = Q->data_ptr(), *k = K->data_ptr(), *v = V->data_ptr();
-  void *o = O->data_ptr(), *stream = current_stream();
   int st = COTTN_E_ARG;
   const char* where = "";
-  switch (variant) {
-    case CAUSAL:
-      where = "cottn_fwd_causal";
-      st = lib.fwd_causal(q, k, v, s, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
-      break;
-    case CAUSAL_FROM_STATE:
-      where = "cottn_fwd_causal_from_state";
-      st = lib.fwd_causal_from_state(q, k, v, s, state_in, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
-      break;
-    case CAUSAL_VARLEN:
-      where = "cottn_fwd_causal_varlen";
-      st = lib.fwd_causal_varlen(q, k, v, s, seq_len, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
-      break;
-    case CAUSAL_DKDV:
-      where = "cottn_fwd_causal_dkdv";
-      st = lib.fwd_causal_dkdv(q, k, v, s, o, state, workspace, have, B, H, N, dk, dv, chunk, dt, eps, stream);
-      break;
-    case BIDIR:
-      where = "cottn_fwd_bidir";
-      st = lib.fwd_bidir(q, k, v, s, o, state, workspace, have, B, H, N, dk, dt, eps, stream);
-      break;
-    case BIDIR_VARLEN:
-      where = "cottn_fwd_bidir_varlen";
-      st = lib.fwd_bidir_varlen(q, k, v, s, seq_len, o, state, workspace, have, B, H, N, dk, dt, eps, stream);
-      break;
-    case BIDIR_DKDV:
-      where = "cottn_fwd_bidir_dkdv";
-      st = lib.fwd_bidir_dkdv(q, k, v, s, o, state, workspace, have, B, H, N, dk, dv, dt, eps, stream);
-      break;
+  {
+    const Unlocked unlocked;
+    if (O == nullptr) {
+      made = at::empty(V->sizes(), V->options());
+      O = &made;
+    }
+    if (!given_workspace && have > 0) {
+      scratch = at::empty({int64_t(have)}, Q->options().dtype(at::kByte));
+      workspace = scratch.data_ptr();
+    }
+    const void *q = Q->data_ptr(), *k = K->data_ptr(), *v = V->data_ptr();
+    void *o = O->data_ptr(), *stream = current_stream();
+    switch (variant) {
+      case CAUSAL:
+        where = "cottn_fwd_causal";
+        st = lib.fwd_causal(q, k, v, s, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
+        break;
+      case CAUSAL_FROM_STATE:
+        where = "cottn_fwd_causal_from_state";
+        st = lib.fwd_causal_from_state(q, k, v, s, state_in, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
+        break;
+      case CAUSAL_VARLEN:
+        where = "cottn_fwd_causal_varlen";
+        st = lib.fwd_causal_varlen(q, k, v, s, seq_len, o, state, workspace, have, B, H, N, dk, chunk, dt, eps, stream);
+        break;
+      case CAUSAL_DKDV:
+        where = "cottn_fwd_causal_dkdv";
+        st = lib.fwd_causal_dkdv(q, k, v, s, o, state, workspace, have, B, H, N, dk, dv, chunk, dt, eps, stream);
+        break;
+      case BIDIR:
+        where = "cottn_fwd_bidir";
+        st = lib.fwd_bidir(q, k, v, s, o, state, workspace, have, B, H, N, dk, dt, eps, stream);
+        break;
+      case BIDIR_VARLEN:
+        where = "cottn_fwd_bidir_varlen";
+        st = lib.fwd_bidir_varlen(q, k, v, s, seq_len, o, state, workspace, have, B, H, N, dk, dt, eps, stream);
+        break;
+      case BIDIR_DKDV:
+        where = "cottn_fwd_bidir_dkdv";
+        st = lib.fwd_bidir_dkdv(q, k, v, s, o, state, workspace, have, B, H, N, dk, dv, dt, eps, stream);
+        break;
+    }
   }
   if (st != COTTN_OK) return raise_status(st, where);
   return result(given_O, made);
@@ -310,60 +321,63 @@ PyObject* bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (have == size_t(-1)) Py_RETURN_NONE;
   }
   at::Tensor made[4], scratch;
-  for (int i = 0; i < 3; ++i)
-    if (grads[i] == nullptr) {
-      const at::Tensor* ref = i < 2 ? Q : V;
-      made[i] = at::empty(ref->sizes(), ref->options());
-      grads[i] = &made[i];
-    }
-  if (given[3] == Py_None) {
-    made[3] = has_lengths(variant) ? at::empty({B, H}, Q->options().dtype(at::kFloat)) : at::empty({H}, Q->options().dtype(at::kFloat));
-    ds = static_cast<float*>(made[3].data_ptr());
-  }
-  if (!given_workspace && have > 0) {
-    scratch = at::empty({int64_t(have)}, Q->options().dtype(at::kByte));
-    workspace = scratch.data_ptr();
-  }
-  const void *q = Q->data_ptr(), *k = K->data_ptr(), *v = V->data_ptr(), *go = dO->data_ptr();
-  void *dq = grads[0]->data_ptr(), *dkey = grads[1]->data_ptr(), *dval = grads[2]->data_ptr(), *stream = current_stream();
   int st = COTTN_E_ARG;
   const char* where = "";
-  switch (variant) {
-    case CAUSAL:
-      where = "cottn_bwd_causal";
-      st = lib.bwd_causal(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, chunk, dt,
-                          eps, stream);
-      break;
-    case CAUSAL_FROM_STATE:
-      where = "cottn_bwd_causal_from_state";
-      st = lib.bwd_causal_from_state(q, k, v, s, go, state_in, rev_in, dq, dkey, dval, ds, rev_out, fwd_workspace, fwd_have,
-                                     workspace, have, B, H, N, dk, chunk, dt, eps, stream);
-      break;
-    case CAUSAL_VARLEN:
-      where = "cottn_bwd_causal_varlen";
-      st = lib.bwd_causal_varlen(q, k, v, s, seq_len, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H,
-                                 N, dk, chunk, dt, eps, stream);
-      break;
-    case CAUSAL_DKDV:
-      where = "cottn_bwd_causal_dkdv";
-      st = lib.bwd_causal_dkdv(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dv,
-                               chunk, dt, eps, stream);
-      break;
-    case BIDIR:
-      where = "cottn_bwd_bidir";
-      st = lib.bwd_bidir(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dt, eps,
-                         stream);
-      break;
-    case BIDIR_VARLEN:
-      where = "cottn_bwd_bidir_varlen";
-      st = lib.bwd_bidir_varlen(q, k, v, s, seq_len, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H,
-                                N, dk, dt, eps, stream);
-      break;
-    case BIDIR_DKDV:
-      where = "cottn_bwd_bidir_dkdv";
-      st = lib.bwd_bidir_dkdv(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dv,
-                              dt, eps, stream);
-      break;
+  {
+    const Unlocked unlocked;
+    for (int i = 0; i < 3; ++i)
+      if (grads[i] == nullptr) {
+        const at::Tensor* ref = i < 2 ? Q : V;
+        made[i] = at::empty(ref->sizes(), ref->options());
+        grads[i] = &made[i];
+      }
+    if (given[3] == Py_None) {
+      made[3] = has_lengths(variant) ? at::empty({B, H}, Q->options().dtype(at::kFloat)) : at::empty({H}, Q->options().dtype(at::kFloat));
+      ds = static_cast<float*>(made[3].data_ptr());
+    }
+    if (!given_workspace && have > 0) {
+      scratch = at::empty({int64_t(have)}, Q->options().dtype(at::kByte));
+      workspace = scratch.data_ptr();
+    }
+    const void *q = Q->data_ptr(), *k = K->data_ptr(), *v = V->data_ptr(), *go = dO->data_ptr();
+    void *dq = grads[0]->data_ptr(), *dkey = grads[1]->data_ptr(), *dval = grads[2]->data_ptr(), *stream = current_stream();
+    switch (variant) {
+      case CAUSAL:
+        where = "cottn_bwd_causal";
+        st = lib.bwd_causal(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, chunk, dt,
+                            eps, stream);
+        break;
+      case CAUSAL_FROM_STATE:
+        where = "cottn_bwd_causal_from_state";
+        st = lib.bwd_causal_from_state(q, k, v, s, go, state_in, rev_in, dq, dkey, dval, ds, rev_out, fwd_workspace, fwd_have,
+                                       workspace, have, B, H, N, dk, chunk, dt, eps, stream);
+        break;
+      case CAUSAL_VARLEN:
+        where = "cottn_bwd_causal_varlen";
+        st = lib.bwd_causal_varlen(q, k, v, s, seq_len, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H,
+                                   N, dk, chunk, dt, eps, stream);
+        break;
+      case CAUSAL_DKDV:
+        where = "cottn_bwd_causal_dkdv";
+        st = lib.bwd_causal_dkdv(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dv,
+                                 chunk, dt, eps, stream);
+        break;
+      case BIDIR:
+        where = "cottn_bwd_bidir";
+        st = lib.bwd_bidir(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dt, eps,
+                           stream);
+        break;
+      case BIDIR_VARLEN:
+        where = "cottn_bwd_bidir_varlen";
+        st = lib.bwd_bidir_varlen(q, k, v, s, seq_len, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H,
+                                  N, dk, dt, eps, stream);
+        break;
+      case BIDIR_DKDV:
+        where = "cottn_bwd_bidir_dkdv";
+        st = lib.bwd_bidir_dkdv(q, k, v, s, go, dq, dkey, dval, ds, fwd_workspace, fwd_have, workspace, have, B, H, N, dk, dv,
+                                dt, eps, stream);
+        break;
+    }
   }
   if (st != COTTN_OK) return raise_status(st, where);
   PyObject* all = PyTuple_New(4);
@@ -406,12 +420,16 @@ PyObject* step(PyObject*, PyObject* const* args, Py_ssize_t n) {
   const float eps = c.real();
   if (!c.ok) Py_RETURN_NONE;
   at::Tensor made;
-  if (o == nullptr) {
-    made = at::empty(v->sizes(), v->options());
-    o = &made;
+  int st;
+  {
+    const Unlocked unlocked;
+    if (o == nullptr) {
+      made = at::empty(v->sizes(), v->options());
+      o = &made;
+    }
+    st = lib.step_dkdv(q->data_ptr(), k->data_ptr(), v->data_ptr(), s, state, o->data_ptr(), B, H, dk, dv, dt, eps,
+                       current_stream());
   }
-  const int st = lib.step_dkdv(q->data_ptr(), k->data_ptr(), v->data_ptr(), s, state, o->data_ptr(), B, H, dk, dv, dt, eps,
-                               current_stream());
   if (st != COTTN_OK) return raise_status(st, widths ? "cottn_step_dkdv" : "cottn_step");
   return result(given, made);
   END_HANDLE_TH_ERRORS
@@ -434,14 +452,18 @@ PyObject* scale_varlen(PyObject*, PyObject* const* args, Py_ssize_t n) {
   float* out = static_cast<float*>(c.floats(backward ? H : int64_t(B) * H, true));
   if (!c.ok) Py_RETURN_NONE;
   at::Tensor made;
-  if (given == Py_None) {
-    made = backward ? at::empty({H}, m->options()) : at::empty({B, H}, m->options());
-    out = static_cast<float*>(made.data_ptr());
-  }
   const float* mp = static_cast<const float*>(m->data_ptr());
   const int* lp = static_cast<const int*>(seq_len->data_ptr());
-  const int st = backward ? lib.scale_backward_varlen(mp, lp, ds, out, B, H, current_stream())
-                          : lib.scale_from_m_varlen(mp, lp, out, B, H, current_stream());
+  int st;
+  {
+    const Unlocked unlocked;
+    if (given == Py_None) {
+      made = backward ? at::empty({H}, m->options()) : at::empty({B, H}, m->options());
+      out = static_cast<float*>(made.data_ptr());
+    }
+    st = backward ? lib.scale_backward_varlen(mp, lp, ds, out, B, H, current_stream())
+                  : lib.scale_from_m_varlen(mp, lp, out, B, H, current_stream());
+  }
   if (st != COTTN_OK) return raise_status(st, backward ? "cottn_scale_backward_varlen" : "cottn_scale_from_m_varlen");
   return result(given, made);
   END_HANDLE_TH_ERRORS
