@@ -4,7 +4,7 @@ PyTorch supplies device memory and the stream handle, nothing else.
 
 The marshalling is here, over ctypes, for every call, and once more in C++ (csrc/marshal.cpp, module _marshal) for
 plain tensors on the current stream, which the attention and step calls try first: it does the whole call, or nothing and
-answers None.  Decode step of 16 states 7.4 -> 3.5 us a call, of which the launch is 3.1; five drafted tokens of 128
+answers None.  Decode step of 16 states 7.4 -> 3.7 us a call, of which the launch is 3.1; five drafted tokens of 128
 states 7.9 -> 6.6, a forward of 2 x 256 rows of 32 fp32 with its two allocations 9.9 -> 7.5 (the kernels from there on).
 
 The library must have been built (``python -m paper_2409_18747_amd.build``); there is no
