@@ -8,19 +8,39 @@ answers None.  Decode step of 16 states 7.4 -> 3.7 us a call, of which the launc
 states 7.9 -> 6.6, a forward of 2 x 256 rows of 32 fp32 with its two allocations 9.9 -> 7.5 (the kernels from there on).
 
 The library must have been built (``python -m paper_2409_18747_amd.build``); there is no
-fallback: a missing library raises at first use.
+fallback: a missing library raises at first use.  Without _marshal the calls are the same and take those few us longer:
+that is a warning.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
-try:
-    from . import _marshal
-except ImportError as e:
-    raise ImportError("_marshal.so is not built: run `python -m paper_2409_18747_amd.build`") from e
-
 _HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+class _NoMarshal:
+    """In the place of _marshal where that cannot be used: leaves every call to the code below."""
+    @staticmethod
+    def fwd(*_):
+        return None
+    bwd = step = scale_varlen = bind = fwd
+
+
+def _import_marshal():
+    try:
+        from . import _marshal
+        return _marshal
+    except ImportError as e:
+        built = os.path.exists(os.path.join(_HERE, "_marshal.so"))
+        why = "does not load (%s)" % e if built else "is not built"
+    warnings.warn("_marshal.so %s: calls are marshalled in Python, some us slower each.  Run "
+                  "`python -m paper_2409_18747_amd.build`" % why, RuntimeWarning)
+    return _NoMarshal
+
+
+_marshal = _import_marshal()
 library_path = os.path.join(_HERE, "libcottn.so")
 
 COTTN_F32, COTTN_BF16, COTTN_F16 = 0, 1, 2
