@@ -174,6 +174,21 @@ constexpr int prefix_sets_built(int dk, int dv, bool f32, bool forward) {
 }
 constexpr bool prefix_by_sets(long workgroups) { return workgroups <= 256; }
 
+// Stored states that a wave with this many 16 x 16 tiles of each loads at once when it seeds its accumulators (register
+// budget), and how many where more than those are left.  More at once save latencies until the 64 bytes a cycle of the
+// vector L1 are the bound.  The first number throughout / these, sums in place, forward alone and with backward in us:
+// five to eight tiles, 15 units of 777 rows 16-bit 64 x 128 16.2, 37.4 / 15.0, 35.0 and 128 x 64 16.2, 37.9 / 14.9, 35.9, fp32
+// 23.9, 60.4 / 22.9, 59.3 and 24.4, 62.9 / 23.9, 62.0 (fp32 whose prefixes come carried, one state each, give 0.2 to 0.8 back: 15
+// of 1500 32.9, 79.8 / 32.7, 80.4 and 34.1, 86.6 / 34.0, 87.1); up to two, 4 of 2000 16-bit 64 x 32 9.6, 24.5 / 9.3, 23.7, fp32 32 x 64
+// 14.5, 36.3 / 13.8, 35.1.  Not taken: 5 at four tiles, 15 of 777 at 64 x 64 forward scan 5.8 / 6.5, and 4 at 128 x 128, 96 of 1024
+// forward scan 24.9 / 25.2.  Nor 6 at 64 x 64 by sixteen waves (256-row chunks), whose 128 registers a wave do not hold what they
+// have: twelve more are spilled in the bf16 dQ scan, 96 of 1024 with backward 129.2 / 133.8, 16 of 16384 327.5 / 332.9.
+constexpr int states_at_once(int tiles) { return tiles <= 4 ? 3 : tiles <= 8 ? 2 : 1; }
+constexpr int states_at_once_of_many(int tiles, int elements, int waves) {
+  if (waves >= 16 && elements >= 64 * 64) return states_at_once(tiles);
+  return tiles <= 2 ? 6 : tiles > 4 && tiles <= 8 && elements < 128 * 128 ? 4 : states_at_once(tiles);
+}
+
 // Shapes built for even shares (api.hip: causal_even_share, which asks for no others).
 constexpr bool even_shares_built(int dk, int dv, bool f32) {
   return (dk == 128 && dv == 128) || (f32 && dk >= 64 && dv >= 64);

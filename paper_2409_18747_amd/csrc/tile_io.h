@@ -137,14 +137,9 @@ struct SplitTiles {
   // whether the row-side operand of the state update is among the fragments of the wave's
   // result columns (else it is read separately)
   static constexpr bool ROW_OPERAND_IS_RESULT_COLUMN = CS == 1 ? One::WPC == 1 : true;
-  // Stored states a wave loads at once when it seeds its accumulators, up to BATCH of them and beyond (register budget).
-  // More at once save latencies until the 64 bytes a cycle of the vector L1 are the bound, and the registers cost the
-  // wider scans their schedule.  Kernels with BATCH at once / these: 15 units of 777 rows at 64 x 128 dK/dV 11.3 / 10.1 us,
-  // 4 of 2000 at 32 x 32 forward 5.4 / 5.2 and dK/dV 5.9 / 5.6, fp32 10 of 800 at 32 x 32 forward 6.5 / 5.4.  Not taken:
-  // 5 at four tiles, 15 of 777 at 64 x 64 forward 5.8 / 6.5, and 4 at 128 x 128, 96 of 1024 forward 24.9 / 25.2.
-  static constexpr int TILES = NCT * NRT, STATE_BATCH = TILES <= 4 ? 3 : TILES <= 8 ? 2 : 1;
-  static constexpr int STATE_MANY =
-      TILES <= 2 ? 6 : TILES > 4 && TILES <= 8 && DR * DC < 128 * 128 ? 4 : STATE_BATCH;
+  // stored states a wave loads at once when it seeds its accumulators, up to BATCH of them and beyond
+  static constexpr int TILES = NCT * NRT, STATE_BATCH = states_at_once(TILES),
+                       STATE_MANY = states_at_once_of_many(TILES, DR * DC, RG * CS);
   static_assert(CS == 1 || RT % CS == 0, "column parts must be whole tiles");
   __device__ static __forceinline__ bool active(int rg, int cp) {
     return CS == 1 ? One::active(rg) : rg < CT;

@@ -78,3 +78,13 @@ def test_quotients_of_kernel_arguments(tmp_path):
         xs |= {k * n + e for k in (1, 2, 3, 1000003) for e in (-1, 0, 1)}
         rules += ["quotient(%d, Divisor(%d)) == %d" % (x, n, x // n) for x in sorted(xs) if 0 <= x <= 2147483647]
     holds(tmp_path, rules + ["Divisor(0) == 0"])
+
+
+def test_states_at_once(tmp_path):
+    """Up to two tiles a wave take six stored states at once, five to eight four, but not where sixteen waves hold 64 x 64."""
+    rules = ["states_at_once(%d) == %d" % (t, n) for t, n in ((1, 3), (4, 3), (5, 2), (8, 2), (9, 1), (16, 1))]
+    for waves in (4, 8, 15, 16):
+        for tiles, elements, n in ((1, 64 * 64, 6 if waves < 16 else 3), (2, 64 * 64, 6 if waves < 16 else 3), (1, 32 * 32, 6),
+                                   (4, 64 * 64, 3), (8, 64 * 128, 4 if waves < 16 else 2), (8, 128 * 128, 2), (16, 128 * 128, 1)):
+            rules.append("states_at_once_of_many(%d, %d, %d) == %d" % (tiles, elements, waves, n))
+    holds(tmp_path, rules)
