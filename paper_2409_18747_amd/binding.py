@@ -17,6 +17,8 @@ import warnings
 
 import torch
 
+from .build import marshal_target
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -29,9 +31,13 @@ class _NoMarshal:
 
 
 def _import_marshal():
+    target = marshal_target()
     try:
         from . import _marshal
-        return _marshal
+        built_for = getattr(_marshal, "built_for", "something else")
+        if built_for == target:
+            return _marshal
+        why = "was built for %s, not for %s" % (built_for, target)
     except ImportError as e:
         built = os.path.exists(os.path.join(_HERE, "_marshal.so"))
         why = "does not load (%s)" % e if built else "is not built"

@@ -8,6 +8,7 @@ import concurrent.futures
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -34,12 +35,19 @@ def _compile(src: str) -> str:
     return obj
 
 
+def marshal_target() -> str:
+    """What _marshal.so is compiled against and says so: it holds the layouts of this torch's and this Python's objects."""
+    import torch
+    return "torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+
+
 def _build_marshal() -> None:
     import torch
     base = os.path.dirname(torch.__file__)
     tmp = MARSHAL + ".tmp.%d" % os.getpid()
     proc = subprocess.run(
         [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+         '-DCOTTN_BUILT_FOR="%s"' % marshal_target(),
          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", os.path.join(base, "include"),
          "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
          "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,

@@ -527,4 +527,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// built_for: binding.py compares it with what it runs under (build.py: marshal_target)
+PyMODINIT_FUNC PyInit__marshal(void) {
+  PyObject* made = PyModule_Create(&module);
+  if (made != nullptr && PyModule_AddStringConstant(made, "built_for", COTTN_BUILT_FOR) < 0) Py_CLEAR(made);
+  return made;
+}

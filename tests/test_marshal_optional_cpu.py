@@ -40,7 +40,7 @@ for call, args in ((b.cottn_bwd_causal, (Q, Q, Q, torch.ones(2), Q[:, :1])), (b.
 def warnings_of(tmp_path, marshal, before=""):
     package = tmp_path / "paper_2409_18747_amd"
     package.mkdir()
-    for name in ("__init__.py", "binding.py"):
+    for name in ("__init__.py", "binding.py", "build.py"):
         shutil.copy(os.path.join(os.path.dirname(binding.library_path), name), package / name)
     os.symlink(binding.library_path, package / "libcottn.so")
     if marshal is not None:
@@ -60,3 +60,10 @@ def test_calls_are_made_without_it(tmp_path, marshal, why):
 def test_no_warning_with_it(tmp_path):
     with open(os.path.join(os.path.dirname(binding.library_path), "_marshal.so"), "rb") as f:
         assert warnings_of(tmp_path, f.read()).strip() == "[]"
+
+
+def test_one_built_for_another_torch_is_not_used(tmp_path):
+    """It holds the layout of that torch's tensors."""
+    with open(os.path.join(os.path.dirname(binding.library_path), "_marshal.so"), "rb") as f:
+        said = warnings_of(tmp_path, f.read(), "torch.__version__ = '1.0'")
+    assert "_marshal.so was built for torch" in said and "not for torch 1.0" in said, said
