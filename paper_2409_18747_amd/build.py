@@ -66,10 +66,10 @@ def build(jobs: int = 8) -> str:
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
         marshal = pool.submit(_build_marshal)
         objs = list(pool.map(_compile, sources))
-        marshal.result()
-    tmp = LIB + ".tmp.%d" % os.getpid()
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], check=True)
-    os.replace(tmp, LIB)
+        tmp = LIB + ".tmp.%d" % os.getpid()
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], check=True)
+        os.replace(tmp, LIB)
+        marshal.result()   # the library is there also where this raises, and the binding works with it alone
     return LIB
 
 
