@@ -7,6 +7,7 @@ without a GPU.  Every .hip file is compiled to an object in parallel, then linke
 import concurrent.futures
 import glob
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -49,7 +50,8 @@ def _build_marshal() -> None:
         [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
          '-DCOTTN_BUILT_FOR="%s"' % marshal_target(),
          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", os.path.join(base, "include"),
-         "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+         "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem",
+         os.path.join(os.path.dirname(os.path.dirname(shutil.which(HIPCC) or HIPCC)), "include"),   # of the same ROCm
          "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
          "-L" + os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"],
         capture_output=True, text=True)

@@ -32,3 +32,13 @@ def test_library_is_linked_without_torch(sandbox, monkeypatch):
     with pytest.raises(ImportError):
         build.build()
     assert os.path.exists(build.LIB) and not os.path.exists(build.MARSHAL)
+
+
+def test_headers_of_the_compilers_own_rocm(sandbox, monkeypatch):
+    cxx = sandbox / "cxx"
+    cxx.write_text('#!/bin/sh\necho "$@" > %s/asked\n%s "$@"\n' % (sandbox, build.HIPCC))
+    cxx.chmod(cxx.stat().st_mode | stat.S_IXUSR)
+    monkeypatch.setenv("CXX", str(cxx))
+    build.build()
+    assert os.path.exists(build.LIB) and os.path.exists(build.MARSHAL)
+    assert "-isystem %s/rocm/include" % sandbox in (sandbox / "asked").read_text()
