@@ -50,8 +50,10 @@ def _build_marshal() -> None:
         [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
          '-DCOTTN_BUILT_FOR="%s"' % marshal_target(),
          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", os.path.join(base, "include"),
-         "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem",
-         os.path.join(os.path.dirname(os.path.dirname(shutil.which(HIPCC) or HIPCC)), "include"),   # of the same ROCm
+         "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+         # the HIP headers next to the compiler; where that is a wrapper, the usual place
+         "-isystem", os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC))), "include"),
+         "-isystem", "/opt/rocm/include",
          "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
          "-L" + os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"],
         capture_output=True, text=True)
