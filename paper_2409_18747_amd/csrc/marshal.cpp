@@ -4,7 +4,9 @@
 //
 // Every function either does the whole call, or finds something it does not know or that does not match,
 // has done nothing, and returns None: then binding.py goes through the call itself and says what is
-// wrong, so that what is accepted, refused and returned is written down once, there.
+// wrong.  What passes here is not looked at again, and the kernels index by it: every condition on an argument that
+// binding.py has stands here too, and one that is added there is added here (tests/test_gpu_marshal_refusals.py holds
+// the two together).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
