@@ -113,8 +113,12 @@ def cottn(stand_ins, monkeypatch):
 
     class SizesOnly:
         def __getattr__(self, name):
-            assert "workspace_bytes" in name or name == "cottn_status_string", "%s was called" % name
-            return getattr(real, name)
+            if "workspace_bytes" in name or name == "cottn_status_string":
+                return getattr(real, name)
+
+            def called(*_):
+                raise AssertionError("%s was called" % name)
+            return called
 
     class Watch:
         def __getattr__(self, what):
@@ -152,7 +156,7 @@ def test_refused(cottn, call):
         except (ValueError, TypeError):
             if cottn.answers == [function, None]:
                 continue
-        except cottn.CottnError:
+        except (cottn.CottnError, AssertionError):
             pass
         taken.append(what)
     assert not taken
