@@ -61,12 +61,13 @@ PyObject* raise_status(int status, const char* where) {
   return nullptr;
 }
 
-// Tensors that somebody else has a say in (modes, transforms, lazily conjugated or negated views): binding.py's.
+// Tensors that somebody else has a say in (modes, transforms, lazily conjugated or negated views), or with named dimensions,
+// which their results take over: binding.py's.
 constexpr c10::DispatchKeySet kNotPlain({c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot,
                                          c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper,
                                          c10::DispatchKey::Batched, c10::DispatchKey::Functionalize,
                                          c10::DispatchKey::Conjugate, c10::DispatchKey::Negative,
-                                         c10::DispatchKey::ZeroTensor});
+                                         c10::DispatchKey::ZeroTensor, c10::DispatchKey::Named});
 bool modes_on() { return at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
 // A plain contiguous tensor on a GPU, or null.

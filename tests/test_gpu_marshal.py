@@ -117,3 +117,16 @@ def test_modes_and_transforms_go_the_other_way(cottn):
     assert Count.seen == 1 and torch.equal(O, call(*args))
     with pytest.raises(Exception):
         torch.vmap(lambda q: call(q, *args[1:]))(args[0].expand(2, *args[0].shape))
+
+
+@pytest.mark.filterwarnings("ignore:Named tensors")
+@pytest.mark.parametrize("name", ["fwd_causal", "bwd_bidir", "step"])
+def test_results_keep_dimension_names(cottn, name):
+    """Results of a tensor with named dimensions are allocated like it, names and all."""
+    import torch
+    call, args, shapes = calls(cottn, torch)[name]
+    named = args[0].rename(*"BHNd"[:args[0].dim() - 1], "w")
+    got, plain = (r if isinstance(r, tuple) else (r,) for r in (call(named, *args[1:]), call(*args)))
+    for a, b, shape in zip(got, plain, shapes):
+        assert torch.equal(a.rename(None), b) and b.names == (None,) * len(shape)
+        assert a.names == (named.names if shape == args[0].shape else b.names)
