@@ -112,11 +112,23 @@ def test_modes_and_transforms_go_the_other_way(cottn):
         def __torch_function__(self, f, types, a=(), kw=None):
             Count.seen += f is torch.empty_like
             return f(*a, **(kw or {}))
-    with Count():
-        O = call(*args)
-    assert Count.seen == 1 and torch.equal(O, call(*args))
-    with pytest.raises(Exception):
-        torch.vmap(lambda q: call(q, *args[1:]))(args[0].expand(2, *args[0].shape))
+    answers, marshal = [], cottn._marshal
+
+    class Watch:
+        def fwd(self, *a):
+            answers.append(marshal.fwd(*a))
+            return answers[-1]
+    cottn._marshal = Watch()
+    try:
+        with Count():
+            O = call(*args)
+        assert Count.seen == 1 and answers == [None]
+        with pytest.raises(RuntimeError, match="data pointer"):
+            torch.vmap(lambda q: call(q, *args[1:]))(torch.stack([args[0], args[0]]))
+        assert answers == [None, None]
+    finally:
+        cottn._marshal = marshal
+    assert torch.equal(O, call(*args))
 
 
 @pytest.mark.filterwarnings("ignore:Named tensors")

@@ -1,5 +1,6 @@
-"""The marshalling in C++ lets other threads run Python while it allocates and launches, as ctypes does: a library of
-stand-ins, bound in place of the real one, answers a status if its caller holds the interpreter's lock.  No kernel runs."""
+"""The marshalling in C++ lets other threads run Python while it launches, as ctypes does: a library of stand-ins, bound in
+place of the real one, answers a status if its caller holds the interpreter's lock.  No kernel runs.  (Allocations
+stand in the same scope of marshal.cpp, which this does not show.)"""
 import subprocess
 
 import pytest
