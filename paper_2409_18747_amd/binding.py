@@ -354,7 +354,7 @@ def cottn_bwd_causal(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspa
     since), or None; see include/cottn.h."""
     if stream is None:
         done = _marshal.bwd(_CAUSAL, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, chunk, eps)
+                            fwd_workspace, workspace, chunk, eps)
         if done is not None:
             return done
     B, H, N, d, dt = _dims(Q)
@@ -379,7 +379,7 @@ def cottn_bwd_causal_from_state(Q, K, V, s, dO, state_in=None, rev_state_in=None
     returns (dQ, dK, dV, ds) and fills rev_state_out (float32 [B, H, d, d]) when given."""
     if stream is None:
         done = _marshal.bwd(_CAUSAL_FROM_STATE, Q, K, V, s, None, dO, state_in, rev_state_in, dQ, dK, dV, ds, rev_state_out,
-                         fwd_workspace, workspace, chunk, eps)
+                            fwd_workspace, workspace, chunk, eps)
         if done is not None:
             return done
     B, H, N, d, dt = _dims(Q)
@@ -427,7 +427,7 @@ def cottn_bwd_bidir(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, workspac
     tensor of the matching cottn_fwd_bidir call (untouched since), or None."""
     if stream is None:
         done = _marshal.bwd(_BIDIR, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, 0, eps)
+                            fwd_workspace, workspace, 0, eps)
         if done is not None:
             return done
     B, H, N, d, dt = _dims(Q)
@@ -472,7 +472,7 @@ def cottn_bwd_causal_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, 
     """cottn_bwd_causal for a padded batch; returns (dQ, dK, dV, ds) with ds float32 [B, H]."""
     if stream is None:
         done = _marshal.bwd(_CAUSAL_VARLEN, Q, K, V, s, seq_len, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, chunk, eps)
+                            fwd_workspace, workspace, chunk, eps)
         if done is not None:
             return done
     B, H, N, d, dt = _dims(Q)
@@ -519,7 +519,7 @@ def cottn_bwd_bidir_varlen(Q, K, V, s, seq_len, dO, dQ=None, dK=None, dV=None, d
     """cottn_bwd_bidir for a padded batch; returns (dQ, dK, dV, ds) with ds float32 [B, H]."""
     if stream is None:
         done = _marshal.bwd(_BIDIR_VARLEN, Q, K, V, s, seq_len, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, 0, eps)
+                            fwd_workspace, workspace, 0, eps)
         if done is not None:
             return done
     B, H, N, d, dt = _dims(Q)
@@ -696,7 +696,7 @@ def cottn_bwd_causal_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, wo
     returns (dQ, dK, dV, ds)."""
     if stream is None:
         done = _marshal.bwd(_CAUSAL_DKDV, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, chunk, eps)
+                            fwd_workspace, workspace, chunk, eps)
         if done is not None:
             return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
@@ -741,7 +741,7 @@ def cottn_bwd_bidir_dkdv(Q, K, V, s, dO, dQ=None, dK=None, dV=None, ds=None, wor
     """cottn_bwd_bidir with d_key = Q.shape[-1] and d_value = V.shape[-1]; returns (dQ, dK, dV, ds)."""
     if stream is None:
         done = _marshal.bwd(_BIDIR_DKDV, Q, K, V, s, None, dO, None, None, dQ, dK, dV, ds, None,
-                         fwd_workspace, workspace, 0, eps)
+                            fwd_workspace, workspace, 0, eps)
         if done is not None:
             return done
     B, H, N, dk, dv, dt = _dims_dkdv(Q, V)
