@@ -50,6 +50,14 @@ struct BiCfg {
   static constexpr int SP = tile_pitch(DV, C);
   static constexpr int TILEK = C * TPK, TILEV = C * TPV;
   static constexpr int STATE = DK * SP;
+  // Whether a backward sweep asks for the scale before its first rows, as the forward over segments does.  Behind them
+  // that is one request less to wait for (whole sequences by workgroup and most backwards take 0.2 to 0.7 us less), but the
+  // compiler waits for it where it is first used, in the loop, and with it in every step for the rows of the next one.  The
+  // forwards over segments lose by that (scale behind / before: 20 sequences of 18749 rows of 32 f16 23.0 / 21.2 us, 48 of
+  // 7621 bf16 21.5 / 20.1, 24 of 7380 at 64 x 64 21.8 / 21.3), and of the backwards those of narrow 16-bit values, whose
+  // steps are short (34.2 / 33.1, 43.6 / 42.5; short sequences there give 0.3 back, 8 of 437 at 64 x 32 7.4 / 7.7; 64 x 64
+  // 45.9 / 45.9, fp32 36 of 197 13.9 / 14.2).
+  static constexpr bool BWD_SCALE_FIRST = !ELEM_IS_F32 && DV == 32;
   // the forward stages finished output rows (DV wide) in the wave's own dead query rows when
   // those are wide enough, else in a tile of their own
   static constexpr bool FWD_OWN_STAGE = ELEM * stage_pitch(DV) > LDS_ELEM * TPK;
@@ -208,13 +216,13 @@ COTTN_KERNEL((C * 4), fwd_bidir_apply)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   elem_t* Ou = O + size_t(unit) * N * DV;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
 
   Stage qst;
   qst.fetch(Qu, row_begin, row_end);
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, totals + size_t(unit) * slots * DK * DV, n_sum,
                                   (state != nullptr && g == 0) ? state + size_t(unit) * DK * DV
                                                                : nullptr, un);
@@ -356,6 +364,8 @@ COTTN_KERNEL((C * 4), bwd_bidir_dq)
   const elem_t* Qu = Q + size_t(unit) * N * DK;
   const elem_t* Gu = dO + size_t(unit) * N * DV;
   elem_t* dQu = dQ + size_t(unit) * N * DK;
+  float scale = 0.f;
+  if (Cfg::BWD_SCALE_FIRST) scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
@@ -364,7 +374,7 @@ COTTN_KERNEL((C * 4), bwd_bidir_dq)
   StageV gst;
   qst.fetch(Qu, row_begin, row_end);
   gst.fetch(Gu, row_begin, row_end);
-  const float scale = unit_scale(s, unit, H, s_per_unit);
+  if (!Cfg::BWD_SCALE_FIRST) scale = unit_scale(s, unit, H, s_per_unit);
   stage_summed_matrix<DK, DV, Cfg::NT, Cfg::SP>(Sl, s_totals + size_t(unit) * slots * DK * DV, n_sum, nullptr, un);
 
   // racc[x][y]: element [v] of lane (r, q4) is G[key 16 ct + r][value 16 rt + 4 q4 + v]
@@ -526,6 +536,8 @@ COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
   const elem_t* Vu = V + size_t(unit) * N * DV;
   elem_t* dKu = dK + size_t(unit) * N * DK;
   elem_t* dVu = dV + size_t(unit) * N * DV;
+  float scale = 0.f;
+  if (Cfg::BWD_SCALE_FIRST) scale = unit_scale(s, unit, H, s_per_unit);
   const int row_begin = g * seg_rows;
   const int seg_end = min(N, row_begin + seg_rows);
   const int row_end = max(row_begin, min(valid_rows(seq_len, unit, H, N), seg_end));
@@ -534,7 +546,7 @@ COTTN_KERNEL((C * 4), bwd_bidir_dkdv)
   StageV vst;
   kst.fetch(Ku, row_begin, row_end);
   vst.fetch(Vu, row_begin, row_end);
-  const float scale = unit_scale(s, unit, H, s_per_unit);
+  if (!Cfg::BWD_SCALE_FIRST) scale = unit_scale(s, unit, H, s_per_unit);
 
   // ds[h] = sum of the shares of all batches (ds[b][h], one batch, with a scale per unit)
   if (int(blockIdx.x) < (s_per_unit ? B * H.n : H.n) && w == 0) {
