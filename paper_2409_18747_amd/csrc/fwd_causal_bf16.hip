@@ -204,9 +204,9 @@ template <int DK, int DV, int C, int CS, int WALK, int LDV = DV>
 COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd_causal_scan)
     const elem_t* __restrict__ Q, const elem_t* __restrict__ K, const elem_t* __restrict__ V,
     const float* __restrict__ s, elem_t* __restrict__ O, float* __restrict__ state_out,
-    float* __restrict__ seg_states, const float* __restrict__ state_in, Divisor H, int N, Divisor G,
-    Divisor seg_rows, float inv_eps, int sum_totals, const int* __restrict__ lengths, int s_per_unit,
-    int stream_q, int stream_kv, int units, Divisor unit_rows) {
+    float* __restrict__ seg_states, const float* __restrict__ state_in, Divisor H, Divisor G,
+    Divisor seg_rows, Divisor unit_rows, int N, int units, float inv_eps, int flags,
+    const int* __restrict__ lengths) {
   using Cfg = FwdCfg<DK, DV, C>;
   constexpr bool EVEN = walks_even(WALK);
   constexpr int RG = C / 16;           // row groups of a chunk
@@ -230,8 +230,10 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   __shared__ MaskedExchange<SHARE_MASKED ? 2 : 0> masked;   // P tiles of the two key halves
   constexpr bool SKIP_UNSEEN = skips_unseen(CS, C);
   Unparted un;
-  fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows, inv_eps,
-                     sum_totals, lengths, s_per_unit, stream_q, stream_kv, units, unit_rows);
+  fetch_argument_now(Q, K, V, s, O, state_out, seg_states, state_in, H, G, seg_rows, unit_rows, N, units, inv_eps, flags,
+                     lengths);
+  const bool sum_totals = flags & SUM_TOTALS, s_per_unit = flags & SCALE_PER_UNIT, stream_q = flags & STREAM_Q,
+             stream_kv = flags & STREAM_KV;
   const int* seq_len = WALK == EVEN_SHARES ? nullptr : lengths;
   Span span;
   int part = 0;
@@ -268,9 +270,9 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
   // the first chunk's rows and the stored states are all requested before anything waits
   StageK qst, kst;
   StageV vst;
-  qst.fetch(Qu, row_begin, row_end, stream_q != 0);
-  kst.fetch(Ku, row_begin, row_end, stream_kv != 0);
-  vst.fetch(Vu, row_begin, row_end, stream_kv != 0);
+  qst.fetch(Qu, row_begin, row_end, stream_q);
+  kst.fetch(Ku, row_begin, row_end, stream_kv);
+  vst.fetch(Vu, row_begin, row_end, stream_kv);
   float scale = unit_scale(s, unit, H, s_per_unit);
   // the state the sequence starts from (chunked prefill) belongs to every segment's start state
   f32x4 start[ST::NCT][ST::NRT];
@@ -382,9 +384,9 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
       Vu += size_t(N) * LDV;
     }
     if (more) {
-      qst.fetch(Qu, next_row, next_end, stream_q != 0);
-      kst.fetch(Ku, next_row, next_end, stream_kv != 0);
-      vst.fetch(Vu, next_row, next_end, stream_kv != 0);
+      qst.fetch(Qu, next_row, next_end, stream_q);
+      kst.fetch(Ku, next_row, next_end, stream_kv);
+      vst.fetch(Vu, next_row, next_end, stream_kv);
     }
     if (done_end > 0)
       store_row_pieces<DV, NOT, LDV>(finished, done_O, done_row + 16 * rg, done_end, l, col0);
@@ -528,9 +530,8 @@ COTTN_KERNEL((C * 4 * CS, (FwdCfg<DK, DV, C>::template waves_per_eu<CS>())), fwd
                       CS == 2 && Whole::OP == Cfg::OP,
                   "whole rows fit, and finished ones are staged alike");
     void* const room[] = {Qs, Ks, Vs, Sl, Os, rq, Ps};
-    f32w::fwd_causal_scan<DK, DV, C, CS, WALK, LDV>(room, Q, K, V, s, O, state_out, seg_states, state_in, H, N, G, seg_rows,
-                                                    inv_eps, sum_totals, lengths, s_per_unit, stream_q, stream_kv, units,
-                                                    unit_rows);
+    f32w::fwd_causal_scan<DK, DV, C, CS, WALK, LDV>(room, Q, K, V, s, O, state_out, seg_states, state_in, H, G, seg_rows,
+                                                    unit_rows, N, units, inv_eps, flags, lengths);
   }
 #endif
 }
@@ -567,11 +568,13 @@ hipError_t run_fwd_causal(const CausalArgs& a) {
   const bool stream_kv = a.G == 1 && !even && 2.0 * units * double(a.N) * (DK + DV) * ELEM > 1024.0 * 1024 * 1024;
   float* states = a.G > 1 || even ? ws : nullptr;
   if (a.marked && !even) states = ws + (a.slots - 1) * DK * DV;   // (only the mark)
+  const int flags = (sum_in_scan ? SUM_TOTALS : 0) | (a.s_per_unit ? SCALE_PER_UNIT : 0) | (stream_q ? STREAM_Q : 0) |
+                    (stream_kv ? STREAM_KV : 0);
   const auto scan = [&](auto kernel, int threads, int parts = 1) {
+    static_assert(argument_bytes(decltype(kernel){}) <= 128, "argument_bytes");
     return launch_kernel(COTTN_SYM_STR(fwd_causal_scan), kernel, dim3(a.workgroups * parts), dim3(threads), 0, a.stream, Q, K,
-                         V, a.s, static_cast<elem_t*>(a.O), a.state, states, a.state_in, a.H, a.N,
-                         a.G, a.seg_rows, inv_eps, sum_in_scan ? 1 : 0, a.seq_len, a.s_per_unit, stream_q ? 1 : 0,
-                         stream_kv ? 1 : 0, units, a.unit_rows);
+                         V, a.s, static_cast<elem_t*>(a.O), a.state, states, a.state_in, a.H,
+                         a.G, a.seg_rows, a.unit_rows, a.N, units, inv_eps, flags, a.seq_len);
   };
   constexpr int threads = 4 * C * FwdSplit<DK, DV, C>::CS;
   if constexpr (DV == 128 && !F32_WHOLE) {

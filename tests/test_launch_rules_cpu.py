@@ -88,3 +88,10 @@ def test_states_at_once(tmp_path):
                                    (4, 64 * 64, 3), (8, 64 * 128, 4 if waves < 16 else 2), (8, 128 * 128, 2), (16, 128 * 128, 1)):
             rules.append("states_at_once_of_many(%d, %d, %d) == %d" % (tiles, elements, waves, n))
     holds(tmp_path, rules)
+
+
+def test_argument_bytes(tmp_path):
+    """As the compiler lays kernel arguments out (that those of the forward scan stay within 128 bytes is asserted at its launch)."""
+    holds(tmp_path, ["argument_bytes<void*, int, void*>() == 24", "argument_bytes<int, Divisor, int>() == 16", "argument_bytes<>() == 0",
+                     "argument_bytes<const float*, Divisor, int, const int*, int>() == 36",
+                     "(SUM_TOTALS | SCALE_PER_UNIT | STREAM_Q | STREAM_KV) == 15"])
