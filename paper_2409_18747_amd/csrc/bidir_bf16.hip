@@ -50,13 +50,13 @@ struct BiCfg {
   static constexpr int SP = tile_pitch(DV, C);
   static constexpr int TILEK = C * TPK, TILEV = C * TPV;
   static constexpr int STATE = DK * SP;
-  // Whether a backward sweep asks for the scale before its first rows, as the forward over segments does.  Behind them
-  // that is one request less to wait for (whole sequences by workgroup and most backwards take 0.2 to 0.7 us less), but the
+  // Whether a backward sweep over segments asks for the scale before its first rows, as the forwards do.  Behind them
+  // that is one request less to wait for (most backwards take 0.2 to 0.7 us less), but the
   // compiler waits for it where it is first used, in the loop, and with it in every step for the rows of the next one.  The
-  // forwards over segments lose by that (scale behind / before: 20 sequences of 18749 rows of 32 f16 23.0 / 21.2 us, 48 of
-  // 7621 bf16 21.5 / 20.1, 24 of 7380 at 64 x 64 21.8 / 21.3), and of the backwards those of narrow 16-bit values, whose
-  // steps are short (34.2 / 33.1, 43.6 / 42.5; short sequences there give 0.3 back, 8 of 437 at 64 x 32 7.4 / 7.7; 64 x 64
-  // 45.9 / 45.9, fp32 36 of 197 13.9 / 14.2).
+  // forwards lose by that (scale behind / before: 20 sequences of 18749 rows of 32 f16 23.0 / 21.2 us, 48 of
+  // 7621 bf16 21.5 / 20.1, 24 of 7380 at 64 x 64 21.8 / 21.3, 384 of 512 by workgroup 18.0 / 17.8), and of the backwards those
+  // of narrow 16-bit values, whose steps are short (34.2 / 33.1, 43.6 / 42.5; short sequences there give 0.3 back, 8 of 437 at
+  // 64 x 32 7.4 / 7.7; 64 x 64 45.9 / 45.9, fp32 36 of 197 13.9 / 14.2).
   static constexpr bool BWD_SCALE_FIRST = !ELEM_IS_F32 && DV == 32;
   // the forward stages finished output rows (DV wide) in the wave's own dead query rows when
   // those are wide enough, else in a tile of their own
@@ -608,6 +608,7 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   const elem_t* Ku = K + size_t(unit) * N * DK;
   const elem_t* Vu = V + size_t(unit) * N * DV;
   elem_t* Ou = O + size_t(unit) * N * DV;
+  const float scale = unit_scale(s, unit, H, s_per_unit);
   const int row_end = valid_rows(seq_len, unit, H, N);
 
   f32x4 acc[ST::NCT][ST::NRT];   // layout: add_rows_to_state
@@ -620,7 +621,6 @@ __global__ __launch_bounds__(C * 4) void COTTN_SYM(fwd_bidir_unit)(
   kst.fetch(Ku, 0, row_end);
   vst.fetch(Vu, 0, row_end);
   qst.fetch(Qu, 0, row_end);
-  const float scale = unit_scale(s, unit, H, s_per_unit);
   add_rows_to_state<DK, DV, C, Cfg::NT>(acc, kst, vst, Ks, Vs, Ku, Vu, 0, row_end, inv_eps, w, l, un);
   if (ST::active(w)) {
 #pragma unroll
