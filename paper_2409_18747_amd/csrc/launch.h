@@ -12,8 +12,11 @@ namespace cottn {
 // quotient is a multiplication and a correction.  The compiler's division is a chain of some twenty
 // instructions through the vector ALU, and up to three of them stood before the first row was asked
 // for, in every launch, with the number of workgroups, which comes by a second load.  Without them, and the scale
-// asked for behind the rows, 93 instructions stand there in the 64 x 64 forward scan instead of 198: B8 H12 N1024 forward + backward
-// d64 49.9 -> 49.5 us, d128 108.1 -> 107.0, five launches of 15 units of 777 rows at 64 x 128 41.2 -> 40.6.
+// asked for behind the rows, 93 instructions stand there in the 64 x 64 forward scan instead of 198.  Both together, one set of
+// buffers, in turn, median of nine and lowest to highest: B8 H12 N1024 forward + backward d64 50.5 (50.3 to 50.7) -> 49.7 us (49.6
+// to 49.9), five launches of 15 units of 777 rows at 64 x 128 41.0 (40.9 to 41.2) -> 40.5 (40.4 to 40.6); d128 101.7
+// (101.4 to 102.7) -> 100.8 (100.6 to 102.0), where the runs of one side differ by as much.  Of d64 the backward's scans take the
+// gain, 0.2 and 0.35 us; the forward's time does not change.
 struct Divisor {
   int n;             // 0: nothing is divided by it
   unsigned scaled;

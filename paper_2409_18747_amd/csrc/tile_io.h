@@ -178,7 +178,8 @@ __device__ __forceinline__ int row_group(int w) {
 // queries), and the masked tile of the other half, which costs twelve to 24 matrix instructions and the parting of its
 // values, is left out (the two workgroups of a compute unit have opposite groups on a SIMD, see above).  Causal kernels,
 // formed / left out: B8 H12 N1024 d64 forward 28.6 -> 28.0 us, dK/dV 40.3 -> 39.2; 300 units of 1000 rows 64 x 128 173.5 -> 169.6, dQ
-// 228 -> 204, dK/dV 260 -> 255; 40 of 1024 at 128 x 64 forward 34.1 -> 31.1.  The dQ scan takes it at 128 value columns only: at
+// 228 -> 204, dK/dV 260 -> 255; 40 of 1024 at 128 x 64 forward 34.1 -> 31.1.  (At d64 that is what the runs of the whole pair differ
+// by: 117.3, 116.0 to 120.1 -> 116.8, 113.0 to 119.0.)  The dQ scan takes it at 128 value columns only: at
 // 64 x 64 the branch costs 16 spilled registers (35.7 -> 37.4), at 32 columns it makes no difference.
 constexpr bool skips_unseen(int waves_per_group, int rows) { return SPLIT3 && waves_per_group == 2 && rows == 32; }
 
